@@ -925,7 +925,7 @@ mgc_status mgc_recompose(mgc_ctx ctx, const double* d_coeffs, int ndim, const ui
 
 namespace {
 struct AdjointWs {
-  double *gA, *gB, *Y, *T;
+  double *gA, *gB, *Y;
 };
 AdjointWs carve_adjoint(Carver& c, const Plan& p) {
   const int64_t n_coarse = p.L >= 1 ? p.points(p.L - 1) : 1;
@@ -933,7 +933,6 @@ AdjointWs carve_adjoint(Carver& c, const Plan& p) {
   w.gA = c.take<double>(n_coarse);
   w.gB = c.take<double>(n_coarse);
   w.Y = c.take<double>(n_coarse);
-  w.T = c.take<double>(std::max<int64_t>(p.N, 1));
   return w;
 }
 size_t levels_bytes_of(const Plan& p) {
@@ -976,12 +975,8 @@ mgc_status mgc_recompose_adjoint(mgc_ctx ctx, const double* d_grad_u, int ndim,
       }
       solve_coarse(ctx, geom, w.Y, nullptr, false, false, s);
       {
-        StageScope sc(&ctx->prof, "adj_prolong", s);
-        launch_prolong(w.Y, geom, w.T, s);
-      }
-      {
-        StageScope sc(&ctx->prof, "adj_mass", s);
-        launch_adj_mass(w.T, g, geom, d_grad_coeffs, s);
+        StageScope sc(&ctx->prof, "adj_coeff", s);
+        launch_adj_coeff(w.Y, g, geom, d_grad_coeffs, s);
       }
       g = Gc;
     }

@@ -122,13 +122,12 @@ void launch_rec_tail(const CoeffSrc& src, const CoeffSrc& coarse, int coarse_top
                      const double* q, const LevelGeom* d_geo, int top, const TailTabArgs& tt,
                      void* out, bool out_f32, hipStream_t s);
 // Adjoint of recomposition, one level: Gc = P^T g (also copied to Gc_copy,
-// which the Thomas sweeps then turn into v = M_{l-1}^{-1} Gc); Pv on the fine
-// grid; cbar (stream order) = g - M_l P v at the level's new nodes.
+// which the Thomas sweeps then turn into v = M_{l-1}^{-1} Gc); cbar (stream
+// order) = g - M_l P v at the level's new nodes.
 void launch_adj_restrict(const double* gl, const LevelGeom& g, double* Gc, double* Gc_copy,
                          hipStream_t s);
-void launch_prolong(const double* v, const LevelGeom& g, double* out, hipStream_t s);
-void launch_adj_mass(const double* Pv, const double* gl, const LevelGeom& g, double* cbar,
-                     hipStream_t s);
+void launch_adj_coeff(const double* v, const double* gl, const LevelGeom& g, double* cbar,
+                      hipStream_t s);
 void launch_fill(void* out, bool out_f32, int64_t N, double v, hipStream_t s);
 // Zeroes n (1..4) ranges of whole 4-byte words in one launch.
 void launch_zero_words(void* const* ptrs, const size_t* bytes, int n, hipStream_t s);

@@ -394,19 +394,6 @@ __device__ void load_tabs(const LevelGeom& g, const Tile& tl, TileTabs<E0, E1, E
   if (tid < 8) tb.soff[tid] = (uint32_t)(tid == 0 ? 0 : g.sub_off[tid]);
 }
 
-// Stream position of a fine node with new-node flags n0..n2 (32-bit: N < 2^32).
-__device__ __forceinline__ uint32_t stream_pos(const LevelGeom& g, const Tile& tl,
-                                               const uint32_t* soff, uint32_t i0, uint32_t i1,
-                                               uint32_t i2, bool n0, bool n1, bool n2) {
-  const int m = (n0 ? (1 << g.bit[0]) : 0) | (n1 ? (1 << g.bit[1]) : 0) | (n2 ? (1 << g.bit[2]) : 0);
-  const uint32_t e1 = n1 ? tl.nf[1] - tl.nc[1] : tl.nc[1];
-  const uint32_t e2 = n2 ? tl.nf[2] - tl.nc[2] : tl.nc[2];
-  const uint32_t j0 = n0 ? (i0 >> 1) : cidx32(i0, tl.nf[0]);
-  const uint32_t j1 = n1 ? (i1 >> 1) : cidx32(i1, tl.nf[1]);
-  const uint32_t j2 = n2 ? (i2 >> 1) : cidx32(i2, tl.nf[2]);
-  return (uint32_t)g.level_off + soff[m] + (j0 * e1 + j1) * e2 + j2;
-}
-
 // Offset of subband m from eight uniform values (no indexing of a register
 // array, which would go through scratch memory).
 __device__ __forceinline__ uint32_t sel8(const uint32_t (&so)[8], int m) {
@@ -414,20 +401,6 @@ __device__ __forceinline__ uint32_t sel8(const uint32_t (&so)[8], int m) {
   const uint32_t c = (m & 1) ? so[5] : so[4], d = (m & 1) ? so[7] : so[6];
   const uint32_t ab = (m & 2) ? b : a, cd = (m & 2) ? d : c;
   return (m & 4) ? cd : ab;
-}
-
-// stream_pos with the subband offsets held in registers (no LDS table).
-__device__ __forceinline__ uint32_t stream_pos_r(const LevelGeom& g, const Tile& tl,
-                                                 const uint32_t (&so)[8], uint32_t i0,
-                                                 uint32_t i1, uint32_t i2, bool n0, bool n1,
-                                                 bool n2) {
-  const int m = (n0 ? (1 << g.bit[0]) : 0) | (n1 ? (1 << g.bit[1]) : 0) | (n2 ? (1 << g.bit[2]) : 0);
-  const uint32_t e1 = n1 ? tl.nf[1] - tl.nc[1] : tl.nc[1];
-  const uint32_t e2 = n2 ? tl.nf[2] - tl.nc[2] : tl.nc[2];
-  const uint32_t j0 = n0 ? (i0 >> 1) : cidx32(i0, tl.nf[0]);
-  const uint32_t j1 = n1 ? (i1 >> 1) : cidx32(i1, tl.nf[1]);
-  const uint32_t j2 = n2 ? (i2 >> 1) : cidx32(i2, tl.nf[2]);
-  return (uint32_t)g.level_off + sel8(so, m) + (j0 * e1 + j1) * e2 + j2;
 }
 
 __device__ __forceinline__ void subband_offsets(const LevelGeom& g, uint32_t (&so)[8]) {
@@ -1245,7 +1218,7 @@ __global__ __launch_bounds__(256) void k_rec_restrict(const LevelGeom g, const C
 
 // G_l = P Gc + c_l on the tile's owned fine nodes; the coarse values the tile
 // needs (its coarse outputs plus one more per axis) are staged in LDS.
-// SRC: 0 dequantised symbols, 1 FP64 coefficients, 2 none (plain P Gc).
+// SRC: 0 dequantised symbols, 1 FP64 coefficients.
 // Per coarse cell (see lerp_cells): the cell's coarse value and, at its new
 // nodes, the multilinear interpolant of its corners plus the coefficient.
 // The coarse values the tile needs (its cells and one more per axis) are
@@ -1308,7 +1281,7 @@ __device__ __forceinline__ void rec_interp_body(const double* __restrict__ Gc, c
       const bool ok = (!nx || h2) && (!ny || h1) && (!nz || h0) && live;
       const int m = (nz ? m0 : 0) | (ny ? m1 : 0) | (nx ? m2 : 0);
       const uint32_t bse = ny ? (nx ? bnn : bnc) : (nx ? bcn : bcc);
-      cpos[u][k] = SRC != 2 && ok ? lvl + sel8(so, m) + bse : 0u;
+      cpos[u][k] = ok ? lvl + sel8(so, m) + bse : 0u;
       if (SRC == 1) crv[u][k] = src.raw[cpos[u][k]];
       if (SRC == 0) csv[u][k] = src.sym[cpos[u][k]];
     }
@@ -1343,7 +1316,6 @@ __device__ __forceinline__ void rec_interp_body(const double* __restrict__ Gc, c
     const double ix00 = lin2(wx0, c000, wx1, c001), ix01 = lin2(wx0, c010, wx1, c011);
     const double ix10 = lin2(wx0, c100, wx1, c101), ix11 = lin2(wx0, c110, wx1, c111);
     auto coef = [&](int k) -> double {
-      if (SRC == 2) return 0.0;
       return SRC == 1 ? crv[u][k] : dequant(src, csv[u][k], cpos[u][k], q);
     };
     const uint32_t nf1 = tl.nf[1], nf2 = tl.nf[2];
@@ -1376,49 +1348,163 @@ __global__ __launch_bounds__(256) void k_rec_interp(const double* __restrict__ G
 }
 
 // --------------------------------------------------------- adjoint pieces
-// cbar at the new nodes of level l: g - (M_l Pv), the fine mass matrix applied
-// as a 3x3x3 stencil to the prolongated coarse solution Pv.
-__global__ __launch_bounds__(256) void k_adj_mass(const double* __restrict__ Pv,
-                                                   const double* __restrict__ gl,
-                                                   const LevelGeom g, double* __restrict__ cbar) {
-  const uint32_t nf0 = (uint32_t)g.nf[0], nf1 = (uint32_t)g.nf[1], nf2 = (uint32_t)g.nf[2];
-  const uint32_t i2 = blockIdx.x * 256 + threadIdx.x;
-  if (i2 >= nf2) return;
-  Tile tl;
-  for (int k = 0; k < 3; ++k) {
-    tl.nf[k] = (uint32_t)g.nf[k];
-    tl.nc[k] = (uint32_t)g.nc[k];
-  }
-  uint32_t soff[8];
-#pragma unroll
-  for (int m = 0; m < 8; ++m) soff[m] = (uint32_t)(m == 0 ? 0 : g.sub_off[m]);
-  const bool n2 = is_new32(i2, nf2);
-  const uint32_t rows = nf0 * nf1;
-  for (uint32_t row = blockIdx.y; row < rows; row += gridDim.y) {
-    const uint32_t i0 = row / nf1, i1 = row - i0 * nf1;
-    const bool n0 = is_new32(i0, nf0), n1 = is_new32(i1, nf1);
-    if (!(n0 || n1 || n2)) continue;
-    double acc = 0.0;
-    for (int a = -1; a <= 1; ++a) {
-      const int64_t j0 = (int64_t)i0 + a;
-      if (j0 < 0 || j0 >= nf0) continue;
-      const double w0 = g.ax[0].Mt[3 * i0 + a + 1];
-      for (int b = -1; b <= 1; ++b) {
-        const int64_t j1 = (int64_t)i1 + b;
-        if (j1 < 0 || j1 >= nf1) continue;
-        const double w1 = g.ax[1].Mt[3 * i1 + b + 1];
-        const double* prow = Pv + ((size_t)j0 * nf1 + j1) * nf2;
-        double s2 = 0.0;
-        for (int c = -1; c <= 1; ++c) {
-          const int64_t j2 = (int64_t)i2 + c;
-          if (j2 < 0 || j2 >= nf2) continue;
-          s2 += g.ax[2].Mt[3 * i2 + c + 1] * prow[j2];
-        }
-        acc += w0 * w1 * s2;
-      }
+// cbar at the new nodes of level l: g - M_l P v, straight from the coarse
+// solution v: along one axis M_l P takes a coarse node from its three coarse
+// neighbours and a new node from its two, so the fine field P v is never
+// formed.  A block owns 8 x 32 coarse cells (y, x) and walks a segment of
+// coarse z planes; each plane's cells and a rim of one go through LDS (the
+// next plane's and the gradient's loads in flight), a thread turns its 3 x 3
+// patch into the 2 x 2 (y, x) products of its cell and keeps those of three
+// planes in registers for the z taps.  Bound by HBM: it reads v and g once
+// and writes cbar once.  At 257^3: 67 us (the prolongation to a fine field
+// and a 27-point stencil over it took 35 + 916 us, one 8-byte tap table load
+// per tap and axis; the levels below 138 us).
+constexpr int kAdjTY = 8, kAdjTX = 32;
+
+// Taps of M_l P on coarse cell J of an axis: a on v_{J-1}, v_J, v_{J+1} for
+// its coarse node, b on v_J, v_{J+1} for its new node (zero when it has none).
+__device__ __forceinline__ void adj_taps(const AxisTab& ax, uint32_t J, uint32_t nf, double (&a)[3],
+                                         double (&b)[2]) {
+  const uint32_t p = cpos32(J, nf);
+  const bool h = 2 * J + 1 < nf - 1;
+  const double* M = ax.Mt + 3 * (size_t)p;
+  a[0] = a[2] = b[0] = b[1] = 0.0;
+  a[1] = M[1];
+  if (p > 0) {
+    if (is_new32(p - 1, nf)) {
+      a[0] = M[0] * ax.wl[p - 1];
+      a[1] = fma(M[0], ax.wr[p - 1], a[1]);
+    } else {
+      a[0] = M[0];
     }
-    const uint32_t pos = stream_pos(g, tl, soff, i0, i1, i2, n0, n1, n2);
-    cbar[pos] = gl[((size_t)i0 * nf1 + i1) * nf2 + i2] - acc;
+  }
+  if (h) {
+    const double wl = ax.wl[p + 1], wr = ax.wr[p + 1];
+    a[1] = fma(M[2], wl, a[1]);
+    a[2] = M[2] * wr;
+    b[0] = fma(M[4], wl, M[3]);
+    b[1] = fma(M[4], wr, M[5]);
+  } else if (p + 1 < nf) {
+    a[2] = M[2];
+  }
+}
+
+__global__ __launch_bounds__(256) void k_adj_coeff(const double* __restrict__ v,
+                                                    const double* __restrict__ gl,
+                                                    const LevelGeom g, double* __restrict__ cbar,
+                                                    const int seg, const uint32_t n_blocks) {
+  constexpr int TY = kAdjTY, TX = kAdjTX, RY = TY + 2, RX = TX + 2;
+  __shared__ double pl[2][RY * RX];
+  const uint32_t blk = xcd_tile(blockIdx.x, gridDim.x);
+  if (blk >= n_blocks) return;
+  const uint32_t nf0 = (uint32_t)g.nf[0], nf1 = (uint32_t)g.nf[1], nf2 = (uint32_t)g.nf[2];
+  const uint32_t nc0 = (uint32_t)g.nc[0], nc1 = (uint32_t)g.nc[1], nc2 = (uint32_t)g.nc[2];
+  const uint32_t tiles_x = (nc2 + TX - 1) / TX, tiles_y = (nc1 + TY - 1) / TY;
+  const uint32_t tx = blk % tiles_x, rest = blk / tiles_x;
+  const uint32_t ty = rest % tiles_y, sg = rest / tiles_y;
+  const uint32_t c0y = ty * TY, c0x = tx * TX;
+  const int z0 = (int)(sg * (uint32_t)seg), z1 = min(z0 + seg, (int)nc0);
+  const int tid = threadIdx.x, cy = tid / TX, cx = tid % TX;
+  const uint32_t J1 = c0y + cy, J2 = c0x + cx;
+  const bool own = J1 < nc1 && J2 < nc2;
+  double a1[3] = {0, 0, 0}, b1[2] = {0, 0}, a2[3] = {0, 0, 0}, b2[2] = {0, 0};
+  if (own) {
+    adj_taps(g.ax[1], J1, nf1, a1, b1);
+    adj_taps(g.ax[2], J2, nf2, a2, b2);
+  }
+  const bool h1 = own && 2 * J1 + 1 < nf1 - 1, h2 = own && 2 * J2 + 1 < nf2 - 1;
+  // the thread's slots of a plane's region (rim included): clamped addresses,
+  // zero outside the grid
+  uint32_t goff[2];
+  bool in[2];
+#pragma unroll
+  for (int u = 0; u < 2; ++u) {
+    const int e = min(u * 256 + tid, RY * RX - 1);
+    const int y = (int)c0y + e / RX - 1, x = (int)c0x + e % RX - 1;
+    in[u] = y >= 0 && x >= 0 && y < (int)nc1 && x < (int)nc2;
+    goff[u] = in[u] ? (uint32_t)y * nc2 + (uint32_t)x : 0u;
+  }
+  const size_t cplane = (size_t)nc1 * nc2;
+  double nv[2];
+  auto load_plane = [&](int z) {
+    const bool zin = z >= 0 && z < (int)nc0;
+    const double* src = v + (zin ? (size_t)z * cplane : 0);
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      nv[u] = src[goff[u]];
+      if (!zin || !in[u]) nv[u] = 0.0;
+    }
+  };
+  const int m0 = g.bit[0] >= 0 ? 1 << g.bit[0] : 0, m1 = g.bit[1] >= 0 ? 1 << g.bit[1] : 0,
+            m2 = g.bit[2] >= 0 ? 1 << g.bit[2] : 0;
+  uint32_t so[8];
+  subband_offsets(g, so);
+  const uint32_t lvl = (uint32_t)g.level_off;
+  const uint32_t sb_x = lvl + sel8(so, m2), sb_y = lvl + sel8(so, m1), sb_yx = lvl + sel8(so, m1 | m2),
+                 sb_z = lvl + sel8(so, m0), sb_zx = lvl + sel8(so, m0 | m2),
+                 sb_zy = lvl + sel8(so, m0 | m1), sb_zyx = lvl + sel8(so, m0 | m1 | m2);
+  const uint32_t e1c = nc1, e1n = nf1 - nc1, e2c = nc2, e2n = nf2 - nc2;
+  const uint32_t P1 = own ? cpos32(J1, nf1) : 0u, P2 = own ? cpos32(J2, nf2) : 0u;
+  const uint32_t gy0 = P1 * nf2 + P2, gy1 = (P1 + (h1 ? 1 : 0)) * nf2 + P2, dx = h2 ? 1u : 0u;
+  // (y, x) products of planes z - 1, z, z + 1: {cc, cn, nc, nn}
+  double qa[4], qb[4] = {0, 0, 0, 0}, qc[4] = {0, 0, 0, 0};
+  load_plane(z0 - 1);
+  for (int z = z0 - 1; z <= z1; ++z) {
+    double* buf = pl[z & 1];
+#pragma unroll
+    for (int u = 0; u < 2; ++u)
+      if (u * 256 + tid < RY * RX) buf[u * 256 + tid] = nv[u];
+    if (z < z1) load_plane(z + 1);
+    // gradient values of the cell whose products complete now (plane z - 1)
+    const uint32_t J0 = (uint32_t)max(z - 1, 0);
+    const bool emit = own && z > z0;
+    const bool h0 = 2 * J0 + 1 < nf0 - 1;
+    double gv[7];
+    if (emit) {
+      const uint32_t P0 = cpos32(J0, nf0);
+      const double* ga = gl + (size_t)P0 * nf1 * nf2;
+      const double* gb = ga + (h0 ? (size_t)nf1 * nf2 : 0);
+      gv[0] = ga[gy0 + dx];
+      gv[1] = ga[gy1];
+      gv[2] = ga[gy1 + dx];
+      gv[3] = gb[gy0];
+      gv[4] = gb[gy0 + dx];
+      gv[5] = gb[gy1];
+      gv[6] = gb[gy1 + dx];
+    }
+    __syncthreads();
+    double xc[3], xn[3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) {
+      const double* row = buf + (cy + r) * RX + cx;
+      const double l = row[0], c = row[1], n = row[2];
+      xc[r] = fma(a2[2], n, fma(a2[1], c, a2[0] * l));
+      xn[r] = fma(b2[1], n, b2[0] * c);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      qa[k] = qb[k];
+      qb[k] = qc[k];
+    }
+    qc[0] = fma(a1[2], xc[2], fma(a1[1], xc[1], a1[0] * xc[0]));
+    qc[1] = fma(a1[2], xn[2], fma(a1[1], xn[1], a1[0] * xn[0]));
+    qc[2] = fma(b1[1], xc[2], b1[0] * xc[1]);
+    qc[3] = fma(b1[1], xn[2], b1[0] * xn[1]);
+    if (emit) {
+      double a0[3], b0[2];
+      adj_taps(g.ax[0], J0, nf0, a0, b0);
+      const uint32_t base_cc = (J0 * e1c + J1) * e2c + J2, base_cn = (J0 * e1c + J1) * e2n + J2;
+      const uint32_t base_nc = (J0 * e1n + J1) * e2c + J2, base_nn = (J0 * e1n + J1) * e2n + J2;
+      auto zc = [&](int k) { return fma(a0[2], qc[k], fma(a0[1], qb[k], a0[0] * qa[k])); };
+      auto zn = [&](int k) { return fma(b0[1], qc[k], b0[0] * qb[k]); };
+      if (h2) cbar[sb_x + base_cn] = gv[0] - zc(1);
+      if (h1) cbar[sb_y + base_nc] = gv[1] - zc(2);
+      if (h1 && h2) cbar[sb_yx + base_nn] = gv[2] - zc(3);
+      if (h0) cbar[sb_z + base_cc] = gv[3] - zn(0);
+      if (h0 && h2) cbar[sb_zx + base_cn] = gv[4] - zn(1);
+      if (h0 && h1) cbar[sb_zy + base_nc] = gv[5] - zn(2);
+      if (h0 && h1 && h2) cbar[sb_zyx + base_nn] = gv[6] - zn(3);
+    }
   }
 }
 
@@ -3288,16 +3374,17 @@ void launch_adj_restrict(const double* gl, const LevelGeom& g, double* Gc, doubl
                           OutlierBuf{nullptr, nullptr, nullptr, 0}, nullptr, nullptr, s);
 }
 
-void launch_prolong(const double* v, const LevelGeom& g, double* out, hipStream_t s) {
-  const CoeffSrc none{nullptr, nullptr, nullptr, nullptr, 0};
-  rec_interp_dispatch<double, 2>(v, g, none, 0.0, out, s);
-}
-
-void launch_adj_mass(const double* Pv, const double* gl, const LevelGeom& g, double* cbar,
-                     hipStream_t s) {
-  const int64_t rows = g.nf[0] * g.nf[1];
-  const dim3 grid((unsigned)((g.nf[2] + 255) / 256), (unsigned)(rows < 65535 ? rows : 65535));
-  hipLaunchKernelGGL(k_adj_mass, grid, dim3(256), 0, s, Pv, gl, g, cbar);
+void launch_adj_coeff(const double* v, const double* gl, const LevelGeom& g, double* cbar,
+                      hipStream_t s) {
+  // about 2,048 blocks (two rounds of four 256-thread blocks on every CU),
+  // segments of at least four planes: a segment reads two planes of v more
+  // than it owns
+  const int64_t cols = ((g.nc[2] + kAdjTX - 1) / kAdjTX) * ((g.nc[1] + kAdjTY - 1) / kAdjTY);
+  const int64_t want = std::max<int64_t>(1, 2048 / cols);
+  const int64_t seg = std::max<int64_t>(4, (g.nc[0] + want - 1) / want);
+  const int64_t n = cols * ((g.nc[0] + seg - 1) / seg);
+  hipLaunchKernelGGL(k_adj_coeff, dim3((unsigned)((n + 7) & ~int64_t(7))), dim3(256), 0, s, v, gl,
+                     g, cbar, (int)seg, (uint32_t)n);
 }
 
 void launch_dequant_prefix(const CoeffSrc& src, int64_t m, const LevelBins& lb, double* raw,

@@ -32,6 +32,20 @@ def test_adjoint_matches_oracle(shape):
     assert np.max(np.abs(got - ref)) <= 1e-12 * max(1.0, float(np.max(np.abs(ref))))
 
 
+# coarse grids at the edges of the coefficient kernel's tiles (8 x 32 cells,
+# segments of four planes and more), even and odd lengths, squeezed axes
+@pytest.mark.parametrize("shape", [(15, 15, 63), (16, 16, 64), (7, 17, 65), (18, 18, 66), (9, 14, 62),
+                                   (67, 3, 3), (3, 67, 3), (3, 3, 67), (2, 33, 130), (130, 65), (63, 1, 16)])
+def test_adjoint_at_tile_edges(shape):
+    torch, mgc = gpu()
+    rng = np.random.default_rng(4)
+    y = rng.standard_normal(shape)
+    ref = oracle.recompose_adjoint(y, Hierarchy(shape))
+    got = mgc.recompose_adjoint(torch.from_numpy(y).cuda()).cpu().numpy()
+    # a few hundred FP64 roundings of values of this size
+    assert np.max(np.abs(got - ref)) <= 1e-12 * max(1.0, float(np.max(np.abs(ref))))
+
+
 @pytest.mark.parametrize("shape", [(129, 129, 129), (300, 40, 50), (1025, 513)])
 def test_dot_product_on_gpu(shape):
     torch, mgc = gpu()
