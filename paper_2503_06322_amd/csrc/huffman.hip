@@ -33,22 +33,31 @@
 //  * decoding tables: the same runs on many blocks (k_dt_count / k_dt_rank)
 //    validate the codebook section and build the per-length tables, the
 //    (length, symbol)-ordered symbols and the prefix table.
-//  * decode: one thread per chunk; a 12-bit prefix table in LDS gives the
-//    code length shared by all codes under a prefix (or the lengths to test
-//    against the canonical limits when several share it), and the code's
-//    index in the (length, symbol)-ordered symbol table, also in LDS.  Coded
+//  * decode: one thread per chunk; a 14-bit prefix table in LDS gives the
+//    code length shared by all codes under a prefix (or a node that tests the
+//    canonical limits when several lengths share it); the length gives the
+//    code's index in the (length, symbol)-ordered table, also in LDS.  Coded
 //    words reach each lane's LDS ring as whole aligned pieces; decoded
 //    symbols leave as whole 128-byte rows.
 #include "kernels.hpp"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace mgc {
 
-constexpr int kLutBits = 12;
-// Prefix-table entry flag: the prefix holds codes of several lengths
-// (lengths lo and hi in bits 16..21 and 22..27), or none (lo = 0).
-constexpr uint32_t kLutMixed = 1u << 31;
+constexpr int kLutBits = 14;
+// Prefix-table entries (bytes).  A negative entry is the negated length of
+// the code that every window with the prefix starts with.  Others name a node
+// that compares the window with one canonical limit, or node kLutBad when the
+// prefix's windows start no code.
+constexpr int kLutBad = 0;
+constexpr int kLutNodes = 2 * (kMaxCodeLen + 1);
+// Node of length l: windows below limit l start a code of length l; the
+// others one of length l + 1 (pair node: the prefix holds no other) or
+// continue at l + 1 (chain node).
+__host__ __device__ constexpr int lut_pair(int l) { return l; }
+__host__ __device__ constexpr int lut_chain(int l) { return kMaxCodeLen + 1 + l; }
 
 struct DecodeTables {
   uint32_t first[34];
@@ -57,12 +66,8 @@ struct DecodeTables {
   uint64_t limit[34];   // left-justified exclusive upper bound of each length
   uint32_t maxlen;
   uint32_t valid;               // 1 only after a codebook passed validation
-  // Entry of each kLutBits-bit prefix of the window.  When every window
-  // with that prefix starts with a code of one length d: d << 16 |
-  // ((base[d] - first[d]) mod 2^16), so that the code's index in sorted is
-  // (top d bits of the window + entry) mod 2^16.  Otherwise kLutMixed with
-  // the shortest and longest length under the prefix.
-  uint32_t lut[1 << kLutBits];
+  // entry of each kLutBits-bit prefix of the left-aligned 32-bit window
+  __align__(16) int8_t lut[1 << kLutBits];
   uint16_t sorted[kDict];       // symbols in (length, symbol) order
   // construction scratch: per run of the section, its counts per length and
   // (at 34) whether it holds an invalid length or symbol
@@ -2222,11 +2227,11 @@ __global__ __launch_bounds__(256) void k_dt_rank(const uint8_t* __restrict__ cb,
       dlo += llim[l] <= lo ? 1u : 0u;
       dhi += llim[l] <= hi ? 1u : 0u;
     }
-    uint32_t e;
-    if (dhi > maxlen) e = kLutMixed;  // windows that start no code (one-symbol codebook)
-    else if (dlo == dhi) e = (dlo << 16) | ((lbase[dlo] - lfirst[dlo]) & 0xFFFFu);
-    else e = kLutMixed | (dlo << 16) | (dhi << 22);
-    t->lut[p] = e;
+    int e;
+    if (dhi > maxlen) e = kLutBad;  // windows that start no code (one-symbol codebook)
+    else if (dlo == dhi) e = -(int)dlo;
+    else e = dhi == dlo + 1 ? lut_pair((int)dlo) : lut_chain((int)dlo);
+    t->lut[p] = (int8_t)e;
   }
   if (blockIdx.x == 0 && tid == 0) t->valid = 1;
 }
@@ -2234,20 +2239,31 @@ __global__ __launch_bounds__(256) void k_dt_rank(const uint8_t* __restrict__ cb,
 // One thread per chunk, 64 chunks per wavefront, blockDim/64 wavefronts per
 // block (sized by the launcher so that one pass of blocks covers the CUs).
 //
-// A symbol costs two LDS lookups and no branch on the common path: the
-// 12-bit prefix of the left-aligned window gives the code length d (and a
-// 16-bit offset), the top d bits of the window plus the offset give the
-// code's index in the (length, symbol)-ordered table.  Prefixes holding
-// codes of several lengths (at most one per length boundary) count the
-// canonical limits between their shortest and longest length.
+// The decoder is bound by its serial chain: a code's length is known only
+// after its prefix look-up, and the next look-up needs it.  The chain is kept
+// to that LDS read and five VALU instructions: the table's entry is the
+// negated length itself; the window is cut out of two words with one alignbit
+// whose shift s is lowered by the length (s < 0 moves on by a word); and
+// neither the look-ups that turn the length into the symbol nor the ring read
+// are waited for inside it.  Prefixes that hold codes of several lengths name
+// a node instead, which settles a two-length prefix with one compare; that
+// branch is taken by whole wavefronts (rarely: 14 bits leave one such prefix
+// per length) and ends in a use of its result, so that its join does not wait
+// for every LDS read in flight.  At 513^3 (55,513 codes, 10.5 bits a symbol,
+// two to three wavefronts per SIMD): 293 us, against 426 us with a 64-bit bit
+// buffer and 32-bit table entries (28 VALU instructions a symbol, 16 of them
+// on the chain, a wait for all LDS reads at the join, refills that waited for
+// the stored rows).  Left out in turn, the stores are worth 40 us, the
+// refills 30, the nodes 26; the rest is the chain and the four LDS reads a
+// symbol.  269 chunks of 65^3, where nothing hides the chain: 134 us against
+// 214.
 //
 // Every access to HBM covers whole pieces of a lane's own chunk, since 64
 // lanes read and write 64 chunks far apart and L2 keeps few of their lines
 // between two accesses of one lane:
 //  * coded words arrive in aligned pieces of G words (4G bytes) into a ring
 //    of RW words per lane in LDS; ring index i holds the word 4i bytes past
-//    the lane's first piece, so the chunk's first word sits at index s0 < G
-//    and indices past the chunk's last word read as zero;
+//    the lane's first piece, so the chunk's first word sits at index s0 < G;
 //  * at fixed symbol counts (every P symbols, the same points for every
 //    lane) a lane whose ring has room for G more words writes the piece it
 //    loaded at its previous refill and loads the next one into the same
@@ -2259,6 +2275,17 @@ __global__ __launch_bounds__(256) void k_dt_rank(const uint8_t* __restrict__ cb,
 //  * decoded symbols stay in registers, kDecOB per lane, and leave as whole
 //    128-byte rows (16-byte stores) at the next batch's first refill point.
 constexpr int kDecOB = 64;
+// LDS words, bytes and halves by their 32-bit LDS address (the decoder forms
+// its look-up addresses with one shift-and-add each)
+template <typename T>
+using lds_ptr = const __attribute__((address_space(3))) T*;
+__device__ __forceinline__ uint32_t lds_addr(const void* p) {
+  return (uint32_t)(uintptr_t)(lds_ptr<void>)p;
+}
+template <typename T>
+__device__ __forceinline__ T lds_read(uint32_t a) {
+  return *(lds_ptr<T>)(uintptr_t)a;
+}
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
 __host__ __device__ constexpr size_t dec_sorted_bytes(uint64_t n_codes) {
@@ -2266,7 +2293,7 @@ __host__ __device__ constexpr size_t dec_sorted_bytes(uint64_t n_codes) {
 }
 // dynamic LDS per wavefront beyond the sorted table: the rings
 __host__ __device__ constexpr size_t dec_wave_bytes(int rw) {
-  return (size_t)64 * (size_t)(rw + 1) * 4;
+  return (size_t)64 * (size_t)rw * 4;
 }
 
 template <int RW, int G, int P>
@@ -2277,26 +2304,35 @@ __global__ __launch_bounds__(1024) void k_decode(
   static_assert((RW & (RW - 1)) == 0 && (G & (G - 1)) == 0 && G >= 4 && 2 * G <= RW,
                 "ring of two or more whole pieces");
   static_assert(G >= P && RW - G + 1 >= P && kDecOB % P == 0, "refill points keep P words");
-  constexpr int RS = RW + 1;  // ring row pitch in words (odd: rows start on different banks)
+  // A ring row is RW words on a boundary of its size, so a word's address is
+  // its masked offset OR-ed with the row's; the lanes' read positions drift
+  // apart with their code lengths, which spreads them over the banks.
   constexpr int NQ = G / 4;   // 16-byte loads per piece
-  extern __shared__ __align__(16) unsigned char dsm[];
-  __shared__ uint32_t lut[1 << kLutBits];
-  __shared__ uint32_t lim[kMaxCodeLen + 1], offd[kMaxCodeLen + 1];
+  extern __shared__ __align__(128) unsigned char dsm[];
+  __shared__ __align__(16) int8_t lut[1 << kLutBits];
+  __shared__ __align__(16) int4 node[kLutNodes];  // {limit, entry below, entry from it on}
+  // for length d at kMaxCodeLen - d: the LDS address that twice a code's
+  // value is added to for its entry of sorted
+  __shared__ uint32_t offd[kMaxCodeLen + 1];
   __shared__ uint32_t valid;
   const int nthr = blockDim.x;
-  uint16_t* sorted = reinterpret_cast<uint16_t*>(dsm);
-  uint32_t* ring = reinterpret_cast<uint32_t*>(dsm + dec_sorted_bytes(n_codes));
+  uint16_t* sorted = reinterpret_cast<uint16_t*>(dsm + (size_t)(nthr >> 6) * dec_wave_bytes(RW));
+  // (the rings first: their rows need the alignment)
+  uint32_t* ring = reinterpret_cast<uint32_t*>(dsm);
   if (threadIdx.x == 0) valid = t->valid;
   __syncthreads();
   if (!valid) return;  // table build rejected the codebook (status already set)
-  for (int i = threadIdx.x; i < (1 << kLutBits); i += nthr) lut[i] = t->lut[i];
+  for (int i = threadIdx.x; i < (1 << kLutBits) / 16; i += nthr)
+    reinterpret_cast<uint4*>(lut)[i] = reinterpret_cast<const uint4*>(t->lut)[i];
   const uint32_t maxlen = t->maxlen > (uint32_t)kMaxCodeLen ? kMaxCodeLen : t->maxlen;
-  if (threadIdx.x <= kMaxCodeLen) {
+  if (threadIdx.x == 0) node[kLutBad] = make_int4(0, -1, -1, 0);
+  if (threadIdx.x >= 1 && threadIdx.x <= maxlen) {
     // limits below the longest length are under 2^32 (the longest length's
     // codes lie above them)
-    const int l = threadIdx.x;
-    lim[l] = l >= 1 && (uint32_t)l < maxlen ? (uint32_t)t->limit[l] : 0xFFFFFFFFu;
-    offd[l] = ((uint32_t)l << 16) | ((t->base[l] - t->first[l]) & 0xFFFFu);
+    const int l = threadIdx.x, lm = (int)(uint32_t)t->limit[l];
+    node[lut_pair(l)] = make_int4(lm, -l, -(l + 1), 0);
+    node[lut_chain(l)] = make_int4(lm, -l, l + 1 < (int)maxlen ? lut_chain(l + 1) : -(l + 1), 0);
+    offd[kMaxCodeLen - l] = lds_addr(sorted) + 2 * (t->base[l] - t->first[l]);
   }
   for (uint32_t i = threadIdx.x; i < n_codes; i += nthr) sorted[i] = t->sorted[i];
   __syncthreads();
@@ -2327,7 +2363,6 @@ __global__ __launch_bounds__(1024) void k_decode(
   const int64_t b0 = W + 4 * (int64_t)w0;
   const int64_t rb = ((b0 + aG) & ~int64_t(4 * G - 1)) - aG;
   const uint32_t s0 = (uint32_t)((b0 - rb) >> 2);
-  const uint32_t wend = s0 + (uint32_t)nwc;  // ring indices >= wend read as zero
   // the piece holding ring words i..i+3: pieces before the section read its
   // first piece (their words precede the chunk and are never used); a piece
   // that runs past the section's end is read word by word, clamped
@@ -2342,13 +2377,14 @@ __global__ __launch_bounds__(1024) void k_decode(
     r.w = *reinterpret_cast<const uint32_t*>(in + min(b + 12, e4));
     return r;
   };
-  uint32_t* rg = ring + (size_t)threadIdx.x * RS;
+  uint32_t* rg = ring + (size_t)threadIdx.x * RW;
+  const uint32_t rga = lds_addr(rg);
+  // (words past the chunk's end are the next chunk's: a valid chunk takes
+  // nothing from them, and one that does has used more bits than it has)
   auto put4 = [&](uint32_t i, const u32x4& v) {
-    rg[i % RW] = i < wend ? v.x : 0u;
-    rg[(i + 1) % RW] = i + 1 < wend ? v.y : 0u;
-    rg[(i + 2) % RW] = i + 2 < wend ? v.z : 0u;
-    rg[(i + 3) % RW] = i + 3 < wend ? v.w : 0u;
+    *reinterpret_cast<u32x4*>(rg + (i % RW)) = v;
   };
+  auto ring_word = [&](uint32_t i) { return lds_read<uint32_t>(((i << 2) & (4 * RW - 1)) | rga); };
   // prologue: the first RW words into the ring, the next piece in flight
   u32x4 g[NQ];
   {
@@ -2360,15 +2396,38 @@ __global__ __launch_bounds__(1024) void k_decode(
 #pragma unroll
     for (int q = 0; q < RW / 4; ++q) put4(4 * q, pre[q]);
   }
-  uint64_t buf = ((uint64_t)rg[s0] << 32) | rg[s0 + 1];
-  int nb = 64;                     // valid bits in buf (left-aligned)
-  uint32_t rd = s0 + 2, wt = RW;   // next word into buf; ring words written
-  uint32_t nextw = rg[rd % RW];
+  // the window starts 32 - s bits into hi and goes on in lo (0 <= s < 32)
+  uint32_t hi_w = 0u, lo_w = rg[s0];
+  int s = 0;
+  uint32_t rd = s0 + 1, wt = RW;   // next word into the window; ring words written
+  uint32_t nextw = ring_word(rd);
   bool bad = false;
   uint32_t ob[kDecOB / 2];  // the batch's symbols, two per register
   const bool vec = (C & 7) == 0 && (reinterpret_cast<uintptr_t>(sym) & 15) == 0;
-  auto store_batch = [&](int kb) {
+  // A plain wavefront: whole chunks of whole batches, 16-byte rows, and every
+  // piece from the chunk's first on can be read whole up to piece imax (words
+  // past it are only wanted by a chunk that uses more bits than it has).  Its
+  // refills and stores have no other form to branch to, so the compiler can
+  // count the accesses in flight and a refill waits for its loads alone, not
+  // for the rows stored after them.
+  const int64_t imax = (hi - rb) >> 2;
+  const bool plain = __ballot(live && cnt == C && rb >= lo &&
+                              imax >= (int64_t)(s0 + nwc)) == ~0ull &&
+                     vec && C % kDecOB == 0;
+  const uint32_t imax32 = (uint32_t)min<int64_t>(max<int64_t>(imax, 0), 0x3FFFFFFC);
+  auto ldp_plain = [&](uint32_t i) -> u32x4 {
+    return *reinterpret_cast<const u32x4*>(in + rb + 4 * (int64_t)min(i, imax32));
+  };
+  auto store_batch = [&](auto all, int kb) {
+    constexpr bool ALL = decltype(all)::value;
     const int64_t pos = start + kb;
+    if constexpr (ALL) {
+      uint4* dst = reinterpret_cast<uint4*>(sym + pos);
+#pragma unroll
+      for (int q = 0; q < kDecOB / 8; ++q)
+        dst[q] = make_uint4(ob[4 * q], ob[4 * q + 1], ob[4 * q + 2], ob[4 * q + 3]);
+      return;
+    }
     const int64_t n_here = live ? min<int64_t>(min<int64_t>(kDecOB, C - kb), N - pos) : 0;
     if (vec && n_here == kDecOB) {
       uint4* dst = reinterpret_cast<uint4*>(sym + pos);
@@ -2381,61 +2440,78 @@ __global__ __launch_bounds__(1024) void k_decode(
         if (j < n_here) sym[pos + j] = (uint16_t)(ob[j >> 1] >> (16 * (j & 1)));
     }
   };
-  auto top_up = [&]() {
+  auto top_up = [&](auto all) {
+    constexpr bool ALL = decltype(all)::value;
     if (wt - rd <= (uint32_t)(RW - G)) {
 #pragma unroll
       for (int q = 0; q < NQ; ++q) put4(wt + 4 * q, g[q]);
       wt += G;
 #pragma unroll
-      for (int q = 0; q < NQ; ++q) g[q] = ldp(wt + 4 * q);
+      for (int q = 0; q < NQ; ++q) g[q] = ALL ? ldp_plain(wt + 4 * q) : ldp(wt + 4 * q);
     }
-    nextw = rg[rd % RW];
+    nextw = ring_word(rd);
   };
-  // a prefix with codes of several lengths: count the limits the window
-  // reaches; a window that starts no code marks the chunk bad
-  auto mixed = [&](uint32_t e, uint32_t peek) -> uint32_t {
-    unsigned d = (e >> 16) & 63u;
-    const unsigned dhi = (e >> 22) & 63u;
-    if (d == 0) {
-      bad = true;
-      return (1u << 16) | ((0u - (peek >> 31)) & 0xFFFFu);  // one bit, index 0
-    }
-    while (d < dhi && peek >= lim[d]) ++d;
-    return offd[d];
+  // what an entry that is no length leads to; a window that starts no code
+  // marks the chunk bad
+  auto resolve = [&](int e, uint32_t peek) -> int {
+    if (e < 0) return e;
+    bad |= e == kLutBad;
+    do {
+      const int4 nd = node[e];
+      e = peek < (uint32_t)nd.x ? nd.y : nd.z;
+    } while (e >= 0);
+    return e;
   };
-  for (int k0 = 0; k0 < C; k0 += kDecOB) {
-    // the previous batch's stores follow the refill loads, so that the next
-    // refill point, which waits for those loads, finds no later store
-    top_up();
-    if (k0 > 0) store_batch(k0 - kDecOB);
+  auto decode_all = [&](auto all) {
+    constexpr bool ALL = decltype(all)::value;
+    uint32_t peek = lo_w;
+    const uint32_t offa = lds_addr(offd) + 4 * kMaxCodeLen;
+    int e = lut[peek >> (32 - kLutBits)];
+    for (int k0 = 0; k0 < C; k0 += kDecOB) {
+      // the previous batch's stores follow the refill loads, so that the next
+      // refill point, which waits for those loads, finds no later store
+      top_up(all);
+      if (k0 > 0) store_batch(all, k0 - kDecOB);
 #pragma unroll
-    for (int k1 = 0; k1 < kDecOB; k1 += P) {
-      if (k1 > 0) top_up();
+      for (int k1 = 0; k1 < kDecOB; k1 += P) {
+        if (k1 > 0) top_up(all);
 #pragma unroll
-      for (int k2 = 0; k2 < P; ++k2) {
-        const int k = k1 + k2;
-        const uint32_t peek = (uint32_t)(buf >> 32);
-        uint32_t e = lut[peek >> (32 - kLutBits)];
-        if (e & kLutMixed) e = mixed(e, peek);
-        unsigned d = (e >> 16) & 63u;
-        const uint32_t v = (uint32_t)(((uint64_t)peek << d) >> 32);  // top d bits
-        const uint32_t sv = sorted[(v + e) & 0xFFFFu];
-        ob[k >> 1] = (k & 1) ? (ob[k >> 1] | (sv << 16)) : sv;
-        d = k0 + k < cnt ? d : 0u;  // past the chunk's last symbol nothing is consumed
-        buf <<= d;
-        nb -= (int)d;
-        const bool need = nb < 32;
-        buf |= (uint64_t)(need ? nextw : 0u) << ((32 - nb) & 63);
-        nb += need ? 32 : 0;
-        rd += need ? 1u : 0u;
-        nextw = rg[rd % RW];
+        for (int k2 = 0; k2 < P; ++k2) {
+          const int k = k1 + k2;
+          asm volatile("" : "+v"(e));  // (a 32-bit value from here on)
+          if (__any(e >= 0)) {
+            e = resolve(e, peek);
+            asm volatile("" : "+v"(e));  // waits for the node here, not at the join
+          }
+          // the code's value (the window's top bits) and its length's offset
+          const uint32_t v = peek >> ((uint32_t)e & 31u);
+          const uint32_t of = lds_read<uint32_t>(((uint32_t)e << 2) + offa);
+          // (nothing is consumed past the last symbol)
+          const int nd = ALL || k0 + k < cnt ? e : 0;
+          s += nd;
+          const bool need = s < 0;
+          hi_w = need ? lo_w : hi_w;
+          lo_w = need ? nextw : lo_w;
+          peek = __builtin_amdgcn_alignbit(hi_w, lo_w, (uint32_t)s);
+          e = lut[peek >> (32 - kLutBits)];
+          const uint32_t sv = lds_read<uint16_t>((v << 1) + of);
+          s &= 31;
+          rd += need ? 1u : 0u;
+          nextw = ring_word(rd);
+          ob[k >> 1] = (k & 1) ? (ob[k >> 1] | (sv << 16)) : sv;
+        }
       }
     }
+  };
+  if (plain) {
+    decode_all(std::true_type{});
+    store_batch(std::true_type{}, C - kDecOB);
+  } else {
+    decode_all(std::false_type{});
+    store_batch(std::false_type{}, ((C - 1) / kDecOB) * kDecOB);
   }
-  store_batch(((C - 1) / kDecOB) * kDecOB);
-  // bits taken from the chunk: the words moved into the buffer less those
-  // still in it
-  const int64_t used = ((int64_t)rd - s0) * 32 - nb;
+  // bits taken from the chunk
+  const int64_t used = ((int64_t)rd - 1 - s0) * 32 - s;
   if (live && (bad || used > (int64_t)nwc * 32)) atomicOr(status, ST_FORMAT);
 }
 

@@ -258,3 +258,32 @@ def test_decoder_choice_on_large_codebook_and_forced_shapes_that_do_not_fit(forc
                 continue
             assert mgc.decoder_info() == (ring, waves)
             assert bool((back == t).all()), (ring, waves)
+
+
+# one to three wavefronts of chunks, whole and with a partial last chunk (the
+# decoder's plain wavefronts and the others), the words' end near a 16-byte
+# boundary and off it
+@pytest.mark.parametrize("n", [1024 * 64, 1024 * 65, 1024 * 128 + 1, 1024 * 192 - 3, 1024 * 200 + 517])
+@pytest.mark.parametrize("kind", ["one_code_per_length", "two_lengths_per_prefix", "equal"])
+def test_decode_prefix_nodes_and_plain_wavefronts(n, kind):
+    """Codes of one to 25 bits, one per length (chains of prefix nodes past the
+    14-bit table), 40,000 codes of 15 to 17 bits (two lengths under a prefix,
+    values past 2^15) and 256 equal codes: decoded symbols equal the input."""
+    torch, mgc = gpu()
+    rng = np.random.default_rng(n)
+    if kind == "one_code_per_length":
+        f = [1, 1]
+        while sum(f) < n:
+            f.append(f[-1] + f[-2])
+        sym = np.repeat(np.arange(len(f)) * 2521 % 65536, f)[:n]
+        rng.shuffle(sym)
+    elif kind == "two_lengths_per_prefix":
+        sym = np.concatenate([np.arange(40000) + 20000, rng.integers(25000, 40000, size=n)])[:n]
+        rng.shuffle(sym)
+    else:
+        sym = rng.integers(0, 256, size=n) * 7 + 1000
+    t = torch.from_numpy(sym.astype(np.uint16).view(np.int16)).cuda()
+    enc = mgc.huffman_encode(t)
+    back = mgc.huffman_decode(enc, n)
+    assert bool((back == t).all())
+    assert to_bytes(enc) == oracle_huffman_stream(sym, 1024)
