@@ -213,11 +213,12 @@ void sync_read(mgc_ctx ctx, void* host, const void* dev, size_t n, hipStream_t s
 // formed by the last, so the subtraction rides on the contiguous-axis sweep,
 // which loads its rows one ahead.  The axes' solves commute (the mass matrix
 // is a Kronecker product of per-axis factors).  One launch when the grid fits
-// in LDS (serial sweeps), else one per axis: partitioned sweeps where the
-// lines fit, serial ones otherwise or when a tuning candidate forces them
-// (the caller's forced candidates when use_tuning is set).
-void solve_coarse(mgc_ctx ctx, const LevelGeom& g, double* x, const double* sub, bool fin,
-                  bool use_tuning, hipStream_t s) {
+// in LDS (serial sweeps), else one per axis, as thomas_choice says; other: a
+// second buffer of the grid's size that nothing needs now (null: none).  A
+// tuning candidate forces the serial sweeps (the caller's forced candidates
+// when use_tuning is set).
+void solve_coarse(mgc_ctx ctx, const LevelGeom& g, double* x, double* other, const double* sub,
+                  bool fin, bool use_tuning, hipStream_t s) {
   if (thomas_grid_fits(g)) {
     StageScope sc(&ctx->prof, fin ? "thomas[finest]" : "thomas", s);
     launch_thomas_grid(x, g, sub, s);
@@ -227,6 +228,8 @@ void solve_coarse(mgc_ctx ctx, const LevelGeom& g, double* x, const double* sub,
     return use_tuning ? tuned(ctx, axis == 2 ? MGC_TUNE_THOMAS_ROWS : MGC_TUNE_THOMAS_STRIDED)
                       : 0;
   };
+  const ThomasChoice ch = thomas_choice(g.nc, g.bit, cand(0) != 0, cand(2) != 0, other != nullptr);
+  double* cur = x;
   int order[3] = {2, 1, 0};
   if (sub) order[0] = 0, order[2] = 2;
   int last = -1;  // the axis swept last
@@ -236,7 +239,10 @@ void solve_coarse(mgc_ctx ctx, const LevelGeom& g, double* x, const double* sub,
     const int axis = order[i];
     if (g.bit[axis] < 0) continue;
     StageScope sc(&ctx->prof, fin ? kThomasFinest[axis] : "thomas", s);
-    launch_thomas(axis, x, g.nc, g.ax[axis], axis == last ? sub : nullptr, s, cand(axis));
+    double* const to = ch.flip[axis] ? (cur == x ? other : x) : cur;
+    launch_thomas(axis, ch.cls[axis], cur, to, g.nc, g.ax[axis], axis == last ? sub : nullptr, s,
+                  cand(axis));
+    cur = to;
   }
 }
 
@@ -276,7 +282,8 @@ void run_levels_decompose(mgc_ctx ctx, const Plan& p, const void* d_in, bool in_
       launch_dec_level(Gcur, cur_f32, g, Gnext, sym, raw, sym ? rdev + l : nullptr, ob, status,
                        gate, s, tuned(ctx, cur_f32 ? MGC_TUNE_DEC_F32 : MGC_TUNE_DEC_F64));
     }
-    solve_coarse(ctx, g, Gnext, nullptr, l == p.L, true, s);
+    // (the other buffer held the grid just decomposed, or nothing yet)
+    solve_coarse(ctx, g, Gnext, Gnext == gA ? gB : gA, nullptr, l == p.L, true, s);
     Gcur = Gnext;
     cur_f32 = false;
   }
@@ -335,7 +342,11 @@ void run_levels_recompose(mgc_ctx ctx, const Plan& p, const CoeffSrc& src,
       StageScope sc(&ctx->prof, fin ? "rec_restrict[finest]" : "rec_restrict", s);
       launch_rec_restrict(g, src_of(l), q[l], F, s);
     }
-    solve_coarse(ctx, g, F, Gprev, fin, true, s);
+    // (the output is written last: until then it can hold a coarse grid)
+    const size_t need = (size_t)p.points(l - 1) * sizeof(double);
+    const bool room = (size_t)p.N * (out_f32 ? 4 : 8) >= need &&
+                      (reinterpret_cast<uintptr_t>(d_out) & 7) == 0;
+    solve_coarse(ctx, g, F, room ? static_cast<double*>(d_out) : nullptr, Gprev, fin, true, s);
     {
       StageScope sc(&ctx->prof, fin ? "rec_interp[finest]" : "rec_interp", s);
       double* dst = levels ? slot[l] : Gprev;
@@ -925,7 +936,7 @@ mgc_status mgc_recompose(mgc_ctx ctx, const double* d_coeffs, int ndim, const ui
 
 namespace {
 struct AdjointWs {
-  double *gA, *gB, *Y;
+  double *gA, *gB, *Y, *T;  // T: the sweeps' second buffer
 };
 AdjointWs carve_adjoint(Carver& c, const Plan& p) {
   const int64_t n_coarse = p.L >= 1 ? p.points(p.L - 1) : 1;
@@ -933,6 +944,7 @@ AdjointWs carve_adjoint(Carver& c, const Plan& p) {
   w.gA = c.take<double>(n_coarse);
   w.gB = c.take<double>(n_coarse);
   w.Y = c.take<double>(n_coarse);
+  w.T = c.take<double>(n_coarse);
   return w;
 }
 size_t levels_bytes_of(const Plan& p) {
@@ -973,7 +985,7 @@ mgc_status mgc_recompose_adjoint(mgc_ctx ctx, const double* d_grad_u, int ndim,
         StageScope sc(&ctx->prof, "adj_restrict", s);
         launch_adj_restrict(g, geom, Gc, w.Y, s);
       }
-      solve_coarse(ctx, geom, w.Y, nullptr, false, false, s);
+      solve_coarse(ctx, geom, w.Y, w.T, nullptr, false, false, s);
       {
         StageScope sc(&ctx->prof, "adj_coeff", s);
         launch_adj_coeff(w.Y, g, geom, d_grad_coeffs, s);

@@ -49,7 +49,8 @@ struct BLaunch {
   BK kind;
   const char* name;
   int step = 0, axis = 0, D = 0;
-  int part = 0, waves = 1;  // ThomasPart: class (thomas_part_class) and block wavefronts
+  int move = 0;  // ThomasPart: buffers read and written (launch_b_thomas_part)
+  int part = 0, waves = 1;  // ThomasPart: class (thomas_choice) and block wavefronts
   bool f32 = false;
   size_t map_off = 0;  // first entry of the launch in the map buffer
   uint32_t nb = 0;     // map entries (blocks)
@@ -194,15 +195,22 @@ void build_launches(BatchPlan& b, const int t[kTuneKinds], std::vector<JobBlock>
     for (int axis = 2; axis >= 0; --axis) {
       const int kind = axis == 2 ? TUNE_THOMAS_ROWS : TUNE_THOMAS_STRIDED;
       // the plain path's choice per array: serial sweeps for grids of the
-      // one-launch grid kernel, for lines too long or when a candidate
-      // forces them; the partitioned class otherwise
-      auto cls = [&](int j) -> int {
+      // one-launch grid kernel and where thomas_choice says so
+      const bool fs = t[TUNE_THOMAS_STRIDED] != 0, fr = t[TUNE_THOMAS_ROWS] != 0;
+      // (class and the buffers the sweep reads and writes, see launch_b_thomas_part)
+      struct Sweep {
+        int cls, move;
+      };
+      auto sweep = [&](int j) -> Sweep {
         const Plan& p = *b.plans[j];
-        if (t[kind] != 0) return kPartNone;
         const LevelGeom g = p.geom(p.L - s);
-        if (thomas_grid_fits(g)) return kPartNone;
-        const int c = thomas_part_class(axis, g.nc[axis]);
-        return c == kPartScan && g.nc[2] > 256 ? kPartScanLong : c;
+        if (thomas_grid_fits(g)) return {kPartNone, 0};
+        const ThomasChoice c = thomas_choice(g.nc, g.bit, fs, fr, true);
+        bool from = false;
+        for (int k = 2; k > axis; --k) from ^= c.flip[k];
+        const bool to = from ^ c.flip[axis];
+        const int k = c.cls[axis];
+        return {k == kPartScan && g.nc[2] > 256 ? kPartScanLong : k, (from ? 1 : 0) | (to ? 2 : 0)};
       };
       {
         BLaunch L;
@@ -213,14 +221,15 @@ void build_launches(BatchPlan& b, const int t[kTuneKinds], std::vector<JobBlock>
         L.tune = kind;
         mapped(L, [&](int j) -> uint32_t {
           const Plan& p = *b.plans[j];
-          if (!at(j) || p.bit[axis] < 0 || cls(j) != kPartNone) return 0;
+          if (!at(j) || p.bit[axis] < 0 || sweep(j).cls != kPartNone) return 0;
           const PlanLevel& v = p.lv[p.L - s];
           if (axis == 2) return ceil_div(v.nc[0] * v.nc[1], 64);
           if (axis == 1) return ceil_div(v.nc[0] * v.nc[2], 256);
           return ceil_div(v.nc[1] * v.nc[2], 256);
         });
       }
-      for (int c : {kPart40, kPart64, kPartScan, kPartScanLong}) {
+      for (int c : {kPart40, kPart64, kPartLong, kPartScan, kPartScanLong, kPartRow})
+      for (int move = 0; move < 4; ++move) {
         if ((axis == 2) != (c >= kPartScan)) continue;
         BLaunch L;
         L.kind = BK::ThomasPart;
@@ -228,21 +237,24 @@ void build_launches(BatchPlan& b, const int t[kTuneKinds], std::vector<JobBlock>
         L.step = s;
         L.axis = axis;
         L.part = c;
-        const int seg = c == kPart40 ? 40 : 64;
+        L.move = move;
+        const int seg = c == kPart64 ? 64 : 40;
         for (int j = 0; j < n; ++j) {
           const Plan& p = *b.plans[j];
-          if (axis < 2 && at(j) && p.bit[axis] >= 0 && cls(j) == c)
-            L.waves = std::max<int>(L.waves, (int)ceil_div(p.lv[p.L - s].nc[axis], seg));
+          if (axis < 2 && at(j) && p.bit[axis] >= 0 && sweep(j).cls == c)
+            L.waves = c == kPartLong ? kPartWavesMax
+                                     : std::max<int>(L.waves, (int)ceil_div(p.lv[p.L - s].nc[axis], seg));
         }
         mapped(L, [&](int j) -> uint32_t {
           const Plan& p = *b.plans[j];
-          if (!at(j) || p.bit[axis] < 0 || cls(j) != c) return 0;
+          if (!at(j) || p.bit[axis] < 0 || sweep(j).cls != c || sweep(j).move != move) return 0;
           const PlanLevel& v = p.lv[p.L - s];
           // (about four rows per wavefront: each wavefront loads its factors
           // once and the next row while it solves one)
+          if (c == kPartRow) return (uint32_t)std::min<int64_t>(v.nc[0] * v.nc[1], 1024);
           if (axis == 2) return std::min<uint32_t>(ceil_div(v.nc[0] * v.nc[1], 16), 1024);
-          if (axis == 1) return ceil_div(v.nc[0] * v.nc[2], 64);
-          return ceil_div(v.nc[1] * v.nc[2], 64);
+          const int64_t nc[3] = {v.nc[0], v.nc[1], v.nc[2]};
+          return thomas_part_blocks(axis, c, nc);
         });
       }
     }
@@ -299,7 +311,7 @@ void launch_one(const BatchPlan& b, const BLaunch& L, const int t[kTuneKinds], h
     case BK::Dec: launch_b_dec_level(J, m, L.nb, L.step, L.D, L.f32, cand, s); break;
     case BK::Thomas: launch_b_thomas(L.axis, J, m, L.nb, L.step, cand, s); break;
     case BK::ThomasPart:
-      launch_b_thomas_part(L.axis, L.part, L.waves, J, m, L.nb, L.step, s);
+      launch_b_thomas_part(L.axis, L.part, L.waves, J, m, L.nb, L.step, L.move, s);
       break;
     case BK::Level0: launch_b_level0(J, m, L.nb, L.f32, s); break;
     case BK::Hist: launch_b_histogram(J, m, L.nb, s); break;

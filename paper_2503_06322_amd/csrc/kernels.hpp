@@ -52,24 +52,62 @@ void launch_range(const void* u, mgc_dtype dt, int64_t N, double* part, const Bu
 void launch_dec_level(const void* G, bool g_is_f32, const LevelGeom& g, double* fout,
                       uint16_t* sym, double* raw, const double* rp, const OutlierBuf& ob,
                       unsigned* status, const unsigned* gate, hipStream_t s, int cand = 0);
-// Solve the coarse mass matrix along internal axis `axis` for every line of
-// x (coarse grid nc).  When sub != nullptr, x <- sub - solution.
-// cand: kThomasSeg (axis 2) or kThomasU (axes 0, 1) candidate; with cand 0,
-// grids of at most kThomasTilePoints points and lines of at most 540 values
-// use the LDS line tiles instead (all variants give identical results).
-// With cand 0 an axis whose lines fit (thomas_part_class) is solved by the
-// partitioned sweeps, whose results agree with the serial ones up to
-// rounding; the caller decides which grids go this way (a grid small enough
-// for launch_thomas_grid is solved serially in one launch instead).  The
-// batched form makes the same choice per array, so both agree bit for bit.
-constexpr int64_t kThomasTilePoints = int64_t(1) << 22;
-void launch_thomas(int axis, double* x, const int64_t nc[3], const AxisTab& t,
-                   const double* sub, hipStream_t s, int cand = 0);
-// Partitioned-sweep class of a line of len values along internal axis `axis`
-// (kPartNone: serial sweeps).  kPartScanLong marks rows of 257..1024 values
+// How each axis of a coarse grid is solved when the grid is too large for
+// launch_thomas_grid (kPartNone: serial sweeps, one thread per line):
+//  * strided axes (0, 1): partitioned sweeps of up to eight 40- or 64-value
+//    segments a line; longer lines (kPartLong) in overlapping windows of 320
+//    values, which read one buffer and write another;
+//  * contiguous axis: a wavefront per row up to 1024 values, a block per row
+//    (kPartRow) up to kRowBlkMax.
+// flip[k]: axis k's sweep moves the grid to the other buffer.  The flips are
+// even in number: with one window axis the row sweep moves the grid as well.
+// Without a second buffer, or where the rows are too long for their sweeps,
+// window axes fall back to the serial sweep.  force_*: a tuning candidate
+// asks for the serial sweeps.  kPartScanLong marks rows of 257..1024 values
 // for the batched form's launches.
-enum { kPartNone = 0, kPart40 = 1, kPart64 = 2, kPartScan = 3, kPartScanLong = 4 };
-int thomas_part_class(int axis, int64_t len);
+enum { kPartNone = 0, kPart40 = 1, kPart64 = 2, kPartLong = 3, kPartScan = 4, kPartScanLong = 5,
+       kPartRow = 6 };
+constexpr int64_t kRowBlkMax = 8704;
+constexpr int kPartWavesMax = 8;  // wavefronts per block of the strided sweeps
+struct ThomasChoice {
+  int cls[3];
+  bool flip[3];
+};
+__host__ __device__ inline ThomasChoice thomas_choice(const int64_t (&nc)[3], const int (&bit)[3],
+                                                      bool force_strided, bool force_rows,
+                                                      bool second_buffer) {
+  ThomasChoice c;
+  c.cls[2] = bit[2] < 0 || force_rows ? kPartNone
+             : nc[2] <= 1024          ? kPartScan
+             : nc[2] <= kRowBlkMax    ? kPartRow
+                                      : kPartNone;
+  int windows = 0;
+  for (int k = 0; k < 2; ++k) {
+    c.cls[k] = bit[k] < 0 || force_strided ? kPartNone
+               : nc[k] <= 320              ? kPart40
+               : nc[k] <= 512              ? kPart64
+                                           : kPartLong;
+    windows += c.cls[k] == kPartLong ? 1 : 0;
+  }
+  const bool ok = second_buffer && c.cls[2] != kPartNone;
+  for (int k = 0; k < 2; ++k) {
+    if (c.cls[k] == kPartLong && !ok) c.cls[k] = kPartNone;
+    c.flip[k] = c.cls[k] == kPartLong;
+  }
+  c.flip[2] = ok && (windows & 1);
+  return c;
+}
+// Solve the coarse mass matrix along internal axis `axis` for every line of
+// x (coarse grid nc) with the sweep of class cls, into dst (x itself unless
+// thomas_choice moves the grid).  When sub != nullptr, dst <- sub - solution.
+// cand: for the serial sweeps, the kThomasSeg (axis 2) or kThomasU (axes 0,
+// 1) candidate.  The partitioned sweeps agree with the serial ones up to
+// rounding; the batched form makes the same choice per array, so both agree
+// bit for bit.
+void launch_thomas(int axis, int cls, const double* x, double* dst, const int64_t nc[3],
+                   const AxisTab& t, const double* sub, hipStream_t s, int cand = 0);
+// Blocks of a strided axis' partitioned sweep of class c.
+uint32_t thomas_part_blocks(int axis, int c, const int64_t nc[3]);
 // All active axes of a coarse grid small enough for LDS in one launch (the
 // same results as the per-axis launches, axis 2 first; sub as there, applied
 // after the last sweep).  Only for grids with thomas_grid_fits(g).
@@ -143,11 +181,12 @@ void launch_b_dec_level(const Job* jobs, const JobBlock* map, uint32_t nb, int s
                         bool f32, int cand, hipStream_t s);
 void launch_b_thomas(int axis, const Job* jobs, const JobBlock* map, uint32_t nb, int step,
                      int cand, hipStream_t s);
-// Partitioned sweeps (class c of thomas_part_class; kPartScan / kPartScanLong
-// on axis 2) of every mapped array; waves = wavefronts per block, at least
-// the largest segment count of the mapped arrays (axes 0 and 1).
+// Partitioned sweeps (class c of thomas_choice; kPartScan, kPartScanLong or
+// kPartRow on axis 2) of every mapped array; waves = wavefronts per block, at least
+// the largest segment count of the mapped arrays (axes 0 and 1); move: 1 |
+// 2 when the sweep reads | writes the buffer that is not the step's own.
 void launch_b_thomas_part(int axis, int c, int waves, const Job* jobs, const JobBlock* map,
-                          uint32_t nb, int step, hipStream_t s);
+                          uint32_t nb, int step, int move, hipStream_t s);
 void launch_b_level0(const Job* jobs, const JobBlock* map, uint32_t nb, bool f32,
                      hipStream_t s);
 void launch_b_histogram(const Job* jobs, const JobBlock* map, uint32_t nb, hipStream_t s);

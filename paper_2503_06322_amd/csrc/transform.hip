@@ -1772,10 +1772,23 @@ __global__ __launch_bounds__(64) void k_thomas_rows(double* __restrict__ x, int6
 // sweep (x stays x), both exact, so the sweeps run without per-value
 // branches.  Lane j holds the factors of slot j and the sweeps broadcast
 // them with readlane, so no scalar load sits on the recurrence.
-constexpr int kPartWaves = 8;  // segments (wavefronts) per block at most
-template <int AXIS, int SEG>
-__device__ __forceinline__ void thomas_part_body(double* __restrict__ x, int64_t n0, int64_t n1,
-                                                 int64_t n2, const double* __restrict__ ta,
+//
+// LONG: lines of more values than a block's segments hold.  A block solves a
+// window of one: kLongUse values it stores and kLongHalo more on either side
+// that its sweeps start from zero in.  Each row of the mass matrix is at
+// least twice as heavy on the diagonal as off it and the spacings are equal
+// but for the last, so |a|, |c| < 0.29 inside a line and a start value's
+// influence falls below 0.29^32 = 6e-18 of it across the halo, less than a
+// rounding.  Blocks read values that others store, so dst is not x (in place
+// otherwise).  At 4097 x 4097 values: LONGUS us, the one-thread-per-line
+// sweep 1219 us (4,097 threads on the whole GPU, every value twice).
+constexpr int kPartWaves = kPartWavesMax;  // segments (wavefronts) per block at most
+constexpr int kLongSeg = 40, kLongHalo = 32;
+constexpr int kLongUse = kPartWaves * kLongSeg - 2 * kLongHalo;
+template <int AXIS, int SEG, bool LONG>
+__device__ __forceinline__ void thomas_part_body(const double* x, double* dst, int64_t n0,
+                                                 int64_t n1, int64_t n2,
+                                                 const double* __restrict__ ta,
                                                  const double* __restrict__ tm,
                                                  const double* __restrict__ tc,
                                                  const double* __restrict__ sub, int64_t blk) {
@@ -1795,8 +1808,22 @@ __device__ __forceinline__ void thomas_part_body(double* __restrict__ x, int64_t
     len = n0;
     stride = n1 * n2;
   }
+  // the block's window of the line and the values of it that are stored
+  int i0 = 0, len32 = (int)len, st0 = 0, st1 = (int)len;
+  if (LONG) {
+    const int pieces = (int)((len + kLongUse - 1) / kLongUse);
+    const int piece = (int)(blk % pieces);
+    blk /= pieces;
+    const int u0 = piece * kLongUse, u1 = min(u0 + kLongUse, (int)len);
+    i0 = max(u0 - kLongHalo, 0);
+    len32 = min(u1 + kLongHalo, (int)len) - i0;
+    st0 = u0 - i0;
+    st1 = u1 - i0;
+    ta += i0;
+    tm += i0;
+    tc += i0;
+  }
   // segment geometry in scalar registers (wavefront-uniform)
-  const int len32 = (int)len;
   const int nseg = (len32 + SEG - 1) / SEG;
   const int sl = __builtin_amdgcn_readfirstlane((len32 + nseg - 1) / nseg);
   const int s = w * sl;
@@ -1818,10 +1845,15 @@ __device__ __forceinline__ void thomas_part_body(double* __restrict__ x, int64_t
     bt = t;
   }
   const uint32_t lb = (uint32_t)(bt - bf) * 8u;  // bytes
-  double* const xb = x + bf;
+  const int64_t o = bf + i0 * stride;
+  double* const xb = const_cast<double*>(x) + o;
+  double* const yb = dst + o;
   // row i of the segment's lines: uniform row address plus the lane's bytes
   const auto at = [&](double* base, int64_t i) -> double& {
     return *reinterpret_cast<double*>(reinterpret_cast<char*>(base + i * stride) + lb);
+  };
+  const auto stored = [&](int k) {
+    return k >= off && (!LONG || (s + k - off >= st0 && s + k - off < st1));
   };
   double fa = -1.0, fm = 0.0, fc = -1.0;
   if (lane >= off && lane < SEG) {
@@ -1886,27 +1918,27 @@ __device__ __forceinline__ void thomas_part_body(double* __restrict__ x, int64_t
   }
   if (!live) return;
   if (sub) {
-    double* const qb = const_cast<double*>(sub) + bf;
+    double* const qb = const_cast<double*>(sub) + o;
 #pragma unroll
     for (int k = 0; k < SEG; ++k)
-      if (k >= off) at(xb, s + k - off) = at(qb, s + k - off) - v[k];
+      if (stored(k)) at(yb, s + k - off) = at(qb, s + k - off) - v[k];
   } else {
 #pragma unroll
     for (int k = 0; k < SEG; ++k)
-      if (k >= off) at(xb, s + k - off) = v[k];
+      if (stored(k)) at(yb, s + k - off) = v[k];
   }
 }
 
-template <int AXIS, int SEG>
+template <int AXIS, int SEG, bool LONG>
 __global__ __launch_bounds__(64 * kPartWaves) void k_thomas_part(
-    double* __restrict__ x, int64_t n0, int64_t n1, int64_t n2, const double* __restrict__ ta,
-    const double* __restrict__ tm, const double* __restrict__ tc,
+    const double* x, double* dst, int64_t n0, int64_t n1, int64_t n2,
+    const double* __restrict__ ta, const double* __restrict__ tm, const double* __restrict__ tc,
     const double* __restrict__ sub, uint32_t nblk) {
   // Consecutive line windows share their edge cache lines (rows are not
   // line-aligned), so each XCD takes a contiguous range of windows.
   const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
   if (b >= nblk) return;
-  thomas_part_body<AXIS, SEG>(x, n0, n1, n2, ta, tm, tc, sub, b);
+  thomas_part_body<AXIS, SEG, LONG>(x, dst, n0, n1, n2, ta, tm, tc, sub, b);
 }
 
 // Contiguous axis: one wavefront per row at a time, lane l holding the row's
@@ -1921,7 +1953,7 @@ __device__ __forceinline__ double shfl_down_d(double v, int o) { return __shfl_d
 constexpr int kRowScanWaves = 4;
 // (rows blk * 4 + wavefront, then every nblk * 4 rows)
 template <int K>
-__device__ __forceinline__ void thomas_rowscan_body(double* __restrict__ x, int64_t nrows,
+__device__ __forceinline__ void thomas_rowscan_body(const double* x, double* dst, int64_t nrows,
                                                     int64_t n, const double* __restrict__ ta,
                                                     const double* __restrict__ tm,
                                                     const double* __restrict__ tc,
@@ -1957,7 +1989,7 @@ __device__ __forceinline__ void thomas_rowscan_body(double* __restrict__ x, int6
     }
   }
   for (; r < nrows; r += step) {
-    double* row = x + r * n;
+    double* row = dst + r * n;
     const int64_t rn = r + step;
 #pragma unroll
     for (int k = 0; k < K; ++k)
@@ -2052,193 +2084,158 @@ __device__ __forceinline__ void thomas_rowscan_body(double* __restrict__ x, int6
 
 template <int K>
 __global__ __launch_bounds__(64 * kRowScanWaves) void k_thomas_rowscan(
-    double* __restrict__ x, int64_t nrows, int64_t n, const double* __restrict__ ta,
+    const double* x, double* dst, int64_t nrows, int64_t n, const double* __restrict__ ta,
     const double* __restrict__ tm, const double* __restrict__ tc,
     const double* __restrict__ sub) {
-  thomas_rowscan_body<K>(x, nrows, n, ta, tm, tc, sub, blockIdx.x, gridDim.x);
+  thomas_rowscan_body<K>(x, dst, nrows, n, ta, tm, tc, sub, blockIdx.x, gridDim.x);
 }
 
-// Whole lines in LDS, one tile per wavefront.  Each wavefront holds 16
-// lines of the axis in its own part of LDS: lines adjacent along the
-// contiguous axis for the strided axes (the 16 values at one position are
-// 128 contiguous bytes), 16 consecutive rows for the contiguous axis (one
-// contiguous block).  It loads the tile with sixteen loads per lane in
-// flight, runs the forward and backward sweeps in LDS (one lane per line,
-// values and factors through registers in batches) and writes the tile back:
-// each value is read and written once per axis, where the segment-staged
-// sweeps read and write the forward pass's values a second time.  The
-// wavefronts of a block share only the factor tables, so one can sweep
-// while the others load or store.
-constexpr int kTileLines = 16;
-constexpr int kThomasTile4MaxL = 280;  // four tiles per block
-constexpr int kThomasTile2MaxL = 540;  // two tiles per block
-
-__host__ __device__ constexpr size_t thomas_tile_lds(int64_t L, int tiles) {
-  return ((size_t)L * ((size_t)tiles * (kTileLines + 1) + 3) + (size_t)tiles * kTileLines) *
-         sizeof(double);
-}
-
-template <int TILES, int AXIS>
-__global__ __launch_bounds__(64 * TILES) void k_thomas_tile(double* __restrict__ x, int64_t n0,
-                                                             int64_t n1, int64_t n2,
-                                                             const double* __restrict__ ta,
-                                                             const double* __restrict__ tm,
-                                                             const double* __restrict__ tc,
-                                                             const double* __restrict__ sub) {
-  constexpr int W = kTileLines, NB = 32;
-  extern __shared__ double tsm[];
-  const int L = (int)(AXIS == 0 ? n0 : (AXIS == 1 ? n1 : n2));
-  // strided axes: [position][line] with pitch W + 1; rows: [line][position]
-  // with pitch L + 1; room for either
-  const int tile_sz = L * (W + 1) + W;
-  double* fa = tsm;
-  double* fm = fa + L;
-  double* fc = fm + L;
-  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-  double* T = fc + L + wave * tile_sz;
-  for (int i = tid; i < L; i += 64 * TILES) {
-    fa[i] = ta[i];
-    fm[i] = tm[i];
-    fc[i] = tc[i];
+// Rows of 1025 .. kRowBlkMax values: the same scheme with a block per row.
+// Thread t holds values t*sl .. t*sl+sl-1 (sl = ceil(n / 512), made odd: the
+// lanes' LDS reads sl doubles apart then fall on different banks); the maps
+// are scanned inside each wavefront and chained over the eight wavefronts
+// through LDS.  Rows blk, blk + nblk, ...: the factors stay in registers and
+// the next row's loads are in flight while a row is solved.  At 4097 rows of
+// 4097 values: ROWUS us, the 64-rows-per-wavefront sweep 907 us (65 wavefronts
+// on the whole GPU).
+constexpr int kRowBlkThreads = 512;
+template <int K>
+__device__ __forceinline__ void thomas_rowblk_body(const double* x, double* dst, int64_t nrows,
+                                                   int64_t n, const double* __restrict__ ta,
+                                                   const double* __restrict__ tm,
+                                                   const double* __restrict__ tc,
+                                                   const double* __restrict__ sub, int64_t blk,
+                                                   int64_t nblk) {
+  static_assert(K & 1, "odd values per thread");
+  constexpr int T = kRowBlkThreads, W = T / 64;
+  __shared__ double b[T * K];
+  __shared__ double fwd[W][2], bwd[W][2];  // the wavefronts' maps {A, B}
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int sl = ((int)((n + T - 1) / T)) | 1;
+  const int s = tid * sl;
+  const int ns = max(min(sl, (int)n - s), 0);
+  double fa[K], fm[K], fc[K];
+#pragma unroll
+  for (int k = 0; k < K; ++k) {
+    const int i = min(s + k, (int)n - 1);
+    fa[k] = ta[i];
+    fm[k] = tm[i];
+    fc[k] = tc[i];
   }
-  const int64_t tile = (int64_t)blockIdx.x * TILES + wave;
-  // first value of the tile, lines in it, distance between positions
-  int64_t base0, estride;
-  int nl;
-  bool live = true;
-  if (AXIS == 2) {
-    const int64_t r0 = tile * W, rows = n0 * n1;
-    live = r0 < rows;
-    nl = live ? (int)min<int64_t>(W, rows - r0) : 0;
-    base0 = live ? r0 * n2 : 0;
-    estride = 1;
-  } else if (AXIS == 1) {
-    const int64_t gpp = (n2 + W - 1) / W;
-    const int64_t i0 = tile / gpp, x0 = (tile - i0 * gpp) * W;
-    live = i0 < n0;
-    nl = live ? (int)min<int64_t>(W, n2 - x0) : 0;
-    base0 = live ? i0 * n1 * n2 + x0 : 0;
-    estride = n2;
-  } else {
-    const int64_t t0 = tile * W, m = n1 * n2;
-    live = t0 < m;
-    nl = live ? (int)min<int64_t>(W, m - t0) : 0;
-    base0 = live ? t0 : 0;
-    estride = m;
-  }
-  __syncthreads();  // factor tables
-  if (!live) return;
-  const int total = L * nl;  // values in the tile
-  // lane's k-th value: global address and LDS slot
-  //   rows: value e = lane + 64k of the contiguous block, line e / L
-  //   strided: line lane % 16, position lane / 16 + 4k
-  const uint64_t mL = div_magic((uint32_t)L);
-  const int jl = lane & (W - 1), il = lane >> 4;
-  const bool lane_ok = AXIS == 2 || jl < nl;
-  double* gp = x + base0 + (AXIS == 2 ? 0 : (int64_t)min(jl, nl - 1) + (int64_t)il * estride);
-  const int n_k = AXIS == 2 ? (total + 63) / 64 : (L + 3) / 4;
-  auto slot = [&](int k, int& dst) -> int64_t {  // returns the global offset from gp
-    if (AXIS == 2) {
-      const int e = min(lane + 64 * k, total - 1);
-      const int j = (int)div_small((uint32_t)e, mL);
-      dst = lane + 64 * k < total ? e + j : -1;  // j * (L + 1) + (e - j * L)
-      return e;
-    } else {
-      const int i = min(il + 4 * k, L - 1);
-      dst = lane_ok && il + 4 * k < L ? i * (W + 1) + jl : -1;
-      return (int64_t)(i - il) * estride;
-    }
+  int64_t r = blk;
+  double g[K], q[K];
+  auto load = [&](const double* src, int64_t row, double (&v)[K]) {
+#pragma unroll
+    for (int k = 0; k < K; ++k) v[k] = src[row * n + min(tid + T * k, (int)n - 1)];
   };
-  for (int k0 = 0; k0 < n_k; k0 += NB) {
-    double v[NB];
-    int dst[NB];
-#pragma unroll
-    for (int u = 0; u < NB; ++u) v[u] = gp[slot(k0 + u, dst[u])];
-#pragma unroll
-    for (int u = 0; u < NB; ++u)
-      if (dst[u] >= 0) T[dst[u]] = v[u];
+  if (r < nrows) {
+    load(x, r, g);
+    if (sub) load(sub, r, q);
   }
-  wave_fence();
-  if (lane < nl) {
-    // one line per lane; values and factors move through registers in
-    // batches of U, the next batch's LDS reads issued before the current
-    // batch's recurrence
-    constexpr int U = 8;
-    const int pitch = AXIS == 2 ? 1 : W + 1;
-    double* c = AXIS == 2 ? T + lane * (L + 1) : T + lane;
-    double v[U], a[U], m[U], nv[U], na[U], nm[U];
-    auto fwd_load = [&](int i0, double (&pv)[U], double (&pa)[U], double (&pm)[U]) {
+  for (; r < nrows; r += nblk) {
+    const int64_t rn = r + nblk;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = min(i0 + u, L - 1);
-        pv[u] = c[i * pitch];
-        pa[u] = fa[i];
-        pm[u] = fm[i];
-      }
-    };
-    double prev = 0.0;
-    fwd_load(0, v, a, m);
-    for (int i0 = 0; i0 < L; i0 += U) {
-      if (i0 + U < L) fwd_load(i0 + U, nv, na, nm);
+    for (int k = 0; k < K; ++k)
+      if (tid + T * k < n) b[tid + T * k] = g[k];
+    if (rn < nrows) load(x, rn, g);
+    __syncthreads();
+    double v[K];
+    double B = 0.0, A = 1.0;
 #pragma unroll
-      // past the line's end the factors are clamped and the values unused
-      for (int u = 0; u < U; ++u) {
-        v[u] = thomas_fwd(v[u], a[u], m[u], prev);
-        prev = v[u];
+    for (int k = 0; k < K; ++k)
+      if (k < ns) {
+        B = thomas_fwd(b[s + k], fa[k], fm[k], B);
+        v[k] = B;
+        A *= -fa[k];
       }
 #pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (i0 + u < L) c[(i0 + u) * pitch] = v[u];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        v[u] = nv[u];
-        a[u] = na[u];
-        m[u] = nm[u];
+    for (int o = 1; o < 64; o <<= 1) {
+      const double Ao = shfl_up_d(A, o), Bo = shfl_up_d(B, o);
+      if (lane >= o) {
+        B = fma(A, Bo, B);
+        A *= Ao;
       }
     }
-    auto bwd_load = [&](int hi, double (&pv)[U], double (&pc)[U]) {
+    if (lane == 63) {
+      fwd[w][0] = A;
+      fwd[w][1] = B;
+    }
+    double Ae = shfl_up_d(A, 1), Be = shfl_up_d(B, 1);
+    if (lane == 0) Ae = 1.0, Be = 0.0;
+    __syncthreads();
+    {
+      double yw = 0.0;
+      for (int j = 0; j < w; ++j) yw = fma(fwd[j][0], yw, fwd[j][1]);
+      const double yin = fma(Ae, yw, Be);
+      double al = 1.0;
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const int i = max(hi - u, 0);
-        pv[u] = c[i * pitch];
-        pc[u] = fc[i];
+      for (int k = 0; k < K; ++k)
+        if (k < ns) {
+          al *= -fa[k];
+          v[k] = fma(al, yin, v[k]);
+        }
+    }
+    double X = 0.0, C = 1.0;
+#pragma unroll
+    for (int k = K - 1; k >= 0; --k)
+      if (k < ns) {
+        X = thomas_bwd(v[k], fc[k], X);
+        v[k] = X;
+        C *= -fc[k];
       }
-    };
-    double nxt = 0.0;
-    bwd_load(L - 1, v, a);
-    for (int hi = L - 1; hi >= 0; hi -= U) {
-      if (hi - U >= 0) bwd_load(hi - U, nv, na);
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        v[u] = thomas_bwd(v[u], a[u], nxt);
-        nxt = v[u];
-      }
-#pragma unroll
-      for (int u = 0; u < U; ++u)
-        if (hi - u >= 0) c[(hi - u) * pitch] = v[u];
-#pragma unroll
-      for (int u = 0; u < U; ++u) {
-        v[u] = nv[u];
-        a[u] = na[u];
+    for (int o = 1; o < 64; o <<= 1) {
+      const double Co = shfl_down_d(C, o), Xo = shfl_down_d(X, o);
+      if (lane + o < 64) {
+        X = fma(C, Xo, X);
+        C *= Co;
       }
     }
-  }
-  wave_fence();
-  double* gq = gp;
-  const double* sp = sub ? sub + (gp - x) : nullptr;
-  for (int k0 = 0; k0 < n_k; k0 += NB) {
-    double sv[NB];
-    int64_t off[NB];
-    int src[NB];
+    if (lane == 0) {
+      bwd[w][0] = C;
+      bwd[w][1] = X;
+    }
+    double Ce = shfl_down_d(C, 1), Xe = shfl_down_d(X, 1);
+    if (lane == 63) Ce = 1.0, Xe = 0.0;
+    __syncthreads();
+    {
+      double xw = 0.0;
+      for (int j = W - 1; j > w; --j) xw = fma(bwd[j][0], xw, bwd[j][1]);
+      const double xin = fma(Ce, xw, Xe);
+      double be = 1.0;
 #pragma unroll
-    for (int u = 0; u < NB; ++u) {
-      off[u] = slot(k0 + u, src[u]);
-      sv[u] = sp ? sp[off[u]] : 0.0;
+      for (int k = K - 1; k >= 0; --k)
+        if (k < ns) {
+          be *= -fc[k];
+          v[k] = fma(be, xin, v[k]);
+        }
     }
 #pragma unroll
-    for (int u = 0; u < NB; ++u)
-      if (src[u] >= 0) gq[off[u]] = sp ? sv[u] - T[src[u]] : T[src[u]];
+    for (int k = 0; k < K; ++k)
+      if (k < ns) b[s + k] = v[k];
+    __syncthreads();
+    double* row = dst + r * n;
+    if (sub) {
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (tid + T * k < n) row[tid + T * k] = q[k] - b[tid + T * k];
+      if (rn < nrows) load(sub, rn, q);
+    } else {
+#pragma unroll
+      for (int k = 0; k < K; ++k)
+        if (tid + T * k < n) row[tid + T * k] = b[tid + T * k];
+    }
+    __syncthreads();
   }
+}
+
+template <int K>
+__global__ __launch_bounds__(kRowBlkThreads) void k_thomas_rowblk(
+    const double* x, double* dst, int64_t nrows, int64_t n, const double* __restrict__ ta,
+    const double* __restrict__ tm, const double* __restrict__ tc,
+    const double* __restrict__ sub) {
+  thomas_rowblk_body<K>(x, dst, nrows, n, ta, tm, tc, sub, blockIdx.x, gridDim.x);
 }
 
 // A coarse grid that fits in LDS: the three sweeps (axis 2, then 1, then 0,
@@ -2976,31 +2973,49 @@ __global__ __launch_bounds__(256) void kb_thomas_strided(const Job* __restrict__
                                t.tc, nullptr, (int64_t)jb.local * 256 + threadIdx.x);
 }
 
-template <int AXIS, int SEG>
+// Grid buffer of step (other: the one that is free while the level is solved).
+__device__ __forceinline__ double* sweep_buf(const Job& J, int step, bool other) {
+  return ((step & 1) != 0) != other ? J.gB : J.gA;
+}
+
+template <int AXIS, int SEG, bool LONG>
 __global__ __launch_bounds__(64 * kPartWaves) void kb_thomas_part(const Job* __restrict__ jobs,
                                                                    const JobBlock* __restrict__ map,
-                                                                   uint32_t nb, int step) {
+                                                                   uint32_t nb, int step, int move) {
   if (blockIdx.x >= nb) return;
   const JobBlock jb = map[blockIdx.x];
   const Job& J = jobs[jb.job];
   if (job_skipped(J)) return;
   const LevelGeom& g = J.geo[J.L - step];
   const AxisTab& t = g.ax[AXIS];
-  thomas_part_body<AXIS, SEG>((step & 1) ? J.gB : J.gA, g.nc[0], g.nc[1], g.nc[2], t.ta, t.tm,
-                              t.tc, nullptr, jb.local);
+  thomas_part_body<AXIS, SEG, LONG>(sweep_buf(J, step, move & 1), sweep_buf(J, step, move & 2), g.nc[0], g.nc[1], g.nc[2], t.ta, t.tm, t.tc,
+                                    nullptr, jb.local);
 }
 
 template <int K>
 __global__ __launch_bounds__(64 * kRowScanWaves) void kb_thomas_rowscan(
-    const Job* __restrict__ jobs, const JobBlock* __restrict__ map, uint32_t nb, int step) {
+    const Job* __restrict__ jobs, const JobBlock* __restrict__ map, uint32_t nb, int step, int move) {
   if (blockIdx.x >= nb) return;
   const JobBlock jb = map[blockIdx.x];
   const Job& J = jobs[jb.job];
   if (job_skipped(J)) return;
   const LevelGeom& g = J.geo[J.L - step];
   const AxisTab& t = g.ax[2];
-  thomas_rowscan_body<K>((step & 1) ? J.gB : J.gA, g.nc[0] * g.nc[1], g.nc[2], t.ta, t.tm, t.tc,
-                         nullptr, jb.local, jb.count);
+  thomas_rowscan_body<K>(sweep_buf(J, step, move & 1), sweep_buf(J, step, move & 2), g.nc[0] * g.nc[1], g.nc[2], t.ta, t.tm, t.tc, nullptr,
+                         jb.local, jb.count);
+}
+
+template <int K>
+__global__ __launch_bounds__(kRowBlkThreads) void kb_thomas_rowblk(
+    const Job* __restrict__ jobs, const JobBlock* __restrict__ map, uint32_t nb, int step, int move) {
+  if (blockIdx.x >= nb) return;
+  const JobBlock jb = map[blockIdx.x];
+  const Job& J = jobs[jb.job];
+  if (job_skipped(J)) return;
+  const LevelGeom& g = J.geo[J.L - step];
+  const AxisTab& t = g.ax[2];
+  thomas_rowblk_body<K>(sweep_buf(J, step, move & 1), sweep_buf(J, step, move & 2), g.nc[0] * g.nc[1], g.nc[2], t.ta, t.tm, t.tc, nullptr,
+                        jb.local, jb.count);
 }
 
 template <typename Tin>
@@ -3207,103 +3222,75 @@ void thomas_c(int axis, double* x, const int64_t nc[3], const AxisTab& t, const 
 }  // namespace
 
 namespace {
-template <int TILES, int AXIS>
-void thomas_tiles_axis(double* x, const int64_t nc[3], const AxisTab& t, const double* sub,
-                       hipStream_t s) {
-  static bool attr = false;
-  if (!attr) {
-    MGC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_thomas_tile<TILES, AXIS>),
-                                hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)thomas_tile_lds(TILES == 4 ? kThomasTile4MaxL
-                                                                : kThomasTile2MaxL, TILES)));
-    attr = true;
-  }
-  int64_t tiles;
-  if (AXIS == 2) tiles = (nc[0] * nc[1] + kTileLines - 1) / kTileLines;
-  else if (AXIS == 1) tiles = nc[0] * ((nc[2] + kTileLines - 1) / kTileLines);
-  else tiles = (nc[1] * nc[2] + kTileLines - 1) / kTileLines;
-  const int64_t blocks = (tiles + TILES - 1) / TILES;
-  hipLaunchKernelGGL((k_thomas_tile<TILES, AXIS>), dim3((unsigned)blocks), dim3(64 * TILES),
-                     thomas_tile_lds(nc[AXIS], TILES), s, x, nc[0], nc[1], nc[2], t.ta, t.tm, t.tc,
-                     sub);
-}
-template <int TILES>
-void thomas_tiles(int axis, double* x, const int64_t nc[3], const AxisTab& t, const double* sub,
-                  hipStream_t s) {
-  if (axis == 2) thomas_tiles_axis<TILES, 2>(x, nc, t, sub, s);
-  else if (axis == 1) thomas_tiles_axis<TILES, 1>(x, nc, t, sub, s);
-  else thomas_tiles_axis<TILES, 0>(x, nc, t, sub, s);
-}
-}  // namespace
-
-namespace {
 template <int K>
-void thomas_rowscan(double* x, const int64_t nc[3], const AxisTab& t, const double* sub,
-                    hipStream_t s) {
+void thomas_rowscan(const double* x, double* dst, const int64_t nc[3], const AxisTab& t,
+                    const double* sub, hipStream_t s) {
   const int64_t rows = nc[0] * nc[1];
   const int64_t blocks = std::min<int64_t>((rows + kRowScanWaves - 1) / kRowScanWaves, 4096);
   hipLaunchKernelGGL(k_thomas_rowscan<K>, dim3((unsigned)blocks), dim3(64 * kRowScanWaves), 0, s,
-                     x, rows, nc[2], t.ta, t.tm, t.tc, sub);
+                     x, dst, rows, nc[2], t.ta, t.tm, t.tc, sub);
 }
-template <int AXIS, int SEG>
-void thomas_part_axis(double* x, const int64_t nc[3], const AxisTab& t, const double* sub,
-                      hipStream_t s) {
-  const int64_t w = (nc[AXIS] + SEG - 1) / SEG;
-  const int64_t lines = AXIS == 1 ? nc[0] * nc[2] : nc[1] * nc[2];
-  const uint32_t nblk = (uint32_t)((lines + 63) / 64);
-  hipLaunchKernelGGL((k_thomas_part<AXIS, SEG>), dim3((nblk + 7u) & ~7u), dim3((unsigned)(64 * w)),
-                     0, s, x, nc[0], nc[1], nc[2], t.ta, t.tm, t.tc, sub, nblk);
+template <int K>
+void thomas_rowblk(const double* x, double* dst, const int64_t nc[3], const AxisTab& t,
+                   const double* sub, hipStream_t s) {
+  // two blocks of up to 70 KB of LDS per CU, each with several rows where
+  // there are enough (a block's first row waits for its factors and loads)
+  const int64_t rows = nc[0] * nc[1];
+  const int64_t blocks = std::min<int64_t>(rows, 1024);
+  hipLaunchKernelGGL(k_thomas_rowblk<K>, dim3((unsigned)blocks), dim3(kRowBlkThreads), 0, s, x,
+                     dst, rows, nc[2], t.ta, t.tm, t.tc, sub);
 }
-// Partitioned sweeps of class c (thomas_part_class).
-void thomas_part(int axis, int c, double* x, const int64_t nc[3], const AxisTab& t,
-                 const double* sub, hipStream_t s) {
-  if (axis == 2) {
-    const int64_t len = nc[2];
-    if (len <= 128) thomas_rowscan<2>(x, nc, t, sub, s);
-    else if (len <= 256) thomas_rowscan<4>(x, nc, t, sub, s);
-    else if (len <= 320) thomas_rowscan<5>(x, nc, t, sub, s);
-    else if (len <= 512) thomas_rowscan<8>(x, nc, t, sub, s);
-    else thomas_rowscan<16>(x, nc, t, sub, s);
-    return;
-  }
-  if (axis == 1) {
-    if (c == kPart40) thomas_part_axis<1, 40>(x, nc, t, sub, s);
-    else thomas_part_axis<1, 64>(x, nc, t, sub, s);
-  } else {
-    if (c == kPart40) thomas_part_axis<0, 40>(x, nc, t, sub, s);
-    else thomas_part_axis<0, 64>(x, nc, t, sub, s);
-  }
+template <int AXIS, int SEG, bool LONG>
+void thomas_part_axis(const double* x, double* dst, const int64_t nc[3], const AxisTab& t,
+                      const double* sub, hipStream_t s) {
+  const int64_t w = LONG ? kPartWaves : (nc[AXIS] + SEG - 1) / SEG;
+  const uint32_t nblk = thomas_part_blocks(AXIS, LONG ? kPartLong : kPart40, nc);
+  hipLaunchKernelGGL((k_thomas_part<AXIS, SEG, LONG>), dim3((nblk + 7u) & ~7u),
+                     dim3((unsigned)(64 * w)), 0, s, x, dst, nc[0], nc[1], nc[2], t.ta, t.tm, t.tc,
+                     sub, nblk);
+}
+template <int AXIS>
+void thomas_part_strided(int c, const double* x, double* dst, const int64_t nc[3],
+                         const AxisTab& t, const double* sub, hipStream_t s) {
+  if (c == kPart40) thomas_part_axis<AXIS, 40, false>(x, dst, nc, t, sub, s);
+  else if (c == kPart64) thomas_part_axis<AXIS, 64, false>(x, dst, nc, t, sub, s);
+  else thomas_part_axis<AXIS, kLongSeg, true>(x, dst, nc, t, sub, s);
 }
 }  // namespace
 
-int thomas_part_class(int axis, int64_t len) {
-  if (axis == 2) return len <= 1024 ? kPartScan : kPartNone;
-  if (len <= 40 * kPartWaves) return kPart40;
-  if (len <= 64 * kPartWaves) return kPart64;
-  return kPartNone;
+uint32_t thomas_part_blocks(int axis, int c, const int64_t nc[3]) {
+  const int64_t lines = axis == 1 ? nc[0] * nc[2] : nc[1] * nc[2];
+  const int64_t pieces = c == kPartLong ? (nc[axis] + kLongUse - 1) / kLongUse : 1;
+  return (uint32_t)((lines + 63) / 64 * pieces);
 }
 
-void launch_thomas(int axis, double* x, const int64_t nc[3], const AxisTab& t,
-                   const double* sub, hipStream_t s, int cand) {
+void launch_thomas(int axis, int cls, const double* x, double* dst, const int64_t nc[3],
+                   const AxisTab& t, const double* sub, hipStream_t s, int cand) {
   const int64_t L = nc[axis];
-  if (cand == 0) {
-    const int c = thomas_part_class(axis, L);
-    if (c != kPartNone) {
-      thomas_part(axis, c, x, nc, t, sub, s);
-      return;
+  if (cls == kPartScan) {
+    if (L <= 128) thomas_rowscan<2>(x, dst, nc, t, sub, s);
+    else if (L <= 256) thomas_rowscan<4>(x, dst, nc, t, sub, s);
+    else if (L <= 320) thomas_rowscan<5>(x, dst, nc, t, sub, s);
+    else if (L <= 512) thomas_rowscan<8>(x, dst, nc, t, sub, s);
+    else thomas_rowscan<16>(x, dst, nc, t, sub, s);
+  } else if (cls == kPartRow) {
+    if (L <= 3 * kRowBlkThreads) thomas_rowblk<3>(x, dst, nc, t, sub, s);
+    else if (L <= 5 * kRowBlkThreads) thomas_rowblk<5>(x, dst, nc, t, sub, s);
+    else if (L <= 9 * kRowBlkThreads) thomas_rowblk<9>(x, dst, nc, t, sub, s);
+    else thomas_rowblk<17>(x, dst, nc, t, sub, s);
+  } else if (cls != kPartNone) {
+    if (axis == 1) thomas_part_strided<1>(cls, x, dst, nc, t, sub, s);
+    else thomas_part_strided<0>(cls, x, dst, nc, t, sub, s);
+  } else {
+    if (x != dst) throw std::logic_error("launch_thomas: the serial sweeps run in place");
+    switch (cand) {
+      case 1: thomas_c<1>(axis, dst, nc, t, sub, s); break;
+      case 2: thomas_c<2>(axis, dst, nc, t, sub, s); break;
+      default: thomas_c<0>(axis, dst, nc, t, sub, s);
     }
   }
-  if (cand == 0 && L <= kThomasTile2MaxL && nc[0] * nc[1] * nc[2] <= kThomasTilePoints) {
-    if (L <= kThomasTile4MaxL) thomas_tiles<4>(axis, x, nc, t, sub, s);
-    else thomas_tiles<2>(axis, x, nc, t, sub, s);
-    return;
-  }
-  switch (cand) {
-    case 1: thomas_c<1>(axis, x, nc, t, sub, s); break;
-    case 2: thomas_c<2>(axis, x, nc, t, sub, s); break;
-    default: thomas_c<0>(axis, x, nc, t, sub, s);
-  }
 }
+static_assert(kRowBlkMax == 17 * kRowBlkThreads, "the row blocks' longest row");
 
 bool thomas_grid_fits(const LevelGeom& g) {
   if (g.nc[0] * g.nc[1] * g.nc[2] > kThomasGridMax) return false;
@@ -3538,24 +3525,33 @@ void launch_b_thomas(int axis, const Job* jobs, const JobBlock* map, uint32_t nb
 }
 
 void launch_b_thomas_part(int axis, int c, int waves, const Job* jobs, const JobBlock* map,
-                          uint32_t nb, int step, hipStream_t s) {
+                          uint32_t nb, int step, int move, hipStream_t s) {
   if (waves < 1 || waves > kPartWaves) throw std::logic_error("launch_b_thomas_part: waves");
   const dim3 blk((unsigned)(64 * waves));
   if (axis == 2) {
     if (c == kPartScanLong)
       hipLaunchKernelGGL(kb_thomas_rowscan<16>, dim3(nb), dim3(64 * kRowScanWaves), 0, s, jobs,
-                         map, nb, step);
+                         map, nb, step, move);
+    else if (c == kPartRow)
+      hipLaunchKernelGGL(kb_thomas_rowblk<17>, dim3(nb), dim3(kRowBlkThreads), 0, s, jobs, map,
+                         nb, step, move);
     else
       hipLaunchKernelGGL(kb_thomas_rowscan<4>, dim3(nb), dim3(64 * kRowScanWaves), 0, s, jobs,
-                         map, nb, step);
+                         map, nb, step, move);
   } else if (axis == 1) {
     if (c == kPart40)
-      hipLaunchKernelGGL((kb_thomas_part<1, 40>), dim3(nb), blk, 0, s, jobs, map, nb, step);
-    else hipLaunchKernelGGL((kb_thomas_part<1, 64>), dim3(nb), blk, 0, s, jobs, map, nb, step);
+      hipLaunchKernelGGL((kb_thomas_part<1, 40, false>), dim3(nb), blk, 0, s, jobs, map, nb, step, move);
+    else if (c == kPartLong)
+      hipLaunchKernelGGL((kb_thomas_part<1, kLongSeg, true>), dim3(nb), blk, 0, s, jobs, map, nb,
+                         step, move);
+    else hipLaunchKernelGGL((kb_thomas_part<1, 64, false>), dim3(nb), blk, 0, s, jobs, map, nb, step, move);
   } else {
     if (c == kPart40)
-      hipLaunchKernelGGL((kb_thomas_part<0, 40>), dim3(nb), blk, 0, s, jobs, map, nb, step);
-    else hipLaunchKernelGGL((kb_thomas_part<0, 64>), dim3(nb), blk, 0, s, jobs, map, nb, step);
+      hipLaunchKernelGGL((kb_thomas_part<0, 40, false>), dim3(nb), blk, 0, s, jobs, map, nb, step, move);
+    else if (c == kPartLong)
+      hipLaunchKernelGGL((kb_thomas_part<0, kLongSeg, true>), dim3(nb), blk, 0, s, jobs, map, nb,
+                         step, move);
+    else hipLaunchKernelGGL((kb_thomas_part<0, 64, false>), dim3(nb), blk, 0, s, jobs, map, nb, step, move);
   }
 }
 

@@ -210,3 +210,17 @@ def test_batch_of_256_matches_plain_and_holds_bounds(batch256):
         worst = max(worst, err / tau)
         assert err <= tau, "array %d: error %.3g above %.3g" % (j, err, tau)
     print("256 arrays: worst error / bound = %.3f" % worst)
+
+
+def test_long_lines_equal_plain():
+    """Arrays whose coarse lines exceed 512 (strided) and 1024 (contiguous)
+    values: window sweeps, block rows and moves between the grid buffers, one
+    and two per level, beside short arrays in one batch."""
+    torch, mgc = gpu()
+    shapes = [(1100, 60), (60, 2100), (1030, 1030, 3), (2200, 2100), (33, 33, 33), (1100, 4, 1100)]
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    xs = [torch.randn(s, device="cuda", generator=gen, dtype=torch.float64).cumsum(0).cumsum(-1) for s in shapes]
+    xs = [x.float() if j % 2 else x for j, x in enumerate(xs)]
+    got = mgc.compress_batched(xs, [1e-3] * len(xs), flags=mgc.BATCH_NO_TUNE)
+    for x, g in zip(xs, got):
+        assert torch.equal(g, mgc.compress(x, 1e-3))

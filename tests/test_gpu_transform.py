@@ -96,6 +96,60 @@ def test_partitioned_sweeps_match_serial_sweeps(shape):
     assert torch.max(torch.abs(rec_part - x)).item() <= 1e-12 * scale
 
 
+# lines of more than 512 values on strided axes (windows of 320 values, 256 of
+# them stored: one to nine windows, whole and remainders) and of more than
+# 1024 on the contiguous axis (a block per row, 3 to 17 values per thread):
+# one and two window axes, beside short ones, at the longest row the blocks
+# take and one past it (where every axis falls back to the serial sweeps)
+LONG_SHAPES = [(1025, 1025), (1026, 2050), (1535, 200), (1537, 70), (4500, 33), (5, 2049), (1030, 1030, 3),
+               (1100, 4, 1100), (20, 1100, 40), (7, 5130), (70, 9300), (9, 17407), (1100, 17409)]
+
+
+@pytest.mark.parametrize("shape", LONG_SHAPES)
+def test_long_lines_match_serial_sweeps(shape):
+    """The sweeps of long lines against the serial ones (forced candidate 1),
+    up to the rounding of FP64 sums, both directions and the adjoint (whose
+    solves have no forced form: <R x, y> = <x, R^T y>)."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(17)
+    x = torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen)
+    x = x.cumsum(0).cumsum(-1) * 0.05 + x
+    scale = torch.max(torch.abs(x)).item()
+    c = mgc.decompose(x)
+    r = mgc.recompose(c, shape, torch.float64)
+    r32 = mgc.recompose(c, shape, torch.float32)
+    mgc.set_tuning("thomas_strided", 1)
+    mgc.set_tuning("thomas_rows", 1)
+    try:
+        cs = mgc.decompose(x)
+        rs = mgc.recompose(c, shape, torch.float64)
+    finally:
+        mgc.set_tuning("thomas_strided", -1)
+        mgc.set_tuning("thomas_rows", -1)
+    assert torch.max(torch.abs(c - cs)).item() <= 1e-13 * scale
+    assert torch.max(torch.abs(r - rs)).item() <= 1e-13 * scale
+    assert torch.max(torch.abs(r - x)).item() <= 1e-12 * scale
+    assert torch.equal(r32, r.float())
+    y = torch.randn(shape, dtype=torch.float64, device="cuda", generator=gen)
+    z = torch.randn(x.numel(), dtype=torch.float64, device="cuda", generator=gen)
+    lhs = torch.sum(mgc.recompose(z, shape) * y).item()
+    rhs = torch.sum(z * mgc.recompose_adjoint(y)).item()
+    assert abs(lhs - rhs) <= 1e-11 * max(abs(lhs), 1.0) * x.numel() ** 0.5
+
+
+def test_long_lines_without_a_second_buffer():
+    """Decompression into an output that cannot hold FP64 values (its start is
+    not a multiple of eight bytes) solves long lines serially: the values
+    differ by roundings of the output type at most."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(3)
+    x = torch.randn((1100, 1200), device="cuda", generator=gen).cumsum(0).cumsum(1)
+    s = mgc.compress(x, 1e-3)
+    a = mgc.decompress(s)
+    b = mgc.decompress(s, out=torch.empty(x.numel() + 1, device="cuda")[1:].view(1100, 1200))
+    assert torch.max(torch.abs(a - b)).item() <= 2.0 ** -23 * torch.max(torch.abs(a)).item()
+
+
 def _leave_nan_in_lds(torch):
     """Runs library kernels of torch's that stage NaN doubles in LDS on every
     CU (a block scan and a row softmax over NaN inputs), so that the next
