@@ -157,6 +157,14 @@ mgc_status mgc_compress_noalloc(mgc_ctx ctx, const void* d_in, int ndim, const u
  * ---------------------------------------------------------------------- */
 mgc_status mgc_header_info(const void* h_prefix, size_t n, int* ndim, uint64_t* shape3,
                            mgc_dtype* dtype, uint64_t* stream_bytes, size_t* ws_bytes);
+/* The first n (at most 4096) bytes of device memory at d_in to h_out, in stream
+ * order (BLOCKING); and mgc_decompress for a caller that holds the stream's
+ * first bytes (as for mgc_header_info) on the host already, so that the header
+ * is read from the device once. */
+mgc_status mgc_read_prefix(mgc_ctx ctx, const void* d_in, size_t n, void* h_out, void* stream);
+mgc_status mgc_decompress_head(mgc_ctx ctx, const void* h_prefix, size_t n, const void* d_in,
+                               size_t in_bytes, void* d_out, size_t out_cap, void* d_ws,
+                               size_t ws_bytes, void* stream);
 mgc_status mgc_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, void* d_out,
                           size_t out_cap, void* d_ws, size_t ws_bytes, void* stream);
 

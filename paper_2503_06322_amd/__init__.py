@@ -109,6 +109,9 @@ def _load():
             "mgc_header_info": [vp, ctypes.c_size_t, ctypes.POINTER(ctypes.c_int), c_u64p,
                                 ctypes.POINTER(ctypes.c_int), c_u64p, c_szp],
             "mgc_decompress": [vp, vp, ctypes.c_size_t, vp, ctypes.c_size_t, vp, ctypes.c_size_t, vp],
+            "mgc_read_prefix": [vp, vp, ctypes.c_size_t, vp, vp],
+            "mgc_decompress_head": [vp, vp, ctypes.c_size_t, vp, ctypes.c_size_t, vp,
+                                    ctypes.c_size_t, vp, ctypes.c_size_t, vp],
             "mgc_transform_query": [ctypes.c_int, c_u64p, c_szp],
             "mgc_decompose": [vp, vp, ctypes.c_int, c_u64p, ctypes.c_int, vp, vp, ctypes.c_size_t, vp],
             "mgc_recompose": [vp, vp, ctypes.c_int, c_u64p, ctypes.c_int, vp, vp, ctypes.c_size_t, vp],
@@ -339,7 +342,7 @@ def compress(x, error_bound: float, norm: str = "linf", mode: str = "rel",
         ws = workspace if workspace is not None and workspace.numel() >= ws_n else _empty(ws_n, x.device)
         ob = out if out is not None and out.numel() >= out_n else _empty(out_n, x.device)
         compress_async(x, error_bound, norm, mode, outlier_cap, ws, ob, result)
-        st, size = (int(v) for v in result.cpu().tolist())
+        st, size = _result_words(result)
         if st == 3 and size > outlier_cap:
             outlier_cap = size   # more escaped values than room: retry once
             continue
@@ -487,18 +490,41 @@ def decoder_info(device=None):
     return ring.value, waves.value
 
 
+def _prefix(stream, n: int) -> bytes:
+    """The first n bytes (fewer if it is shorter) of a uint8 stream."""
+    n = min(int(stream.numel()), n)
+    if not (stream.is_cuda and stream.is_contiguous() and stream.element_size() == 1):
+        import numpy as np
+        host = stream[:n].cpu().numpy() if stream.is_cuda else np.asarray(stream[:n])
+        return np.ascontiguousarray(host, dtype=np.uint8).tobytes()
+    dev = stream.device.index if stream.device.index is not None else _torch().cuda.current_device()
+    buf = ctypes.create_string_buffer(max(n, 1))
+    _check(_load().mgc_read_prefix(_ctx(dev), ctypes.c_void_p(stream.data_ptr()), n, buf,
+                                   _stream_ptr(dev)))
+    return buf.raw[:n]
+
+
+def _result_words(result):
+    """(status, stream bytes) from the two result words of an enqueued call."""
+    dev = result.device.index
+    buf = (ctypes.c_int64 * 2)()
+    _check(_load().mgc_read_prefix(_ctx(dev), ctypes.c_void_p(result.data_ptr()), 16, buf,
+                                   _stream_ptr(dev)))
+    return buf[0], buf[1]
+
+
 def header_info(stream):
     """Shape, dtype and sizes of a compressed stream (reads its header)."""
-    import numpy as np
-    n = min(int(stream.numel()), HEADER_PREFIX)
-    host = stream[:n].cpu().numpy() if stream.is_cuda else np.asarray(stream[:n])
-    buf = np.ascontiguousarray(host, dtype=np.uint8)
+    return _header_info(_prefix(stream, HEADER_PREFIX))
+
+
+def _header_info(head: bytes):
     ndim = ctypes.c_int()
     shp = (ctypes.c_uint64 * 3)()
     dt = ctypes.c_int()
     total = ctypes.c_uint64()
     ws = ctypes.c_size_t()
-    _check(_load().mgc_header_info(buf.ctypes.data_as(ctypes.c_void_p), n, ctypes.byref(ndim), shp,
+    _check(_load().mgc_header_info(head, len(head), ctypes.byref(ndim), shp,
                                    ctypes.byref(dt), ctypes.byref(total), ctypes.byref(ws)))
     torch = _torch()
     return {"shape": tuple(int(shp[i]) for i in range(ndim.value)),
@@ -515,14 +541,21 @@ def decompress(stream, workspace=None, out=None, info=None):
     _require_gpu(stream, "stream")
     torch = _torch()
     dev = stream.device.index if stream.device.index is not None else torch.cuda.current_device()
-    info = info or header_info(stream)
+    head = None
+    if not info:
+        head = _prefix(stream, HEADER_PREFIX)
+        info = _header_info(head)
     res = out if out is not None else torch.empty(info["shape"], dtype=info["dtype"], device=stream.device)
     ws = workspace if workspace is not None and workspace.numel() >= info["workspace_bytes"] \
         else _empty(info["workspace_bytes"], stream.device)
     stream = stream.contiguous()
-    _check(_load().mgc_decompress(_ctx(dev), ctypes.c_void_p(stream.data_ptr()), stream.numel(),
-                                  ctypes.c_void_p(res.data_ptr()), res.numel() * res.element_size(),
-                                  ctypes.c_void_p(ws.data_ptr()), ws.numel(), _stream_ptr(dev)))
+    args = (ctypes.c_void_p(stream.data_ptr()), stream.numel(), ctypes.c_void_p(res.data_ptr()),
+            res.numel() * res.element_size(), ctypes.c_void_p(ws.data_ptr()), ws.numel(),
+            _stream_ptr(dev))
+    if head is not None:
+        _check(_load().mgc_decompress_head(_ctx(dev), head, len(head), *args))
+    else:
+        _check(_load().mgc_decompress(_ctx(dev), *args))
     return res
 
 
@@ -742,7 +775,7 @@ def hx_compress(x, dict: int | None = None, base: int | None = None, C: int = 10
                                    ctypes.c_void_p(res.data_ptr()), _stream_ptr(dev)))
     if not sync:
         return o, res
-    st, size = (int(v) for v in res.cpu())
+    st, size = _result_words(res)
     if st:
         raise MgcError(st, "Huffman-X compression failed on the device")
     return o[:size]
@@ -750,7 +783,7 @@ def hx_compress(x, dict: int | None = None, base: int | None = None, C: int = 10
 
 def hx_header(stream):
     """(dtype, n, dict, base, C, total) of a Huffman-X stream."""
-    head = stream[:64].cpu().numpy().tobytes()
+    head = _prefix(stream, 64)
     t = ctypes.c_int()
     n = ctypes.c_uint64()
     d = ctypes.c_uint32()
@@ -806,7 +839,7 @@ def zfp_compress(x, rate: float, out=None, result=None, sync: bool = True):
                                     o.numel(), ctypes.c_void_p(res.data_ptr()), _stream_ptr(dev)))
     if not sync:
         return o, res
-    st, size = (int(v) for v in res.cpu())
+    st, size = _result_words(res)
     if st:
         raise MgcError(st, "fixed-rate coding failed: the data holds NaN or Inf")
     return o[:size]
@@ -818,7 +851,7 @@ def zfp_decompress(stream, out=None):
     torch = _torch()
     stream = stream.contiguous()
     dev = stream.device.index if stream.device.index is not None else torch.cuda.current_device()
-    head = stream[:64].cpu().numpy().tobytes()
+    head = _prefix(stream, 64)
     nd = ctypes.c_int()
     shp = (ctypes.c_uint64 * 3)()
     dt = ctypes.c_int()

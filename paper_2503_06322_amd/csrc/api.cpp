@@ -632,7 +632,7 @@ mgc_status mgc_compress_query(int ndim, const uint64_t* shape, mgc_dtype dtype,
                               uint64_t outlier_cap, size_t* ws_bytes, size_t* max_out_bytes) {
   return guard([&] {
     if (dtype != MGC_F32 && dtype != MGC_F64) fail(MGC_EINVAL, "dtype must be f32 or f64");
-    Plan p = build_plan(ndim, shape);
+    Plan p = build_plan(ndim, shape, false);
     const uint64_t cap = outlier_cap ? outlier_cap : default_outlier_cap(p.N);
     Carver c(nullptr);
     carve_compress(c, p, cap);
@@ -850,7 +850,7 @@ mgc_status mgc_header_info(const void* h_prefix, size_t n, int* ndim, uint64_t* 
     if (dtype) *dtype = (mgc_dtype)h.dtype;
     if (stream_bytes) *stream_bytes = h.total;
     if (ws_bytes) {
-      Plan p = build_plan(h.ndim, h.shape);
+      Plan p = build_plan(h.ndim, h.shape, false);
       Carver c(nullptr);
       carve_decompress(c, p);
       *ws_bytes = c.off;
@@ -858,18 +858,30 @@ mgc_status mgc_header_info(const void* h_prefix, size_t n, int* ndim, uint64_t* 
   });
 }
 
-mgc_status mgc_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, void* d_out,
-                          size_t out_cap, void* d_ws, size_t ws_bytes, void* stream) {
+mgc_status mgc_read_prefix(mgc_ctx ctx, const void* d_in, size_t n, void* h_out, void* stream) {
   return guard([&] {
     check_ctx(ctx);
-    if (!d_in) fail(MGC_EINVAL, "null input");
+    if (n > 4096) fail(MGC_EINVAL, "prefixes of at most 4096 bytes");
+    if (n == 0) return;
+    if (!d_in || !h_out) fail(MGC_EINVAL, "null pointer");
+    sync_read(ctx, ctx->pinned, d_in, n, as_stream(stream));
+    std::memcpy(h_out, ctx->pinned, n);
+  });
+}
+
+mgc_status mgc_decompress_head(mgc_ctx ctx, const void* h_prefix, size_t n, const void* d_in,
+                               size_t in_bytes, void* d_out, size_t out_cap, void* d_ws,
+                               size_t ws_bytes, void* stream) {
+  return guard([&] {
+    check_ctx(ctx);
+    if (!d_in || !h_prefix) fail(MGC_EINVAL, "null input");
     hipStream_t s = as_stream(stream);
-    const size_t pre = std::min<size_t>(in_bytes, kHeaderBytes + 8 * (kMaxLevels + 1));
+    const size_t pre = std::min(std::min(n, in_bytes),
+                                (size_t)kHeaderBytes + 8 * (kMaxLevels + 1));
     if (pre < (size_t)kHeaderBytes) fail(MGC_EFORMAT, "stream shorter than its header");
-    sync_read(ctx, ctx->pinned, d_in, pre, s);
-    std::vector<uint8_t> head(ctx->pinned, ctx->pinned + pre);
     const unsigned* status =
-        decompress_enqueue(ctx, head.data(), pre, d_in, in_bytes, d_out, out_cap, d_ws, ws_bytes, s);
+        decompress_enqueue(ctx, static_cast<const uint8_t*>(h_prefix), pre, d_in, in_bytes, d_out,
+                           out_cap, d_ws, ws_bytes, s);
     if (!status) return;
     unsigned st = 0;
     sync_read(ctx, ctx->pinned, status, sizeof(unsigned), s);
@@ -878,9 +890,24 @@ mgc_status mgc_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, void* 
   });
 }
 
+mgc_status mgc_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, void* d_out,
+                          size_t out_cap, void* d_ws, size_t ws_bytes, void* stream) {
+  uint8_t head[kHeaderBytes + 8 * (kMaxLevels + 1)];
+  const size_t pre = std::min(in_bytes, sizeof(head));
+  const mgc_status st = guard([&] {
+    check_ctx(ctx);
+    if (!d_in) fail(MGC_EINVAL, "null input");
+  });
+  if (st != MGC_OK) return st;
+  const mgc_status rd = mgc_read_prefix(ctx, d_in, pre, head, stream);
+  if (rd != MGC_OK) return rd;
+  return mgc_decompress_head(ctx, head, pre, d_in, in_bytes, d_out, out_cap, d_ws, ws_bytes,
+                             stream);
+}
+
 mgc_status mgc_transform_query(int ndim, const uint64_t* shape, size_t* ws_bytes) {
   return guard([&] {
-    Plan p = build_plan(ndim, shape);
+    Plan p = build_plan(ndim, shape, false);
     const int64_t n_coarse = p.L >= 1 ? p.points(p.L - 1) : 1;
     Carver c(nullptr);
     c.take<double>(n_coarse);
@@ -956,7 +983,7 @@ size_t levels_bytes_of(const Plan& p) {
 
 mgc_status mgc_adjoint_query(int ndim, const uint64_t* shape, size_t* ws_bytes) {
   return guard([&] {
-    Plan p = build_plan(ndim, shape);
+    Plan p = build_plan(ndim, shape, false);
     Carver c(nullptr);
     carve_adjoint(c, p);
     if (ws_bytes) *ws_bytes = c.off;
@@ -1001,7 +1028,7 @@ mgc_status mgc_recompose_adjoint(mgc_ctx ctx, const double* d_grad_u, int ndim,
 
 mgc_status mgc_levels_query(int ndim, const uint64_t* shape, size_t* levels_bytes) {
   return guard([&] {
-    Plan p = build_plan(ndim, shape);
+    Plan p = build_plan(ndim, shape, false);
     if (levels_bytes) *levels_bytes = levels_bytes_of(p);
   });
 }

@@ -465,7 +465,7 @@ mgc_status mgc_batch_query(int n, const int* ndims, const uint64_t* shapes,
     check_batch_args(n, ndims, shapes, dtypes);
     std::vector<Plan> plans;
     plans.reserve(n);
-    for (int j = 0; j < n; ++j) plans.push_back(build_plan(ndims[j], shapes + 3 * j));
+    for (int j = 0; j < n; ++j) plans.push_back(build_plan(ndims[j], shapes + 3 * j, false));
     std::vector<const Plan*> pp;
     for (auto& p : plans) pp.push_back(&p);
     std::vector<uint64_t> cap;

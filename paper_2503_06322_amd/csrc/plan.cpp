@@ -50,7 +50,7 @@ double mass_entry(const std::vector<double>& x, int64_t f, int64_t g) {
 
 }  // namespace
 
-Plan build_plan(int ndim, const uint64_t* shape) {
+Plan build_plan(int ndim, const uint64_t* shape, bool tables) {
   Plan p;
   if (ndim < 1) fail(MGC_EINVAL, "ndim must be at least 1");
   if (ndim > 3) fail(MGC_EUNSUPPORTED, "ndim above 3 is not supported");
@@ -75,7 +75,7 @@ Plan build_plan(int ndim, const uint64_t* shape) {
   // hierarchy: collect levels finest first
   std::vector<std::array<int64_t, 3>> fine_first{{p.n[0], p.n[1], p.n[2]}};
   std::vector<std::array<std::vector<double>, 3>> coords(1);
-  for (int k = 0; k < 3; ++k) {
+  for (int k = 0; k < 3 && tables; ++k) {
     coords[0][k].resize(p.n[k]);
     for (int64_t i = 0; i < p.n[k]; ++i) coords[0][k][i] = (double)i;
   }
@@ -89,13 +89,8 @@ Plan build_plan(int ndim, const uint64_t* shape) {
       std::array<int64_t, 3> nxt;
       std::array<std::vector<double>, 3> c;
       for (int k = 0; k < 3; ++k) {
-        if (p.bit[k] >= 0) {
-          c[k] = coarse_coords(coords.back()[k]);
-          nxt[k] = (int64_t)c[k].size();
-        } else {
-          c[k] = coords.back()[k];
-          nxt[k] = cur[k];
-        }
+        nxt[k] = p.bit[k] >= 0 ? cur[k] / 2 + 1 : cur[k];
+        if (tables) c[k] = p.bit[k] >= 0 ? coarse_coords(coords.back()[k]) : coords.back()[k];
       }
       fine_first.push_back(nxt);
       coords.push_back(c);
@@ -136,8 +131,7 @@ Plan build_plan(int ndim, const uint64_t* shape) {
         }
         acc += sz;
       }
-      // tables
-      for (int k = 0; k < 3; ++k) {
+      for (int k = 0; k < 3 && tables; ++k) {
         const int64_t nf = v.nf[k], nc = v.nc[k];
         const auto& xf = coords[l][k];
         const auto& xc = coords[l - 1][k];

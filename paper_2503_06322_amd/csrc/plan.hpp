@@ -44,7 +44,9 @@ struct Plan {
 };
 
 // Builds the plan (host tables only).  Throws Fail on invalid shapes.
-Plan build_plan(int ndim, const uint64_t* shape);
+// With tables false only the level sizes and stream offsets are filled in
+// (all that size queries need; the tables take 0.1 ms at 513^3, 0.5 ms at 8193^2).
+Plan build_plan(int ndim, const uint64_t* shape, bool tables = true);
 void upload_plan(Plan& p);
 // The plan's device block as host bytes, with every device pointer of the
 // plan (tables, bin factors, geometry) set to point into a block at `base`;
