@@ -53,6 +53,109 @@ __device__ __forceinline__ void emit_q(int64_t pos, double c, double r, uint16_t
   }
 }
 
+// Escaped values of a block on their way to the outlier records: every device
+// atomic on the one record counter costs about 3 ns, whichever blocks they
+// come from (at half a percent of escapes the finest level of 300x400x500
+// took 785 us with one per coefficient and wavefront, 605 us with one per cell
+// and wavefront and takes 179 us with this list), so a block collects them in LDS
+// and reserves their records together.  Values that find the list full take
+// records of their own.
+template <int CAP>
+struct EscList {
+  unsigned n, lim;          // slots reserved; the first reservation that did not fit
+  unsigned long long base;  // first record of the flush in progress
+  int64_t val[CAP];
+  uint32_t pos[CAP];
+};
+template <int CAP>
+__device__ __forceinline__ void esc_reset(EscList<CAP>& el) {
+  if (threadIdx.x == 0) {
+    el.n = 0;
+    el.lim = CAP;
+  }
+}
+// Whole block, between barriers that order it against emit_cell.
+template <int CAP>
+__device__ __forceinline__ void esc_flush(EscList<CAP>& el, const OutlierBuf& ob) {
+  const unsigned n = min(el.n, el.lim);
+  if (threadIdx.x == 0) el.base = atomicAdd(ob.count, (unsigned long long)n);
+  __syncthreads();
+  const unsigned long long base = el.base;
+  for (unsigned i = threadIdx.x; i < n; i += blockDim.x) {
+    if (base + i < ob.cap) {
+      ob.pos[base + i] = el.pos[i];
+      ob.val[base + i] = el.val[i];
+    }
+  }
+}
+
+// The (up to seven) coefficients of a coarse cell at once: the symbols are
+// stored, and the escaped values of the wavefront take their slots with one
+// LDS add (or, past the list, their records with one device add).
+template <bool QUANT, int CAP>
+__device__ __forceinline__ void emit_cell(const uint32_t (&pos)[7], const double (&v)[7],
+                                          const bool (&ok)[7], double r, uint16_t* sym,
+                                          double* raw, const OutlierBuf& ob, unsigned* status,
+                                          EscList<CAP>& el) {
+  if constexpr (!QUANT) {
+#pragma unroll
+    for (int k = 0; k < 7; ++k)
+      if (ok[k]) raw[pos[k]] = v[k];
+    return;
+  }
+  double t[7];
+  unsigned esc = 0;
+#pragma unroll
+  for (int k = 0; k < 7; ++k) {
+    t[k] = rint(v[k] * r);
+    const bool in = fabs(t[k]) < 32768.0;
+    if (ok[k]) sym[pos[k]] = (uint16_t)(int)((in ? t[k] : -32768.0) + 32768.0);
+    esc |= ok[k] && !in ? 1u << k : 0u;
+  }
+  if (__ballot(esc != 0) == 0) return;
+  // exclusive prefix of the escapes (at most 7) over the lanes, from the three
+  // bits of their number
+  const unsigned ne = (unsigned)__popc(esc);
+  const int lane = (int)__lane_id();
+  const uint64_t lt = (1ull << lane) - 1;
+  unsigned excl = 0, tot = 0;
+#pragma unroll
+  for (int bit = 0; bit < 3; ++bit) {
+    const uint64_t bm = __ballot((ne >> bit) & 1u);
+    excl += (unsigned)__popcll(bm & lt) << bit;
+    tot += (unsigned)__popcll(bm) << bit;
+  }
+  const int leader = __ffsll((unsigned long long)__ballot(true)) - 1;
+  unsigned slot = 0;
+  unsigned long long rec = 0;
+  if (lane == leader) {
+    slot = atomicAdd(&el.n, tot);
+    if (slot + tot > (unsigned)CAP) {
+      atomicMin(&el.lim, slot);
+      rec = atomicAdd(ob.count, (unsigned long long)tot);
+    }
+  }
+  slot = (unsigned)__shfl((int)slot, leader, 64);
+  const bool listed = slot + tot <= (unsigned)CAP;
+  if (!listed) rec = __shfl(rec, leader, 64);
+  unsigned long long j = (listed ? slot : rec) + excl;
+#pragma unroll
+  for (int k = 0; k < 7; ++k) {
+    if (!((esc >> k) & 1u)) continue;
+    int64_t kv = 0;
+    if (fabs(t[k]) < 4611686018427387904.0) kv = (int64_t)t[k];
+    else atomicOr(status, ST_RANGE);
+    if (listed) {
+      el.pos[j] = pos[k];
+      el.val[j] = kv;
+    } else if (j < ob.cap) {
+      ob.pos[j] = pos[k];
+      ob.val[j] = kv;
+    }
+    ++j;
+  }
+}
+
 // Coefficient at stream position pos: raw FP64, or dequantised k * q with
 // escaped values found by binary search in the sorted outlier positions.
 // w0 a + w1 b as one multiply and one fused multiply-add (every variant of
@@ -552,11 +655,13 @@ __device__ void restrict_tile(const V* tile, double* A, double* B, const Tile& t
 // seven stream positions share (J0*e1 + J1)*e2 + J2 with per-subband extents,
 // and consecutive threads take consecutive cells along x, so each subband's
 // stores are contiguous.
+constexpr int kTileEsc = 96;  // escaped values a tile collects
 template <typename Tin, int TZ, int TY, int TX, int E1, int E2, bool QUANT, typename TT>
 __device__ __forceinline__ void lerp_cells(const Tin* tile, const Tile& tl, const TT& tb,
                                            const LevelGeom& g, uint16_t* __restrict__ sym,
                                            double* __restrict__ raw, double r,
-                                           const OutlierBuf& ob, unsigned* __restrict__ status) {
+                                           const OutlierBuf& ob, unsigned* __restrict__ status,
+                                           EscList<kTileEsc>& el) {
   constexpr int NC = TZ * TY * TX;
   const uint32_t e1c = tl.nc[1], e1n = tl.nf[1] - tl.nc[1];
   const uint32_t e2c = tl.nc[2], e2n = tl.nf[2] - tl.nc[2];
@@ -564,16 +669,13 @@ __device__ __forceinline__ void lerp_cells(const Tin* tile, const Tile& tl, cons
   const int m0 = g.bit[0] >= 0 ? 1 << g.bit[0] : 0, m1 = g.bit[1] >= 0 ? 1 << g.bit[1] : 0,
             m2 = g.bit[2] >= 0 ? 1 << g.bit[2] : 0;
   auto T = [&](int z, int y, int x) -> double { return (double)tile[(z * E1 + y) * E2 + x]; };
-  auto emit = [&](uint32_t pos, double v) {
-    if (QUANT) emit_q(pos, v, r, sym, ob, status);
-    else raw[pos] = v;
-  };
   for (int e = threadIdx.x; e < NC; e += 256) {
     const int cx = e % TX, rest = e / TX, cy = rest % TY, cz = rest / TY;
     if (cz >= tl.tk[0] || cy >= tl.tk[1] || cx >= tl.tk[2]) continue;
     const uint32_t J0 = tl.c0[0] + cz, J1 = tl.c0[1] + cy, J2 = tl.c0[2] + cx;
-    const bool h0 = 2 * J0 + 1 < tl.nf[0] - 1, h1 = 2 * J1 + 1 < tl.nf[1] - 1,
-               h2 = 2 * J2 + 1 < tl.nf[2] - 1;
+    // (an extent of one marks an inactive axis, which has no new nodes)
+    const bool h0 = TZ > 1 && 2 * J0 + 1 < tl.nf[0] - 1,
+               h1 = TY > 1 && 2 * J1 + 1 < tl.nf[1] - 1, h2 = 2 * J2 + 1 < tl.nf[2] - 1;
     if (!(h0 || h1 || h2)) continue;
     // tile-relative fine positions: cell origin p, new node p+1, next corner
     const int p0 = (int)(cpos32(J0, tl.nf[0]) - tl.lo[0]);
@@ -591,19 +693,21 @@ __device__ __forceinline__ void lerp_cells(const Tin* tile, const Tile& tl, cons
     const double ix10 = lin2(wx0, c100, wx1, c101), ix11 = lin2(wx0, c110, wx1, c111);
     const uint32_t base_cc = (J0 * e1c + J1) * e2c + J2, base_cn = (J0 * e1c + J1) * e2n + J2;
     const uint32_t base_nc = (J0 * e1n + J1) * e2c + J2, base_nn = (J0 * e1n + J1) * e2n + J2;
-    if (h2) emit(lvl + tb.soff[m2] + base_cn, T(p0, p1, q2) - ix00);
-    if (h1) emit(lvl + tb.soff[m1] + base_nc, T(p0, q1, p2) - (lin2(wy0, c000, wy1, c010)));
-    if (h1 && h2)
-      emit(lvl + tb.soff[m1 | m2] + base_nn, T(p0, q1, q2) - (lin2(wy0, ix00, wy1, ix01)));
-    if (h0) emit(lvl + tb.soff[m0] + base_cc, T(q0, p1, p2) - (lin2(wz0, c000, wz1, c100)));
-    if (h0 && h2)
-      emit(lvl + tb.soff[m0 | m2] + base_cn, T(q0, p1, q2) - (lin2(wz0, ix00, wz1, ix10)));
-    if (h0 && h1)
-      emit(lvl + tb.soff[m0 | m1] + base_nc,
-           T(q0, q1, p2) - (lin2(wz0, lin2(wy0, c000, wy1, c010), wz1, lin2(wy0, c100, wy1, c110))));
-    if (h0 && h1 && h2)
-      emit(lvl + tb.soff[m0 | m1 | m2] + base_nn,
-           T(q0, q1, q2) - (lin2(wz0, lin2(wy0, ix00, wy1, ix01), wz1, lin2(wy0, ix10, wy1, ix11))));
+    const bool ok[7] = {h2, h1, h1 && h2, h0, h0 && h2, h0 && h1, h0 && h1 && h2};
+    const uint32_t pos[7] = {lvl + tb.soff[m2] + base_cn,           lvl + tb.soff[m1] + base_nc,
+                             lvl + tb.soff[m1 | m2] + base_nn,      lvl + tb.soff[m0] + base_cc,
+                             lvl + tb.soff[m0 | m2] + base_cn,      lvl + tb.soff[m0 | m1] + base_nc,
+                             lvl + tb.soff[m0 | m1 | m2] + base_nn};
+    const double iy0 = lin2(wy0, c000, wy1, c010), iy1 = lin2(wy0, c100, wy1, c110);
+    const double ixy0 = lin2(wy0, ix00, wy1, ix01), ixy1 = lin2(wy0, ix10, wy1, ix11);
+    const double v[7] = {T(p0, p1, q2) - ix00,
+                         T(p0, q1, p2) - iy0,
+                         T(p0, q1, q2) - ixy0,
+                         T(q0, p1, p2) - lin2(wz0, c000, wz1, c100),
+                         T(q0, p1, q2) - lin2(wz0, ix00, wz1, ix10),
+                         T(q0, q1, p2) - lin2(wz0, iy0, wz1, iy1),
+                         T(q0, q1, q2) - lin2(wz0, ixy0, wz1, ixy1)};
+    emit_cell<QUANT>(pos, v, ok, r, sym, raw, ob, status, el);
   }
 }
 
@@ -624,7 +728,9 @@ __device__ __forceinline__ void dec_level_body(const Tin* __restrict__ G, const 
   __shared__ __align__(16) unsigned char smem[TILE_BYTES];
   __shared__ double A[E0 * E1 * TX];
   __shared__ TileTabs<E0, E1, E2, TZ, TY, TX> tb;
+  __shared__ EscList<kTileEsc> el;
   Tin* tile = reinterpret_cast<Tin*>(smem);
+  if (MODE == 0) esc_reset(el);
 
   const uint32_t tiles_x = (uint32_t)((g.nc[2] + TX - 1) / TX);
   const uint32_t tiles_y = (uint32_t)((g.nc[1] + TY - 1) / TY);
@@ -659,9 +765,12 @@ __device__ __forceinline__ void dec_level_body(const Tin* __restrict__ G, const 
 
   // lerp + quantise the owned new nodes, one coarse cell (the 2x2x2 fine
   // nodes a coarse node owns) at a time
-  if (MODE != 2) lerp_cells<Tin, TZ, TY, TX, E1, E2, MODE == 0>(tile, tl, tb, g, sym, raw, r, ob, status);
+  if (MODE != 2)
+    lerp_cells<Tin, TZ, TY, TX, E1, E2, MODE == 0>(tile, tl, tb, g, sym, raw, r, ob, status, el);
   // mass_trans (or P^T for the adjoint): separable restriction to the coarse outputs
   restrict_tile(tile, A, reinterpret_cast<double*>(smem), tl, tb, fout, MODE == 2 ? raw : nullptr);
+  // (the restriction's barriers lie between the cells and this)
+  if (MODE == 0 && el.n != 0) esc_flush(el, ob);
 }
 
 template <typename Tin, int TZ, int TY, int TX, int MODE>
@@ -682,48 +791,50 @@ __global__ __launch_bounds__(256) void k_dec_level(const Tin* __restrict__ G, co
 
 // ------------------------------- decomposition of a 3-axis level, streamed
 // A block owns a column of SY x SX coarse outputs (fine region with a
-// two-node halo in y and x) and walks a segment of coarse z planes.  Each
-// fine plane is loaded once (the next plane's loads in flight while the
-// current one is processed), restricted along x and then y; the y results of
-// the last five fine planes and the raw values of the last three stay in
-// LDS rings.  When the five planes around a coarse plane are in, its outputs
-// are restricted along z and its cells are interpolated and quantised.  The
-// sums are formed in the same order as in the tiled kernel (x, y, z; taps in
-// order), so the results are the same; the z halo is paid once per segment
-// instead of once per tile.
+// two-node halo in y and x) and walks a segment of coarse z planes, two fine
+// planes a step: they go to an LDS ring (the next two's loads in flight), are
+// restricted along x into LDS and along y by the thread that owns the output,
+// which keeps the last five planes' values in registers for the z taps, and
+// then finishes one coarse plane: its restriction, and its cell's
+// interpolation and quantisation from the raw ring.  The corners a cell shares
+// with the one below come over in registers.  The sums are formed in the same
+// order as in the tiled kernel (x, y, z; taps in order), so the results are
+// the same; the z halo is paid once per segment instead of once per tile.
+// The region's slots outside the grid hold zeros and every tap index is a
+// base plus a constant, so LDS reads pair up.
+// Bound by instruction issue and LDS, with two barriers a step (513^3 FP32:
+// 397 us; with one plane a step, four barriers and the y results and corners
+// through LDS, 509 us).
 constexpr int kStreamSY = 8, kStreamSX = 32;
 constexpr int kStreamE1 = 2 * kStreamSY + 3, kStreamE2 = 2 * kStreamSX + 3;
 constexpr int kStreamNLD = (kStreamE1 * kStreamE2 + 255) / 256;
+constexpr int kStreamEsc = 320;  // escaped values a block collects between flushes
 constexpr int kStreamPF = 2;     // fine planes whose loads are in flight (recomposition)
-constexpr int kDecStreamPF = 1;  // (decomposition: registers go to the cells)
 // levels with fewer fine points use the tiled kernel (measured faster there)
 constexpr int64_t kStreamMinPoints = int64_t(1) << 25;
 // Recomposition's restriction (one value per coarse node from the dequantised
 // new nodes) gains from streaming already at half that size.
 constexpr int64_t kRecStreamMinPoints = int64_t(1) << 24;
 
+// Raw planes kept: the three a cell spans and, where LDS allows four blocks
+// per CU, the two the next step writes while slower wavefronts still read
+// (FP64 planes would leave two blocks: three planes and one more barrier).
 template <typename Tin>
-struct StreamSmem {
-  Tin raw[3][kStreamE1][kStreamE2];
-  double X[kStreamE1][kStreamSX];
-  double Y[5][kStreamSY][kStreamSX];
-  double wl1[kStreamE1], wr1[kStreamE1], wl2[kStreamE2], wr2[kStreamE2];
-  double W1[kStreamSY][5], W2[kStreamSX][5];
-  int P1[kStreamSY], P2[kStreamSX];
-};
+constexpr int kStreamRing = sizeof(Tin) == 4 ? 5 : 3;
 
 template <typename Tin, bool QUANT>
-__global__ __launch_bounds__(256, 4) void k_dec_stream(const Tin* __restrict__ G, const LevelGeom g,
-                                                     double* __restrict__ fout,
-                                                     uint16_t* __restrict__ sym,
-                                                     double* __restrict__ raw,
-                                                     const double* __restrict__ rp,
-                                                     const OutlierBuf ob,
-                                                     unsigned* __restrict__ status,
-                                                     const unsigned* __restrict__ gate,
-                                                     const int seg, const uint32_t n_blocks) {
-  constexpr int SY = kStreamSY, SX = kStreamSX, E2 = kStreamE2;
-  __shared__ StreamSmem<Tin> sm;
+__global__ __launch_bounds__(256, sizeof(Tin) == 4 ? 4 : 3) void k_dec_stream(
+    const Tin* __restrict__ G, const LevelGeom g, double* __restrict__ fout,
+    uint16_t* __restrict__ sym, double* __restrict__ raw, const double* __restrict__ rp,
+    const OutlierBuf ob, unsigned* __restrict__ status, const unsigned* __restrict__ gate,
+    const int seg, const uint32_t n_blocks) {
+  constexpr int SY = kStreamSY, SX = kStreamSX, E1 = kStreamE1, E2 = kStreamE2, NLD = kStreamNLD;
+  constexpr int RING = kStreamRing<Tin>, PL = E1 * E2;
+  static_assert(SY * SX == 256 && E1 > 16 && E1 <= 24, "one output per thread, three row steps");
+  __shared__ Tin ring[RING][PL];
+  __shared__ double X[2][E1][SX];
+  __shared__ EscList<kStreamEsc> el;
+  esc_reset(el);
   const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
   if (b >= n_blocks || gate_closed(gate)) return;
   const double r = rp ? *rp : 0.0;
@@ -733,175 +844,169 @@ __global__ __launch_bounds__(256, 4) void k_dec_stream(const Tin* __restrict__ G
   const uint32_t tx = b % tiles_x, rest = b / tiles_x;
   const uint32_t ty = rest % tiles_y, sg = rest / tiles_y;
   const uint32_t c0y = ty * SY, c0x = tx * SX;
-  const int tky = (int)min<uint32_t>(SY, nc1 - c0y), tkx = (int)min<uint32_t>(SX, nc2 - c0x);
-  const uint32_t py0 = cpos32(c0y, nf1), px0 = cpos32(c0x, nf2);
-  const uint32_t lo1 = py0 >= 2 ? py0 - 2 : 0, lo2 = px0 >= 2 ? px0 - 2 : 0;
-  const int ext1 = (int)(min<uint32_t>(cpos32(c0y + tky - 1, nf1) + 2, nf1 - 1) - lo1 + 1);
-  const int ext2 = (int)(min<uint32_t>(cpos32(c0x + tkx - 1, nf2) + 2, nf2 - 1) - lo2 + 1);
-  const uint32_t cz0 = sg * (uint32_t)seg, cz1 = min<uint32_t>(cz0 + seg, nc0);
-  const uint32_t pz0 = cpos32(cz0, nf0);
-  const uint32_t zs = pz0 >= 2 ? pz0 - 2 : 0;
-  const uint32_t ze = min<uint32_t>(cpos32(cz1 - 1, nf0) + 2, nf0 - 1);
+  const int cz0 = (int)(sg * (uint32_t)seg), cz1 = min(cz0 + seg, (int)nc0);
+  // the region's first fine node (two before the first output; may be outside)
+  const int lo1 = (int)cpos32(c0y, nf1) - 2, lo2 = (int)cpos32(c0x, nf2) - 2;
   const int tid = threadIdx.x;
-  // per-block tables
-  for (int i = tid; i < ext1; i += 256) {
-    sm.wl1[i] = g.ax[1].wl[lo1 + i];
-    sm.wr1[i] = g.ax[1].wr[lo1 + i];
-  }
-  for (int i = tid; i < ext2; i += 256) {
-    sm.wl2[i] = g.ax[2].wl[lo2 + i];
-    sm.wr2[i] = g.ax[2].wr[lo2 + i];
-  }
-  for (int i = tid; i < 5 * tky; i += 256) sm.W1[i / 5][i % 5] = g.ax[1].W[5 * c0y + i];
-  for (int i = tid; i < 5 * tkx; i += 256) sm.W2[i / 5][i % 5] = g.ax[2].W[5 * c0x + i];
-  for (int i = tid; i < tky; i += 256) sm.P1[i] = (int)(cpos32(c0y + i, nf1) - lo1);
-  for (int i = tid; i < tkx; i += 256) sm.P2[i] = (int)(cpos32(c0x + i, nf2) - lo2);
-  // the lane's values of a plane: offsets inside the plane and LDS slots
-  const int n_pl = ext1 * ext2;
-  const uint64_t m2 = div_magic((uint32_t)ext2);
-  uint32_t goff[kStreamNLD];
-  int ldst[kStreamNLD];
+  // the thread's slots of a plane
+  uint32_t goff[NLD];
+  unsigned in = 0;
 #pragma unroll
-  for (int u = 0; u < kStreamNLD; ++u) {
-    const int e = min(u * 256 + tid, n_pl - 1);
-    const int y = (int)div_small((uint32_t)e, m2), x = e - y * ext2;
-    goff[u] = (lo1 + y) * nf2 + lo2 + x;
-    ldst[u] = u * 256 + tid < n_pl ? y * E2 + x : -1;
+  for (int u = 0; u < NLD; ++u) {
+    const int e = min(u * 256 + tid, PL - 1);
+    const int y = lo1 + e / E2, x = lo2 + e % E2;
+    in |= y >= 0 && x >= 0 && y < (int)nf1 && x < (int)nf2 ? 1u << u : 0u;
+    goff[u] = (uint32_t)min(max(y, 0), (int)nf1 - 1) * nf2 + (uint32_t)min(max(x, 0), (int)nf2 - 1);
   }
   const size_t plane = (size_t)nf1 * nf2;
-  // kDecStreamPF planes of loads in flight, one register set per plane in
-  // fixed roles (the plane loop is unrolled by kDecStreamPF); a set is reloaded
-  // with the plane kDecStreamPF ahead right after it has gone to LDS.
-  Tin pv[kDecStreamPF][kStreamNLD];
-  auto load_plane = [&](uint32_t z, Tin (&v)[kStreamNLD]) {
-    const Tin* src = G + (size_t)z * plane;
+  Tin pv[2][NLD];
+  auto load_planes = [&](int z) {  // fine planes z, z + 1 (clamped to the grid)
 #pragma unroll
-    for (int u = 0; u < kStreamNLD; ++u) v[u] = src[goff[u]];
+    for (int p = 0; p < 2; ++p) {
+      const Tin* src = G + (size_t)min(max(z + p, 0), (int)nf0 - 1) * plane;
+#pragma unroll
+      for (int u = 0; u < NLD; ++u) pv[p][u] = src[goff[u]];
+    }
   };
-  // x pass: thread column cx, rows y = rsub, rsub + 8, ...
-  const int xcol = tid & 31, xrow = tid >> 5;
-  int xf[5];
-  double xw[5];
-  {
-    __syncthreads();  // tables
-    const int p = xcol < tkx ? sm.P2[xcol] : 0;
-#pragma unroll
-    for (int d = 0; d < 5; ++d) {
-      xf[d] = min(max(p + d - 2, 0), ext2 - 1);
-      xw[d] = xcol < tkx ? sm.W2[xcol][d] : 0.0;
-    }
-  }
-  // y pass / z pass / cells: thread (cy, cx)
-  const int ocy = tid >> 5, ocx = tid & 31;
-  const bool own = ocy < tky && ocx < tkx;
-  int yf[5];
-  double yw[5];
-  {
-    const int p = own ? sm.P1[ocy] : 0;
-#pragma unroll
-    for (int d = 0; d < 5; ++d) {
-      yf[d] = min(max(p + d - 2, 0), ext1 - 1);
-      yw[d] = own ? sm.W1[ocy][d] : 0.0;
-    }
-  }
-  // cell geometry along y and x (fixed per thread)
-  const uint32_t J1 = c0y + ocy, J2 = c0x + ocx;
+  // the thread's output column (cy, cx): taps, weights, slot of its first tap
+  const int cy = tid >> 5, cx = tid & 31;
+  const uint32_t J1 = c0y + cy, J2 = c0x + cx;
+  const bool own = J1 < nc1 && J2 < nc2;
+  const uint32_t K1 = min(J1, nc1 - 1), K2 = min(J2, nc2 - 1);
+  const uint32_t P1 = cpos32(K1, nf1), P2 = cpos32(K2, nf2);
   const bool h1 = own && 2 * J1 + 1 < nf1 - 1, h2 = own && 2 * J2 + 1 < nf2 - 1;
-  const int p1 = own ? (int)(cpos32(J1, nf1) - lo1) : 0, p2 = own ? (int)(cpos32(J2, nf2) - lo2) : 0;
-  const int q1 = h1 ? p1 + 1 : p1, q2 = h2 ? p2 + 1 : p2;
-  const int s1 = h1 ? p1 + 2 : p1, s2 = h2 ? p2 + 2 : p2;
-  const double wy0 = sm.wl1[q1], wy1 = sm.wr1[q1], wx0 = sm.wl2[q2], wx1 = sm.wr2[q2];
+  double xw[5], yw[5];
+#pragma unroll
+  for (int d = 0; d < 5; ++d) {
+    xw[d] = g.ax[2].W[5 * (size_t)K2 + d];
+    yw[d] = g.ax[1].W[5 * (size_t)K1 + d];
+  }
+  const double wy0 = g.ax[1].wl[h1 ? P1 + 1 : P1], wy1 = g.ax[1].wr[h1 ? P1 + 1 : P1];
+  const double wx0 = g.ax[2].wl[h2 ? P2 + 1 : P2], wx1 = g.ax[2].wr[h2 ? P2 + 1 : P2];
+  const int xb = (int)P2 - lo2 - 2, yb = (int)P1 - lo1 - 2;  // slots of the taps' first nodes
+  const int cell = (yb + 2) * E2 + xb + 2;                   // slot of the cell's origin
+  // stream positions of the next coarse plane's coefficients, and their steps
   const uint32_t e1c = nc1, e1n = nf1 - nc1, e2c = nc2, e2n = nf2 - nc2;
-  const uint32_t lvl = (uint32_t)g.level_off;
   const int m0 = g.bit[0] >= 0 ? 1 << g.bit[0] : 0, m1 = g.bit[1] >= 0 ? 1 << g.bit[1] : 0,
-            m2b = g.bit[2] >= 0 ? 1 << g.bit[2] : 0;
-  // first stream position of each subband of the level (uniform)
+            m2 = g.bit[2] >= 0 ? 1 << g.bit[2] : 0;
   uint32_t so[8];
   subband_offsets(g, so);
-  const uint32_t sb_x = lvl + sel8(so, m2b), sb_y = lvl + sel8(so, m1),
-                 sb_yx = lvl + sel8(so, m1 | m2b), sb_z = lvl + sel8(so, m0),
-                 sb_zx = lvl + sel8(so, m0 | m2b), sb_zy = lvl + sel8(so, m0 | m1),
-                 sb_zyx = lvl + sel8(so, m0 | m1 | m2b);
-  uint32_t next_cz = cz0;
-#pragma unroll
-  for (int d = 0; d < kDecStreamPF; ++d) load_plane(min<uint32_t>(zs + d, ze), pv[d]);
-  for (uint32_t zb = zs; zb <= ze; zb += kDecStreamPF) {
-#pragma unroll
-  for (int d = 0; d < kDecStreamPF; ++d) {
-    const uint32_t zf = zb + d;
-    if (zf > ze) break;
-    const int s3 = (int)(zf % 3u), s5 = (int)(zf % 5u);
-#pragma unroll
-    for (int u = 0; u < kStreamNLD; ++u)
-      if (ldst[u] >= 0) (&sm.raw[s3][0][0])[ldst[u]] = pv[d][u];
-    if (zf + kDecStreamPF <= ze) load_plane(zf + kDecStreamPF, pv[d]);
-    __syncthreads();
-    if (xcol < tkx) {
-      for (int y = xrow; y < ext1; y += 8) {
-        const Tin* row = sm.raw[s3][y];
-        double acc = 0.0;
-#pragma unroll
-        for (int d = 0; d < 5; ++d) acc = fma(xw[d], (double)row[xf[d]], acc);
-        sm.X[y][xcol] = acc;
-      }
-    }
-    __syncthreads();
+  const uint32_t lvl = (uint32_t)g.level_off;
+  const uint32_t sb[7] = {lvl + sel8(so, m2),      lvl + sel8(so, m1),      lvl + sel8(so, m1 | m2),
+                          lvl + sel8(so, m0),      lvl + sel8(so, m0 | m2), lvl + sel8(so, m0 | m1),
+                          lvl + sel8(so, m0 | m1 | m2)};
+  double Y[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // y results of fine planes 2i - 2 .. 2i + 2
+  double c000 = 0.0, c010 = 0.0, ix00 = 0.0, ix01 = 0.0;  // corners on plane 2i
+  const int oy = tid >> 5;  // x pass: rows oy, oy + 8, oy + 16 of output column cx
+  // the coarse plane J0 with its restriction's z results in Z and its raw
+  // planes in ring slots r0 (its own), rq and rs (the two above)
+  auto finish = [&](uint32_t J0, const double (&Z)[5], int rq, int rs, int r0) {
+    const double* W0 = g.ax[0].W + 5 * (size_t)J0;
     if (own) {
       double acc = 0.0;
 #pragma unroll
-      for (int d = 0; d < 5; ++d) acc = fma(yw[d], sm.X[yf[d]][ocx], acc);
-      sm.Y[s5][ocy][ocx] = acc;
+      for (int d = 0; d < 5; ++d) acc = fma(W0[d], Z[d], acc);
+      fout[((size_t)J0 * nc1 + J1) * nc2 + J2] = acc;
     }
-    __syncthreads();
-    // coarse planes whose last fine plane is this one
-    while (next_cz < cz1 && min<uint32_t>(cpos32(next_cz, nf0) + 2, nf0 - 1) == zf) {
-      const uint32_t J0 = next_cz;
-      const uint32_t P0 = cpos32(J0, nf0);
-      const bool h0 = 2 * J0 + 1 < nf0 - 1;
-      const double* W0 = g.ax[0].W + 5 * (size_t)J0;
-      if (own) {
-        double acc = 0.0;
+    const uint32_t P0 = cpos32(J0, nf0);
+    const bool h0 = own && 2 * J0 + 1 < nf0 - 1;
+    const double wz0 = g.ax[0].wl[h0 ? P0 + 1 : P0], wz1 = g.ax[0].wr[h0 ? P0 + 1 : P0];
+    const Tin *a = ring[r0] + cell, *q = ring[rq] + cell, *t = ring[rs] + cell;
+    const double c100 = (double)t[0], c101 = (double)t[2], c110 = (double)t[2 * E2],
+                 c111 = (double)t[2 * E2 + 2];
+    const double ix10 = lin2(wx0, c100, wx1, c101), ix11 = lin2(wx0, c110, wx1, c111);
+    const double iy0 = lin2(wy0, c000, wy1, c010), iy1 = lin2(wy0, c100, wy1, c110);
+    const double ixy0 = lin2(wy0, ix00, wy1, ix01), ixy1 = lin2(wy0, ix10, wy1, ix11);
+    const uint32_t cc = (J0 * e1c + J1) * e2c + J2, cn = (J0 * e1c + J1) * e2n + J2;
+    const uint32_t nc = (J0 * e1n + J1) * e2c + J2, nn = (J0 * e1n + J1) * e2n + J2;
+    const bool ok[7] = {h2, h1, h1 && h2, h0, h0 && h2, h0 && h1, h0 && h1 && h2};
+    const uint32_t pos[7] = {sb[0] + cn, sb[1] + nc, sb[2] + nn, sb[3] + cc,
+                             sb[4] + cn, sb[5] + nc, sb[6] + nn};
+    const double v[7] = {(double)a[1] - ix00,
+                         (double)a[E2] - iy0,
+                         (double)a[E2 + 1] - ixy0,
+                         (double)q[0] - lin2(wz0, c000, wz1, c100),
+                         (double)q[1] - lin2(wz0, ix00, wz1, ix10),
+                         (double)q[E2] - lin2(wz0, iy0, wz1, iy1),
+                         (double)q[E2 + 1] - lin2(wz0, ixy0, wz1, ixy1)};
+    emit_cell<QUANT>(pos, v, ok, r, sym, raw, ob, status, el);
+    c000 = c100;
+    c010 = c110;
+    ix00 = ix10;
+    ix01 = ix11;
+  };
+  // Step i takes fine planes 2i + 1 and 2i + 2 and finishes coarse plane i;
+  // two steps before the segment fill the taps (planes outside the grid
+  // repeat the nearest one: their weights are zero).
+  int slot = 0;  // ring slot of plane 2i + 1
+  load_planes(2 * (cz0 - 2) + 1);
+  for (int i = cz0 - 2; i < cz1; ++i) {
+    const int sq = slot, st = slot + 1 < RING ? slot + 1 : 0;
+    const int sa = slot > 0 ? slot - 1 : RING - 1;  // plane 2i
+    slot = st + 1 < RING ? st + 1 : 0;
 #pragma unroll
-        for (int d = 0; d < 5; ++d) {
-          const int zz = min(max((int)P0 + d - 2, 0), (int)nf0 - 1);
-          acc = fma(W0[d], sm.Y[zz % 5][ocy][ocx], acc);
+    for (int u = 0; u < NLD; ++u) {
+      if (u < NLD - 1 || u * 256 + tid < PL) {
+        ring[sq][u * 256 + tid] = (in >> u) & 1u ? pv[0][u] : (Tin)0;
+        ring[st][u * 256 + tid] = (in >> u) & 1u ? pv[1][u] : (Tin)0;
+      }
+    }
+    if (i + 1 < cz1) load_planes(2 * (i + 1) + 1);
+    __syncthreads();
+    if (QUANT && el.n > kStreamEsc / 2) {
+      esc_flush(el, ob);
+      __syncthreads();
+      esc_reset(el);  // (ordered against the next cells by the barrier below)
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const Tin* src = ring[p == 0 ? sq : st] + oy * E2 + xb;
+#pragma unroll
+      for (int k = 0; k < 3; ++k) {
+        if (k < 2 || oy + 16 < E1) {
+          double acc = 0.0;
+#pragma unroll
+          for (int d = 0; d < 5; ++d) acc = fma(xw[d], (double)src[8 * k * E2 + d], acc);
+          X[p][oy + 8 * k][cx] = acc;
         }
-        fout[((size_t)J0 * nc1 + J1) * nc2 + J2] = acc;
       }
-      if (own && (h0 || h1 || h2)) {
-        const int r0 = (int)(P0 % 3u), rq = (int)((h0 ? P0 + 1 : P0) % 3u),
-                  rs = (int)((h0 ? P0 + 2 : P0) % 3u);
-        const double wz0 = h0 ? g.ax[0].wl[P0 + 1] : 1.0, wz1 = h0 ? g.ax[0].wr[P0 + 1] : 0.0;
-        auto T = [&](int pz, int y, int x) -> double { return (double)sm.raw[pz][y][x]; };
-        const double c000 = T(r0, p1, p2), c001 = T(r0, p1, s2), c010 = T(r0, s1, p2),
-                     c011 = T(r0, s1, s2), c100 = T(rs, p1, p2), c101 = T(rs, p1, s2),
-                     c110 = T(rs, s1, p2), c111 = T(rs, s1, s2);
-        const double ix00 = lin2(wx0, c000, wx1, c001), ix01 = lin2(wx0, c010, wx1, c011);
-        const double ix10 = lin2(wx0, c100, wx1, c101), ix11 = lin2(wx0, c110, wx1, c111);
-        const uint32_t base_cc = (J0 * e1c + J1) * e2c + J2, base_cn = (J0 * e1c + J1) * e2n + J2;
-        const uint32_t base_nc = (J0 * e1n + J1) * e2c + J2, base_nn = (J0 * e1n + J1) * e2n + J2;
-        auto emit = [&](uint32_t pos, double v) {
-          if (QUANT) emit_q(pos, v, r, sym, ob, status);
-          else raw[pos] = v;
-        };
-        if (h2) emit(sb_x + base_cn, T(r0, p1, q2) - ix00);
-        if (h1) emit(sb_y + base_nc, T(r0, q1, p2) - (lin2(wy0, c000, wy1, c010)));
-        if (h1 && h2)
-          emit(sb_yx + base_nn, T(r0, q1, q2) - (lin2(wy0, ix00, wy1, ix01)));
-        if (h0) emit(sb_z + base_cc, T(rq, p1, p2) - (lin2(wz0, c000, wz1, c100)));
-        if (h0 && h2)
-          emit(sb_zx + base_cn, T(rq, p1, q2) - (lin2(wz0, ix00, wz1, ix10)));
-        if (h0 && h1)
-          emit(sb_zy + base_nc,
-               T(rq, q1, p2) - (lin2(wz0, lin2(wy0, c000, wy1, c010), wz1, lin2(wy0, c100, wy1, c110))));
-        if (h0 && h1 && h2)
-          emit(sb_zyx + base_nn,
-               T(rq, q1, q2) - (lin2(wz0, lin2(wy0, ix00, wy1, ix01), wz1, lin2(wy0, ix10, wy1, ix11))));
-      }
-      ++next_cz;
     }
     __syncthreads();
+    Y[0] = Y[2];
+    Y[1] = Y[3];
+    Y[2] = Y[4];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      double acc = 0.0;
+#pragma unroll
+      for (int d = 0; d < 5; ++d) acc = fma(yw[d], X[p][yb + d][cx], acc);
+      Y[3 + p] = acc;
+    }
+    if (i >= cz0) {
+      finish((uint32_t)i, Y, sq, st, sa);
+    } else if (i == cz0 - 1) {  // plane 2i + 2 holds the first cells' lower corners
+      const Tin* t = ring[st] + cell;
+      c000 = (double)t[0];
+      c010 = (double)t[2 * E2];
+      ix00 = lin2(wx0, c000, wx1, (double)t[2]);
+      ix01 = lin2(wx0, c010, wx1, (double)t[2 * E2 + 2]);
+    }
+    // an even axis ends on a coarse plane of its own, 2i + 1 of the step before
+    if (!(nf0 & 1u) && i == (int)nc0 - 2 && cz1 == (int)nc0) {
+      const Tin* t = ring[sq] + cell;
+      c000 = (double)t[0];
+      c010 = (double)t[2 * E2];
+      ix00 = lin2(wx0, c000, wx1, (double)t[2]);
+      ix01 = lin2(wx0, c010, wx1, (double)t[2 * E2 + 2]);
+      const double Z[5] = {Y[1], Y[2], Y[3], Y[3], Y[3]};
+      finish(nc0 - 1, Z, sq, sq, sq);
+      break;
+    }
+    if (RING < 5) __syncthreads();
   }
+  if (QUANT) {
+    __syncthreads();
+    if (el.n != 0) esc_flush(el, ob);
   }
 }
 

@@ -19,7 +19,7 @@ import synthetic
 from oracle import Hierarchy
 from oracle.quantize import from_symbols
 from oracle.stream import decode_symbols, parse_header
-from tests.gpu_common import gpu, to_bytes
+from tests.gpu_common import assert_stream_matches_oracle, gpu, to_bytes
 
 pytestmark = pytest.mark.gpu
 
@@ -280,3 +280,39 @@ def test_full_size_fp64_and_non_dyadic(name, norm, rel):
         k[esc] = oval[where]
     assert np.count_nonzero(k != k_ref) <= 1e-6 * u.size
     assert np.all(np.abs(k - k_ref) <= 1)
+
+
+@pytest.mark.parametrize("shape,dtype", [((325, 322, 321), "float32"), ((322, 326, 323), "float64")])
+@pytest.mark.parametrize("share", [0.0, 0.002, 0.4])
+def test_streamed_level_equals_tiled_with_escapes(shape, dtype, share):
+    """The z-streamed finest level against the tiled one (forced candidate 1),
+    axes of odd and even length, with no, some and many escaped values (the
+    block's list stays empty, is flushed now and then, and overflows): equal
+    streams, since escaped values are placed by rank."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(5)
+    x = torch.randn(shape, device="cuda", generator=gen).cumsum(0).cumsum(1).cumsum(2) * 1e-3
+    spike = torch.rand(shape, device="cuda", generator=gen) < share
+    x = torch.where(spike, torch.randn(shape, device="cuda", generator=gen) * 300.0, x).to(getattr(torch, dtype))
+    n = x.numel()
+    a = mgc.compress(x, 1e-3, mode="abs", outlier_cap=n)
+    kind = "dec_f32" if dtype == "float32" else "dec_f64"
+    mgc.set_tuning(kind, 1)
+    try:
+        b = mgc.compress(x, 1e-3, mode="abs", outlier_cap=n)
+    finally:
+        mgc.set_tuning(kind, -1)
+    assert torch.equal(a, b)
+    y = mgc.decompress(a)
+    assert torch.max(torch.abs(y.double() - x.double())).item() <= 1e-3
+
+
+@pytest.mark.parametrize("shape", [(33, 34, 35), (130, 70), (3000,)])
+def test_mostly_escaped_values_match_oracle(shape):
+    """Noise at a bound that escapes most values: every tile's list overflows."""
+    torch, mgc = gpu()
+    u = np.random.default_rng(9).standard_normal(shape)
+    blob = to_bytes(mgc.compress(torch.from_numpy(u).cuda(), 1e-7, mode="abs"))
+    ref = oracle.compress(u, 1e-7, mode="abs")
+    assert oracle.parse_header(ref)["n_outliers"] > 0.5 * u.size
+    assert_stream_matches_oracle(blob, ref, "linf")
