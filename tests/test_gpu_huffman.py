@@ -287,3 +287,18 @@ def test_decode_prefix_nodes_and_plain_wavefronts(n, kind):
     back = mgc.huffman_decode(enc, n)
     assert bool((back == t).all())
     assert to_bytes(enc) == oracle_huffman_stream(sym, 1024)
+
+
+# one block and many, below and above the eight vectors per thread from which
+# a block samples its symbols; all symbols equally likely (half of them outside
+# the histogram's window: read twice) and one in a hundred outside (read once)
+@pytest.mark.parametrize("n", [65535, 8 * 8192 + 3, 1 << 20])
+@pytest.mark.parametrize("share", [0.5, 0.01])
+def test_histogram_outside_its_window(n, share):
+    torch, mgc = gpu()
+    rng = np.random.default_rng(n)
+    inner = 32768 + np.round(rng.laplace(0.0, 200.0, size=n)).astype(np.int64)
+    outer = (rng.integers(49152, 49152 + 32768, size=n)) % 65536
+    sym = np.where(rng.random(n) < share, outer, np.clip(inner, 16384, 49151))
+    t = torch.from_numpy(sym.astype(np.uint16).view(np.int16)).cuda()
+    assert to_bytes(mgc.huffman_encode(t)) == oracle_huffman_stream(sym, 1024)
