@@ -459,6 +459,115 @@ __device__ __forceinline__ unsigned long long merge_threshold(unsigned m, uint32
   return a + b;
 }
 
+// Block barrier that orders LDS accesses only: global stores in flight are
+// not waited for.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Counts of the entries <= t in two ascending LDS ranges, by each wavefront on
+// its own: 32 lanes take a range each and narrow it to a 32nd per step.
+__device__ __forceinline__ void wave_count2(const uint32_t* a0, unsigned n0, const uint32_t* a1,
+                                            unsigned n1, uint32_t t, unsigned& c0, unsigned& c1) {
+  const int lane = threadIdx.x & 63;
+  const unsigned l = lane & 31;
+  const uint32_t* a = lane < 32 ? a0 : a1;
+  unsigned base = 0, n = lane < 32 ? n0 : n1;
+  while (__any(n != 0)) {
+    const unsigned S = (n + 31) / 32, i = l * S;
+    const bool le = i < n && a[base + min(i, n - 1)] <= t;
+    const uint64_t m = __ballot(le);
+    const unsigned c = (unsigned)__popc((uint32_t)(lane < 32 ? m : m >> 32));
+    // entry (c - 1) S is <= t; the boundary lies behind it, before entry c S
+    const unsigned skip = c ? (c - 1) * S + 1 : 0;
+    n = c ? min(S - 1, n - skip) : 0;
+    base += skip;
+  }
+  c0 = (unsigned)__builtin_amdgcn_readlane((int)base, 0);
+  c1 = (unsigned)__builtin_amdgcn_readlane((int)base, 32);
+}
+
+// The merge's remaining rounds with every remaining node in LDS: leaves AL
+// (leaf li0 first), internal nodes AI (node ii0 first; those not created yet
+// hold the children added so far).  Every thread carries the round's state, so
+// a round is one search of both queues, the ranks of the taken nodes, the adds
+// into their parents and one barrier that waits on LDS alone.
+constexpr unsigned kLdsNodes = sizeof(CbBig) / 4;
+__device__ __forceinline__ bool merge_in_lds(const unsigned n, unsigned m, unsigned li,
+                                             unsigned ii, unsigned nI, unsigned long long t,
+                                             const uint32_t* __restrict__ Lw, uint32_t lastw,
+                                             const CodebookScratch& s, CbSmem& sm,
+                                             uint32_t* mem) {
+  const unsigned tid = threadIdx.x, li0 = li, ii0 = ii;
+  uint32_t* const AL = mem;
+  uint32_t* const AI = mem + (n - li0);
+  unsigned rounds = sm.rounds;
+  for (unsigned k = tid; k < n - li0; k += 1024) AL[k] = Lw[li0 + k];
+  for (unsigned y = ii0 + tid; y < n - 1; y += 1024)
+    AI[y - ii0] = y < nI ? s.Iw[y] : (y == nI && (m & 1) ? lastw : 0u);
+  __syncthreads();
+  while (m < 2 * n - 2) {
+    if (tid == 0 && rounds < (unsigned)kMaxRounds) sm.round_lo[rounds] = nI;
+    const uint32_t* L = AL + (li - li0);
+    const uint32_t* I = AI + (ii - ii0);
+    unsigned nl, ni;
+    wave_count2(L, n - li, I, nI - ii, (uint32_t)(t < 0xFFFFFFFFull ? t : 0xFFFFFFFFull), nl, ni);
+    if (nl + ni == 0) return false;  // every round takes at least the smallest node
+    // one half of the block ranks the leaves, the other the internal nodes
+    if (tid < 512) {
+      for (unsigned k0 = tid; k0 < nl; k0 += 2048) {
+        uint32_t w[4];
+        unsigned pos[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w[u] = L[min(k0 + u * 512, nl - 1)];
+        if (ni) lds_count4<false>(I, ni, w, pos);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const unsigned k = k0 + u * 512;
+          if (k < nl) {
+            const unsigned par = (m + k + pos[u]) >> 1;
+            s.leafPar[li + k] = par;
+            atomicAdd(&AI[par - ii0], w[u]);
+          }
+        }
+      }
+    } else {
+      for (unsigned k0 = tid - 512; k0 < ni; k0 += 2048) {
+        uint32_t w[4];
+        unsigned pos[4] = {0u, 0u, 0u, 0u};
+#pragma unroll
+        for (int u = 0; u < 4; ++u) w[u] = I[min(k0 + u * 512, ni - 1)];
+        if (nl) lds_count4<true>(L, nl, w, pos);
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+          const unsigned k = k0 + u * 512;
+          if (k < ni) {
+            const unsigned par = (m + k + pos[u]) >> 1;
+            s.parA[ii + k] = par;
+            atomicAdd(&AI[par - ii0], w[u]);
+          }
+        }
+      }
+    }
+    lastw = max(nl ? L[nl - 1] : 0u, ni ? I[ni - 1] : 0u);
+    m += nl + ni;
+    li += nl;
+    ii += ni;
+    nI = m >> 1;
+    ++rounds;
+    lds_barrier();
+    const unsigned long long INF = ~0ull;
+    const auto lw = [&](unsigned x) -> unsigned long long { return x < n ? AL[x - li0] : INF; };
+    const auto iw = [&](unsigned y) -> unsigned long long { return y < nI ? AI[y - ii0] : INF; };
+    t = merge_threshold(m, lastw, lw(li), lw(li + 1), iw(ii), iw(ii + 1));
+  }
+  if (tid == 0) sm.rounds = rounds;
+  __syncthreads();
+  return true;
+}
+
 // 1. non-zero keys in ascending symbol order (each thread owns 64 symbols,
 //    read as sixteen 16-byte vectors kept in registers); returns their count
 __device__ unsigned compact_keys(const unsigned* __restrict__ hist, const CodebookScratch& s,
@@ -701,7 +810,8 @@ __device__ __forceinline__ void codebook_body(const unsigned* __restrict__ hist,
     //    (integer sums, so the order of the adds does not matter).  The next
     //    round's threshold is read from the same windows.  A round that
     //    takes more than a window's worth of one queue runs from global
-    //    memory instead.
+    //    memory instead.  Once the nodes not yet taken fit in LDS the rounds stay
+    //    there (merge_in_lds).
     if (tid == 0) {
       sm.m = 0;
       sm.li = 0;
@@ -718,6 +828,14 @@ __device__ __forceinline__ void codebook_body(const unsigned* __restrict__ hist,
       const unsigned m = sm.m, li = sm.li, ii = sm.ii, nI = sm.nI;
       const unsigned long long t = sm.t;
       if (m == 2 * n - 2) break;
+      if (2 * n - 1 - m <= kLdsNodes) {  // the remaining nodes fit in LDS
+        const uint32_t lastw = sm.lastw;
+        if (!merge_in_lds(n, m, li, ii, nI, t, Lw, lastw, s, sm, reinterpret_cast<uint32_t*>(&big))) {
+          if (tid == 0) lay->status |= ST_INTERNAL;
+          return;
+        }
+        break;
+      }
       // internal nodes created in this round: [nI, m_new / 2)
       if (tid == 0 && sm.rounds < kMaxRounds) sm.round_lo[sm.rounds] = nI;
       const unsigned availL = min((unsigned)kWin, n - li);
@@ -959,7 +1077,7 @@ __device__ __forceinline__ void codebook_body(const unsigned* __restrict__ hist,
                 if (y < hi) dep[y] = y == root ? 0 : (uint8_t)min(dv[u] + 1u, 255u);
               }
             }
-            __syncthreads();
+            lds_barrier();
           }
           r = r0 - 1;
         } else {
