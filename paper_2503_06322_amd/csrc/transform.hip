@@ -809,7 +809,6 @@ constexpr int kStreamSY = 8, kStreamSX = 32;
 constexpr int kStreamE1 = 2 * kStreamSY + 3, kStreamE2 = 2 * kStreamSX + 3;
 constexpr int kStreamNLD = (kStreamE1 * kStreamE2 + 255) / 256;
 constexpr int kStreamEsc = 320;  // escaped values a block collects between flushes
-constexpr int kStreamPF = 2;     // fine planes whose loads are in flight (recomposition)
 // levels with fewer fine points use the tiled kernel (measured faster there)
 constexpr int64_t kStreamMinPoints = int64_t(1) << 25;
 // Recomposition's restriction (one value per coarse node from the dequantised
@@ -1010,28 +1009,227 @@ __global__ __launch_bounds__(256, sizeof(Tin) == 4 ? 4 : 3) void k_dec_stream(
   }
 }
 
-// ------------------------ recomposition restriction of a 3-axis level, streamed
-// f = (P^T M_l) c_l with the same z streaming as k_dec_stream: each fine
-// plane of the block's region is assembled from the dequantised coefficients
-// (zero at the nodes coarse along every axis) and restricted along x and y;
-// the y results of the last five planes stay in an LDS ring for the z pass.
-// A lane's region slots are fixed, so a coefficient's stream position is a
-// per-slot base (for the plane's new or coarse z) plus j0 times the
-// subband's plane stride.
-struct RecStreamSmem {
-  double P[kStreamE1][kStreamE2];
-  double X[kStreamE1][kStreamSX];
-  double Y[5][kStreamSY][kStreamSX];
-  double W1[kStreamSY][5], W2[kStreamSX][5];
-  int P1[kStreamSY], P2[kStreamSX];
+// ------------------------------- decomposition of a 2-axis level, streamed
+// As the 3-axis kernel, with the rows of the plane in the place of planes: a
+// block owns kStream2SX coarse columns and walks a segment of coarse rows, two
+// fine rows a step.  The x results of its column stay in a thread's registers
+// for the y taps, so a step has one barrier (the raw rows: five in a ring).
+// Each thread loads two neighbouring nodes of a row.  Bound by HBM latency and
+// issue (8193 x 8193 FP64: 204 us, the tiled kernel 293 us: a tile of 8 x 32
+// outputs reads 19 x 67 values for 16 x 64).
+constexpr int kStream2SX = 254;                // outputs of a block: 512 region slots
+constexpr int kStream2E = 2 * 256;
+// levels with fewer fine points use the tiled kernels: a streamed column's
+// steps are a serial chain (2049^2: 26 us streamed, 24 tiled; 4097^2: 53 and
+// 78; the restriction of recomposition 18 and 23 us, 33 and 78)
+constexpr int64_t kStream2MinPoints = int64_t(1) << 23;
+constexpr int64_t kRecStream2MinPoints = int64_t(1) << 22;
+
+template <typename Tin, bool QUANT>
+__global__ __launch_bounds__(256) void k_dec_stream2(
+    const Tin* __restrict__ G, const LevelGeom g, double* __restrict__ fout,
+    uint16_t* __restrict__ sym, double* __restrict__ raw, const double* __restrict__ rp,
+    const OutlierBuf ob, unsigned* __restrict__ status, const unsigned* __restrict__ gate,
+    const int seg, const uint32_t n_blocks) {
+  constexpr int SX = kStream2SX, E = kStream2E, RING = 5;
+  __shared__ Tin ring[RING][E];
+  __shared__ EscList<kTileEsc> el;
+  __shared__ bool full[2];
+  esc_reset(el);
+  const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
+  if (b >= n_blocks || gate_closed(gate)) return;
+  const double r = rp ? *rp : 0.0;
+  const uint32_t nf1 = (uint32_t)g.nf[1], nf2 = (uint32_t)g.nf[2];
+  const uint32_t nc1 = (uint32_t)g.nc[1], nc2 = (uint32_t)g.nc[2];
+  const uint32_t tiles_x = (nc2 + SX - 1) / SX;
+  const uint32_t tx = b % tiles_x, sg = b / tiles_x;
+  const uint32_t c0x = tx * SX;
+  const int cy0 = (int)(sg * (uint32_t)seg), cy1 = min(cy0 + seg, (int)nc1);
+  const int lo2 = (int)cpos32(c0x, nf2) - 2;
+  const int tid = threadIdx.x;
+  const int x0 = lo2 + 2 * tid, xa = min(max(x0, 0), (int)nf2 - 1), xe = min(max(x0 + 1, 0), (int)nf2 - 1);
+  const bool in0 = x0 >= 0 && x0 < (int)nf2, in1 = x0 + 1 >= 0 && x0 + 1 < (int)nf2;
+  Tin pv[2][2];
+  auto load_rows = [&](int y) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const Tin* src = G + (size_t)min(max(y + p, 0), (int)nf1 - 1) * nf2;
+      pv[p][0] = src[xa];
+      pv[p][1] = src[xe];
+    }
+  };
+  const uint32_t J2 = c0x + tid, K2 = min(J2, nc2 - 1);
+  const bool own = tid < SX && J2 < nc2;
+  const uint32_t P2 = cpos32(K2, nf2);
+  const bool h2 = own && 2 * J2 + 1 < nf2 - 1;
+  double xw[5];
+#pragma unroll
+  for (int d = 0; d < 5; ++d) xw[d] = g.ax[2].W[5 * (size_t)K2 + d];
+  const double wx0 = g.ax[2].wl[h2 ? P2 + 1 : P2], wx1 = g.ax[2].wr[h2 ? P2 + 1 : P2];
+  const int xb = own ? (int)P2 - lo2 - 2 : 0;  // slot of the first tap
+  const int m1 = 1 << g.bit[1], m2 = 1 << g.bit[2];
+  uint32_t so[8];
+  subband_offsets(g, so);
+  const uint32_t lvl = (uint32_t)g.level_off, e2c = nc2, e2n = nf2 - nc2;
+  const uint32_t sb_x = lvl + sel8(so, m2), sb_y = lvl + sel8(so, m1), sb_yx = lvl + sel8(so, m1 | m2);
+  double Y[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // x results of fine rows 2i - 2 .. 2i + 2
+  double c0 = 0.0, ix0 = 0.0;               // the cell's corner and interpolant on row 2i
+  auto corners = [&](int slot) {
+    const Tin* t = ring[slot] + xb + 2;
+    c0 = (double)t[0];
+    ix0 = lin2(wx0, c0, wx1, (double)t[2]);
+  };
+  auto finish = [&](uint32_t J1, const double (&Z)[5], int rq, int rs, int r0) {
+    const double* W1 = g.ax[1].W + 5 * (size_t)J1;
+    if (own) {
+      double acc = 0.0;
+#pragma unroll
+      for (int d = 0; d < 5; ++d) acc = fma(W1[d], Z[d], acc);
+      fout[(size_t)J1 * nc2 + J2] = acc;
+    }
+    const uint32_t P1 = cpos32(J1, nf1);
+    const bool h1 = own && 2 * J1 + 1 < nf1 - 1;
+    const double wy0 = g.ax[1].wl[h1 ? P1 + 1 : P1], wy1 = g.ax[1].wr[h1 ? P1 + 1 : P1];
+    const Tin *a = ring[r0] + xb + 2, *q = ring[rq] + xb + 2;
+    const double va = (double)a[1] - ix0, cold = c0, iold = ix0;
+    corners(rs);
+    const bool ok[7] = {h2, h1, h1 && h2, false, false, false, false};
+    const uint32_t pos[7] = {sb_x + J1 * e2n + J2, sb_y + J1 * e2c + J2, sb_yx + J1 * e2n + J2,
+                             0u, 0u, 0u, 0u};
+    const double v[7] = {va, (double)q[0] - lin2(wy0, cold, wy1, c0),
+                         (double)q[1] - lin2(wy0, iold, wy1, ix0), 0.0, 0.0, 0.0, 0.0};
+    emit_cell<QUANT>(pos, v, ok, r, sym, raw, ob, status, el);
+  };
+  // Step i takes fine rows 2i + 1 and 2i + 2 and finishes coarse row i (see
+  // the 3-axis kernel).
+  int slot = 0;
+  load_rows(2 * (cy0 - 2) + 1);
+  for (int i = cy0 - 2; i < cy1; ++i) {
+    const int sq = slot, st = slot + 1 < RING ? slot + 1 : 0;
+    const int sa = slot > 0 ? slot - 1 : RING - 1;
+    slot = st + 1 < RING ? st + 1 : 0;
+    ring[sq][2 * tid] = in0 ? pv[0][0] : (Tin)0;
+    ring[sq][2 * tid + 1] = in1 ? pv[0][1] : (Tin)0;
+    ring[st][2 * tid] = in0 ? pv[1][0] : (Tin)0;
+    ring[st][2 * tid + 1] = in1 ? pv[1][1] : (Tin)0;
+    if (i + 1 < cy1) load_rows(2 * (i + 1) + 1);
+    // (one thread's view, so that the block agrees while cells add to the list)
+    if (QUANT && tid == 0) full[i & 1] = el.n > kTileEsc / 2;
+    __syncthreads();
+    if (QUANT && full[i & 1]) {
+      esc_flush(el, ob);
+      __syncthreads();
+      esc_reset(el);
+      __syncthreads();
+    }
+    Y[0] = Y[2];
+    Y[1] = Y[3];
+    Y[2] = Y[4];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const Tin* src = ring[p == 0 ? sq : st] + xb;
+      double acc = 0.0;
+#pragma unroll
+      for (int d = 0; d < 5; ++d) acc = fma(xw[d], (double)src[d], acc);
+      Y[3 + p] = acc;
+    }
+    if (i >= cy0) finish((uint32_t)i, Y, sq, st, sa);
+    else if (i == cy0 - 1) corners(st);
+    // an even axis ends on a coarse row of its own, 2i + 1 of the step before
+    if (!(nf1 & 1u) && i == (int)nc1 - 2 && cy1 == (int)nc1) {
+      corners(sq);
+      const double Z[5] = {Y[1], Y[2], Y[3], Y[3], Y[3]};
+      finish(nc1 - 1, Z, sq, sq, sq);
+      break;
+    }
+  }
+  if (QUANT) {
+    __syncthreads();
+    if (el.n != 0) esc_flush(el, ob);
+  }
+}
+
+// ------------------- recomposition restrictions of 3- and 2-axis levels, streamed
+// f = (P^T M_l) c_l with the same streaming: the fine planes (rows) are
+// assembled from the dequantised coefficients, zero at the nodes coarse along
+// every axis.  A thread takes pairs of neighbouring region slots, one of each
+// parity, so that consecutive lanes read consecutive positions of a subband;
+// a slot's stream position in the next coarse and the next new plane is kept
+// and advanced by the subband's plane stride, since planes come in order, once
+// each.  (513^3: 281 us, the pass over planes one at a time with a position
+// and a load per slot 315 us; 8193 x 8193: 95 us, the tiled kernel 295 us.)
+struct CoeffSlot {
+  uint32_t pc, pn, stride;  // positions in the next coarse / new plane, their step
 };
+// Slot of the node (i1, i2) of a plane along axis 0 (3-axis levels) or of the
+// node i2 of a row along axis 1 (2-axis levels, i1 unused); first: the first
+// fine plane (row) that is loaded.  yx: new along an axis within the plane.
+template <bool D3>
+__device__ __forceinline__ CoeffSlot coeff_slot(const LevelGeom& g, const uint32_t (&so)[8],
+                                                uint32_t i1, uint32_t i2, uint32_t first,
+                                                bool& yx) {
+  const uint32_t nf1 = (uint32_t)g.nf[1], nf2 = (uint32_t)g.nf[2];
+  const uint32_t nc1 = (uint32_t)g.nc[1], nc2 = (uint32_t)g.nc[2];
+  const int ms = 1 << g.bit[D3 ? 0 : 1];  // the streamed axis' subband bit
+  const bool n1 = D3 && is_new32(i1, nf1), n2 = is_new32(i2, nf2);
+  const uint32_t j1 = D3 ? (n1 ? (i1 >> 1) : cidx32(i1, nf1)) : 0u;
+  const uint32_t j2 = n2 ? (i2 >> 1) : cidx32(i2, nf2);
+  const uint32_t ex1 = D3 ? (n1 ? nf1 - nc1 : nc1) : 1u, ex2 = n2 ? nf2 - nc2 : nc2;
+  const int m = (n1 ? 1 << g.bit[1] : 0) | (n2 ? 1 << g.bit[2] : 0);
+  CoeffSlot c;
+  c.stride = ex1 * ex2;
+  const uint32_t at = (uint32_t)g.level_off + j1 * ex2 + j2;
+  // the first coarse plane at or after `first` has index (first + 1) / 2, the
+  // first new one first / 2
+  c.pc = at + sel8(so, m) + ((first + 1) >> 1) * c.stride;
+  c.pn = at + sel8(so, m | ms) + (first >> 1) * c.stride;
+  yx = n1 || n2;
+  return c;
+}
+// Loads of one plane's coefficient for a slot: has = the node holds one.
+template <bool RAW>
+__device__ __forceinline__ void coeff_load(const CoeffSrc& src, CoeffSlot& c, bool in, bool yx,
+                                           bool newp, uint32_t& pos, uint32_t& sv, double& rv) {
+  const bool has = in && (newp || yx);
+  pos = has ? (newp ? c.pn : c.pc) : 0u;
+  if (newp) c.pn += c.stride;
+  else c.pc += c.stride;
+  if (RAW) rv = has ? src.raw[pos] : 0.0;
+  else sv = has ? (uint32_t)src.sym[pos] : 32768u;  // 32768: zero
+}
+// Values of N loaded coefficients: one branch for all of them when any lane
+// of the wavefront holds an escaped one.
+template <bool RAW, int N>
+__device__ __forceinline__ void coeff_values(const CoeffSrc& src, const uint32_t (&pos)[N],
+                                             const uint32_t (&sv)[N], const double (&rv)[N],
+                                             double q, double (&v)[N]) {
+  if constexpr (RAW) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) v[k] = rv[k];
+  } else {
+    uint32_t least = sv[0];
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+      v[k] = (double)((int)sv[k] - 32768) * q;
+      least = min(least, sv[k]);
+    }
+    if (__any(least == 0)) {
+#pragma unroll
+      for (int k = 0; k < N; ++k)
+        if (sv[k] == 0) v[k] = (double)escaped_k(src, pos[k]) * q;
+    }
+  }
+}
 
 template <bool RAW>
 __global__ __launch_bounds__(256, 4) void k_rec_stream(const LevelGeom g, const CoeffSrc src,
                                                      const double q, double* __restrict__ fout,
                                                      const int seg, const uint32_t n_blocks) {
-  constexpr int SY = kStreamSY, SX = kStreamSX, E2 = kStreamE2;
-  __shared__ RecStreamSmem sm;
+  constexpr int SY = kStreamSY, SX = kStreamSX, E1 = kStreamE1;
+  constexpr int NP = (kStreamE2 + 1) / 2, PITCH = 2 * NP + 1, NLD = (E1 * NP + 255) / 256;
+  static_assert(SY * SX == 256 && E1 > 16 && E1 <= 24, "one output per thread, three row steps");
+  __shared__ double P[2][E1 * PITCH];
+  __shared__ double X[2][E1][SX];
   const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
   if (b >= n_blocks) return;
   const uint32_t nf0 = (uint32_t)g.nf[0], nf1 = (uint32_t)g.nf[1], nf2 = (uint32_t)g.nf[2];
@@ -1040,177 +1238,213 @@ __global__ __launch_bounds__(256, 4) void k_rec_stream(const LevelGeom g, const 
   const uint32_t tx = b % tiles_x, rest = b / tiles_x;
   const uint32_t ty = rest % tiles_y, sg = rest / tiles_y;
   const uint32_t c0y = ty * SY, c0x = tx * SX;
-  const int tky = (int)min<uint32_t>(SY, nc1 - c0y), tkx = (int)min<uint32_t>(SX, nc2 - c0x);
-  const uint32_t py0 = cpos32(c0y, nf1), px0 = cpos32(c0x, nf2);
-  const uint32_t lo1 = py0 >= 2 ? py0 - 2 : 0, lo2 = px0 >= 2 ? px0 - 2 : 0;
-  const int ext1 = (int)(min<uint32_t>(cpos32(c0y + tky - 1, nf1) + 2, nf1 - 1) - lo1 + 1);
-  const int ext2 = (int)(min<uint32_t>(cpos32(c0x + tkx - 1, nf2) + 2, nf2 - 1) - lo2 + 1);
-  const uint32_t cz0 = sg * (uint32_t)seg, cz1 = min<uint32_t>(cz0 + seg, nc0);
-  const uint32_t pz0 = cpos32(cz0, nf0);
-  const uint32_t zs = pz0 >= 2 ? pz0 - 2 : 0;
-  const uint32_t ze = min<uint32_t>(cpos32(cz1 - 1, nf0) + 2, nf0 - 1);
+  const int cz0 = (int)(sg * (uint32_t)seg), cz1 = min(cz0 + seg, (int)nc0);
+  const int lo1 = (int)cpos32(c0y, nf1) - 2, lo2 = (int)cpos32(c0x, nf2) - 2;
   const int tid = threadIdx.x;
-  for (int i = tid; i < 5 * tky; i += 256) sm.W1[i / 5][i % 5] = g.ax[1].W[5 * c0y + i];
-  for (int i = tid; i < 5 * tkx; i += 256) sm.W2[i / 5][i % 5] = g.ax[2].W[5 * c0x + i];
-  for (int i = tid; i < tky; i += 256) sm.P1[i] = (int)(cpos32(c0y + i, nf1) - lo1);
-  for (int i = tid; i < tkx; i += 256) sm.P2[i] = (int)(cpos32(c0x + i, nf2) - lo2);
-  // the lane's region slots: stream position = pbase[n0] + j0 * pstride
-  // (n0: the plane's z is a new node); coarse along all axes -> no value
-  const int n_pl = ext1 * ext2;
-  const uint64_t m2 = div_magic((uint32_t)ext2);
-  const uint32_t e1c = nc1, e1n = nf1 - nc1, e2c = nc2, e2n = nf2 - nc2;
-  const int mb0 = g.bit[0] >= 0 ? 1 << g.bit[0] : 0, mb1 = g.bit[1] >= 0 ? 1 << g.bit[1] : 0,
-            mb2 = g.bit[2] >= 0 ? 1 << g.bit[2] : 0;
+  // planes are loaded from z_first on; those before the grid hold zeros
+  const int z_first = 2 * (cz0 - 2) + 1, z0 = max(z_first, 0);
   uint32_t so[8];
   subband_offsets(g, so);
-  const uint32_t lvl = (uint32_t)g.level_off;
-  // stream position of slot u on a plane that is new (n0) or coarse along z:
-  // base + j0 * stride (j0: the plane's index among the planes of its kind)
-  auto slot_base = [&](int u, bool n0, uint32_t& stride, bool& yx) -> uint32_t {
-    const int e = min(u * 256 + tid, n_pl - 1);
-    const int y = (int)div_small((uint32_t)e, m2), x = e - y * ext2;
-    const uint32_t i1 = lo1 + y, i2 = lo2 + x;
-    const bool n1 = is_new32(i1, nf1), n2 = is_new32(i2, nf2);
-    const uint32_t j1 = n1 ? (i1 >> 1) : cidx32(i1, nf1);
-    const uint32_t j2 = n2 ? (i2 >> 1) : cidx32(i2, nf2);
-    const uint32_t ex1 = n1 ? e1n : e1c, ex2 = n2 ? e2n : e2c;
-    const int myx = (n1 ? mb1 : 0) | (n2 ? mb2 : 0);
-    stride = ex1 * ex2;
-    yx = n1 || n2;
-    return lvl + sel8(so, n0 ? (myx | mb0) : myx) + j1 * ex2 + j2;
-  };
-  // running positions of the next coarse and the next new plane to load
-  // (planes are loaded once each, in order; the first coarse plane at or
-  // after zs has j0 = (zs + 1) / 2, the first new one j0 = zs / 2)
-  uint32_t pc[kStreamNLD], pn[kStreamNLD], pstride[kStreamNLD];
-  int ldst[kStreamNLD];  // LDS slot | 1 << 30 when new along y or x; -1: none
+  CoeffSlot cs[NLD][2];
+  int lds0[NLD];
+  unsigned in = 0, yx = 0;
 #pragma unroll
-  for (int u = 0; u < kStreamNLD; ++u) {
-    uint32_t st;
-    bool yx;
-    const uint32_t bc = slot_base(u, false, st, yx), bn = slot_base(u, true, st, yx);
-    pstride[u] = st;
-    pc[u] = bc + ((zs + 1) >> 1) * st;
-    pn[u] = bn + (zs >> 1) * st;
-    const int e = min(u * 256 + tid, n_pl - 1);
-    const int y = (int)div_small((uint32_t)e, m2), x = e - y * ext2;
-    ldst[u] = u * 256 + tid < n_pl ? ((y * E2 + x) | (yx ? 1 << 30 : 0)) : -1;
-  }
-  const int xcol = tid & 31, xrow = tid >> 5;
-  int xf[5];
-  double xw[5];
-  __syncthreads();  // tables
-  {
-    const int p = xcol < tkx ? sm.P2[xcol] : 0;
+  for (int u = 0; u < NLD; ++u) {
+    const int e = min(u * 256 + tid, E1 * NP - 1);
+    const int y = lo1 + e / NP;
+    lds0[u] = e / NP * PITCH + 2 * (e % NP);
 #pragma unroll
-    for (int d = 0; d < 5; ++d) {
-      xf[d] = min(max(p + d - 2, 0), ext2 - 1);
-      xw[d] = xcol < tkx ? sm.W2[xcol][d] : 0.0;
+    for (int k = 0; k < 2; ++k) {
+      const int x = lo2 + 2 * (e % NP) + k;
+      const bool ok = y >= 0 && x >= 0 && y < (int)nf1 && x < (int)nf2 && u * 256 + tid < E1 * NP;
+      bool w;
+      cs[u][k] = coeff_slot<true>(g, so, (uint32_t)min(max(y, 0), (int)nf1 - 1),
+                                  (uint32_t)min(max(x, 0), (int)nf2 - 1), (uint32_t)z0, w);
+      in |= ok ? 1u << (2 * u + k) : 0u;
+      yx |= w ? 1u << (2 * u + k) : 0u;
     }
   }
-  const int ocy = tid >> 5, ocx = tid & 31;
-  const bool own = ocy < tky && ocx < tkx;
-  int yf[5];
-  double yw[5];
-  {
-    const int p = own ? sm.P1[ocy] : 0;
+  uint32_t pos[2][2 * NLD], sv[2][2 * NLD];
+  double rv[2][2 * NLD];
+  auto load_planes = [&](int z) {
 #pragma unroll
-    for (int d = 0; d < 5; ++d) {
-      yf[d] = min(max(p + d - 2, 0), ext1 - 1);
-      yw[d] = own ? sm.W1[ocy][d] : 0.0;
+    for (int p = 0; p < 2; ++p) {
+      const bool zin = z + p >= 0 && z + p < (int)nf0;
+      const bool newp = zin && is_new32((uint32_t)(z + p), nf0);
+#pragma unroll
+      for (int u = 0; u < NLD; ++u)
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+          if (zin) {
+            coeff_load<RAW>(src, cs[u][k], (in >> (2 * u + k)) & 1u, (yx >> (2 * u + k)) & 1u, newp,
+                            pos[p][2 * u + k], sv[p][2 * u + k], rv[p][2 * u + k]);
+          } else {
+            pos[p][2 * u + k] = 0u;
+            sv[p][2 * u + k] = 32768u;
+            rv[p][2 * u + k] = 0.0;
+          }
+        }
     }
+  };
+  const int cy = tid >> 5, cx = tid & 31;
+  const uint32_t J1 = c0y + cy, J2 = c0x + cx;
+  const bool own = J1 < nc1 && J2 < nc2;
+  const uint32_t K1 = min(J1, nc1 - 1), K2 = min(J2, nc2 - 1);
+  double xw[5], yw[5];
+#pragma unroll
+  for (int d = 0; d < 5; ++d) {
+    xw[d] = g.ax[2].W[5 * (size_t)K2 + d];
+    yw[d] = g.ax[1].W[5 * (size_t)K1 + d];
   }
-  const uint32_t J1 = c0y + ocy, J2 = c0x + ocx;
-  // coefficient loads of a plane (symbols or FP64 values): kStreamPF planes
-  // in flight, one register set per plane in fixed roles (the plane loop is
-  // unrolled by kStreamPF)
-  // (a set holds only the loaded values: a slot's stream position and
-  // whether it holds a coefficient are recomputed from the plane index)
-  struct PlaneRegs {
-    uint32_t sv[kStreamNLD];
-    double rv[kStreamNLD];
-  };
-  PlaneRegs pr[kStreamPF];
-  auto load_plane = [&](uint32_t z, PlaneRegs& R) {
-    const bool n0 = is_new32(z, nf0);
+  const int xb = (int)cpos32(K2, nf2) - lo2 - 2, yb = (int)cpos32(K1, nf1) - lo1 - 2;
+  double Y[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  auto finish = [&](uint32_t J0, const double (&Z)[5]) {
+    if (!own) return;
+    const double* W0 = g.ax[0].W + 5 * (size_t)J0;
+    double acc = 0.0;
 #pragma unroll
-    for (int u = 0; u < kStreamNLD; ++u) {
-      const bool has = ldst[u] >= 0 && (n0 || (ldst[u] >> 30) != 0);
-      const uint32_t pos = has ? (n0 ? pn[u] : pc[u]) : 0u;
-      if (n0) pn[u] += pstride[u];
-      else pc[u] += pstride[u];
-      if (RAW) R.rv[u] = src.raw[pos];
-      else R.sv[u] = src.sym[pos];
+    for (int d = 0; d < 5; ++d) acc = fma(W0[d], Z[d], acc);
+    fout[((size_t)J0 * nc1 + J1) * nc2 + J2] = acc;
+  };
+  load_planes(z_first);
+  for (int i = cz0 - 2; i < cz1; ++i) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      double v[2 * NLD];
+      coeff_values<RAW>(src, pos[p], sv[p], rv[p], q, v);
+#pragma unroll
+      for (int u = 0; u < NLD; ++u)
+        if (u < NLD - 1 || u * 256 + tid < E1 * NP) {
+          P[p][lds0[u]] = v[2 * u];
+          P[p][lds0[u] + 1] = v[2 * u + 1];
+        }
     }
-  };
-  uint32_t next_cz = cz0;
+    if (i + 1 < cz1) load_planes(2 * (i + 1) + 1);
+    __syncthreads();
 #pragma unroll
-  for (int d = 0; d < kStreamPF; ++d)
-    if (zs + d <= ze) load_plane(zs + d, pr[d]);
-  for (uint32_t zb = zs; zb <= ze; zb += kStreamPF) {
+    for (int p = 0; p < 2; ++p) {
+      const double* row = P[p] + (tid >> 5) * PITCH + xb;
 #pragma unroll
-  for (int d = 0; d < kStreamPF; ++d) {
-    const uint32_t zf = zb + d;
-    if (zf > ze) break;
-    const int s5 = (int)(zf % 5u);
-    const bool n0 = is_new32(zf, nf0);
+      for (int k = 0; k < 3; ++k) {
+        if (k < 2 || (tid >> 5) + 16 < E1) {
+          double acc = 0.0;
 #pragma unroll
-    for (int u = 0; u < kStreamNLD; ++u) {
-      if (ldst[u] < 0) continue;
-      double v = 0.0;
-      if (n0 || (ldst[u] >> 30) != 0) {
-        if (RAW) {
-          v = pr[d].rv[u];
-        } else if (pr[d].sv[u] != 0) {
-          v = (double)((int)pr[d].sv[u] - 32768) * q;
-        } else {
-          // escaped value (rare): its stream position from scratch
-          uint32_t st;
-          bool yx;
-          const uint32_t j0 = n0 ? (zf >> 1) : cidx32(zf, nf0);
-          v = (double)escaped_k(src, slot_base(u, n0, st, yx) + j0 * st) * q;
+          for (int d = 0; d < 5; ++d) acc = fma(xw[d], row[8 * k * PITCH + d], acc);
+          X[p][(tid >> 5) + 8 * k][cx] = acc;
         }
       }
-      (&sm.P[0][0])[ldst[u] & 0xFFFF] = v;
     }
     __syncthreads();
-    if (zf + kStreamPF <= ze) load_plane(zf + kStreamPF, pr[d]);
-    if (xcol < tkx) {
-      for (int y = xrow; y < ext1; y += 8) {
-        const double* row = sm.P[y];
-        double acc = 0.0;
+    Y[0] = Y[2];
+    Y[1] = Y[3];
+    Y[2] = Y[4];
 #pragma unroll
-        for (int d = 0; d < 5; ++d) acc = fma(xw[d], row[xf[d]], acc);
-        sm.X[y][xcol] = acc;
-      }
-    }
-    __syncthreads();
-    if (own) {
+    for (int p = 0; p < 2; ++p) {
       double acc = 0.0;
 #pragma unroll
-      for (int d = 0; d < 5; ++d) acc = fma(yw[d], sm.X[yf[d]][ocx], acc);
-      sm.Y[s5][ocy][ocx] = acc;
+      for (int d = 0; d < 5; ++d) acc = fma(yw[d], X[p][yb + d][cx], acc);
+      Y[3 + p] = acc;
     }
-    __syncthreads();
-    while (next_cz < cz1 && min<uint32_t>(cpos32(next_cz, nf0) + 2, nf0 - 1) == zf) {
-      const uint32_t J0 = next_cz;
-      const uint32_t P0 = cpos32(J0, nf0);
-      const double* W0 = g.ax[0].W + 5 * (size_t)J0;
-      if (own) {
-        double acc = 0.0;
-#pragma unroll
-        for (int d = 0; d < 5; ++d) {
-          const int zz = min(max((int)P0 + d - 2, 0), (int)nf0 - 1);
-          acc = fma(W0[d], sm.Y[zz % 5][ocy][ocx], acc);
-        }
-        fout[((size_t)J0 * nc1 + J1) * nc2 + J2] = acc;
-      }
-      ++next_cz;
+    if (i >= cz0) finish((uint32_t)i, Y);
+    if (!(nf0 & 1u) && i == (int)nc0 - 2 && cz1 == (int)nc0) {
+      const double Z[5] = {Y[1], Y[2], Y[3], Y[3], Y[3]};
+      finish(nc0 - 1, Z);
+      break;
     }
-  }
   }
 }
 
+template <bool RAW>
+__global__ __launch_bounds__(256) void k_rec_stream2(const LevelGeom g, const CoeffSrc src,
+                                                     const double q, double* __restrict__ fout,
+                                                     const int seg, const uint32_t n_blocks) {
+  constexpr int SX = kStream2SX, E = kStream2E;
+  __shared__ double P[2][2][E];  // the rows of two steps
+  const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
+  if (b >= n_blocks) return;
+  const uint32_t nf1 = (uint32_t)g.nf[1], nf2 = (uint32_t)g.nf[2];
+  const uint32_t nc1 = (uint32_t)g.nc[1], nc2 = (uint32_t)g.nc[2];
+  const uint32_t tiles_x = (nc2 + SX - 1) / SX;
+  const uint32_t tx = b % tiles_x, sg = b / tiles_x;
+  const uint32_t c0x = tx * SX;
+  const int cy0 = (int)(sg * (uint32_t)seg), cy1 = min(cy0 + seg, (int)nc1);
+  const int lo2 = (int)cpos32(c0x, nf2) - 2;
+  const int tid = threadIdx.x;
+  const int y_first = 2 * (cy0 - 2) + 1, y0 = max(y_first, 0);
+  uint32_t so[8];
+  subband_offsets(g, so);
+  CoeffSlot cs[2];
+  bool in[2], yx[2];
+#pragma unroll
+  for (int k = 0; k < 2; ++k) {
+    const int x = lo2 + 2 * tid + k;
+    in[k] = x >= 0 && x < (int)nf2;
+    cs[k] = coeff_slot<false>(g, so, 0u, (uint32_t)min(max(x, 0), (int)nf2 - 1), (uint32_t)y0, yx[k]);
+  }
+  uint32_t pos[2][2], sv[2][2];
+  double rv[2][2];
+  auto load_rows = [&](int y) {
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      const bool yin = y + p >= 0 && y + p < (int)nf1;
+      const bool newp = yin && is_new32((uint32_t)(y + p), nf1);
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if (yin) {
+          coeff_load<RAW>(src, cs[k], in[k], yx[k], newp, pos[p][k], sv[p][k], rv[p][k]);
+        } else {
+          pos[p][k] = 0u;
+          sv[p][k] = 32768u;
+          rv[p][k] = 0.0;
+        }
+      }
+    }
+  };
+  const uint32_t J2 = c0x + tid, K2 = min(J2, nc2 - 1);
+  const bool own = tid < SX && J2 < nc2;
+  double xw[5];
+#pragma unroll
+  for (int d = 0; d < 5; ++d) xw[d] = g.ax[2].W[5 * (size_t)K2 + d];
+  const int xb = own ? (int)cpos32(K2, nf2) - lo2 - 2 : 0;
+  double Y[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+  auto finish = [&](uint32_t J1, const double (&Z)[5]) {
+    if (!own) return;
+    const double* W1 = g.ax[1].W + 5 * (size_t)J1;
+    double acc = 0.0;
+#pragma unroll
+    for (int d = 0; d < 5; ++d) acc = fma(W1[d], Z[d], acc);
+    fout[(size_t)J1 * nc2 + J2] = acc;
+  };
+  load_rows(y_first);
+  for (int i = cy0 - 2; i < cy1; ++i) {
+    double(*row)[E] = P[i & 1];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      double v[2];
+      coeff_values<RAW>(src, pos[p], sv[p], rv[p], q, v);
+      row[p][2 * tid] = v[0];
+      row[p][2 * tid + 1] = v[1];
+    }
+    if (i + 1 < cy1) load_rows(2 * (i + 1) + 1);
+    __syncthreads();
+    Y[0] = Y[2];
+    Y[1] = Y[3];
+    Y[2] = Y[4];
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      double acc = 0.0;
+#pragma unroll
+      for (int d = 0; d < 5; ++d) acc = fma(xw[d], row[p][xb + d], acc);
+      Y[3 + p] = acc;
+    }
+    if (i >= cy0) finish((uint32_t)i, Y);
+    if (!(nf1 & 1u) && i == (int)nc1 - 2 && cy1 == (int)nc1) {
+      const double Z[5] = {Y[1], Y[2], Y[3], Y[3], Y[3]};
+      finish(nc1 - 1, Z);
+      break;
+    }
+  }
+}
 
 // --------------------------------------------- recomposition of one level
 // f = (P^T M_l) c_l: the tile holds the dequantised coefficients (zero at the
@@ -3182,6 +3416,19 @@ StreamGrid stream_grid(const LevelGeom& g) {
   return sg;
 }
 
+// The same for 2-axis levels: about 2,048 blocks (eight 256-thread blocks fit
+// a CU), segments of at least 16 coarse rows (two steps of a segment only fill
+// its taps).
+StreamGrid stream2_grid(const LevelGeom& g) {
+  const int64_t tiles_x = (g.nc[2] + kStream2SX - 1) / kStream2SX;
+  const int64_t want = std::max<int64_t>(1, 2048 / tiles_x);
+  StreamGrid sg;
+  sg.seg = (int)std::max<int64_t>(16, (g.nc[1] + want - 1) / want);
+  sg.n_blocks = (uint32_t)(tiles_x * ((g.nc[1] + sg.seg - 1) / sg.seg));
+  sg.grid = (sg.n_blocks + 7) & ~7u;
+  return sg;
+}
+
 int active_axes(const LevelGeom& g) {
   return (g.bit[0] >= 0) + (g.bit[1] >= 0) + (g.bit[2] >= 0);
 }
@@ -3216,6 +3463,10 @@ void dec_dispatch(const void* G, const LevelGeom& g, double* fout, uint16_t* sym
       case 3: dec_3<Tin, MODE, 3>(Gp, g, fout, sym, raw, rp, ob, status, gate, s); break;
       default: dec_3<Tin, MODE, 0>(Gp, g, fout, sym, raw, rp, ob, status, gate, s);
     }
+  } else if (D == 2 && MODE != 2 && cand == 0 && g.nf[1] * g.nf[2] >= kStream2MinPoints) {
+    const StreamGrid sg = stream2_grid(g);
+    hipLaunchKernelGGL((k_dec_stream2<Tin, MODE == 0>), dim3(sg.grid), dim3(256), 0, s, Gp, g, fout,
+                       sym, raw, rp, ob, status, gate, sg.seg, sg.n_blocks);
   } else if (D == 2) {
     constexpr TileShape ts = sizeof(Tin) == 4 ? kDecTile2F32 : kDecTile2F64;
     const TileGrid t = tile_grid(g, ts.z, ts.y, ts.x);
@@ -3243,6 +3494,10 @@ void rec_restrict_dispatch(const LevelGeom& g, const CoeffSrc& src, double q, do
     const TileGrid t = tile_grid(g, 4, 8, 8);
     hipLaunchKernelGGL((k_rec_restrict<4, 8, 8, RAW>), dim3(t.grid), dim3(256), 0, s, g, src, q,
                        fout, t.n_tiles);
+  } else if (D == 2 && g.nf[1] * g.nf[2] >= kRecStream2MinPoints) {
+    const StreamGrid sg = stream2_grid(g);
+    hipLaunchKernelGGL((k_rec_stream2<RAW>), dim3(sg.grid), dim3(256), 0, s, g, src, q, fout,
+                       sg.seg, sg.n_blocks);
   } else if (D == 2) {
     const TileGrid t = tile_grid(g, 1, 8, 32);
     hipLaunchKernelGGL((k_rec_restrict<1, 8, 32, RAW>), dim3(t.grid), dim3(256), 0, s, g, src, q,

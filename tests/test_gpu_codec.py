@@ -307,6 +307,35 @@ def test_streamed_level_equals_tiled_with_escapes(shape, dtype, share):
     assert torch.max(torch.abs(y.double() - x.double())).item() <= 1e-3
 
 
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("shape,share", [((2897, 2897), 0.0), ((2898, 2899), 1e-3),
+                                         ((16385, 513), 0.05), ((514, 16400), 0.3),
+                                         ((2049, 2050), 0.01)])
+def test_streamed_rows_equal_tiled_with_escapes(shape, share, dtype):
+    """2-axis levels streamed along the rows (2^23 points and more down, 2^22
+    back) against the tiled decomposition (forced candidate 1): equal streams
+    with no, some and many escaped values, axes of odd and even length; and the
+    streamed way back meets the bound, its error in FP64 that of rounding."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(6)
+    x = torch.randn(shape, device="cuda", generator=gen).cumsum(0).cumsum(1) * 1e-3
+    spike = torch.rand(shape, device="cuda", generator=gen) < share
+    x = torch.where(spike, torch.randn(shape, device="cuda", generator=gen) * 300.0, x).to(getattr(torch, dtype))
+    n = x.numel()
+    a = mgc.compress(x, 1e-3, mode="abs", outlier_cap=n)
+    kind = "dec_f32" if dtype == "float32" else "dec_f64"
+    mgc.set_tuning(kind, 1)
+    try:
+        b = mgc.compress(x, 1e-3, mode="abs", outlier_cap=n)
+    finally:
+        mgc.set_tuning(kind, -1)
+    assert torch.equal(a, b)
+    assert torch.max(torch.abs(mgc.decompress(a).double() - x.double())).item() <= 1e-3
+    if dtype == "float64":
+        back = mgc.recompose(mgc.decompose(x), shape)
+        assert torch.max(torch.abs(back - x)).item() <= 1e-11 * float(x.abs().max())
+
+
 @pytest.mark.parametrize("shape", [(33, 34, 35), (130, 70), (3000,)])
 def test_mostly_escaped_values_match_oracle(shape):
     """Noise at a bound that escapes most values: every tile's list overflows."""
