@@ -1686,6 +1686,163 @@ __global__ __launch_bounds__(256) void k_rec_interp(const double* __restrict__ G
   rec_interp_body<Tout, TZ, TY, TX, SRC>(Gc, g, src, q, out, t);
 }
 
+// Levels with fewer fine points use the tiled kernel, whose blocks have no
+// chain of cells: 129^3 FP64 10.3 us streamed and 11.1 tiled, 65^3 10.4 and
+// 6.2; 1025 x 1025 8.2 and 8.7, 513 x 513 7.4 and 6.1; 75 x 100 x 125 8.2 and 8.0.
+constexpr int64_t kInterpStreamMin = int64_t(1) << 20;
+
+// Two neighbouring outputs with one store: rows start on any multiple of the
+// value's size, which global stores of 8 and 16 bytes take on this target.
+template <typename T>
+__device__ __forceinline__ void store_pair(T* p, T a, T b) {
+  typedef T pair __attribute__((ext_vector_type(2), aligned(alignof(T))));
+  pair v = {a, b};
+  *reinterpret_cast<pair*>(p) = v;
+}
+
+// The interpolation of large levels: a thread owns the coarse cells of one
+// column along the streamed axis (axis 0 of 3-axis levels, axis 1 of 2-axis
+// ones) and walks a segment of them, so a cell computes one plane's (row's)
+// corner value and in-plane interpolants and keeps those of the plane before,
+// positions advance by additions, and nothing is shared: no LDS, no barrier,
+// no tile edges.  The corners of the next two planes and the coefficients of
+// the next cell are in flight.  Values are formed by the tiled kernel's
+// operations in its order.  Bound by HBM (513^3 FP32: 188 us, the tiled
+// kernel 328 us with 685 vector and 600 scalar instructions for two cells a
+// lane; 8193 x 8193 FP64: 157 us, 222 us).
+template <typename Tout, int SRC, bool D3>
+__global__ __launch_bounds__(256) void k_rec_interp_stream(const double* __restrict__ Gc,
+                                                            const LevelGeom g, const CoeffSrc src,
+                                                            const double q,
+                                                            Tout* __restrict__ out, const int seg,
+                                                            const uint32_t cols,
+                                                            const uint32_t n_blocks) {
+  constexpr int A = D3 ? 0 : 1;   // the streamed axis
+  constexpr int NK = D3 ? 7 : 3;  // coefficients of a cell
+  const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
+  if (b >= n_blocks) return;
+  const uint32_t nfs = (uint32_t)g.nf[A], ncs = (uint32_t)g.nc[A];
+  const uint32_t nf1 = D3 ? (uint32_t)g.nf[1] : 1u, nc1 = D3 ? (uint32_t)g.nc[1] : 1u;
+  const uint32_t nf2 = (uint32_t)g.nf[2], nc2 = (uint32_t)g.nc[2];
+  const uint32_t id = (b % cols) * 256 + threadIdx.x, sg = b / cols;
+  const uint32_t z0 = sg * (uint32_t)seg, z1 = min(z0 + seg, ncs);
+  if (id >= nc1 * nc2) return;
+  const uint32_t J1 = D3 ? id / nc2 : 0u, J2 = D3 ? id - J1 * nc2 : id;
+  const bool h1 = D3 && 2 * J1 + 1 < nf1 - 1, h2 = 2 * J2 + 1 < nf2 - 1;
+  const uint32_t P1 = D3 ? cpos32(J1, nf1) : 0u, P2 = cpos32(J2, nf2);
+  const double wx0 = g.ax[2].wl[h2 ? P2 + 1 : P2], wx1 = g.ax[2].wr[h2 ? P2 + 1 : P2];
+  const double wy0 = D3 ? g.ax[1].wl[h1 ? P1 + 1 : P1] : 0.0,
+               wy1 = D3 ? g.ax[1].wr[h1 ? P1 + 1 : P1] : 0.0;
+  // corner offsets inside a coarse plane
+  const uint32_t o00 = J1 * nc2 + J2, dx = h2 ? 1u : 0u, dy = h1 ? nc2 : 0u;
+  const size_t cplane = (size_t)nc1 * nc2, fplane = (size_t)nf1 * nf2;
+  double nxt[4];
+  auto load_corners = [&](uint32_t z) {
+    const double* p = Gc + (size_t)min(z, ncs - 1) * cplane + o00;
+    nxt[0] = p[0];
+    nxt[1] = p[dx];
+    if constexpr (D3) {
+      nxt[2] = p[dy];
+      nxt[3] = p[dy + dx];
+    }
+  };
+  // stream positions of the cell's coefficients on coarse plane z0 and their
+  // steps: node k has bit 0: x new, bit 1: y new (D3), top bit: streamed axis new
+  const int ms = 1 << g.bit[A], m1 = D3 ? 1 << g.bit[1] : 0, m2 = 1 << g.bit[2];
+  uint32_t so[8];
+  subband_offsets(g, so);
+  const uint32_t e1[2] = {nc1, nf1 - nc1}, e2[2] = {nc2, nf2 - nc2};
+  uint32_t pos[NK], step[NK];
+  bool ok[NK];
+#pragma unroll
+  for (int k = 0; k < NK; ++k) {
+    const bool nx = (k + 1) & 1, ny = D3 && ((k + 1) & 2), ns = (k + 1) & (D3 ? 4 : 2);
+    const uint32_t x2 = e2[nx ? 1 : 0], x1 = D3 ? e1[ny ? 1 : 0] : 1u;
+    step[k] = x1 * x2;
+    ok[k] = (!nx || h2) && (!ny || h1);
+    pos[k] = (uint32_t)g.level_off + sel8(so, (nx ? m2 : 0) | (ny ? m1 : 0) | (ns ? ms : 0)) +
+             z0 * step[k] + J1 * x2 + J2;
+  }
+  uint32_t cv[NK];
+  double cr[NK];
+  auto here = [&](int k, bool hs) { return ok[k] && (!((k + 1) & (D3 ? 4 : 2)) || hs); };
+  auto load_coeffs = [&](bool hs) {  // of the cell at pos; 0 for nodes that are not there
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+      const uint32_t at = here(k, hs) ? pos[k] : 0u;
+      if (SRC == 1) cr[k] = src.raw[at];
+      else cv[k] = src.sym[at];
+    }
+  };
+  auto is_cell = [&](uint32_t z) { return 2 * z + 1 < nfs - 1; };
+  // one plane's corner value and interpolants: {c, ix, iy, ixy}
+  auto plane_vals = [&](double (&v)[4]) {
+    v[0] = nxt[0];
+    v[1] = lin2(wx0, nxt[0], wx1, nxt[1]);
+    if constexpr (D3) {
+      const double ix1 = lin2(wx0, nxt[2], wx1, nxt[3]);
+      v[2] = lin2(wy0, nxt[0], wy1, nxt[2]);
+      v[3] = lin2(wy0, v[1], wy1, ix1);
+    }
+  };
+  double cur[4], up[4];
+  load_corners(z0);
+  load_coeffs(is_cell(z0));
+  plane_vals(cur);
+  load_corners(z0 + 1);
+  Tout* o = out + (size_t)cpos32(z0, nfs) * fplane + (size_t)P1 * nf2 + P2;
+  for (uint32_t z = z0; z < z1; ++z) {
+    const bool hs = is_cell(z);
+    plane_vals(up);
+    double c[NK];
+    if constexpr (SRC == 1) {
+#pragma unroll
+      for (int k = 0; k < NK; ++k) c[k] = cr[k];
+    } else {
+      uint32_t least = cv[0];
+#pragma unroll
+      for (int k = 0; k < NK; ++k) {
+        c[k] = (double)((int)cv[k] - 32768) * q;
+        least = min(least, cv[k]);
+      }
+      if (__any(least == 0)) {
+#pragma unroll
+        for (int k = 0; k < NK; ++k)
+          if (cv[k] == 0 && here(k, hs)) c[k] = (double)escaped_k(src, pos[k]) * q;
+      }
+    }
+    if (z + 1 < z1) {
+      load_corners(z + 2);
+#pragma unroll
+      for (int k = 0; k < NK; ++k) pos[k] += step[k];
+      load_coeffs(is_cell(z + 1));
+    }
+    const double wz0 = hs ? g.ax[A].wl[2 * z + 1] : 0.0, wz1 = hs ? g.ax[A].wr[2 * z + 1] : 0.0;
+    auto put_row = [&](Tout* p, double a, double bx) {
+      if (h2) store_pair<Tout>(p, (Tout)a, (Tout)bx);
+      else *p = (Tout)a;
+    };
+    put_row(o, cur[0], cur[1] + c[0]);
+    if constexpr (D3) {
+      if (h1) put_row(o + nf2, cur[2] + c[1], cur[3] + c[2]);
+    }
+    if (hs) {
+      Tout* p = o + fplane;
+      if constexpr (D3) {
+        put_row(p, lin2(wz0, cur[0], wz1, up[0]) + c[3], lin2(wz0, cur[1], wz1, up[1]) + c[4]);
+        if (h1)
+          put_row(p + nf2, lin2(wz0, cur[2], wz1, up[2]) + c[5],
+                  lin2(wz0, cur[3], wz1, up[3]) + c[6]);
+      } else {
+        put_row(p, lin2(wz0, cur[0], wz1, up[0]) + c[1], lin2(wz0, cur[1], wz1, up[1]) + c[2]);
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < (D3 ? 4 : 2); ++k) cur[k] = up[k];
+    o += hs ? 2 * fplane : fplane;  // (an even axis ends on two adjacent coarse planes)
+  }
+}
+
 // --------------------------------------------------------- adjoint pieces
 // cbar at the new nodes of level l: g - M_l P v, straight from the coarse
 // solution v: along one axis M_l P takes a coarse node from its three coarse
@@ -3513,6 +3670,26 @@ template <typename Tout, int SRC>
 void rec_interp_dispatch(const double* Gc, const LevelGeom& g, const CoeffSrc& src, double q,
                          Tout* out, hipStream_t s) {
   const int D = active_axes(g);
+  const int64_t points = g.nf[0] * g.nf[1] * g.nf[2];
+  if (D >= 2 && points >= kInterpStreamMin) {
+    // Segments of eight cells at least (a segment reads one coarse plane more
+    // than it owns and sets up anew; 513^3 FP32: 188 us, with 18 cells, 3,885
+    // blocks, 229), at most 8,192 blocks; of four where eight would leave the
+    // card fewer than four blocks a CU (150 x 200 x 250 FP64: 54 -> 42 us).
+    const int64_t cells = D == 3 ? g.nc[1] * g.nc[2] : g.nc[2], len = g.nc[D == 3 ? 0 : 1];
+    const int64_t cols = (cells + 255) / 256, want = std::max<int64_t>(1, 8192 / cols);
+    const int64_t least = cols * ((len + 7) / 8) < 1024 ? 4 : 8;
+    const int64_t seg = std::max<int64_t>(least, (len + want - 1) / want);
+    const int64_t n = cols * ((len + seg - 1) / seg);
+    const dim3 grid((unsigned)((n + 7) & ~int64_t(7)));
+    if (D == 3)
+      hipLaunchKernelGGL((k_rec_interp_stream<Tout, SRC, true>), grid, dim3(256), 0, s, Gc, g, src,
+                         q, out, (int)seg, (uint32_t)cols, (uint32_t)n);
+    else
+      hipLaunchKernelGGL((k_rec_interp_stream<Tout, SRC, false>), grid, dim3(256), 0, s, Gc, g, src,
+                         q, out, (int)seg, (uint32_t)cols, (uint32_t)n);
+    return;
+  }
   if (D == 3) {
     const TileGrid t = tile_grid(g, 4, 8, 16);
     hipLaunchKernelGGL((k_rec_interp<Tout, 4, 8, 16, SRC>), dim3(t.grid), dim3(256), 0, s, Gc, g,

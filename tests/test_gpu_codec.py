@@ -336,6 +336,27 @@ def test_streamed_rows_equal_tiled_with_escapes(shape, share, dtype):
         assert torch.max(torch.abs(back - x)).item() <= 1e-11 * float(x.abs().max())
 
 
+@pytest.mark.parametrize("shape", [(3, 600, 601), (600, 3, 602), (601, 602, 3), (4, 513, 520),
+                                   (129, 130, 131), (130, 129, 64), (1025, 1024), (1024, 1025),
+                                   (3, 16500, 22), (65, 16500)])
+@pytest.mark.parametrize("share", [0.0, 0.02])
+def test_streamed_interpolation_holds_bound_and_inverts(shape, share):
+    """Levels of 2^20 points and more go back through the streamed
+    interpolation: both kinds of axis ends, one and several blocks and segments
+    a column, escaped values absent and present, both output types; FP64
+    coefficients invert to rounding."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(7)
+    x = torch.randn(shape, device="cuda", generator=gen, dtype=torch.float64) * 1e-2
+    spike = torch.rand(shape, device="cuda", generator=gen) < share
+    x = torch.where(spike, torch.randn(shape, device="cuda", generator=gen, dtype=torch.float64) * 300.0, x)
+    for y in (x, x.float()):
+        a = mgc.compress(y, 1e-3, mode="abs", outlier_cap=y.numel())
+        assert torch.max(torch.abs(mgc.decompress(a).double() - y.double())).item() <= 1e-3
+    back = mgc.recompose(mgc.decompose(x), shape)
+    assert torch.max(torch.abs(back - x)).item() <= 1e-11 * float(x.abs().max())
+
+
 @pytest.mark.parametrize("shape", [(33, 34, 35), (130, 70), (3000,)])
 def test_mostly_escaped_values_match_oracle(shape):
     """Noise at a bound that escapes most values: every tile's list overflows."""
