@@ -811,8 +811,9 @@ constexpr int kStreamNLD = (kStreamE1 * kStreamE2 + 255) / 256;
 constexpr int kStreamEsc = 320;  // escaped values a block collects between flushes
 // levels with fewer fine points use the tiled kernel (measured faster there)
 constexpr int64_t kStreamMinPoints = int64_t(1) << 25;
-// Recomposition's restriction (one value per coarse node from the dequantised
-// new nodes) gains from streaming already at half that size.
+// The same for recomposition's restriction: below, its few wavefronts leave
+// the chip idle (129^3 22 us, tiled 18; 150 x 200 x 250 with many escaped values
+// 167 us, tiled 87; 257^3 32 us, tiled 55).
 constexpr int64_t kRecStreamMinPoints = int64_t(1) << 24;
 
 // Raw planes kept: the three a cell spans and, where LDS allows four blocks
@@ -1149,44 +1150,37 @@ __global__ __launch_bounds__(256) void k_dec_stream2(
   }
 }
 
-// ------------------- recomposition restrictions of 3- and 2-axis levels, streamed
-// f = (P^T M_l) c_l with the same streaming: the fine planes (rows) are
-// assembled from the dequantised coefficients, zero at the nodes coarse along
-// every axis.  A thread takes pairs of neighbouring region slots, one of each
-// parity, so that consecutive lanes read consecutive positions of a subband;
-// a slot's stream position in the next coarse and the next new plane is kept
-// and advanced by the subband's plane stride, since planes come in order, once
-// each.  (513^3: 281 us, the pass over planes one at a time with a position
-// and a load per slot 315 us; 8193 x 8193: 95 us, the tiled kernel 295 us.)
+// ------------------- recomposition restriction of 2-axis levels, streamed
+// f = (P^T M_l) c_l along the rows: the fine rows are assembled from the
+// dequantised coefficients, zero at the nodes coarse along both axes.  A thread
+// takes pairs of neighbouring region slots, one of each parity, so that
+// consecutive lanes read consecutive positions of a subband; a slot's stream
+// position in the next coarse and the next new row is kept and advanced by the
+// subband's row stride, since rows come in order, once each.  (8193 x 8193:
+// 95 us, the tiled kernel 295 us.)
 struct CoeffSlot {
-  uint32_t pc, pn, stride;  // positions in the next coarse / new plane, their step
+  uint32_t pc, pn, stride;  // positions in the next coarse / new row, their step
 };
-// Slot of the node (i1, i2) of a plane along axis 0 (3-axis levels) or of the
-// node i2 of a row along axis 1 (2-axis levels, i1 unused); first: the first
-// fine plane (row) that is loaded.  yx: new along an axis within the plane.
-template <bool D3>
+// Slot of node i2 of a row along axis 1; first: the first fine row that is
+// loaded.  yx: new along axis 2.
 __device__ __forceinline__ CoeffSlot coeff_slot(const LevelGeom& g, const uint32_t (&so)[8],
-                                                uint32_t i1, uint32_t i2, uint32_t first,
-                                                bool& yx) {
-  const uint32_t nf1 = (uint32_t)g.nf[1], nf2 = (uint32_t)g.nf[2];
-  const uint32_t nc1 = (uint32_t)g.nc[1], nc2 = (uint32_t)g.nc[2];
-  const int ms = 1 << g.bit[D3 ? 0 : 1];  // the streamed axis' subband bit
-  const bool n1 = D3 && is_new32(i1, nf1), n2 = is_new32(i2, nf2);
-  const uint32_t j1 = D3 ? (n1 ? (i1 >> 1) : cidx32(i1, nf1)) : 0u;
+                                                uint32_t i2, uint32_t first, bool& yx) {
+  const uint32_t nf2 = (uint32_t)g.nf[2], nc2 = (uint32_t)g.nc[2];
+  const int ms = 1 << g.bit[1];
+  const bool n2 = is_new32(i2, nf2);
   const uint32_t j2 = n2 ? (i2 >> 1) : cidx32(i2, nf2);
-  const uint32_t ex1 = D3 ? (n1 ? nf1 - nc1 : nc1) : 1u, ex2 = n2 ? nf2 - nc2 : nc2;
-  const int m = (n1 ? 1 << g.bit[1] : 0) | (n2 ? 1 << g.bit[2] : 0);
+  const int m = n2 ? 1 << g.bit[2] : 0;
   CoeffSlot c;
-  c.stride = ex1 * ex2;
-  const uint32_t at = (uint32_t)g.level_off + j1 * ex2 + j2;
-  // the first coarse plane at or after `first` has index (first + 1) / 2, the
+  c.stride = n2 ? nf2 - nc2 : nc2;
+  const uint32_t at = (uint32_t)g.level_off + j2;
+  // the first coarse row at or after `first` has index (first + 1) / 2, the
   // first new one first / 2
   c.pc = at + sel8(so, m) + ((first + 1) >> 1) * c.stride;
   c.pn = at + sel8(so, m | ms) + (first >> 1) * c.stride;
-  yx = n1 || n2;
+  yx = n2;
   return c;
 }
-// Loads of one plane's coefficient for a slot: has = the node holds one.
+// Loads of one row's coefficient for a slot: has = the node holds one.
 template <bool RAW>
 __device__ __forceinline__ void coeff_load(const CoeffSrc& src, CoeffSlot& c, bool in, bool yx,
                                            bool newp, uint32_t& pos, uint32_t& sv, double& rv) {
@@ -1221,137 +1215,251 @@ __device__ __forceinline__ void coeff_values(const CoeffSrc& src, const uint32_t
   }
 }
 
+// ------------------------------------ 3-axis levels by columns of wavefronts
+// A wavefront owns kColX coarse columns along x (one a lane, and one more lane
+// on each side) times kColY coarse rows, and marches along z.  A lane holds the
+// two nodes of its coarse cell, old (coarse) and new, of every fine row and
+// plane, so a row's loads are consecutive lanes at consecutive positions from
+// a base that the whole wavefront shares.  The neighbour cells' values along x
+// come from the neighbour lanes, rows and planes are added to the running sums
+// of the outputs that they reach, in the order of the taps: no LDS, no barrier.
+constexpr int kColX = 62, kColY = 4;
+constexpr uint32_t kColEsc = 256;  // escaped values of a wavefront's plane that are searched together
+
+// Tap d of coarse node J's restriction in the order old(J - 1), new(J - 1),
+// old(J), new(J), old(J + 1); 0 where the axis has no such node.  An even axis
+// ends on two adjacent coarse nodes.
+__device__ __forceinline__ double cell_tap(const double* W, int J, int nf, int nc, int d) {
+  J = min(max(J, 0), nc - 1);
+  const bool even = !(nf & 1), last = J == nc - 1, before = even && J == nc - 2;
+  int k = d;
+  bool zero = J == 0 && d < 2;
+  if (last) {
+    zero = zero || d > 2;
+    if (even) {  // its left neighbour is a coarse node, one fine step away
+      zero = zero || d == 1;
+      if (d == 0) k = 1;
+    }
+  }
+  if (before) {  // its right neighbour is the last coarse node
+    zero = zero || d == 3;
+    if (d == 4) k = 3;
+  }
+  return zero ? 0.0 : W[5 * (size_t)J + k];
+}
+
+// Orders a wavefront's accesses of its own LDS list.
+__device__ __forceinline__ void wave_lds_fence() {
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+}
+
+// Value of the lane to the left / right (0 at the wavefront's ends).
+template <int CTRL>
+__device__ __forceinline__ double lane_shift(double v) {
+  const int lo = __builtin_amdgcn_mov_dpp(__double2loint(v), CTRL, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_mov_dpp(__double2hiint(v), CTRL, 0xf, 0xf, true);
+  return __hiloint2double(hi, lo);
+}
+__device__ __forceinline__ double from_left(double v) { return lane_shift<0x138>(v); }
+__device__ __forceinline__ double from_right(double v) { return lane_shift<0x130>(v); }
+
+// f = (P^T M_l) c_l; the nodes coarse along every axis hold none.  513^3: 133
+// us (135 M symbols of two bytes; the streamed pass through LDS 281 us, at 58 %
+// vector instructions most of which found slots and positions; here about 460 a
+// step of two planes), 257^3 32 us (46), 300 x 400 x 500 65 us (129), FP64
+// coefficients of 257^3 50 us (51).  Three rows a wavefront 139 us.
 template <bool RAW>
-__global__ __launch_bounds__(256, 4) void k_rec_stream(const LevelGeom g, const CoeffSrc src,
-                                                     const double q, double* __restrict__ fout,
-                                                     const int seg, const uint32_t n_blocks) {
-  constexpr int SY = kStreamSY, SX = kStreamSX, E1 = kStreamE1;
-  constexpr int NP = (kStreamE2 + 1) / 2, PITCH = 2 * NP + 1, NLD = (E1 * NP + 255) / 256;
-  static_assert(SY * SX == 256 && E1 > 16 && E1 <= 24, "one output per thread, three row steps");
-  __shared__ double P[2][E1 * PITCH];
-  __shared__ double X[2][E1][SX];
+__global__ __launch_bounds__(256, 4) void k_rec_cols(const LevelGeom g, const CoeffSrc src,
+                                                   const double q, double* __restrict__ fout,
+                                                   const int seg, const uint32_t n_blocks) {
+  constexpr int R = kColY, NR = 2 * R + 3;
+  __shared__ double esc_list[RAW ? 1 : 4][RAW ? 1 : kColEsc];  // a list for each wavefront
+  using V = typename std::conditional<RAW, double, uint32_t>::type;
   const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
   if (b >= n_blocks) return;
-  const uint32_t nf0 = (uint32_t)g.nf[0], nf1 = (uint32_t)g.nf[1], nf2 = (uint32_t)g.nf[2];
-  const uint32_t nc0 = (uint32_t)g.nc[0], nc1 = (uint32_t)g.nc[1], nc2 = (uint32_t)g.nc[2];
-  const uint32_t tiles_x = (nc2 + SX - 1) / SX, tiles_y = (nc1 + SY - 1) / SY;
+  const int nf0 = (int)g.nf[0], nf1 = (int)g.nf[1], nf2 = (int)g.nf[2];
+  const int nc0 = (int)g.nc[0], nc1 = (int)g.nc[1], nc2 = (int)g.nc[2];
+  const int nn0 = nf0 - nc0, nn1 = nf1 - nc1, nn2 = nf2 - nc2;  // new nodes of an axis
+  const uint32_t tiles_x = (uint32_t)(nc2 + kColX - 1) / kColX;
+  const uint32_t tiles_y = (uint32_t)(nc1 + 4 * R - 1) / (4 * R);
   const uint32_t tx = b % tiles_x, rest = b / tiles_x;
   const uint32_t ty = rest % tiles_y, sg = rest / tiles_y;
-  const uint32_t c0y = ty * SY, c0x = tx * SX;
-  const int cz0 = (int)(sg * (uint32_t)seg), cz1 = min(cz0 + seg, (int)nc0);
-  const int lo1 = (int)cpos32(c0y, nf1) - 2, lo2 = (int)cpos32(c0x, nf2) - 2;
-  const int tid = threadIdx.x;
-  // planes are loaded from z_first on; those before the grid hold zeros
-  const int z_first = 2 * (cz0 - 2) + 1, z0 = max(z_first, 0);
-  uint32_t so[8];
-  subband_offsets(g, so);
-  CoeffSlot cs[NLD][2];
-  int lds0[NLD];
-  unsigned in = 0, yx = 0;
-#pragma unroll
-  for (int u = 0; u < NLD; ++u) {
-    const int e = min(u * 256 + tid, E1 * NP - 1);
-    const int y = lo1 + e / NP;
-    lds0[u] = e / NP * PITCH + 2 * (e % NP);
-#pragma unroll
-    for (int k = 0; k < 2; ++k) {
-      const int x = lo2 + 2 * (e % NP) + k;
-      const bool ok = y >= 0 && x >= 0 && y < (int)nf1 && x < (int)nf2 && u * 256 + tid < E1 * NP;
-      bool w;
-      cs[u][k] = coeff_slot<true>(g, so, (uint32_t)min(max(y, 0), (int)nf1 - 1),
-                                  (uint32_t)min(max(x, 0), (int)nf2 - 1), (uint32_t)z0, w);
-      in |= ok ? 1u << (2 * u + k) : 0u;
-      yx |= w ? 1u << (2 * u + k) : 0u;
-    }
-  }
-  uint32_t pos[2][2 * NLD], sv[2][2 * NLD];
-  double rv[2][2 * NLD];
-  auto load_planes = [&](int z) {
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const bool zin = z + p >= 0 && z + p < (int)nf0;
-      const bool newp = zin && is_new32((uint32_t)(z + p), nf0);
-#pragma unroll
-      for (int u = 0; u < NLD; ++u)
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-          if (zin) {
-            coeff_load<RAW>(src, cs[u][k], (in >> (2 * u + k)) & 1u, (yx >> (2 * u + k)) & 1u, newp,
-                            pos[p][2 * u + k], sv[p][2 * u + k], rv[p][2 * u + k]);
-          } else {
-            pos[p][2 * u + k] = 0u;
-            sv[p][2 * u + k] = 32768u;
-            rv[p][2 * u + k] = 0.0;
-          }
-        }
-    }
-  };
-  const int cy = tid >> 5, cx = tid & 31;
-  const uint32_t J1 = c0y + cy, J2 = c0x + cx;
-  const bool own = J1 < nc1 && J2 < nc2;
-  const uint32_t K1 = min(J1, nc1 - 1), K2 = min(J2, nc2 - 1);
-  double xw[5], yw[5];
+  const int c1 = ((int)ty * 4 + __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6))) * R;
+  if (c1 >= nc1) return;
+  const int z0 = (int)sg * seg, z1 = min(z0 + seg, nc0);
+  const int lane = (int)(threadIdx.x & 63), J2 = (int)tx * kColX - 1 + lane;
+  const bool own = lane >= 1 && lane <= kColX && J2 < nc2;
+  // positions outside the grid read a node at its edge and count with tap 0
+  const uint32_t xo = (uint32_t)min(max(J2, 0), nc2 - 1), xn = (uint32_t)min(max(J2, 0), nn2 - 1);
+  double xw[5], yw[R][5];
 #pragma unroll
   for (int d = 0; d < 5; ++d) {
-    xw[d] = g.ax[2].W[5 * (size_t)K2 + d];
-    yw[d] = g.ax[1].W[5 * (size_t)K1 + d];
-  }
-  const int xb = (int)cpos32(K2, nf2) - lo2 - 2, yb = (int)cpos32(K1, nf1) - lo1 - 2;
-  double Y[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
-  auto finish = [&](uint32_t J0, const double (&Z)[5]) {
-    if (!own) return;
-    const double* W0 = g.ax[0].W + 5 * (size_t)J0;
-    double acc = 0.0;
+    xw[d] = cell_tap(g.ax[2].W, J2, nf2, nc2, d);
 #pragma unroll
-    for (int d = 0; d < 5; ++d) acc = fma(W0[d], Z[d], acc);
-    fout[((size_t)J0 * nc1 + J1) * nc2 + J2] = acc;
+    for (int j = 0; j < R; ++j) yw[j][d] = cell_tap(g.ax[1].W, c1 + j, nf1, nc1, d);
+  }
+  uint32_t so[8];
+  subband_offsets(g, so);
+  const int m0 = 1 << g.bit[0], m1 = 1 << g.bit[1], m2 = 1 << g.bit[2];
+  // row r of a plane: the old (r even) or new node row r / 2 of the strip;
+  // its first position on plane J (zn: a new plane), old or new along x
+  auto row_at = [&](bool zn, int J, int r, bool xnew) -> uint32_t {
+    const int n = (r & 1) ? nn1 : nc1, row = min(max(c1 - 1 + r / 2, 0), n - 1);
+    const int m = (zn ? m0 : 0) | ((r & 1) ? m1 : 0) | (xnew ? m2 : 0);
+    return (uint32_t)g.level_off + sel8(so, m) +
+           (uint32_t)(J * n + row) * (uint32_t)(xnew ? nn2 : nc2);
   };
-  load_planes(z_first);
-  for (int i = cz0 - 2; i < cz1; ++i) {
+  auto at = [&](uint32_t base, uint32_t x) -> V {
+    if constexpr (RAW)
+      return *reinterpret_cast<const double*>(reinterpret_cast<const char*>(src.raw + base) + 8 * x);
+    else
+      return *reinterpret_cast<const uint16_t*>(reinterpret_cast<const char*>(src.sym + base) + 2 * x);
+  };
+  struct Plane {
+    V o[NR], n[NR];
+  };
+  Plane po, pn;  // the next old and the next new plane
+  auto load = [&](auto zn, int J, Plane& p) {
+    J = min(max(J, 0), (zn ? nn0 : nc0) - 1);
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      double v[2 * NLD];
-      coeff_values<RAW>(src, pos[p], sv[p], rv[p], q, v);
-#pragma unroll
-      for (int u = 0; u < NLD; ++u)
-        if (u < NLD - 1 || u * 256 + tid < E1 * NP) {
-          P[p][lds0[u]] = v[2 * u];
-          P[p][lds0[u] + 1] = v[2 * u + 1];
-        }
+    for (int r = 0; r < NR; ++r) {
+      if (zn || (r & 1)) p.o[r] = at(row_at(zn, J, r, false), xo);
+      p.n[r] = at(row_at(zn, J, r, true), xn);
     }
-    if (i + 1 < cz1) load_planes(2 * (i + 1) + 1);
-    __syncthreads();
+  };
+  auto x_sum = [&](bool both, double o, double n) {
+    double X = 0.0;
+    if (both) X = fma(xw[0], from_left(o), 0.0);
+    X = fma(xw[1], from_left(n), X);
+    if (both) X = fma(xw[2], o, X);
+    X = fma(xw[3], n, X);
+    if (both) X = fma(xw[4], from_right(o), X);
+    return X;
+  };
+  // the lanes below this one in mask m
+  auto below = [](uint64_t m) -> uint32_t {
+    return __builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
+  };
+  // a plane's restriction along x and y at the strip's rows
+  auto rows = [&](auto zn, auto value, double (&Y)[R]) {
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const double* row = P[p] + (tid >> 5) * PITCH + xb;
+    for (int j = 0; j < R; ++j) Y[j] = 0.0;
 #pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        if (k < 2 || (tid >> 5) + 16 < E1) {
-          double acc = 0.0;
+    for (int r = 0; r < NR; ++r) {
+      const bool both = zn || (r & 1);
+      const double n = value(r, true), o = both ? value(r, false) : 0.0;
+      const double X = x_sum(both, o, n);
 #pragma unroll
-          for (int d = 0; d < 5; ++d) acc = fma(xw[d], row[8 * k * PITCH + d], acc);
-          X[p][(tid >> 5) + 8 * k][cx] = acc;
-        }
+      for (int j = 0; j < R; ++j)
+        if (r - 2 * j >= 0 && r - 2 * j < 5) Y[j] = fma(yw[j][r - 2 * j], X, Y[j]);
+    }
+  };
+  // A plane with escaped values: the wavefront lists their positions and its
+  // lanes search the records for one each, so a plane usually costs one search
+  // instead of one a row.  Rolled loops over symbols read again: unrolled, the
+  // searches took registers from the planes without any.
+  auto reduce_escaped = [&](bool zn, int J, double (&Y)[R]) {
+    J = min(max(J, 0), (zn ? nn0 : nc0) - 1);
+    double* list = esc_list[threadIdx.x >> 6];
+    uint32_t n = 0;
+    auto collect = [&](uint32_t pos) {
+      const bool e = src.sym[pos] == 0;
+      const uint64_t m = __ballot(e);
+      const uint32_t k = n + below(m);
+      if (e && k < kColEsc) list[k] = (double)pos;
+      n += (uint32_t)__popcll(m);
+    };
+#pragma unroll 1
+    for (int r = 0; r < NR; ++r) {
+      collect(row_at(zn, J, r, true) + xn);
+      if (zn || (r & 1)) collect(row_at(zn, J, r, false) + xo);
+    }
+    wave_lds_fence();
+    for (uint32_t k = (uint32_t)lane; k < min(n, kColEsc); k += 64)
+      list[k] = (double)escaped_k(src, (uint64_t)list[k]) * q;
+    wave_lds_fence();
+    n = 0;
+    auto value = [&](uint32_t pos) -> double {
+      const uint32_t s = src.sym[pos];
+      const uint64_t m = __ballot(s == 0);
+      const uint32_t k = n + below(m);
+      n += (uint32_t)__popcll(m);
+      if (s != 0) return (double)((int)s - 32768) * q;
+      return k < kColEsc ? list[k] : (double)escaped_k(src, pos) * q;
+    };
+#pragma unroll
+    for (int j = 0; j < R; ++j) Y[j] = 0.0;
+#pragma unroll 1
+    for (int r = 0; r < NR; ++r) {
+      const bool both = zn || (r & 1);
+      const double c = value(row_at(zn, J, r, true) + xn);
+      const double o = both ? value(row_at(zn, J, r, false) + xo) : 0.0;
+      const double X = x_sum(both, o, c);
+#pragma unroll
+      for (int j = 0; j < R; ++j)
+        if (r - 2 * j >= 0 && r - 2 * j < 5)
+          Y[j] = fma(cell_tap(g.ax[1].W, c1 + j, nf1, nc1, r - 2 * j), X, Y[j]);
+    }
+    wave_lds_fence();
+  };
+  auto reduce = [&](auto zn, int J, const Plane& p, double (&Y)[R]) {
+    if constexpr (RAW) {
+      rows(zn, [&](int r, bool xnew) -> double { return xnew ? p.n[r] : p.o[r]; }, Y);
+    } else {
+      uint32_t least = 1;
+#pragma unroll
+      for (int r = 0; r < NR; ++r) {
+        least = min(least, p.n[r]);
+        if (zn || (r & 1)) least = min(least, p.o[r]);
       }
+      if (__builtin_expect(__any(least == 0), 0))
+        reduce_escaped(zn, J, Y);
+      else
+        rows(zn, [&](int r, bool xnew) -> double {
+          return (double)((int)(xnew ? p.n[r] : p.o[r]) - 32768) * q;
+        }, Y);
     }
-    __syncthreads();
-    Y[0] = Y[2];
-    Y[1] = Y[3];
-    Y[2] = Y[4];
+  };
+  auto zw = [&](int J, int d) { return cell_tap(g.ax[0].W, J, nf0, nc0, d); };
+  auto store = [&](int J, const double (&f)[R]) {
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      double acc = 0.0;
+    for (int j = 0; j < R; ++j)
+      if (own && c1 + j < nc1) fout[((size_t)J * nc1 + c1 + j) * nc2 + J2] = f[j];
+  };
+  constexpr std::false_type OLD{};
+  constexpr std::true_type NEW{};
+  // sums of coarse planes p - 1, p and p + 1; the planes old(p), new(p) follow
+  const int pb = max(z0 - 1, 0);
+  double prev[R], cur[R], next[R], Y[R];
 #pragma unroll
-      for (int d = 0; d < 5; ++d) acc = fma(yw[d], X[p][yb + d][cx], acc);
-      Y[3 + p] = acc;
+  for (int j = 0; j < R; ++j) prev[j] = cur[j] = 0.0;
+  load(OLD, pb, po);
+  for (int p = pb; p < z1; ++p) {
+    load(NEW, p, pn);
+    const double w4 = zw(p - 1, 4), w2 = zw(p, 2), w0 = zw(p + 1, 0);
+    reduce(OLD, p, po, Y);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      prev[j] = fma(w4, Y[j], prev[j]);
+      cur[j] = fma(w2, Y[j], cur[j]);
+      next[j] = fma(w0, Y[j], 0.0);
     }
-    if (i >= cz0) finish((uint32_t)i, Y);
-    if (!(nf0 & 1u) && i == (int)nc0 - 2 && cz1 == (int)nc0) {
-      const double Z[5] = {Y[1], Y[2], Y[3], Y[3], Y[3]};
-      finish(nc0 - 1, Z);
-      break;
+    if (p > z0) store(p - 1, prev);
+    load(OLD, p + 1, po);
+    const double w3 = zw(p, 3), w1 = zw(p + 1, 1);
+    reduce(NEW, p, pn, Y);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      prev[j] = fma(w3, Y[j], cur[j]);
+      cur[j] = fma(w1, Y[j], next[j]);
     }
   }
+  reduce(OLD, z1, po, Y);
+  const double w4 = zw(z1 - 1, 4);
+#pragma unroll
+  for (int j = 0; j < R; ++j) prev[j] = fma(w4, Y[j], prev[j]);
+  store(z1 - 1, prev);
 }
 
 template <bool RAW>
@@ -1379,7 +1487,7 @@ __global__ __launch_bounds__(256) void k_rec_stream2(const LevelGeom g, const Co
   for (int k = 0; k < 2; ++k) {
     const int x = lo2 + 2 * tid + k;
     in[k] = x >= 0 && x < (int)nf2;
-    cs[k] = coeff_slot<false>(g, so, 0u, (uint32_t)min(max(x, 0), (int)nf2 - 1), (uint32_t)y0, yx[k]);
+    cs[k] = coeff_slot(g, so, (uint32_t)min(max(x, 0), (int)nf2 - 1), (uint32_t)y0, yx[k]);
   }
   uint32_t pos[2][2], sv[2][2];
   double rv[2][2];
@@ -3573,6 +3681,19 @@ StreamGrid stream_grid(const LevelGeom& g) {
   return sg;
 }
 
+// Blocks of four wavefronts, one above the other along y: about 2,048 (eight a
+// CU, half of them resident), segments of at least 8 coarse planes (a segment
+// reads three fine planes more than it owns).
+StreamGrid cols_grid(const LevelGeom& g) {
+  const int64_t cols = ((g.nc[2] + kColX - 1) / kColX) * ((g.nc[1] + 4 * kColY - 1) / (4 * kColY));
+  const int64_t want = std::max<int64_t>(1, 2048 / cols);
+  StreamGrid sg;
+  sg.seg = (int)std::max<int64_t>(8, (g.nc[0] + want - 1) / want);
+  sg.n_blocks = (uint32_t)(cols * ((g.nc[0] + sg.seg - 1) / sg.seg));
+  sg.grid = (sg.n_blocks + 7) & ~7u;
+  return sg;
+}
+
 // The same for 2-axis levels: about 2,048 blocks (eight 256-thread blocks fit
 // a CU), segments of at least 16 coarse rows (two steps of a segment only fill
 // its taps).
@@ -3642,9 +3763,9 @@ void rec_restrict_dispatch(const LevelGeom& g, const CoeffSrc& src, double q, do
                            hipStream_t s) {
   const int D = active_axes(g);
   if (D == 3 && g.nf[0] * g.nf[1] * g.nf[2] >= kRecStreamMinPoints) {
-    const StreamGrid sg = stream_grid(g);
-    hipLaunchKernelGGL((k_rec_stream<RAW>), dim3(sg.grid), dim3(256), 0, s, g, src, q, fout,
-                       sg.seg, sg.n_blocks);
+    const StreamGrid sg = cols_grid(g);
+    hipLaunchKernelGGL((k_rec_cols<RAW>), dim3(sg.grid), dim3(256), 0, s, g, src, q, fout, sg.seg,
+                       sg.n_blocks);
     return;
   }
   if (D == 3) {

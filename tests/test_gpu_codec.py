@@ -357,6 +357,26 @@ def test_streamed_interpolation_holds_bound_and_inverts(shape, share):
     assert torch.max(torch.abs(back - x)).item() <= 1e-11 * float(x.abs().max())
 
 
+@pytest.mark.parametrize("shape,share", [((257, 258, 259), 0.0), ((258, 257, 256), 1e-4),
+                                         ((3, 2400, 2401), 0.02), ((2400, 3, 2402), 0.3),
+                                         ((2401, 2402, 3), 0.0), ((4, 2049, 2050), 0.3),
+                                         ((2050, 4, 2049), 1e-4), ((2050, 2049, 4), 0.02)])
+def test_column_restriction_holds_bound_and_inverts(shape, share):
+    """3-axis levels of 2^24 points and more: columns of wavefronts with both
+    kinds of axis ends, partial strips and columns, one and many segments; no
+    escaped value in a plane, some, more than are searched together."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(8)
+    x = torch.randn(shape, device="cuda", generator=gen, dtype=torch.float64) * 1e-2
+    spike = torch.rand(shape, device="cuda", generator=gen) < share
+    x = torch.where(spike, torch.randn(shape, device="cuda", generator=gen, dtype=torch.float64) * 300.0, x)
+    for y in (x, x.float()):
+        a = mgc.compress(y, 1e-3, mode="abs", outlier_cap=y.numel())
+        assert torch.max(torch.abs(mgc.decompress(a).double() - y.double())).item() <= 1e-3
+    back = mgc.recompose(mgc.decompose(x), shape)
+    assert torch.max(torch.abs(back - x)).item() <= 1e-11 * float(x.abs().max())
+
+
 @pytest.mark.parametrize("shape", [(33, 34, 35), (130, 70), (3000,)])
 def test_mostly_escaped_values_match_oracle(shape):
     """Noise at a bound that escapes most values: every tile's list overflows."""
