@@ -789,233 +789,16 @@ __global__ __launch_bounds__(256) void k_dec_level(const Tin* __restrict__ G, co
   dec_level_body<Tin, TZ, TY, TX, MODE>(G, g, fout, sym, raw, r, ob, status, t);
 }
 
-// ------------------------------- decomposition of a 3-axis level, streamed
-// A block owns a column of SY x SX coarse outputs (fine region with a
-// two-node halo in y and x) and walks a segment of coarse z planes, two fine
-// planes a step: they go to an LDS ring (the next two's loads in flight), are
-// restricted along x into LDS and along y by the thread that owns the output,
-// which keeps the last five planes' values in registers for the z taps, and
-// then finishes one coarse plane: its restriction, and its cell's
-// interpolation and quantisation from the raw ring.  The corners a cell shares
-// with the one below come over in registers.  The sums are formed in the same
-// order as in the tiled kernel (x, y, z; taps in order), so the results are
-// the same; the z halo is paid once per segment instead of once per tile.
-// The region's slots outside the grid hold zeros and every tap index is a
-// base plus a constant, so LDS reads pair up.
-// Bound by instruction issue and LDS, with two barriers a step (513^3 FP32:
-// 397 us; with one plane a step, four barriers and the y results and corners
-// through LDS, 509 us).
-constexpr int kStreamSY = 8, kStreamSX = 32;
-constexpr int kStreamE1 = 2 * kStreamSY + 3, kStreamE2 = 2 * kStreamSX + 3;
-constexpr int kStreamNLD = (kStreamE1 * kStreamE2 + 255) / 256;
-constexpr int kStreamEsc = 320;  // escaped values a block collects between flushes
-// levels with fewer fine points use the tiled kernel (measured faster there)
-constexpr int64_t kStreamMinPoints = int64_t(1) << 25;
-// The same for recomposition's restriction: below, its few wavefronts leave
-// the chip idle (129^3 22 us, tiled 18; 150 x 200 x 250 with many escaped values
-// 167 us, tiled 87; 257^3 32 us, tiled 55).
-constexpr int64_t kRecStreamMinPoints = int64_t(1) << 24;
-
-// Raw planes kept: the three a cell spans and, where LDS allows four blocks
-// per CU, the two the next step writes while slower wavefronts still read
-// (FP64 planes would leave two blocks: three planes and one more barrier).
-template <typename Tin>
-constexpr int kStreamRing = sizeof(Tin) == 4 ? 5 : 3;
-
-template <typename Tin, bool QUANT>
-__global__ __launch_bounds__(256, sizeof(Tin) == 4 ? 4 : 3) void k_dec_stream(
-    const Tin* __restrict__ G, const LevelGeom g, double* __restrict__ fout,
-    uint16_t* __restrict__ sym, double* __restrict__ raw, const double* __restrict__ rp,
-    const OutlierBuf ob, unsigned* __restrict__ status, const unsigned* __restrict__ gate,
-    const int seg, const uint32_t n_blocks) {
-  constexpr int SY = kStreamSY, SX = kStreamSX, E1 = kStreamE1, E2 = kStreamE2, NLD = kStreamNLD;
-  constexpr int RING = kStreamRing<Tin>, PL = E1 * E2;
-  static_assert(SY * SX == 256 && E1 > 16 && E1 <= 24, "one output per thread, three row steps");
-  __shared__ Tin ring[RING][PL];
-  __shared__ double X[2][E1][SX];
-  __shared__ EscList<kStreamEsc> el;
-  esc_reset(el);
-  const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
-  if (b >= n_blocks || gate_closed(gate)) return;
-  const double r = rp ? *rp : 0.0;
-  const uint32_t nf0 = (uint32_t)g.nf[0], nf1 = (uint32_t)g.nf[1], nf2 = (uint32_t)g.nf[2];
-  const uint32_t nc0 = (uint32_t)g.nc[0], nc1 = (uint32_t)g.nc[1], nc2 = (uint32_t)g.nc[2];
-  const uint32_t tiles_x = (nc2 + SX - 1) / SX, tiles_y = (nc1 + SY - 1) / SY;
-  const uint32_t tx = b % tiles_x, rest = b / tiles_x;
-  const uint32_t ty = rest % tiles_y, sg = rest / tiles_y;
-  const uint32_t c0y = ty * SY, c0x = tx * SX;
-  const int cz0 = (int)(sg * (uint32_t)seg), cz1 = min(cz0 + seg, (int)nc0);
-  // the region's first fine node (two before the first output; may be outside)
-  const int lo1 = (int)cpos32(c0y, nf1) - 2, lo2 = (int)cpos32(c0x, nf2) - 2;
-  const int tid = threadIdx.x;
-  // the thread's slots of a plane
-  uint32_t goff[NLD];
-  unsigned in = 0;
-#pragma unroll
-  for (int u = 0; u < NLD; ++u) {
-    const int e = min(u * 256 + tid, PL - 1);
-    const int y = lo1 + e / E2, x = lo2 + e % E2;
-    in |= y >= 0 && x >= 0 && y < (int)nf1 && x < (int)nf2 ? 1u << u : 0u;
-    goff[u] = (uint32_t)min(max(y, 0), (int)nf1 - 1) * nf2 + (uint32_t)min(max(x, 0), (int)nf2 - 1);
-  }
-  const size_t plane = (size_t)nf1 * nf2;
-  Tin pv[2][NLD];
-  auto load_planes = [&](int z) {  // fine planes z, z + 1 (clamped to the grid)
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const Tin* src = G + (size_t)min(max(z + p, 0), (int)nf0 - 1) * plane;
-#pragma unroll
-      for (int u = 0; u < NLD; ++u) pv[p][u] = src[goff[u]];
-    }
-  };
-  // the thread's output column (cy, cx): taps, weights, slot of its first tap
-  const int cy = tid >> 5, cx = tid & 31;
-  const uint32_t J1 = c0y + cy, J2 = c0x + cx;
-  const bool own = J1 < nc1 && J2 < nc2;
-  const uint32_t K1 = min(J1, nc1 - 1), K2 = min(J2, nc2 - 1);
-  const uint32_t P1 = cpos32(K1, nf1), P2 = cpos32(K2, nf2);
-  const bool h1 = own && 2 * J1 + 1 < nf1 - 1, h2 = own && 2 * J2 + 1 < nf2 - 1;
-  double xw[5], yw[5];
-#pragma unroll
-  for (int d = 0; d < 5; ++d) {
-    xw[d] = g.ax[2].W[5 * (size_t)K2 + d];
-    yw[d] = g.ax[1].W[5 * (size_t)K1 + d];
-  }
-  const double wy0 = g.ax[1].wl[h1 ? P1 + 1 : P1], wy1 = g.ax[1].wr[h1 ? P1 + 1 : P1];
-  const double wx0 = g.ax[2].wl[h2 ? P2 + 1 : P2], wx1 = g.ax[2].wr[h2 ? P2 + 1 : P2];
-  const int xb = (int)P2 - lo2 - 2, yb = (int)P1 - lo1 - 2;  // slots of the taps' first nodes
-  const int cell = (yb + 2) * E2 + xb + 2;                   // slot of the cell's origin
-  // stream positions of the next coarse plane's coefficients, and their steps
-  const uint32_t e1c = nc1, e1n = nf1 - nc1, e2c = nc2, e2n = nf2 - nc2;
-  const int m0 = g.bit[0] >= 0 ? 1 << g.bit[0] : 0, m1 = g.bit[1] >= 0 ? 1 << g.bit[1] : 0,
-            m2 = g.bit[2] >= 0 ? 1 << g.bit[2] : 0;
-  uint32_t so[8];
-  subband_offsets(g, so);
-  const uint32_t lvl = (uint32_t)g.level_off;
-  const uint32_t sb[7] = {lvl + sel8(so, m2),      lvl + sel8(so, m1),      lvl + sel8(so, m1 | m2),
-                          lvl + sel8(so, m0),      lvl + sel8(so, m0 | m2), lvl + sel8(so, m0 | m1),
-                          lvl + sel8(so, m0 | m1 | m2)};
-  double Y[5] = {0.0, 0.0, 0.0, 0.0, 0.0};  // y results of fine planes 2i - 2 .. 2i + 2
-  double c000 = 0.0, c010 = 0.0, ix00 = 0.0, ix01 = 0.0;  // corners on plane 2i
-  const int oy = tid >> 5;  // x pass: rows oy, oy + 8, oy + 16 of output column cx
-  // the coarse plane J0 with its restriction's z results in Z and its raw
-  // planes in ring slots r0 (its own), rq and rs (the two above)
-  auto finish = [&](uint32_t J0, const double (&Z)[5], int rq, int rs, int r0) {
-    const double* W0 = g.ax[0].W + 5 * (size_t)J0;
-    if (own) {
-      double acc = 0.0;
-#pragma unroll
-      for (int d = 0; d < 5; ++d) acc = fma(W0[d], Z[d], acc);
-      fout[((size_t)J0 * nc1 + J1) * nc2 + J2] = acc;
-    }
-    const uint32_t P0 = cpos32(J0, nf0);
-    const bool h0 = own && 2 * J0 + 1 < nf0 - 1;
-    const double wz0 = g.ax[0].wl[h0 ? P0 + 1 : P0], wz1 = g.ax[0].wr[h0 ? P0 + 1 : P0];
-    const Tin *a = ring[r0] + cell, *q = ring[rq] + cell, *t = ring[rs] + cell;
-    const double c100 = (double)t[0], c101 = (double)t[2], c110 = (double)t[2 * E2],
-                 c111 = (double)t[2 * E2 + 2];
-    const double ix10 = lin2(wx0, c100, wx1, c101), ix11 = lin2(wx0, c110, wx1, c111);
-    const double iy0 = lin2(wy0, c000, wy1, c010), iy1 = lin2(wy0, c100, wy1, c110);
-    const double ixy0 = lin2(wy0, ix00, wy1, ix01), ixy1 = lin2(wy0, ix10, wy1, ix11);
-    const uint32_t cc = (J0 * e1c + J1) * e2c + J2, cn = (J0 * e1c + J1) * e2n + J2;
-    const uint32_t nc = (J0 * e1n + J1) * e2c + J2, nn = (J0 * e1n + J1) * e2n + J2;
-    const bool ok[7] = {h2, h1, h1 && h2, h0, h0 && h2, h0 && h1, h0 && h1 && h2};
-    const uint32_t pos[7] = {sb[0] + cn, sb[1] + nc, sb[2] + nn, sb[3] + cc,
-                             sb[4] + cn, sb[5] + nc, sb[6] + nn};
-    const double v[7] = {(double)a[1] - ix00,
-                         (double)a[E2] - iy0,
-                         (double)a[E2 + 1] - ixy0,
-                         (double)q[0] - lin2(wz0, c000, wz1, c100),
-                         (double)q[1] - lin2(wz0, ix00, wz1, ix10),
-                         (double)q[E2] - lin2(wz0, iy0, wz1, iy1),
-                         (double)q[E2 + 1] - lin2(wz0, ixy0, wz1, ixy1)};
-    emit_cell<QUANT>(pos, v, ok, r, sym, raw, ob, status, el);
-    c000 = c100;
-    c010 = c110;
-    ix00 = ix10;
-    ix01 = ix11;
-  };
-  // Step i takes fine planes 2i + 1 and 2i + 2 and finishes coarse plane i;
-  // two steps before the segment fill the taps (planes outside the grid
-  // repeat the nearest one: their weights are zero).
-  int slot = 0;  // ring slot of plane 2i + 1
-  load_planes(2 * (cz0 - 2) + 1);
-  for (int i = cz0 - 2; i < cz1; ++i) {
-    const int sq = slot, st = slot + 1 < RING ? slot + 1 : 0;
-    const int sa = slot > 0 ? slot - 1 : RING - 1;  // plane 2i
-    slot = st + 1 < RING ? st + 1 : 0;
-#pragma unroll
-    for (int u = 0; u < NLD; ++u) {
-      if (u < NLD - 1 || u * 256 + tid < PL) {
-        ring[sq][u * 256 + tid] = (in >> u) & 1u ? pv[0][u] : (Tin)0;
-        ring[st][u * 256 + tid] = (in >> u) & 1u ? pv[1][u] : (Tin)0;
-      }
-    }
-    if (i + 1 < cz1) load_planes(2 * (i + 1) + 1);
-    __syncthreads();
-    if (QUANT && el.n > kStreamEsc / 2) {
-      esc_flush(el, ob);
-      __syncthreads();
-      esc_reset(el);  // (ordered against the next cells by the barrier below)
-    }
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const Tin* src = ring[p == 0 ? sq : st] + oy * E2 + xb;
-#pragma unroll
-      for (int k = 0; k < 3; ++k) {
-        if (k < 2 || oy + 16 < E1) {
-          double acc = 0.0;
-#pragma unroll
-          for (int d = 0; d < 5; ++d) acc = fma(xw[d], (double)src[8 * k * E2 + d], acc);
-          X[p][oy + 8 * k][cx] = acc;
-        }
-      }
-    }
-    __syncthreads();
-    Y[0] = Y[2];
-    Y[1] = Y[3];
-    Y[2] = Y[4];
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      double acc = 0.0;
-#pragma unroll
-      for (int d = 0; d < 5; ++d) acc = fma(yw[d], X[p][yb + d][cx], acc);
-      Y[3 + p] = acc;
-    }
-    if (i >= cz0) {
-      finish((uint32_t)i, Y, sq, st, sa);
-    } else if (i == cz0 - 1) {  // plane 2i + 2 holds the first cells' lower corners
-      const Tin* t = ring[st] + cell;
-      c000 = (double)t[0];
-      c010 = (double)t[2 * E2];
-      ix00 = lin2(wx0, c000, wx1, (double)t[2]);
-      ix01 = lin2(wx0, c010, wx1, (double)t[2 * E2 + 2]);
-    }
-    // an even axis ends on a coarse plane of its own, 2i + 1 of the step before
-    if (!(nf0 & 1u) && i == (int)nc0 - 2 && cz1 == (int)nc0) {
-      const Tin* t = ring[sq] + cell;
-      c000 = (double)t[0];
-      c010 = (double)t[2 * E2];
-      ix00 = lin2(wx0, c000, wx1, (double)t[2]);
-      ix01 = lin2(wx0, c010, wx1, (double)t[2 * E2 + 2]);
-      const double Z[5] = {Y[1], Y[2], Y[3], Y[3], Y[3]};
-      finish(nc0 - 1, Z, sq, sq, sq);
-      break;
-    }
-    if (RING < 5) __syncthreads();
-  }
-  if (QUANT) {
-    __syncthreads();
-    if (el.n != 0) esc_flush(el, ob);
-  }
-}
-
 // ------------------------------- decomposition of a 2-axis level, streamed
-// As the 3-axis kernel, with the rows of the plane in the place of planes: a
-// block owns kStream2SX coarse columns and walks a segment of coarse rows, two
-// fine rows a step.  The x results of its column stay in a thread's registers
-// for the y taps, so a step has one barrier (the raw rows: five in a ring).
-// Each thread loads two neighbouring nodes of a row.  Bound by HBM latency and
+// A block owns kStream2SX coarse columns (with a two-node halo) and walks a
+// segment of coarse rows, two fine rows a step: they go to an LDS ring (the
+// next two's loads in flight), are restricted along x by the thread that owns
+// the column, which keeps the last five rows' values in registers for the y
+// taps, and then finishes one coarse row: its restriction, and its cell's
+// interpolation and quantisation from the raw ring.  The sums are formed in the
+// tiled kernel's order, so the results are the same; the halo is paid once per
+// segment; a step has one barrier (the raw rows: five in the ring).  Each thread
+// loads two neighbouring nodes of a row.  Bound by HBM latency and
 // issue (8193 x 8193 FP64: 204 us, the tiled kernel 293 us: a tile of 8 x 32
 // outputs reads 19 x 67 values for 16 x 64).
 constexpr int kStream2SX = 254;                // outputs of a block: 512 region slots
@@ -1224,11 +1007,27 @@ __device__ __forceinline__ void coeff_values(const CoeffSrc& src, const uint32_t
 // come from the neighbour lanes, rows and planes are added to the running sums
 // of the outputs that they reach, in the order of the taps: no LDS, no barrier.
 constexpr int kColX = 62, kColY = 4;
+// Levels with fewer fine points use the tiled kernels: there are too few
+// wavefronts to fill the chip, each a serial chain of planes.  Decomposition in
+// FP64: 129^3 26 us (tiled 18), 75 x 100 x 125 with many escaped values 42
+// (32), 150 x 200 x 250 50 (69), 257^3 59 (94).  Restriction of coefficients:
+// 129^3 22 us (18), 150 x 200 x 250 with many escaped values 167 (87), 257^3 34
+// (55).
+constexpr int64_t kDecColsMin = int64_t(1) << 22, kRecColsMin = int64_t(1) << 24;
 constexpr uint32_t kColEsc = 256;  // escaped values of a wavefront's plane that are searched together
+
+// Value i (the same for the wavefront) of a table that no kernel writes while
+// it is read: a scalar load.  (A vector load would be waited for in order,
+// behind every load and store in flight.)
+__device__ __forceinline__ double table_at(const double* t, int64_t i) {
+  typedef const double __attribute__((address_space(4))) constant_double;
+  return ((constant_double*)(uintptr_t)t)[i];
+}
 
 // Tap d of coarse node J's restriction in the order old(J - 1), new(J - 1),
 // old(J), new(J), old(J + 1); 0 where the axis has no such node.  An even axis
-// ends on two adjacent coarse nodes.
+// ends on two adjacent coarse nodes.  UNI: J is the same for the wavefront.
+template <bool UNI>
 __device__ __forceinline__ double cell_tap(const double* W, int J, int nf, int nc, int d) {
   J = min(max(J, 0), nc - 1);
   const bool even = !(nf & 1), last = J == nc - 1, before = even && J == nc - 2;
@@ -1245,7 +1044,8 @@ __device__ __forceinline__ double cell_tap(const double* W, int J, int nf, int n
     zero = zero || d == 3;
     if (d == 4) k = 3;
   }
-  return zero ? 0.0 : W[5 * (size_t)J + k];
+  const double w = UNI ? table_at(W, 5 * (int64_t)J + k) : W[5 * (size_t)J + k];
+  return zero ? 0.0 : w;
 }
 
 // Orders a wavefront's accesses of its own LDS list.
@@ -1264,13 +1064,273 @@ __device__ __forceinline__ double lane_shift(double v) {
 __device__ __forceinline__ double from_left(double v) { return lane_shift<0x138>(v); }
 __device__ __forceinline__ double from_right(double v) { return lane_shift<0x130>(v); }
 
+// A row of n values at p as a buffer: a store past its end is dropped by the
+// range check of the store itself, which takes the place of a branch.  (A store
+// behind a branch may or may not be in flight, so the wait for any load before
+// it would have to drain all.)  With present = false the row has no values.
+template <typename T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buffer(T* p, uint32_t n, bool present) {
+  return __builtin_amdgcn_make_buffer_rsrc(p, 0, present ? (int)(n * (uint32_t)sizeof(T)) : 0,
+                                           0x00027000);
+}
+constexpr uint32_t kNoColumn = 0xfffffff0u;  // byte offset of a lane that stores nothing
+__device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t row, uint32_t bytes, double v) {
+  typedef uint32_t u2 __attribute__((ext_vector_type(2)));
+  const u2 w = {(uint32_t)__double2loint(v), (uint32_t)__double2hiint(v)};
+  __builtin_amdgcn_raw_buffer_store_b64(w, row, (int)bytes, 0, 0);
+}
+__device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t row, uint32_t bytes, uint16_t v) {
+  __builtin_amdgcn_raw_buffer_store_b16(v, row, (int)bytes, 0, 0);
+}
+
+// The decomposition of a level: coefficients (value minus the interpolant of
+// the cell's corners on the old planes around it) and restriction of all
+// values, in the tiled kernel's order of operations.  Old plane p + 1 is taken
+// before new plane p, whose cells need the corners above.  Each wavefront has
+// its own list of escaped values, which holds a plane's at least.
+// 513^3 FP32: 286 us, 300 x 400 x 500 FP32 143 us, 257^3 FP64 59 us; the pass
+// through LDS, two barriers a step, 397, 179 and (tiled) 94 us.  946 MB at
+// 513^3 take 190 us; 146 us are vector instructions.  Stores behind branches,
+// whose waits drained every access in flight, 373 us.  Two rows a wavefront: of
+// three the registers (156) leave three wavefronts a SIMD, 384 us against 373.
+constexpr int kDecColEsc = 768;  // escaped values a wavefront collects between flushes
+constexpr int kDecColY = 2;
+static_assert(kDecColEsc >= 64 * 4 * kDecColY, "a plane's escaped values fit");
+
+template <typename Tin, bool QUANT>
+__global__ __launch_bounds__(256) void k_dec_cols(
+    const Tin* __restrict__ G, const LevelGeom g, double* __restrict__ fout,
+    uint16_t* __restrict__ sym, double* __restrict__ raw, const double* __restrict__ rp,
+    const OutlierBuf ob, unsigned* __restrict__ status, const unsigned* __restrict__ gate,
+    const int seg, const uint32_t n_blocks) {
+  constexpr int R = kDecColY, NR = 2 * R + 3, NE = QUANT ? kDecColEsc : 1;
+  __shared__ double esc_val[4][NE];  // a list for each wavefront
+  __shared__ uint32_t esc_pos[4][NE], esc_n[4];
+  const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
+  if (b >= n_blocks || gate_closed(gate)) return;
+  const double rq = rp ? *rp : 0.0;
+  const int nf0 = (int)g.nf[0], nf1 = (int)g.nf[1], nf2 = (int)g.nf[2];
+  const int nc0 = (int)g.nc[0], nc1 = (int)g.nc[1], nc2 = (int)g.nc[2];
+  const int nn0 = nf0 - nc0, nn1 = nf1 - nc1, nn2 = nf2 - nc2;  // new nodes of an axis
+  const uint32_t tiles_x = (uint32_t)(nc2 + kColX - 1) / kColX;
+  const uint32_t tiles_y = (uint32_t)(nc1 + 4 * R - 1) / (4 * R);
+  const uint32_t tx = b % tiles_x, rest = b / tiles_x;
+  const uint32_t ty = rest % tiles_y, sg = rest / tiles_y;
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int c1 = ((int)ty * 4 + wave) * R;
+  if (c1 >= nc1) return;
+  const int z0 = (int)sg * seg, z1 = min(z0 + seg, nc0);
+  const int lane = (int)(threadIdx.x & 63), J2 = (int)tx * kColX - 1 + lane;
+  if (lane == 0) esc_n[wave] = 0;
+  wave_lds_fence();
+  const bool own = lane >= 1 && lane <= kColX && J2 < nc2;
+  // A lane reads the pair of fine nodes of its cell, the last coarse node's
+  // (and what lies outside the grid) as the second of the row's last pair;
+  // nodes that are not there count with tap 0 and have no coefficient.
+  const int K2 = min(max(J2, 0), nc2 - 1);
+  const bool second = K2 == nc2 - 1;
+  const uint32_t xoff = (uint32_t)min(2 * K2, nf2 - 2);
+  double xw[5], yw[R][5], wy0[R], wy1[R];
+#pragma unroll
+  for (int d = 0; d < 5; ++d) {
+    xw[d] = cell_tap<false>(g.ax[2].W, J2, nf2, nc2, d);
+#pragma unroll
+    for (int j = 0; j < R; ++j) yw[j][d] = cell_tap<true>(g.ax[1].W, c1 + j, nf1, nc1, d);
+  }
+  const int i2 = min(2 * K2 + 1, nf2 - 1);
+  const double wx0 = g.ax[2].wl[i2], wx1 = g.ax[2].wr[i2];
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int i1 = min(2 * (c1 + j) + 1, nf1 - 1);
+    wy0[j] = table_at(g.ax[1].wl, i1);
+    wy1[j] = table_at(g.ax[1].wr, i1);
+  }
+  uint32_t so[8];
+  subband_offsets(g, so);
+  const int m0 = 1 << g.bit[0], m1 = 1 << g.bit[1], m2 = 1 << g.bit[2];
+  const size_t fplane = (size_t)nf1 * nf2;
+  struct Plane {
+    Tin e[NR][2];
+  };
+  Plane po, pn;  // the next old and the next new plane, as read
+  // fine plane 2J (old) or 2J + 1 (new); row r: fine row 2 (c1 - 1) + r
+  auto load = [&](int z, Plane& p) {
+    typedef Tin pair __attribute__((ext_vector_type(2), aligned(alignof(Tin))));
+    const Tin* pl = G + (size_t)min(z, nf0 - 1) * fplane;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const int y = min(max(2 * (c1 - 1) + r, r & 1), nf1 - 1);
+      const char* rowp = reinterpret_cast<const char*>(pl + (size_t)y * nf2);
+      const pair v = *reinterpret_cast<const pair*>(rowp + (uint32_t)sizeof(Tin) * xoff);
+      p.e[r][0] = v[0];
+      p.e[r][1] = v[1];
+    }
+  };
+  struct Corner {
+    double c[R], ix[R], iy[R], ixy[R];  // corner values and interpolants of a plane's cells
+  };
+  // hands the list's records over once it might not hold another plane's
+  auto flush = [&](uint32_t keep) {
+    if constexpr (!QUANT) return;
+    wave_lds_fence();
+    const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)esc_n[wave]);
+    if (n <= keep) return;
+    unsigned long long base = 0;
+    if (lane == 0) base = atomicAdd(ob.count, (unsigned long long)n);
+    base = __shfl(base, 0, 64);
+    for (uint32_t k = (uint32_t)lane; k < n; k += 64) {
+      const double t = esc_val[wave][k];
+      int64_t kv = 0;
+      if (fabs(t) < 4611686018427387904.0) kv = (int64_t)t;
+      else atomicOr(status, ST_RANGE);
+      if (base + k < ob.cap) {
+        ob.pos[base + k] = esc_pos[wave][k];
+        ob.val[base + k] = kv;
+      }
+    }
+    wave_lds_fence();
+    if (lane == 0) esc_n[wave] = 0;
+    wave_lds_fence();
+  };
+  const uint32_t at2 = own ? 2u * (uint32_t)J2 : kNoColumn, at8 = own ? 8u * (uint32_t)J2 : kNoColumn;
+  // coefficient v of the lane's node in the subband row (zn, yn, xn: new along
+  // the axis) of cell row J0, J1; present: the row is there
+  auto emit = [&](bool zn, bool yn, bool xn, int J0, int J1, bool present, double v) {
+    const int m = (zn ? m0 : 0) | (yn ? m1 : 0) | (xn ? m2 : 0);
+    const uint32_t n = (uint32_t)(xn ? nn2 : nc2);
+    const uint32_t base = (uint32_t)g.level_off + sel8(so, m) + (uint32_t)(J0 * (yn ? nn1 : nc1) + J1) * n;
+    if constexpr (QUANT) {
+      double t = rint(v * rq);
+      if (__builtin_expect(!(fabs(t) < 32768.0), 0)) {
+        if (present && own && (uint32_t)J2 < n) {
+          const uint32_t k = atomicAdd(&esc_n[wave], 1u);
+          esc_val[wave][k] = t;
+          esc_pos[wave][k] = base + (uint32_t)J2;
+        }
+        t = -32768.0;
+      }
+      row_store(row_buffer(sym + base, n, present), at2, (uint16_t)(int)(t + 32768.0));
+    } else {
+      row_store(row_buffer(raw + base, n, present), at8, v);
+    }
+  };
+  // One row's restriction along x, added to the outputs Y that it reaches.
+  auto add_row = [&](int r, double o, double n, double right, double (&Y)[R]) {
+    double X = fma(xw[0], from_left(o), 0.0);
+    X = fma(xw[1], from_left(n), X);
+    X = fma(xw[2], o, X);
+    X = fma(xw[3], n, X);
+    X = fma(xw[4], right, X);
+#pragma unroll
+    for (int j = 0; j < R; ++j)
+      if (r - 2 * j >= 0 && r - 2 * j < 5) {
+        Y[j] = fma(yw[j][r - 2 * j], X, Y[j]);
+        // keeps the sums here: sunk to their use at the plane's end, each row
+        // would hold its five inputs until then (229 registers instead of 113)
+        asm volatile("" : "+v"(Y[j]));
+      }
+  };
+  // An old plane: its restriction along x and y, its cells' corners and, where
+  // the segment owns it, its coefficients.
+  auto old_plane = [&](int J0, bool mine, double (&Y)[R], Corner& k) {
+    double c = 0.0, ix = 0.0;  // corner and interpolant of the coarse row before
+#pragma unroll
+    for (int j = 0; j < R; ++j) Y[j] = 0.0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const double n = (double)po.e[r][1], o = second ? n : (double)po.e[r][0];
+      const double right = from_right(o);
+      add_row(r, o, n, right, Y);
+      if (r < 2 || (r & 1)) continue;
+      const int j = r / 2 - 2;  // the cell row that this one ends
+      const double ix1 = lin2(wx0, o, wx1, right);
+      if (j >= 0) {
+        k.c[j] = c;
+        k.ix[j] = ix;
+        k.iy[j] = lin2(wy0[j], c, wy1[j], o);
+        k.ixy[j] = lin2(wy0[j], ix, wy1[j], ix1);
+        const int J1 = c1 + j;
+        const bool in1 = mine && J1 < nc1, h1 = mine && J1 < nn1;
+        const double fn = (double)po.e[r - 1][1], fo = second ? fn : (double)po.e[r - 1][0];
+        emit(false, false, true, J0, J1, in1, (double)po.e[r - 2][1] - ix);
+        emit(false, true, false, J0, J1, h1, fo - k.iy[j]);
+        emit(false, true, true, J0, J1, h1, fn - k.ixy[j]);
+      }
+      c = o;
+      ix = ix1;
+    }
+  };
+  // New plane p between the corners lo and up.
+  auto new_plane = [&](int p, bool mine, double (&Y)[R], const Corner& lo, const Corner& up) {
+    const int i0 = min(2 * p + 1, nf0 - 1);
+    const double wz0 = table_at(g.ax[0].wl, i0), wz1 = table_at(g.ax[0].wr, i0);
+    double po_ = 0.0, pn_ = 0.0;  // the row before
+#pragma unroll
+    for (int j = 0; j < R; ++j) Y[j] = 0.0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      const double n = (double)pn.e[r][1], o = second ? n : (double)pn.e[r][0];
+      add_row(r, o, n, from_right(o), Y);
+      const int j = r / 2 - 1;
+      if ((r & 1) && j >= 0) {
+        const int J1 = c1 + j;
+        const bool in1 = mine && J1 < nc1, h1 = mine && J1 < nn1;
+        emit(true, false, false, p, J1, in1, po_ - lin2(wz0, lo.c[j], wz1, up.c[j]));
+        emit(true, false, true, p, J1, in1, pn_ - lin2(wz0, lo.ix[j], wz1, up.ix[j]));
+        emit(true, true, false, p, J1, h1, o - lin2(wz0, lo.iy[j], wz1, up.iy[j]));
+        emit(true, true, true, p, J1, h1, n - lin2(wz0, lo.ixy[j], wz1, up.ixy[j]));
+      }
+      po_ = o;
+      pn_ = n;
+    }
+  };
+  auto zw = [&](int J, int d) { return cell_tap<true>(g.ax[0].W, J, nf0, nc0, d); };
+  // the sums of coarse planes p and p + 1
+  double cur[R], next[R], Yo[R], Yn[R];
+  Corner lo, up;
+  int p = max(z0 - 1, 0);
+  load(2 * p, po);
+  {
+    const double w2 = zw(p, 2), w0 = zw(p + 1, 0);
+    old_plane(p, p == z0, Yo, lo);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      cur[j] = fma(w2, Yo[j], 0.0);
+      next[j] = fma(w0, Yo[j], 0.0);
+    }
+  }
+  load(2 * (p + 1), po);
+  load(2 * p + 1, pn);
+  for (; p < z1; ++p) {
+    flush(kDecColEsc - 64 * 3 * R);
+    old_plane(p + 1, p + 1 < z1, Yo, up);
+    load(2 * (p + 2), po);  // (unconditional, as the stores are: past the end the last plane)
+    flush(kDecColEsc - 64 * 4 * R);
+    new_plane(p, p >= z0 && p < nn0, Yn, lo, up);
+    load(2 * (p + 1) + 1, pn);
+    const double w3 = zw(p, 3), w4 = zw(p, 4), w1 = zw(p + 1, 1), w2 = zw(p + 1, 2),
+                 w0 = zw(p + 2, 0);
+#pragma unroll
+    for (int j = 0; j < R; ++j) {
+      const double f = fma(w4, Yo[j], fma(w3, Yn[j], cur[j]));
+      row_store(row_buffer(fout + ((size_t)p * nc1 + c1 + j) * nc2, (uint32_t)nc2,
+                           p >= z0 && c1 + j < nc1),
+                at8, f);
+      cur[j] = fma(w2, Yo[j], fma(w1, Yn[j], next[j]));
+      next[j] = fma(w0, Yo[j], 0.0);
+    }
+    lo = up;
+  }
+  flush(0);
+}
+
 // f = (P^T M_l) c_l; the nodes coarse along every axis hold none.  513^3: 133
 // us (135 M symbols of two bytes; the streamed pass through LDS 281 us, at 58 %
 // vector instructions most of which found slots and positions; here about 460 a
 // step of two planes), 257^3 32 us (46), 300 x 400 x 500 65 us (129), FP64
 // coefficients of 257^3 50 us (51).  Three rows a wavefront 139 us.
 template <bool RAW>
-__global__ __launch_bounds__(256, 4) void k_rec_cols(const LevelGeom g, const CoeffSrc src,
+__global__ __launch_bounds__(256, RAW ? 3 : 4) void k_rec_cols(const LevelGeom g, const CoeffSrc src,
                                                    const double q, double* __restrict__ fout,
                                                    const int seg, const uint32_t n_blocks) {
   constexpr int R = kColY, NR = 2 * R + 3;
@@ -1290,14 +1350,15 @@ __global__ __launch_bounds__(256, 4) void k_rec_cols(const LevelGeom g, const Co
   const int z0 = (int)sg * seg, z1 = min(z0 + seg, nc0);
   const int lane = (int)(threadIdx.x & 63), J2 = (int)tx * kColX - 1 + lane;
   const bool own = lane >= 1 && lane <= kColX && J2 < nc2;
+  const uint32_t at8 = own ? 8u * (uint32_t)J2 : kNoColumn;
   // positions outside the grid read a node at its edge and count with tap 0
   const uint32_t xo = (uint32_t)min(max(J2, 0), nc2 - 1), xn = (uint32_t)min(max(J2, 0), nn2 - 1);
   double xw[5], yw[R][5];
 #pragma unroll
   for (int d = 0; d < 5; ++d) {
-    xw[d] = cell_tap(g.ax[2].W, J2, nf2, nc2, d);
+    xw[d] = cell_tap<false>(g.ax[2].W, J2, nf2, nc2, d);
 #pragma unroll
-    for (int j = 0; j < R; ++j) yw[j][d] = cell_tap(g.ax[1].W, c1 + j, nf1, nc1, d);
+    for (int j = 0; j < R; ++j) yw[j][d] = cell_tap<true>(g.ax[1].W, c1 + j, nf1, nc1, d);
   }
   uint32_t so[8];
   subband_offsets(g, so);
@@ -1399,7 +1460,7 @@ __global__ __launch_bounds__(256, 4) void k_rec_cols(const LevelGeom g, const Co
 #pragma unroll
       for (int j = 0; j < R; ++j)
         if (r - 2 * j >= 0 && r - 2 * j < 5)
-          Y[j] = fma(cell_tap(g.ax[1].W, c1 + j, nf1, nc1, r - 2 * j), X, Y[j]);
+          Y[j] = fma(cell_tap<true>(g.ax[1].W, c1 + j, nf1, nc1, r - 2 * j), X, Y[j]);
     }
     wave_lds_fence();
   };
@@ -1421,11 +1482,13 @@ __global__ __launch_bounds__(256, 4) void k_rec_cols(const LevelGeom g, const Co
         }, Y);
     }
   };
-  auto zw = [&](int J, int d) { return cell_tap(g.ax[0].W, J, nf0, nc0, d); };
+  auto zw = [&](int J, int d) { return cell_tap<true>(g.ax[0].W, J, nf0, nc0, d); };
   auto store = [&](int J, const double (&f)[R]) {
 #pragma unroll
     for (int j = 0; j < R; ++j)
-      if (own && c1 + j < nc1) fout[((size_t)J * nc1 + c1 + j) * nc2 + J2] = f[j];
+      row_store(row_buffer(fout + ((size_t)J * nc1 + c1 + j) * nc2, (uint32_t)nc2,
+                           J >= z0 && c1 + j < nc1),
+                at8, f[j]);
   };
   constexpr std::false_type OLD{};
   constexpr std::true_type NEW{};
@@ -1445,7 +1508,7 @@ __global__ __launch_bounds__(256, 4) void k_rec_cols(const LevelGeom g, const Co
       cur[j] = fma(w2, Y[j], cur[j]);
       next[j] = fma(w0, Y[j], 0.0);
     }
-    if (p > z0) store(p - 1, prev);
+    store(p - 1, prev);  // (none of plane z0 - 1 and before)
     load(OLD, p + 1, po);
     const double w3 = zw(p, 3), w1 = zw(p + 1, 1);
     reduce(NEW, p, pn, Y);
@@ -3658,34 +3721,18 @@ TileGrid tile_grid(const LevelGeom& g, int tz, int ty, int tx) {
   return t;
 }
 
-// Blocks of the z-streamed level kernels: (y, x) columns times z segments,
-// at most one block per resident slot (four per CU) so that every block runs
-// in the same pass; a segment is at least 8 coarse planes long (its 3-plane
-// halo then costs at most 3/16 of the planes).
+// Blocks of the streamed level kernels: columns times segments.
 struct StreamGrid {
   int seg;
   uint32_t n_blocks;
   unsigned grid;
 };
 
-StreamGrid stream_grid(const LevelGeom& g) {
-  const int64_t tiles_x = (g.nc[2] + kStreamSX - 1) / kStreamSX;
-  const int64_t tiles_y = (g.nc[1] + kStreamSY - 1) / kStreamSY;
-  const int64_t cols = tiles_x * tiles_y;
-  const int64_t want = std::max<int64_t>(1, std::min<int64_t>(g.nc[0], 1024 / cols));
-  StreamGrid sg;
-  sg.seg = (int)std::min<int64_t>(g.nc[0], std::max<int64_t>(8, (g.nc[0] + want - 1) / want));
-  const int64_t segs = (g.nc[0] + sg.seg - 1) / sg.seg;
-  sg.n_blocks = (uint32_t)(cols * segs);
-  sg.grid = (sg.n_blocks + 7) & ~7u;
-  return sg;
-}
-
 // Blocks of four wavefronts, one above the other along y: about 2,048 (eight a
 // CU, half of them resident), segments of at least 8 coarse planes (a segment
 // reads three fine planes more than it owns).
-StreamGrid cols_grid(const LevelGeom& g) {
-  const int64_t cols = ((g.nc[2] + kColX - 1) / kColX) * ((g.nc[1] + 4 * kColY - 1) / (4 * kColY));
+StreamGrid cols_grid(const LevelGeom& g, int rows) {
+  const int64_t cols = ((g.nc[2] + kColX - 1) / kColX) * ((g.nc[1] + 4 * rows - 1) / (4 * rows));
   const int64_t want = std::max<int64_t>(1, 2048 / cols);
   StreamGrid sg;
   sg.seg = (int)std::max<int64_t>(8, (g.nc[0] + want - 1) / want);
@@ -3694,7 +3741,7 @@ StreamGrid cols_grid(const LevelGeom& g) {
   return sg;
 }
 
-// The same for 2-axis levels: about 2,048 blocks (eight 256-thread blocks fit
+// Blocks of the streamed 2-axis levels: about 2,048 (eight 256-thread blocks fit
 // a CU), segments of at least 16 coarse rows (two steps of a segment only fill
 // its taps).
 StreamGrid stream2_grid(const LevelGeom& g) {
@@ -3727,9 +3774,9 @@ void dec_dispatch(const void* G, const LevelGeom& g, double* fout, uint16_t* sym
                   const unsigned* gate, hipStream_t s, int cand = 0) {
   const Tin* Gp = static_cast<const Tin*>(G);
   const int D = active_axes(g);
-  if (D == 3 && MODE != 2 && cand == 0 && g.nf[0] * g.nf[1] * g.nf[2] >= kStreamMinPoints) {
-    const StreamGrid sg = stream_grid(g);
-    hipLaunchKernelGGL((k_dec_stream<Tin, MODE == 0>), dim3(sg.grid), dim3(256), 0, s, Gp, g, fout,
+  if (D == 3 && MODE != 2 && cand == 0 && g.nf[0] * g.nf[1] * g.nf[2] >= kDecColsMin) {
+    const StreamGrid sg = cols_grid(g, kDecColY);
+    hipLaunchKernelGGL((k_dec_cols<Tin, MODE == 0>), dim3(sg.grid), dim3(256), 0, s, Gp, g, fout,
                        sym, raw, rp, ob, status, gate, sg.seg, sg.n_blocks);
     return;
   }
@@ -3762,8 +3809,8 @@ template <bool RAW>
 void rec_restrict_dispatch(const LevelGeom& g, const CoeffSrc& src, double q, double* fout,
                            hipStream_t s) {
   const int D = active_axes(g);
-  if (D == 3 && g.nf[0] * g.nf[1] * g.nf[2] >= kRecStreamMinPoints) {
-    const StreamGrid sg = cols_grid(g);
+  if (D == 3 && g.nf[0] * g.nf[1] * g.nf[2] >= kRecColsMin) {
+    const StreamGrid sg = cols_grid(g, kColY);
     hipLaunchKernelGGL((k_rec_cols<RAW>), dim3(sg.grid), dim3(256), 0, s, g, src, q, fout, sg.seg,
                        sg.n_blocks);
     return;

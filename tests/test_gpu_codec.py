@@ -377,6 +377,33 @@ def test_column_restriction_holds_bound_and_inverts(shape, share):
     assert torch.max(torch.abs(back - x)).item() <= 1e-11 * float(x.abs().max())
 
 
+@pytest.mark.parametrize("dtype", ["float32", "float64"])
+@pytest.mark.parametrize("shape,share", [((162, 163, 161), 0.0), ((161, 162, 164), 1e-4),
+                                         ((3, 1200, 1201), 0.02), ((1200, 3, 1202), 0.3),
+                                         ((1201, 1202, 3), 0.0), ((4, 1025, 1050), 0.3),
+                                         ((1026, 4, 1049), 1e-4), ((1050, 1025, 4), 0.02)])
+def test_columns_equal_tiled_with_escapes(shape, share, dtype):
+    """3-axis levels of 2^22 points and more, columns of wavefronts, against the
+    tiled decomposition (forced candidate 1): equal streams for both kinds of
+    axis ends, partial strips and columns, one and many segments, and no, some
+    and many escaped values (the list stays empty, is handed over now and then,
+    every plane)."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(9)
+    x = torch.randn(shape, device="cuda", generator=gen) * 1e-2
+    spike = torch.rand(shape, device="cuda", generator=gen) < share
+    x = torch.where(spike, torch.randn(shape, device="cuda", generator=gen) * 300.0, x).to(getattr(torch, dtype))
+    n = x.numel()
+    a = mgc.compress(x, 1e-3, mode="abs", outlier_cap=n)
+    kind = "dec_f32" if dtype == "float32" else "dec_f64"
+    mgc.set_tuning(kind, 1)
+    try:
+        b = mgc.compress(x, 1e-3, mode="abs", outlier_cap=n)
+    finally:
+        mgc.set_tuning(kind, -1)
+    assert torch.equal(a, b)
+
+
 @pytest.mark.parametrize("shape", [(33, 34, 35), (130, 70), (3000,)])
 def test_mostly_escaped_values_match_oracle(shape):
     """Noise at a bound that escapes most values: every tile's list overflows."""
