@@ -6,8 +6,8 @@
 //    quantised coefficients cluster around the dictionary centre), global
 //    atomics for the rest.
 //  * codebook: the non-zero keys are sorted by (frequency, symbol) with a
-//    stable LSD radix sort over many blocks (k_cbs_count / k_cbs_pass).  Code
-//    lengths follow the
+//    stable LSD radix sort over many blocks (k_cbs_count / k_cbs_pass; large
+//    batches sort in the one workgroup below).  Code lengths follow the
 //    two-queue construction (leaves in that order, internal nodes in creation
 //    order, ties to the leaf), computed by one workgroup of 1024 threads in
 //    rounds: with m nodes already taken, no node created later can weigh less
@@ -19,7 +19,7 @@
 //    the frequencies and rebuild.  Codes are canonical (RFC 1951
 //    construction), assigned on many blocks (k_canon_count / k_canon_rank:
 //    each wavefront a run of the symbols with its count of each length in
-//    one lane).
+//    one lane; large batches assign them in their one workgroup).
 //  * chunk lengths and layout: one wavefront per chunk sums the code lengths
 //    (and, in a compression, counts the escape symbols per chunk and lane);
 //    an exclusive scan of the chunk word counts over many blocks gives the
@@ -568,6 +568,36 @@ __device__ __forceinline__ bool merge_in_lds(const unsigned n, unsigned m, unsig
   return true;
 }
 
+// 1. non-zero keys in ascending symbol order (each thread owns 64 symbols,
+//    read as sixteen 16-byte vectors kept in registers); returns their count
+__device__ unsigned compact_keys(const unsigned* __restrict__ hist, const CodebookScratch& s,
+                                 CbSmem& sm) {
+  const int tid = threadIdx.x;
+  uint4 hv[16];
+  const uint4* h4 = reinterpret_cast<const uint4*>(hist) + tid * 16;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) hv[k] = h4[k];
+  unsigned cnt = 0;
+#pragma unroll
+  for (int k = 0; k < 16; ++k)
+    cnt += (hv[k].x != 0) + (hv[k].y != 0) + (hv[k].z != 0) + (hv[k].w != 0);
+  unsigned total;
+  unsigned off = block_excl_scan(cnt, sm.sm32, &total);
+#pragma unroll
+  for (int k = 0; k < 16; ++k) {
+    const unsigned f4[4] = {hv[k].x, hv[k].y, hv[k].z, hv[k].w};
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      if (f4[q]) {
+        s.symAsc[off] = tid * 64 + 4 * k + q;
+        s.freqAsc[off] = f4[q];
+        ++off;
+      }
+    }
+  }
+  return total;
+}
+
 // Canonical codes (RFC 1951 construction): count per length, first code per
 // length, then the rank of each symbol among equal lengths in ascending
 // symbol order.  A wavefront takes a contiguous run [i0, i1) of the symbols
@@ -674,23 +704,63 @@ __device__ __forceinline__ void first_codes(const unsigned* tot, unsigned* first
   if (write) lay->max_len = ml;
 }
 
-// Code lengths from the leaves that the multi-block sort (cbs_count_body /
-// cbs_pass_body) has sorted, beside the non-zero keys in symbol order; the
-// canonical codes follow on many blocks (canon_count_body / canon_rank_body).
-__device__ __forceinline__ void codebook_body(const CodebookScratch& s, uint8_t* __restrict__ clen,
+// The canonical codes of n symbols in one block of 1024 threads (lengths in
+// symbol order in lenAsc): a counting pass, the scan of the counts over the
+// wavefronts (which also gives the counts per length), the ranking pass.
+__device__ void canonical_codes(const unsigned n, const uint8_t* lenAsc, const CodebookScratch& s,
+                                uint32_t* __restrict__ code, uint8_t* __restrict__ cb_out,
+                                Layout* __restrict__ lay, CbSmem& sm) {
+  const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+  const unsigned run = ((n + 1023) / 1024) * 64;
+  const unsigned i0 = min(n, (unsigned)wave * run), i1 = min(n, i0 + run);
+  const unsigned cnt = wave_len_counts(lenAsc, i0, i1);
+  if (lane < 34) sm.wl[wave][lane] = cnt;
+  __syncthreads();
+  if (tid < 34) {
+    unsigned acc = 0;
+    for (int w = 0; w < 16; ++w) {
+      const unsigned c = sm.wl[w][tid];
+      sm.wl[w][tid] = acc;
+      acc += c;
+    }
+    sm.lcount[tid] = acc;
+  }
+  __syncthreads();
+  if (tid == 0) first_codes(sm.lcount, sm.lfirst, s.pk, lay, true);
+  __syncthreads();
+  wave_len_ranks(lenAsc, i0, i1, lane < 34 ? sm.wl[wave][lane] : 0u,
+                 lane < 34 ? sm.lfirst[lane] : 0u, s, code, cb_out, n);
+}
+
+// SPREAD: the leaf sort of the first round was done by the multi-block sort
+// (cbs_count_body / cbs_pass_body), which also wrote the non-zero keys in
+// symbol order, and the canonical codes follow on many blocks (canon_count_body
+// / canon_rank_body); otherwise the block does all of it itself.
+template <bool SPREAD>
+__device__ __forceinline__ void codebook_body(const unsigned* __restrict__ hist,
+                                              const CodebookScratch& s,
+                                              uint32_t* __restrict__ code,
+                                              uint8_t* __restrict__ clen,
+                                              uint8_t* __restrict__ cb_out,
                                               Layout* __restrict__ lay) {
   __shared__ CbSmem sm;
   __shared__ __align__(16) CbBig big;
   const int tid = threadIdx.x;
-  // item count: every non-zero bin is counted once in the first pass's
-  // (digit, tile) table
-  unsigned n;
-  unsigned c = 0;
-  for (unsigned i = tid; i < 256u * kSortTiles; i += 1024) c += s.hcnt[i];
-  unsigned fm = 0;
-  for (int t = 0; t < kSortTiles; ++t) fm = max(fm, s.fmaxT[t]);
-  const unsigned pre_passes = (32 - __clz(fm) + 7) / 8;
-  block_excl_scan(c, sm.sm32, &n);
+  unsigned n, pre_passes = 0;
+  if (SPREAD) {
+    // item count: every non-zero bin is counted once in the first pass's
+    // (digit, tile) table
+    unsigned c = 0;
+    for (unsigned i = tid; i < 256u * kSortTiles; i += 1024) c += s.hcnt[i];
+    unsigned fm = 0;
+    for (int t = 0; t < kSortTiles; ++t) fm = max(fm, s.fmaxT[t]);
+    pre_passes = (32 - __clz(fm) + 7) / 8;
+    unsigned total;
+    block_excl_scan(c, sm.sm32, &total);
+    n = total;
+  } else {
+    n = compact_keys(hist, s, sm);
+  }
   __syncthreads();
 
   if (n == 0) {
@@ -716,7 +786,7 @@ __device__ __forceinline__ void codebook_body(const CodebookScratch& s, uint8_t*
     // 2. sort leaves by (frequency, symbol): stable radix sort of indices
     //    into the ascending-symbol list, keyed by frequency
     bool inB;
-    if (flatten == 0) {
+    if (SPREAD && flatten == 0) {
       inB = pre_passes & 1;  // passes alternate B, A, B, A
     } else {
       unsigned fmax = 0;
@@ -1105,17 +1175,22 @@ __device__ __forceinline__ void codebook_body(const CodebookScratch& s, uint8_t*
     for (unsigned i = tid; i < kDict / 16; i += 1024) clen4[i] = tab4[i];
   }
   if (tid == 0) lay->n_codes = n;
-  // lengths in symbol order for the canonical pass, as bytes over the sort
-  // keys (dead now)
-  const uint32_t* len4 = reinterpret_cast<const uint32_t*>(&big) + kDict / 4;
-  for (unsigned i = tid; i < (n + 3) / 4; i += 1024) s.keyA[i] = len4[i];
+  if (SPREAD) {
+    // lengths in symbol order for the canonical pass, as bytes over the sort
+    // keys (dead now)
+    const uint32_t* len4 = reinterpret_cast<const uint32_t*>(&big) + kDict / 4;
+    for (unsigned i = tid; i < (n + 3) / 4; i += 1024) s.keyA[i] = len4[i];
+  } else {
+    // 6-7. canonical codes in this block (lengths in LDS)
+    canonical_codes(n, reinterpret_cast<const uint8_t*>(&big) + kDict, s, code, cb_out, lay, sm);
+  }
 }
 
 __global__ __launch_bounds__(1024) void k_codebook(CodebookScratch s, uint8_t* __restrict__ clen,
                                                     Layout* __restrict__ lay,
                                                     const unsigned* __restrict__ gate) {
   if (gate_closed(gate)) return;
-  codebook_body(s, clen, lay);
+  codebook_body<true>(nullptr, s, nullptr, clen, nullptr, lay);
 }
 
 // The canonical codes of the codebook k_codebook built (its lengths in
@@ -2655,7 +2730,12 @@ __global__ __launch_bounds__(256) void kb_cbs_pass(const Job* __restrict__ jobs)
 }
 __global__ __launch_bounds__(1024) void kb_codebook(const Job* __restrict__ jobs) {
   const Job& J = jobs[blockIdx.x];
-  if (!job_skipped_h(J)) codebook_body(J.cbs, J.clen, J.lay);
+  if (!job_skipped_h(J)) codebook_body<true>(nullptr, J.cbs, nullptr, J.clen, nullptr, J.lay);
+}
+__global__ __launch_bounds__(1024) void kb_codebook_whole(const Job* __restrict__ jobs) {
+  const Job& J = jobs[blockIdx.x];
+  if (!job_skipped_h(J))
+    codebook_body<false>(J.hist, J.cbs, J.code, J.clen, J.out + job_cb_off(J), J.lay);
 }
 __global__ __launch_bounds__(256) void kb_canon_count(const Job* __restrict__ jobs) {
   const Job& J = jobs[blockIdx.y];
@@ -2780,9 +2860,14 @@ void launch_b_histogram(const Job* jobs, const JobBlock* map, uint32_t nb, hipSt
   hipLaunchKernelGGL(kb_histogram, dim3(nb), dim3(1024), 0, s, jobs, map, nb);
 }
 void launch_b_codebook(const Job* jobs, int n, hipStream_t s) {
-  // (one workgroup per array sorted its leaves and assigned its codes: 540 us
-  // for 48 arrays of up to 32,000 codes, of which 160 to 300 in the largest
-  // arrays' sorts; 350 us in these launches)
+  // One workgroup per array for everything takes as long as its largest array
+  // (540 us with 48 arrays of up to 32,000 codes, 545 with 256); the sort and
+  // the codes on many blocks take that out but their launches grow with the
+  // arrays (350 us with 48, 950 with 256: 2.9 us an array): even at about 115.
+  if (n > 96) {
+    hipLaunchKernelGGL(kb_codebook_whole, dim3((unsigned)n), dim3(1024), 0, s, jobs);
+    return;
+  }
   const dim3 tiles(kSortTiles, (unsigned)n), runs(kCanonBlocks, (unsigned)n);
   hipLaunchKernelGGL(kb_cbs_count, tiles, dim3(256), 0, s, jobs);
   hipLaunchKernelGGL(kb_cbs_pass<0>, tiles, dim3(256), 0, s, jobs);

@@ -224,3 +224,16 @@ def test_long_lines_equal_plain():
     got = mgc.compress_batched(xs, [1e-3] * len(xs), flags=mgc.BATCH_NO_TUNE)
     for x, g in zip(xs, got):
         assert torch.equal(g, mgc.compress(x, 1e-3))
+
+
+@pytest.mark.parametrize("n", [96, 97])
+def test_codebooks_spread_and_whole_equal_plain(n):
+    """Up to 96 arrays sort their leaves and assign their codes on many blocks,
+    more of them in one workgroup each: the plain call's streams either way."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    xs = [torch.randn((17 + k % 5, 9 + k % 3, 12), device="cuda", generator=gen) for k in range(n)]
+    bounds = [10.0 ** -(1 + k % 4) for k in range(n)]
+    got = mgc.compress_batched(xs, bounds, flags=mgc.BATCH_NO_TUNE)
+    for x, b, s in zip(xs, bounds, got):
+        assert torch.equal(s, mgc.compress(x, b))
