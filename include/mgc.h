@@ -24,8 +24,11 @@
  *    length 1 are squeezed out.  dtype is float32 or float64.  Arithmetic is
  *    FP64 throughout (inputs are read and outputs written in their dtype).
  *  - Sizes: at most 2^32 - 1 values per array.
- *  - Calls on one context from several host threads must be serialised by
- *    the caller; distinct contexts are independent.
+ *  - Several host threads may be inside calls on one context at once, each
+ *    with buffers and a stream of its own (mgc_last_error is per thread).
+ *    Batched calls, the allocation-free compression (one scratch a device),
+ *    mgc_set_tuning / mgc_set_decoder, stage timing and mgc_destroy must not
+ *    overlap other calls on the context; distinct contexts are independent.
  */
 #ifndef MGC_H
 #define MGC_H

@@ -17,6 +17,10 @@ Entry points (same names as the C functions, without the ``mgc_`` prefix):
 ``pipe_compress(host_x, bound)`` / ``pipe_decompress(container)`` / ``pipe_profile`` (host-resident arrays)
 ``zfp_compress(x, rate)`` / ``zfp_decompress(stream)`` (fixed-rate block transform coding)
 ``header_info(stream)``, ``profile_enable / profile_reset / profile_read``
+
+Threads: calls may be under way in several threads at once, each on a stream and
+with tensors of its own, except those that mgc.h names (batched and
+allocation-free calls, settings, stage timing).
 """
 from __future__ import annotations
 
@@ -387,7 +391,8 @@ class Batch:
     ``run`` enqueues the compression of one list of tensors (asynchronous);
     ``streams`` waits for it and returns one uint8 GPU tensor per array (views
     into the shared output buffer; an array whose escaped values overflowed
-    the capacity is compressed again alone with the capacity it needs).
+    the capacity is compressed again alone with the capacity it needs).  Calls
+    of ``run`` by several threads on one device must not overlap.
     """
 
     def __init__(self, shapes, dtypes, outlier_cap: int = 0, device=None):

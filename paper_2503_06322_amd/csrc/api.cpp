@@ -176,11 +176,56 @@ const Plan& get_plan(mgc_ctx ctx, int ndim, const uint64_t* shape) {
   if (ndim > 3) fail(MGC_EUNSUPPORTED, "ndim above 3 is not supported");
   std::vector<uint64_t> key(shape, shape + ndim);
   key.insert(key.begin(), (uint64_t)ndim);
+  std::lock_guard<std::mutex> lk(ctx->mu);  // (map entries stay where they are)
   auto it = ctx->plans.find(key);
   if (it != ctx->plans.end()) return it->second;
   Plan p = build_plan(ndim, shape);
   upload_plan(p);
   return ctx->plans.emplace(key, std::move(p)).first->second;
+}
+
+namespace {
+Staging new_staging() {
+  Staging st;
+  if (hipHostMalloc((void**)&st.host, kStagingBytes, hipHostMallocDefault) != hipSuccess)
+    fail(MGC_EDEVICE, "hipHostMalloc failed");
+  if (hipHostGetDevicePointer((void**)&st.dev, st.host, 0) != hipSuccess) {
+    (void)hipHostFree(st.host);
+    fail(MGC_EDEVICE, "hipHostGetDevicePointer failed");
+  }
+  return st;
+}
+}  // namespace
+
+StagingLease::StagingLease(mgc_ctx ctx) : ctx_(ctx) {
+  std::lock_guard<std::mutex> lk(ctx->mu);
+  if (ctx->staging_free.empty()) {
+    ctx->staging_all.reserve(ctx->staging_all.size() + 1);
+    ctx->staging_free.reserve(ctx->staging_all.size() + 1);  // (the return cannot fail)
+    st_ = new_staging();
+    ctx->staging_all.push_back(st_);
+    return;
+  }
+  st_ = ctx->staging_free.back();
+  ctx->staging_free.pop_back();
+}
+StagingLease::~StagingLease() {
+  if (!idle_) return;
+  std::lock_guard<std::mutex> lk(ctx_->mu);
+  ctx_->staging_free.push_back(st_);
+}
+void StagingLease::read(void* h_out, const void* d_in, size_t n, hipStream_t s) {
+  if (n > kStagingBytes) fail(MGC_EINVAL, "staging read too large");
+  busy();
+  launch_copy_bytes(st_.dev, d_in, n, s);
+  MGC_HIP(hipGetLastError());
+  MGC_HIP(hipStreamSynchronize(s));
+  idle();
+  std::memcpy(h_out, st_.host, n);
+}
+void sync_read(mgc_ctx ctx, void* h_out, const void* d_in, size_t n, hipStream_t s) {
+  StagingLease st(ctx);
+  st.read(h_out, d_in, n, s);
 }
 }  // namespace mgc
 
@@ -199,13 +244,10 @@ int tuned(mgc_ctx ctx, int kind) {
 const char* const kThomasFinest[3] = {"thomas_ax0[finest]", "thomas_ax1[finest]",
                                       "thomas_ax2[finest]"};
 
-// Reads n bytes of device memory into ctx->pinned (n <= 4 KiB): a one-block
-// copy into the mapped staging buffer, then a stream synchronisation.
-void sync_read(mgc_ctx ctx, void* host, const void* dev, size_t n, hipStream_t s) {
-  if (host != ctx->pinned || n > 4096) fail(MGC_EINVAL, "staging read too large");
-  launch_copy_bytes(ctx->pinned_dev, dev, n, s);
-  MGC_HIP(hipGetLastError());
-  MGC_HIP(hipStreamSynchronize(s));
+// Keeps the launch shape a decode used (mgc_decoder_info).
+void note_decode(mgc_ctx ctx, const DecodeShape& used) {
+  std::lock_guard<std::mutex> lk(ctx->mu);
+  ctx->dec_last = used;
 }
 
 // The solves on one level's coarse grid x: axis 2, then 1, then 0 (the
@@ -556,9 +598,9 @@ const unsigned* decompress_enqueue(mgc_ctx ctx, const uint8_t* head, size_t head
   }
   {
     StageScope st(&ctx->prof, "decode", s);
-    ctx->dec_last = launch_decode(in, off, words, h.n_chunks, h.n_words, (int)h.C, p.N,
-                                  h.n_codes, static_cast<const DecodeTables*>(w.tables),
-                                  w.sym, w.status, s, ctx->dec_force);
+    note_decode(ctx, launch_decode(in, off, words, h.n_chunks, h.n_words, (int)h.C, p.N, h.n_codes,
+                                   static_cast<const DecodeTables*>(w.tables), w.sym, w.status, s,
+                                   ctx->dec_force));
   }
   CoeffSrc src{w.sym, nullptr, reinterpret_cast<const uint64_t*>(in + opos),
                reinterpret_cast<const int64_t*>(in + oval), (int64_t)h.n_outliers};
@@ -602,14 +644,11 @@ mgc_status mgc_create(int device, mgc_ctx* out) {
     scratch_setup(device);
     auto* c = new mgc_ctx_s;
     c->device = device;
-    if (hipHostMalloc((void**)&c->pinned, 4096, hipHostMallocDefault) != hipSuccess) {
+    try {
+      StagingLease first(c);  // (so that no later call of one thread allocates)
+    } catch (...) {
       delete c;
-      fail(MGC_EDEVICE, "hipHostMalloc failed");
-    }
-    if (hipHostGetDevicePointer((void**)&c->pinned_dev, c->pinned, 0) != hipSuccess) {
-      (void)hipHostFree(c->pinned);
-      delete c;
-      fail(MGC_EDEVICE, "hipHostGetDevicePointer failed");
+      throw;
     }
     *out = c;
   });
@@ -623,7 +662,7 @@ mgc_status mgc_destroy(mgc_ctx ctx) {
     for (auto& kv : ctx->batches) free_batch_plan(kv.second);
     if (ctx->capture_stream) (void)hipStreamDestroy(ctx->capture_stream);
     for (auto& kv : ctx->plans) free_plan(kv.second);
-    if (ctx->pinned) (void)hipHostFree(ctx->pinned);
+    for (auto& st : ctx->staging_all) (void)hipHostFree(st.host);
     delete ctx;
   });
 }
@@ -759,18 +798,19 @@ mgc_status mgc_compress_blocking(mgc_ctx ctx, const void* d_in, int ndim, const 
     const Plan& p = compress_checks(ctx, d_in, ndim, shape, dtype, error_bound, norm, mode, &cap,
                                     d_out, out_cap, d_ws, ws_bytes);
     hipStream_t s = as_stream(stream);
+    StagingLease st(ctx);
     unsigned long long* res = nullptr;
     if (p.N > 0) {
       Carver c(d_ws);
       res = carve_compress(c, p, cap).info;
-    } else {
-      res = reinterpret_cast<unsigned long long*>(ctx->pinned_dev + 2048);
+    } else {  // (no workspace: the far half of the piece)
+      st.busy();
+      res = reinterpret_cast<unsigned long long*>(st.dev() + kStagingBytes / 2);
     }
     compress_enqueue(ctx, p, d_in, ndim, shape, dtype, error_bound, norm, mode, cap, d_out, d_ws,
                      res, s);
     unsigned long long r[2];
-    sync_read(ctx, ctx->pinned, res, sizeof(r), s);
-    std::memcpy(r, ctx->pinned, sizeof(r));
+    st.read(r, res, sizeof(r), s);
     *h_out_size = r[1];
     switch ((int)r[0]) {
       case MGC_OK: return;
@@ -864,8 +904,7 @@ mgc_status mgc_read_prefix(mgc_ctx ctx, const void* d_in, size_t n, void* h_out,
     if (n > 4096) fail(MGC_EINVAL, "prefixes of at most 4096 bytes");
     if (n == 0) return;
     if (!d_in || !h_out) fail(MGC_EINVAL, "null pointer");
-    sync_read(ctx, ctx->pinned, d_in, n, as_stream(stream));
-    std::memcpy(h_out, ctx->pinned, n);
+    sync_read(ctx, h_out, d_in, n, as_stream(stream));
   });
 }
 
@@ -884,8 +923,7 @@ mgc_status mgc_decompress_head(mgc_ctx ctx, const void* h_prefix, size_t n, cons
                            out_cap, d_ws, ws_bytes, s);
     if (!status) return;
     unsigned st = 0;
-    sync_read(ctx, ctx->pinned, status, sizeof(unsigned), s);
-    std::memcpy(&st, ctx->pinned, sizeof(unsigned));
+    sync_read(ctx, &st, status, sizeof(unsigned), s);
     if (st & ST_FORMAT) fail(MGC_EFORMAT, "corrupt coded data");
   });
 }
@@ -1098,8 +1136,7 @@ mgc_status mgc_huffman_encode(mgc_ctx ctx, const uint16_t* d_sym, uint64_t n, ui
     launch_huff_header(out, C, n, n_chunks, w.lay, info, s);
     MGC_HIP(hipGetLastError());
     unsigned long long inf[3];
-    sync_read(ctx, ctx->pinned, info, sizeof(inf), s);
-    std::memcpy(inf, ctx->pinned, sizeof(inf));
+    sync_read(ctx, inf, info, sizeof(inf), s);
     if (inf[0]) fail(MGC_EDEVICE, "huffman encode failed");
     *h_out_size = inf[2];
   });
@@ -1111,9 +1148,8 @@ mgc_status mgc_huffman_decode(mgc_ctx ctx, const void* d_in, size_t in_bytes, ui
     check_ctx(ctx);
     if (in_bytes < (size_t)kHuffHeaderBytes) fail(MGC_EFORMAT, "stream shorter than its header");
     hipStream_t s = as_stream(stream);
-    sync_read(ctx, ctx->pinned, d_in, kHuffHeaderBytes, s);
     HuffHeader h;
-    std::memcpy(&h, ctx->pinned, kHuffHeaderBytes);
+    sync_read(ctx, &h, d_in, kHuffHeaderBytes, s);
     uint64_t off = 0, words = 0;
     check_huff_header(h, n, in_bytes, &off, &words);
     Carver meas(nullptr);
@@ -1133,15 +1169,13 @@ mgc_status mgc_huffman_decode(mgc_ctx ctx, const void* d_in, size_t in_bytes, ui
     }
     {
       StageScope st(&ctx->prof, "decode", s);
-      ctx->dec_last = launch_decode(in, off, words, h.n_chunks, h.n_words, (int)h.C,
-                                    (int64_t)n, h.n_codes,
-                                    static_cast<const DecodeTables*>(tables), d_sym, status, s,
-                                    ctx->dec_force);
+      note_decode(ctx, launch_decode(in, off, words, h.n_chunks, h.n_words, (int)h.C, (int64_t)n,
+                                     h.n_codes, static_cast<const DecodeTables*>(tables), d_sym,
+                                     status, s, ctx->dec_force));
     }
     MGC_HIP(hipGetLastError());
     unsigned st = 0;
-    sync_read(ctx, ctx->pinned, status, sizeof(unsigned), s);
-    std::memcpy(&st, ctx->pinned, sizeof(unsigned));
+    sync_read(ctx, &st, status, sizeof(unsigned), s);
     if (st & ST_FORMAT) fail(MGC_EFORMAT, "corrupt coded data");
   });
 }
@@ -1230,9 +1264,8 @@ mgc_status mgc_zfp_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, vo
     if (reinterpret_cast<uintptr_t>(d_in) % 8) fail(MGC_EINVAL, "stream not 8-byte aligned");
     if (in_bytes < (size_t)kZfpHeaderBytes) fail(MGC_EFORMAT, "stream shorter than its header");
     hipStream_t s = as_stream(stream);
-    sync_read(ctx, ctx->pinned, d_in, kZfpHeaderBytes, s);
     ZfpHead h;
-    std::memcpy(&h, ctx->pinned, kZfpHeaderBytes);
+    sync_read(ctx, &h, d_in, kZfpHeaderBytes, s);
     int nd = 0;
     uint64_t shp[3];
     mgc_dtype dt;
@@ -1361,9 +1394,8 @@ mgc_status mgc_hx_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, voi
     hipStream_t s = as_stream(stream);
     const size_t head = in_bytes >= (size_t)(kHxHeaderBytes + kHuffHeaderBytes)
                             ? kHxHeaderBytes + kHuffHeaderBytes : kHxHeaderBytes;
-    sync_read(ctx, ctx->pinned, d_in, head, s);
     uint8_t hb[kHxHeaderBytes + kHuffHeaderBytes] = {};
-    std::memcpy(hb, ctx->pinned, head);
+    sync_read(ctx, hb, d_in, head, s);
     mgc_hx_type t;
     uint64_t hn, total, n_esc, secb;
     uint32_t dict, C;
@@ -1407,8 +1439,8 @@ mgc_status mgc_hx_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, voi
     }
     {
       StageScope st(&ctx->prof, "decode", s);
-      ctx->dec_last = launch_decode(sec, off, words, h.n_chunks, h.n_words, (int)C, (int64_t)n,
-                                    h.n_codes, w.tables, key, w.status, s, ctx->dec_force);
+      note_decode(ctx, launch_decode(sec, off, words, h.n_chunks, h.n_words, (int)C, (int64_t)n,
+                                     h.n_codes, w.tables, key, w.status, s, ctx->dec_force));
     }
     if (type != MGC_HX_U16) {
       StageScope st(&ctx->prof, "hx_values", s);
@@ -1422,8 +1454,7 @@ mgc_status mgc_hx_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, voi
     }
     MGC_HIP(hipGetLastError());
     unsigned st = 0;
-    sync_read(ctx, ctx->pinned, w.status, sizeof(unsigned), s);
-    std::memcpy(&st, ctx->pinned, sizeof(unsigned));
+    sync_read(ctx, &st, w.status, sizeof(unsigned), s);
     if (st & ST_FORMAT) fail(MGC_EFORMAT, "corrupt coded data");
   });
 }

@@ -3,6 +3,7 @@
 #pragma once
 
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -124,14 +125,23 @@ mgc_status guard(F&& f) {
 struct BatchPlan;
 void free_batch_plan(BatchPlan* b);
 
+// Pinned, mapped host memory that a call reads device words through.
+constexpr size_t kStagingBytes = 4096;
+struct Staging {
+  uint8_t* host = nullptr;
+  uint8_t* dev = nullptr;  // the same memory as seen by the device
+};
+
 }  // namespace mgc
 
 struct mgc_ctx_s {
   int device = 0;
   std::map<std::vector<uint64_t>, mgc::Plan> plans;
   mgc::Profiler prof;
-  uint8_t* pinned = nullptr;      // 4 KiB host staging (pinned, mapped)
-  uint8_t* pinned_dev = nullptr;  // the same memory as seen by the device
+  // Guards plans, the staging pieces and dec_last: calls of several threads may
+  // be under way at once (batched calls, settings and stage timing aside).
+  std::mutex mu;
+  std::vector<mgc::Staging> staging_all, staging_free;
   // batched form: plans by batch signature, the stream graphs are captured
   // on, and tuning choices forced by the caller (-1 = autotune)
   std::map<std::vector<uint64_t>, mgc::BatchPlan*> batches;
@@ -145,6 +155,34 @@ struct mgc_ctx_s {
 
 namespace mgc {
 void check_ctx(mgc_ctx ctx);
+
+// A staging piece for the length of one call: calls that wait on different
+// streams at the same time each read through their own.  As many pieces exist
+// as calls ever waited at once; they go with the context.
+class StagingLease {
+ public:
+  explicit StagingLease(mgc_ctx ctx);
+  ~StagingLease();
+  StagingLease(const StagingLease&) = delete;
+  StagingLease& operator=(const StagingLease&) = delete;
+  uint8_t* host() const { return st_.host; }
+  uint8_t* dev() const { return st_.dev; }
+  // Between a launch that writes the piece and the wait for it: a call that
+  // fails there leaves the piece out of use until the context goes.
+  void busy() { idle_ = false; }
+  void idle() { idle_ = true; }
+  // Copies n bytes of device memory to host memory through the piece, in
+  // stream order, and waits (a kernel copy, so the read does not wait behind a
+  // copy engine).
+  void read(void* h_out, const void* d_in, size_t n, hipStream_t s);
+
+ private:
+  mgc_ctx ctx_;
+  Staging st_;
+  bool idle_ = true;
+};
+// The same with a piece taken for this read alone.
+void sync_read(mgc_ctx ctx, void* h_out, const void* d_in, size_t n, hipStream_t s);
 const Plan& get_plan(mgc_ctx ctx, int ndim, const uint64_t* shape);
 // Decompression launches on stream s for a stream whose header and bins
 // (the first head_bytes, at least 128 + 8 (L + 1)) the host already holds;

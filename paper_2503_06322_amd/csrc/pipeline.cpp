@@ -29,7 +29,8 @@ namespace {
 constexpr uint32_t kPipeMagic = 0x5043474Du;  // "MGCP"
 constexpr size_t kPipeHead = 64;
 constexpr size_t kPipeEntry = 32;
-constexpr size_t kPinSlot = 2048;  // results read through ctx->pinned from this offset
+constexpr size_t kMaxChunks = 512;  // chunk status words of a decompression in one staging piece
+static_assert(4 * kMaxChunks <= kStagingBytes, "a status word per chunk");
 constexpr uint64_t kDefaultInit = 64ull << 20;
 constexpr uint64_t kDefaultLimit = 1ull << 30;
 
@@ -203,15 +204,6 @@ void check_request(int ndim, const uint64_t* shape, mgc_dtype dt, double bound, 
     fail(MGC_EINVAL, "bad norm or mode");
 }
 
-// Reads n bytes of device memory through the mapped staging area (a kernel
-// copy, so the read does not wait behind a copy engine), then waits.
-void read_small(mgc_ctx ctx, void* host, const void* dev, size_t n, hipStream_t s) {
-  launch_copy_bytes(ctx->pinned_dev + kPinSlot, dev, n, s);
-  MGC_HIP(hipGetLastError());
-  MGC_HIP(hipStreamSynchronize(s));
-  std::memcpy(host, ctx->pinned + kPinSlot, n);
-}
-
 // min, max, sum of squares of the whole array: chunks streamed through the
 // range pass on two streams.  With `resident` (a device copy of the whole
 // array) the chunks are copied there and stay for the compression.
@@ -337,7 +329,6 @@ mgc_status mgc_pipe_compress(mgc_ctx ctx, const void* h_in, int ndim, const uint
       }
     }
     const size_t K = ent.size();
-    if (kPinSlot + 16 > 4096) fail(MGC_EDEVICE, "staging area");
     const size_t table = kPipeHead + K * kPipeEntry;
     if (out_cap < table) fail(MGC_ENOSPC, "output too small");
     // device buffers sized for the largest chunk
@@ -400,7 +391,7 @@ mgc_status mgc_pipe_compress(mgc_ctx ctx, const void* h_in, int ndim, const uint
                                    obuf, ocap, W.p, W.n, res, s);
       if (rc != MGC_OK) throw Fail{rc};
       uint64_t r2[2];
-      read_small(ctx, r2, res, 16, s);
+      sync_read(ctx, r2, res, 16, s);
       if (r2[0] == MGC_ENOSPC) {
         // more escaped values than the default capacity: this chunk again
         const uint64_t cap = r2[1];
@@ -416,7 +407,7 @@ mgc_status mgc_pipe_compress(mgc_ctx ctx, const void* h_in, int ndim, const uint
         rc = mgc_compress(ctx, input_of(i), ndim, cs, dtype, tc, norm, MGC_ABS, cap, obuf, ocap,
                           W.p, W.n, res, s);
         if (rc != MGC_OK) throw Fail{rc};
-        read_small(ctx, r2, res, 16, s);
+        sync_read(ctx, r2, res, 16, s);
       }
       tl.end(t_k[i], s);
       if (r2[0] != MGC_OK) fail((mgc_status)r2[0], "chunk compression failed");
@@ -506,7 +497,7 @@ mgc_status mgc_pipe_decompress(mgc_ctx ctx, const void* h_in, size_t in_bytes, v
     }
     if (p0 != h.shape[0]) fail(MGC_EFORMAT, "chunks do not cover the array");
     if (out_cap < h.shape[0] * pb) fail(MGC_ENOSPC, "output too small");
-    if (K > (4096 - kPinSlot) / 4) fail(MGC_EUNSUPPORTED, "too many chunks");
+    if (K > kMaxChunks) fail(MGC_EUNSUPPORTED, "too many chunks");
     size_t ws = 0;
     uint64_t cs[3];
     for (auto& e : ent) {
@@ -554,7 +545,9 @@ mgc_status mgc_pipe_decompress(mgc_ctx ctx, const void* h_in, size_t in_bytes, v
                              hipMemcpyHostToDevice, s));
       tl.end(t_in[i], s);
     };
-    unsigned* flags = reinterpret_cast<unsigned*>(ctx->pinned + kPinSlot);
+    StagingLease words(ctx);
+    unsigned* flags = reinterpret_cast<unsigned*>(words.host());
+    words.busy();
     std::memset(flags, 0, 4 * K);
     copy_in(0);
     for (size_t i = 0; i < K; ++i) {
@@ -574,7 +567,7 @@ mgc_status mgc_pipe_decompress(mgc_ctx ctx, const void* h_in, size_t in_bytes, v
       const unsigned* sw = decompress_enqueue(ctx, in + ent[i].offset, head, in_of(i),
                                               ent[i].bytes, out_of(i), ent[i].planes * pb, W.p,
                                               W.n, s);
-      if (sw) launch_copy_bytes(ctx->pinned_dev + kPinSlot + 4 * i, sw, 4, s);
+      if (sw) launch_copy_bytes(words.dev() + 4 * i, sw, 4, s);
       tl.end(t_k[i], s);
       t_out[i] = tl.begin(2, s);
       MGC_HIP(hipMemcpyAsync(out + ent[i].first * pb, out_of(i), ent[i].planes * pb,
@@ -582,6 +575,7 @@ mgc_status mgc_pipe_decompress(mgc_ctx ctx, const void* h_in, size_t in_bytes, v
       tl.end(t_out[i], s);
     }
     for (auto s : Q.q) MGC_HIP(hipStreamSynchronize(s));
+    words.idle();
     for (size_t i = 0; i < K; ++i)
       if (flags[i] & ST_FORMAT) fail(MGC_EFORMAT, "corrupt coded data in a chunk");
     if (stats) {
