@@ -59,7 +59,8 @@ typedef struct mgc_ctx_s* mgc_ctx;
 
 /* Context = per-device plan cache (the paper's context-memory cache,
  * Section III-B: reduction contexts are built once per shape and reused).
- * `device` is the HIP device ordinal; it is made current by every call. */
+ * `device` is the HIP device ordinal; it is made current by every call that
+ * works on it. */
 mgc_status mgc_create(int device, mgc_ctx* out);
 mgc_status mgc_destroy(mgc_ctx ctx);
 const char* mgc_last_error(void);
@@ -161,9 +162,9 @@ mgc_status mgc_compress_noalloc(mgc_ctx ctx, const void* d_in, int ndim, const u
 mgc_status mgc_header_info(const void* h_prefix, size_t n, int* ndim, uint64_t* shape3,
                            mgc_dtype* dtype, uint64_t* stream_bytes, size_t* ws_bytes);
 /* The first n (at most 4096) bytes of device memory at d_in to h_out, in stream
- * order (BLOCKING); and mgc_decompress for a caller that holds the stream's
- * first bytes (as for mgc_header_info) on the host already, so that the header
- * is read from the device once. */
+ * order (BLOCKING; the caller's current device stays); and mgc_decompress for a
+ * caller that holds the stream's first bytes (as for mgc_header_info) on the
+ * host already, so that the header is read from the device once. */
 mgc_status mgc_read_prefix(mgc_ctx ctx, const void* d_in, size_t n, void* h_out, void* stream);
 mgc_status mgc_decompress_head(mgc_ctx ctx, const void* h_prefix, size_t n, const void* d_in,
                                size_t in_bytes, void* d_out, size_t out_cap, void* d_ws,

@@ -504,6 +504,9 @@ def _prefix(stream, n: int) -> bytes:
         return np.ascontiguousarray(host, dtype=np.uint8).tobytes()
     dev = stream.device.index if stream.device.index is not None else _torch().cuda.current_device()
     buf = ctypes.create_string_buffer(max(n, 1))
+    if dev not in _ctxs:   # (creating a context makes its device current)
+        with _torch().cuda.device(dev):
+            _ctx(dev)
     _check(_load().mgc_read_prefix(_ctx(dev), ctypes.c_void_p(stream.data_ptr()), n, buf,
                                    _stream_ptr(dev)))
     return buf.raw[:n]

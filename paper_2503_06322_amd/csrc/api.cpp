@@ -900,6 +900,13 @@ mgc_status mgc_header_info(const void* h_prefix, size_t n, int* ndim, uint64_t* 
 
 mgc_status mgc_read_prefix(mgc_ctx ctx, const void* d_in, size_t n, void* h_out, void* stream) {
   return guard([&] {
+    // (a look at a header, which is no work on the device: the caller's current
+    // device stays)
+    struct KeepDevice {
+      int dev = -1;
+      KeepDevice() { MGC_HIP(hipGetDevice(&dev)); }
+      ~KeepDevice() { (void)hipSetDevice(dev); }
+    } keep;
     check_ctx(ctx);
     if (n > 4096) fail(MGC_EINVAL, "prefixes of at most 4096 bytes");
     if (n == 0) return;

@@ -29,7 +29,7 @@ def on_stub(tmp_path_factory):
 
     def run(program):
         head = "import ctypes, threading\nhip = ctypes.CDLL(%r)\nlib = ctypes.CDLL(%r)\n" % (soname, path)
-        env = dict(os.environ, LD_LIBRARY_PATH=str(out))
+        env = dict(os.environ, LD_LIBRARY_PATH=str(out), PYTHONPATH=ROOT)
         r = subprocess.run([sys.executable, "-c", head + program], capture_output=True, text=True, env=env, timeout=100)
         assert r.returncode == 0, r.stdout + r.stderr
     return run
@@ -58,4 +58,47 @@ threads = [threading.Thread(target=reader, args=(t,)) for t in range(1, 5)]
 [t.join() for t in threads]
 assert not wrong, "%d of 400 reads returned another thread's words" % len(wrong)
 assert lib.mgc_destroy(ctx) == 0
+""")
+
+
+def test_reading_a_header_leaves_the_current_device(on_stub):
+    """A program works on device 1 and looks at a stream that lies on device 0."""
+    on_stub(OPEN + """
+words = (ctypes.c_uint64 * 4)(1, 2, 3, 4)
+got = (ctypes.c_uint64 * 4)()
+hip.hipSetDevice(1)
+assert lib.mgc_read_prefix(ctx, words, ctypes.c_size_t(32), got, None) == 0
+dev = ctypes.c_int(-1)
+hip.hipGetDevice(ctypes.byref(dev))
+assert list(got) == [1, 2, 3, 4] and dev.value == 1, (list(got), dev.value)
+# a refused read too
+assert lib.mgc_read_prefix(ctx, words, ctypes.c_size_t(5000), got, None) == 1
+hip.hipGetDevice(ctypes.byref(dev))
+assert dev.value == 1
+""")
+
+
+def test_first_look_at_a_header_leaves_the_current_device(on_stub):
+    """The same through the binding, where the look also creates the library's context."""
+    on_stub("""
+import contextlib, struct, types
+import paper_2503_06322_amd as mgc
+@contextlib.contextmanager
+def device(d):
+    before = ctypes.c_int()
+    hip.hipGetDevice(ctypes.byref(before))
+    hip.hipSetDevice(d)
+    yield
+    hip.hipSetDevice(before.value)
+cuda = types.SimpleNamespace(device=device, current_stream=lambda d: types.SimpleNamespace(cuda_stream=0))
+mgc._torch = lambda: types.SimpleNamespace(cuda=cuda)
+buf = (ctypes.c_uint64 * 8)(5, 6, 7)
+stream = types.SimpleNamespace(numel=lambda: 64, is_cuda=True, is_contiguous=lambda: True, element_size=lambda: 1,
+                               device=types.SimpleNamespace(index=0), data_ptr=lambda: ctypes.addressof(buf))
+hip.hipSetDevice(1)
+for _ in range(2):
+    assert struct.unpack("<3Q", mgc._prefix(stream, 24)) == (5, 6, 7)
+    dev = ctypes.c_int(-1)
+    hip.hipGetDevice(ctypes.byref(dev))
+    assert dev.value == 1, dev.value
 """)
