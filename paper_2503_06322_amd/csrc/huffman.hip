@@ -52,12 +52,16 @@ constexpr int kLutBits = 14;
 // that compares the window with one canonical limit, or node kLutBad when the
 // prefix's windows start no code.
 constexpr int kLutBad = 0;
-constexpr int kLutNodes = 2 * (kMaxCodeLen + 1);
+constexpr int kLutNodes = 1 + 2 * (kMaxCodeLen - kLutBits);
 // Node of length l: windows below limit l start a code of length l; the
 // others one of length l + 1 (pair node: the prefix holds no other) or
-// continue at l + 1 (chain node).
-__host__ __device__ constexpr int lut_pair(int l) { return l; }
-__host__ __device__ constexpr int lut_chain(int l) { return kMaxCodeLen + 1 + l; }
+// continue at l + 1 (chain node).  Only for l > kLutBits: the limit of a shorter
+// length falls between two prefixes.
+__host__ __device__ constexpr int lut_pair(int l) { return l - kLutBits; }
+__host__ __device__ constexpr int lut_chain(int l) { return kMaxCodeLen - 2 * kLutBits + l; }
+static_assert(lut_pair(kLutBits + 1) == 1 && lut_chain(kLutBits + 1) == lut_pair(kMaxCodeLen) + 1 &&
+                  lut_chain(kMaxCodeLen) == kLutNodes - 1,
+              "nodes in a row, after kLutBad");
 
 struct DecodeTables {
   uint32_t first[34];
@@ -2513,8 +2517,10 @@ __global__ __launch_bounds__(1024) void k_decode(
     // limits below the longest length are under 2^32 (the longest length's
     // codes lie above them)
     const int l = threadIdx.x, lm = (int)(uint32_t)t->limit[l];
-    node[lut_pair(l)] = make_int4(lm, -l, -(l + 1), 0);
-    node[lut_chain(l)] = make_int4(lm, -l, l + 1 < (int)maxlen ? lut_chain(l + 1) : -(l + 1), 0);
+    if (l > kLutBits) {
+      node[lut_pair(l)] = make_int4(lm, -l, -(l + 1), 0);
+      node[lut_chain(l)] = make_int4(lm, -l, l + 1 < (int)maxlen ? lut_chain(l + 1) : -(l + 1), 0);
+    }
     offd[kMaxCodeLen - l] = lds_addr(sorted) + 2 * (t->base[l] - t->first[l]);
   }
   for (uint32_t i = threadIdx.x; i < n_codes; i += nthr) sorted[i] = t->sorted[i];

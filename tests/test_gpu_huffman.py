@@ -302,3 +302,18 @@ def test_histogram_outside_its_window(n, share):
     sym = np.where(rng.random(n) < share, outer, np.clip(inner, 16384, 49151))
     t = torch.from_numpy(sym.astype(np.uint16).view(np.int16)).cuda()
     assert to_bytes(mgc.huffman_encode(t)) == oracle_huffman_stream(sym, 1024)
+
+
+# codebooks within a few words of what a block of two and of three wavefronts can
+# hold beside 64-byte pieces
+@pytest.mark.parametrize("codes,waves", [(65136, 2), (60912, 3)])
+def test_forced_shape_beside_the_largest_codebook_it_fits(codes, waves, forced_decoder):
+    torch, mgc = gpu()
+    rng = np.random.default_rng(codes)
+    sym = np.concatenate([np.arange(codes), rng.integers(0, codes, size=200_000)])
+    rng.shuffle(sym)
+    t = torch.from_numpy(sym.astype(np.uint16).view(np.int16)).cuda()
+    enc = mgc.huffman_encode(t)
+    forced_decoder(1, waves)
+    assert bool((mgc.huffman_decode(enc, len(sym)) == t).all())
+    assert mgc.decoder_info() == (1, waves)
