@@ -259,8 +259,9 @@ void note_decode(mgc_ctx ctx, const DecodeShape& used) {
 // second buffer of the grid's size that nothing needs now (null: none).  A
 // tuning candidate forces the serial sweeps (the caller's forced candidates
 // when use_tuning is set).
+// seen: reports from the windows of long lines, acted on here.
 void solve_coarse(mgc_ctx ctx, const LevelGeom& g, double* x, double* other, const double* sub,
-                  bool fin, bool use_tuning, hipStream_t s) {
+                  bool fin, bool use_tuning, const NonFinite& seen, hipStream_t s) {
   if (thomas_grid_fits(g)) {
     StageScope sc(&ctx->prof, fin ? "thomas[finest]" : "thomas", s);
     launch_thomas_grid(x, g, sub, s);
@@ -282,11 +283,26 @@ void solve_coarse(mgc_ctx ctx, const LevelGeom& g, double* x, double* other, con
     if (g.bit[axis] < 0) continue;
     StageScope sc(&ctx->prof, fin ? kThomasFinest[axis] : "thomas", s);
     double* const to = ch.flip[axis] ? (cur == x ? other : x) : cur;
-    launch_thomas(axis, ch.cls[axis], cur, to, g.nc, g.ax[axis], axis == last ? sub : nullptr, s,
-                  cand(axis));
+    launch_thomas(axis, ch.cls[axis], cur, to, g.nc, g.ax[axis], axis == last ? sub : nullptr, seen,
+                  s, cand(axis));
     cur = to;
   }
+  if (seen.bits && (ch.cls[0] == kPartLong || ch.cls[1] == kPartLong))
+    launch_spread_nonfinite(x, g.nc[0] * g.nc[1] * g.nc[2], seen, s);
 }
+
+// The cleared word that a transform call's windows report in, one bit a level;
+// null when no line is long enough for windows.
+unsigned* clear_nonfinite(const Plan& p, unsigned* word, hipStream_t s) {
+  if (p.L < 1) return nullptr;
+  const PlanLevel& v = p.lv[p.L];
+  if (v.nc[0] <= kPartWholeMax && v.nc[1] <= kPartWholeMax) return nullptr;
+  void* const zp[1] = {word};
+  const size_t zb[1] = {sizeof(unsigned)};
+  launch_zero_words(zp, zb, 1, s);
+  return word;
+}
+NonFinite nonfinite_of(unsigned* bits, int level) { return {bits, 1u << (level & 31)}; }
 
 // The levels 1..top that run in one workgroup with their grids in LDS (0:
 // none): the largest top whose levels all fit, their tables within the LDS
@@ -307,11 +323,12 @@ int tail_top(const Plan& p, TailTabArgs* tt) {
 }
 
 // rdev: device reciprocal bins r_0..r_L (quantising runs, sym != nullptr);
-// gate: the compression's status word (null: ungated).
+// gate: the compression's status word (null: ungated); seen: a transform call's
+// word of clear_nonfinite.
 void run_levels_decompose(mgc_ctx ctx, const Plan& p, const void* d_in, bool in_f32,
                           double* gA, double* gB, uint16_t* sym, double* raw,
                           const double* rdev, const OutlierBuf& ob, unsigned* status,
-                          const unsigned* gate, hipStream_t s) {
+                          const unsigned* gate, hipStream_t s, unsigned* seen = nullptr) {
   const void* Gcur = d_in;
   bool cur_f32 = in_f32;
   TailTabArgs tt{};
@@ -325,7 +342,8 @@ void run_levels_decompose(mgc_ctx ctx, const Plan& p, const void* d_in, bool in_
                        gate, s, tuned(ctx, cur_f32 ? MGC_TUNE_DEC_F32 : MGC_TUNE_DEC_F64));
     }
     // (the other buffer held the grid just decomposed, or nothing yet)
-    solve_coarse(ctx, g, Gnext, Gnext == gA ? gB : gA, nullptr, l == p.L, true, s);
+    solve_coarse(ctx, g, Gnext, Gnext == gA ? gB : gA, nullptr, l == p.L, true,
+                 nonfinite_of(seen, l), s);
     Gcur = Gnext;
     cur_f32 = false;
   }
@@ -342,11 +360,12 @@ void run_levels_decompose(mgc_ctx ctx, const Plan& p, const void* d_in, bool in_
 
 // levels (optional) receives G_0 .. G_{L-1}, level after level.
 // coarse (optional): FP64 coefficients read for levels 0 .. coarse_top
-// instead of src.
+// instead of src.  seen as for the decomposition.
 void run_levels_recompose(mgc_ctx ctx, const Plan& p, const CoeffSrc& src,
                           const std::vector<double>& q, double* gA, double* gB, void* d_out,
                           bool out_f32, hipStream_t s, double* levels = nullptr,
-                          const CoeffSrc* coarse = nullptr, int coarse_top = -1) {
+                          const CoeffSrc* coarse = nullptr, int coarse_top = -1,
+                          unsigned* seen = nullptr) {
   auto src_of = [&](int l) -> const CoeffSrc& {
     return coarse && l <= coarse_top ? *coarse : src;
   };
@@ -388,7 +407,8 @@ void run_levels_recompose(mgc_ctx ctx, const Plan& p, const CoeffSrc& src,
     const size_t need = (size_t)p.points(l - 1) * sizeof(double);
     const bool room = (size_t)p.N * (out_f32 ? 4 : 8) >= need &&
                       (reinterpret_cast<uintptr_t>(d_out) & 7) == 0;
-    solve_coarse(ctx, g, F, room ? static_cast<double*>(d_out) : nullptr, Gprev, fin, true, s);
+    solve_coarse(ctx, g, F, room ? static_cast<double*>(d_out) : nullptr, Gprev, fin, true,
+                 nonfinite_of(seen, l), s);
     {
       StageScope sc(&ctx->prof, fin ? "rec_interp[finest]" : "rec_interp", s);
       double* dst = levels ? slot[l] : Gprev;
@@ -979,7 +999,7 @@ mgc_status mgc_decompose(mgc_ctx ctx, const void* d_in, int ndim, const uint64_t
     hipStream_t s = as_stream(stream);
     OutlierBuf ob{nullptr, nullptr, nullptr, 0};
     run_levels_decompose(ctx, p, d_in, dtype == MGC_F32, gA, gB, nullptr, d_coeffs, nullptr, ob,
-                         status, nullptr, s);
+                         status, nullptr, s, clear_nonfinite(p, status, s));
     MGC_HIP(hipGetLastError());
   });
 }
@@ -996,12 +1016,13 @@ mgc_status mgc_recompose(mgc_ctx ctx, const double* d_coeffs, int ndim, const ui
     Carver c(d_ws);
     double* gA = c.take<double>(n_coarse);
     double* gB = c.take<double>(n_coarse);
-    c.take<unsigned>(4);
+    unsigned* status = c.take<unsigned>(4);
     if (ws_bytes < c.off) fail(MGC_ENOSPC, "workspace too small");
     hipStream_t s = as_stream(stream);
     CoeffSrc src{nullptr, d_coeffs, nullptr, nullptr, 0};
     run_levels_recompose(ctx, p, src, std::vector<double>(p.L + 1, 1.0), gA, gB, d_out,
-                         out_dtype == MGC_F32, s);
+                         out_dtype == MGC_F32, s, nullptr, nullptr, -1,
+                         clear_nonfinite(p, status, s));
     MGC_HIP(hipGetLastError());
   });
 }
@@ -1009,6 +1030,7 @@ mgc_status mgc_recompose(mgc_ctx ctx, const double* d_coeffs, int ndim, const ui
 namespace {
 struct AdjointWs {
   double *gA, *gB, *Y, *T;  // T: the sweeps' second buffer
+  unsigned* seen;
 };
 AdjointWs carve_adjoint(Carver& c, const Plan& p) {
   const int64_t n_coarse = p.L >= 1 ? p.points(p.L - 1) : 1;
@@ -1017,6 +1039,7 @@ AdjointWs carve_adjoint(Carver& c, const Plan& p) {
   w.gB = c.take<double>(n_coarse);
   w.Y = c.take<double>(n_coarse);
   w.T = c.take<double>(n_coarse);
+  w.seen = c.take<unsigned>(1);
   return w;
 }
 size_t levels_bytes_of(const Plan& p) {
@@ -1050,6 +1073,7 @@ mgc_status mgc_recompose_adjoint(mgc_ctx ctx, const double* d_grad_u, int ndim,
     AdjointWs w = carve_adjoint(c, p);
     hipStream_t s = as_stream(stream);
     const double* g = d_grad_u;
+    unsigned* const seen = clear_nonfinite(p, w.seen, s);
     for (int l = p.L; l >= 1; --l) {
       const LevelGeom geom = p.geom(l);
       double* Gc = (g == w.gA) ? w.gB : w.gA;
@@ -1057,7 +1081,7 @@ mgc_status mgc_recompose_adjoint(mgc_ctx ctx, const double* d_grad_u, int ndim,
         StageScope sc(&ctx->prof, "adj_restrict", s);
         launch_adj_restrict(g, geom, Gc, w.Y, s);
       }
-      solve_coarse(ctx, geom, w.Y, w.T, nullptr, false, false, s);
+      solve_coarse(ctx, geom, w.Y, w.T, nullptr, false, false, nonfinite_of(seen, l), s);
       {
         StageScope sc(&ctx->prof, "adj_coeff", s);
         launch_adj_coeff(w.Y, g, geom, d_grad_coeffs, s);
@@ -1092,11 +1116,13 @@ mgc_status mgc_recompose_levels(mgc_ctx ctx, const double* d_coeffs, int ndim,
     Carver c(d_ws);
     double* gA = c.take<double>(n_coarse);
     double* gB = c.take<double>(n_coarse);
-    c.take<unsigned>(4);
+    unsigned* status = c.take<unsigned>(4);
     if (ws_bytes < c.off) fail(MGC_ENOSPC, "workspace too small");
     CoeffSrc src{nullptr, d_coeffs, nullptr, nullptr, 0};
+    hipStream_t s = as_stream(stream);
     run_levels_recompose(ctx, p, src, std::vector<double>(p.L + 1, 1.0), gA, gB, d_out,
-                         out_dtype == MGC_F32, as_stream(stream), d_levels);
+                         out_dtype == MGC_F32, s, d_levels, nullptr, -1,
+                         clear_nonfinite(p, status, s));
     MGC_HIP(hipGetLastError());
   });
 }

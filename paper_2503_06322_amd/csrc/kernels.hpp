@@ -69,6 +69,7 @@ enum { kPartNone = 0, kPart40 = 1, kPart64 = 2, kPartLong = 3, kPartScan = 4, kP
        kPartRow = 6 };
 constexpr int64_t kRowBlkMax = 8704;
 constexpr int kPartWavesMax = 8;  // wavefronts per block of the strided sweeps
+constexpr int64_t kPartWholeMax = 512;  // longest strided line without windows
 struct ThomasChoice {
   int cls[3];
   bool flip[3];
@@ -85,7 +86,7 @@ __host__ __device__ inline ThomasChoice thomas_choice(const int64_t (&nc)[3], co
   for (int k = 0; k < 2; ++k) {
     c.cls[k] = bit[k] < 0 || force_strided ? kPartNone
                : nc[k] <= 320              ? kPart40
-               : nc[k] <= 512              ? kPart64
+               : nc[k] <= kPartWholeMax    ? kPart64
                                            : kPartLong;
     windows += c.cls[k] == kPartLong ? 1 : 0;
   }
@@ -104,8 +105,17 @@ __host__ __device__ inline ThomasChoice thomas_choice(const int64_t (&nc)[3], co
 // 1) candidate.  The partitioned sweeps agree with the serial ones up to
 // rounding; the batched form makes the same choice per array, so both agree
 // bit for bit.
+// seen: where the windows report values that are not finite (the transform calls;
+// compression refuses such data), one bit a level; with bits null nobody asks.
+struct NonFinite {
+  unsigned* bits = nullptr;  // device
+  unsigned bit = 0;
+};
 void launch_thomas(int axis, int cls, const double* x, double* dst, const int64_t nc[3],
-                   const AxisTab& t, const double* sub, hipStream_t s, int cand = 0);
+                   const AxisTab& t, const double* sub, const NonFinite& seen, hipStream_t s,
+                   int cand = 0);
+// Fills the solved grid with NaN, as sweeps over whole lines do, when seen's bit is set.
+void launch_spread_nonfinite(double* x, int64_t n, const NonFinite& seen, hipStream_t s);
 // Blocks of a strided axis' partitioned sweep of class c.
 uint32_t thomas_part_blocks(int axis, int c, const int64_t nc[3]);
 // All active axes of a coarse grid small enough for LDS in one launch (the

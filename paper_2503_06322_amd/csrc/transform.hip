@@ -17,6 +17,7 @@
 // G_l = P G_l[coarse] + c_l.
 #include "kernels.hpp"
 
+#include <cfloat>
 #include <cmath>
 #include <type_traits>
 
@@ -2307,7 +2308,8 @@ __device__ __forceinline__ void thomas_rows_body(double* __restrict__ x, int64_t
                                                  int64_t n, const double* __restrict__ ta,
                                                  const double* __restrict__ tm,
                                                  const double* __restrict__ tc,
-                                                 const double* __restrict__ sub, int64_t blk) {
+                                                 const double* __restrict__ sub, int64_t blk,
+                                                 const NonFinite seen = {}) {
   static_assert(SEG <= 64 && 64 % SEG == 0, "segment divides the wavefront");
   constexpr int RP = 64 / SEG;  // rows per wavefront load (SEG lanes per row)
   constexpr int K = SEG;        // loads per lane per segment (64 rows)
@@ -2447,8 +2449,11 @@ __global__ __launch_bounds__(64) void k_thomas_rows(double* __restrict__ x, int6
 // but for the last, so |a|, |c| < 0.29 inside a line and a start value's
 // influence falls below 0.29^32 = 6e-18 of it across the halo, less than a
 // rounding.  Blocks read values that others store, so dst is not x (in place
-// otherwise).  At 4097 x 4097 values: LONGUS us, the one-thread-per-line
-// sweep 1219 us (4,097 threads on the whole GPU, every value twice).
+// otherwise).  A NaN or an infinity reaches every value of its line, beyond the
+// windows that hold it: a block that reads one says so in *seen.bits (where the
+// caller wants to know), and launch_spread_nonfinite fills the grid.  At
+// 4097 x 4097 values: LONGUS us, the one-thread-per-line sweep 1219 us (4,097
+// threads on the whole GPU, every value twice).
 constexpr int kPartWaves = kPartWavesMax;  // segments (wavefronts) per block at most
 constexpr int kLongSeg = 40, kLongHalo = 32;
 constexpr int kLongUse = kPartWaves * kLongSeg - 2 * kLongHalo;
@@ -2458,7 +2463,8 @@ __device__ __forceinline__ void thomas_part_body(const double* x, double* dst, i
                                                  const double* __restrict__ ta,
                                                  const double* __restrict__ tm,
                                                  const double* __restrict__ tc,
-                                                 const double* __restrict__ sub, int64_t blk) {
+                                                 const double* __restrict__ sub, int64_t blk,
+                                                 const NonFinite seen = {}) {
   static_assert(SEG <= 64, "one factor slot per lane");
   __shared__ double cy[kPartWaves][64], cx[kPartWaves][64];
   __shared__ double ca[kPartWaves], cb[kPartWaves];
@@ -2539,6 +2545,13 @@ __device__ __forceinline__ void thomas_part_body(const double* x, double* dst, i
 #pragma unroll
     for (int k = 0; k < SEG; ++k) v[k] = 0.0;
   }
+  if (LONG && seen.bits) {
+    bool bad = false;
+#pragma unroll
+    for (int k = 0; k < SEG; ++k) bad = bad || !(fabs(v[k]) <= DBL_MAX);
+    const uint64_t m = __ballot(bad);
+    if (m && lane == __ffsll((unsigned long long)m) - 1) atomicOr(seen.bits, seen.bit);
+  }
   // forward sweep of the segment from a zero start
   double prev = 0.0, A = 1.0;
 #pragma unroll
@@ -2600,12 +2613,12 @@ template <int AXIS, int SEG, bool LONG>
 __global__ __launch_bounds__(64 * kPartWaves) void k_thomas_part(
     const double* x, double* dst, int64_t n0, int64_t n1, int64_t n2,
     const double* __restrict__ ta, const double* __restrict__ tm, const double* __restrict__ tc,
-    const double* __restrict__ sub, uint32_t nblk) {
+    const double* __restrict__ sub, uint32_t nblk, const NonFinite seen) {
   // Consecutive line windows share their edge cache lines (rows are not
   // line-aligned), so each XCD takes a contiguous range of windows.
   const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
   if (b >= nblk) return;
-  thomas_part_body<AXIS, SEG, LONG>(x, dst, n0, n1, n2, ta, tm, tc, sub, b);
+  thomas_part_body<AXIS, SEG, LONG>(x, dst, n0, n1, n2, ta, tm, tc, sub, b, seen);
 }
 
 // Contiguous axis: one wavefront per row at a time, lane l holding the row's
@@ -3947,19 +3960,19 @@ void thomas_rowblk(const double* x, double* dst, const int64_t nc[3], const Axis
 }
 template <int AXIS, int SEG, bool LONG>
 void thomas_part_axis(const double* x, double* dst, const int64_t nc[3], const AxisTab& t,
-                      const double* sub, hipStream_t s) {
+                      const double* sub, const NonFinite& seen, hipStream_t s) {
   const int64_t w = LONG ? kPartWaves : (nc[AXIS] + SEG - 1) / SEG;
   const uint32_t nblk = thomas_part_blocks(AXIS, LONG ? kPartLong : kPart40, nc);
   hipLaunchKernelGGL((k_thomas_part<AXIS, SEG, LONG>), dim3((nblk + 7u) & ~7u),
                      dim3((unsigned)(64 * w)), 0, s, x, dst, nc[0], nc[1], nc[2], t.ta, t.tm, t.tc,
-                     sub, nblk);
+                     sub, nblk, seen);
 }
 template <int AXIS>
 void thomas_part_strided(int c, const double* x, double* dst, const int64_t nc[3],
-                         const AxisTab& t, const double* sub, hipStream_t s) {
-  if (c == kPart40) thomas_part_axis<AXIS, 40, false>(x, dst, nc, t, sub, s);
-  else if (c == kPart64) thomas_part_axis<AXIS, 64, false>(x, dst, nc, t, sub, s);
-  else thomas_part_axis<AXIS, kLongSeg, true>(x, dst, nc, t, sub, s);
+                         const AxisTab& t, const double* sub, const NonFinite& seen, hipStream_t s) {
+  if (c == kPart40) thomas_part_axis<AXIS, 40, false>(x, dst, nc, t, sub, seen, s);
+  else if (c == kPart64) thomas_part_axis<AXIS, 64, false>(x, dst, nc, t, sub, seen, s);
+  else thomas_part_axis<AXIS, kLongSeg, true>(x, dst, nc, t, sub, seen, s);
 }
 }  // namespace
 
@@ -3970,7 +3983,8 @@ uint32_t thomas_part_blocks(int axis, int c, const int64_t nc[3]) {
 }
 
 void launch_thomas(int axis, int cls, const double* x, double* dst, const int64_t nc[3],
-                   const AxisTab& t, const double* sub, hipStream_t s, int cand) {
+                   const AxisTab& t, const double* sub, const NonFinite& seen, hipStream_t s,
+                   int cand) {
   const int64_t L = nc[axis];
   if (cls == kPartScan) {
     if (L <= 128) thomas_rowscan<2>(x, dst, nc, t, sub, s);
@@ -3984,8 +3998,8 @@ void launch_thomas(int axis, int cls, const double* x, double* dst, const int64_
     else if (L <= 9 * kRowBlkThreads) thomas_rowblk<9>(x, dst, nc, t, sub, s);
     else thomas_rowblk<17>(x, dst, nc, t, sub, s);
   } else if (cls != kPartNone) {
-    if (axis == 1) thomas_part_strided<1>(cls, x, dst, nc, t, sub, s);
-    else thomas_part_strided<0>(cls, x, dst, nc, t, sub, s);
+    if (axis == 1) thomas_part_strided<1>(cls, x, dst, nc, t, sub, seen, s);
+    else thomas_part_strided<0>(cls, x, dst, nc, t, sub, seen, s);
   } else {
     if (x != dst) throw std::logic_error("launch_thomas: the serial sweeps run in place");
     switch (cand) {
@@ -3996,6 +4010,20 @@ void launch_thomas(int axis, int cls, const double* x, double* dst, const int64_
   }
 }
 static_assert(kRowBlkMax == 17 * kRowBlkThreads, "the row blocks' longest row");
+
+namespace {
+// (few blocks: the grid is filled only when something in it is not finite)
+__global__ __launch_bounds__(256) void k_spread_nonfinite(double* __restrict__ x, int64_t n,
+                                                           const NonFinite seen) {
+  if (!(*seen.bits & seen.bit)) return;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (int64_t)gridDim.x * 256)
+    x[i] = __longlong_as_double(0x7FF8000000000000ll);
+}
+}  // namespace
+void launch_spread_nonfinite(double* x, int64_t n, const NonFinite& seen, hipStream_t s) {
+  hipLaunchKernelGGL(k_spread_nonfinite, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 256)),
+                     dim3(256), 0, s, x, n, seen);
+}
 
 bool thomas_grid_fits(const LevelGeom& g) {
   if (g.nc[0] * g.nc[1] * g.nc[2] > kThomasGridMax) return false;

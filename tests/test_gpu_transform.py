@@ -3,8 +3,11 @@
 Arithmetic is FP64 on both sides (FP32 inputs are read exactly), so the
 coefficients must agree to 1e-12 of max|u| per entry.
 """
+import functools
+
 import numpy as np
 import pytest
+import scipy.linalg
 
 import oracle
 import synthetic
@@ -231,3 +234,33 @@ def test_small_levels_in_one_workgroup_equal_per_level_launches(shape, dtype):
     one = mgc.recompose(c, shape, dt)
     per_level, _ = mgc.recompose_levels(c, shape, dt)
     assert torch.equal(one, per_level)
+
+
+# lines of more than 512 values on one and on two strided axes, beside rows that
+# one wavefront and that one block solves
+@pytest.mark.parametrize("shape", [(1100, 60), (1100, 1200), (9, 1100, 21), (1100, 4, 1100)])
+@pytest.mark.parametrize("value", [np.nan, np.inf, -np.inf])
+@pytest.mark.parametrize("where", [0.0, 0.37, 1.0])
+def test_non_finite_values_reach_whole_lines(shape, value, where, monkeypatch):
+    """One value that is not finite among the nodal values, the coefficients or the
+    gradient: the same values of the result are not finite as the oracle's solves
+    of whole lines give, however many windows a line takes.  (In the gradient's
+    coarsest grid, which no solve reaches, taps of weight zero may add some.)"""
+    torch, mgc = gpu()
+    solve = functools.partial(scipy.linalg.solve_banded, check_finite=False)
+    monkeypatch.setattr(scipy.linalg, "solve_banded", solve)
+    h = Hierarchy(shape)
+    u = np.random.default_rng(5).standard_normal(shape)
+    u.reshape(-1)[int(where * (u.size - 1))] = value
+    x = torch.from_numpy(u).cuda()
+
+    def lost(t):
+        return ~np.isfinite(t.cpu().numpy() if torch.is_tensor(t) else t).reshape(-1)
+
+    with np.errstate(all="ignore"):
+        c, v, g = oracle.decompose(u, h), oracle.recompose(u.reshape(-1), h), oracle.recompose_adjoint(u, h)
+    assert np.array_equal(lost(mgc.decompose(x)), lost(c))
+    assert np.array_equal(lost(mgc.recompose(x.reshape(-1), shape)), lost(v))
+    assert np.array_equal(lost(mgc.recompose_levels(x.reshape(-1), shape)[0]), lost(v))
+    got, n0 = lost(mgc.recompose_adjoint(x)), int(np.prod(h.sizes[0]))
+    assert np.array_equal(got[n0:], lost(g)[n0:]) and np.all(got[:n0] >= lost(g)[:n0])
