@@ -1,0 +1,39 @@
+// Which of two kernels a call takes, where that depends on sizes alone: plain
+// host functions, so that the rules can be looked at without a GPU.
+#pragma once
+
+#include <cstdint>
+
+namespace mgc {
+
+constexpr int64_t route_ceil(int64_t a, int64_t b) { return (a + b - 1) / b; }
+
+// 3-axis levels of fewer fine points use the tiled kernels: there are too few
+// wavefronts of columns to fill the chip, each a serial chain of planes.
+// Decomposition in FP64: 129^3 26 us (tiled 18), 75 x 100 x 125 with many escaped
+// values 42 (32), 150 x 200 x 250 50 (69), 257^3 59 (94).  Restriction of
+// coefficients: 129^3 22 us (18), 150 x 200 x 250 with many escaped values 167
+// (87), 257^3 34 (55).
+constexpr int64_t kDecColsMin = int64_t(1) << 22, kRecColsMin = int64_t(1) << 24;
+constexpr int kColX = 62;                   // coarse columns of a wavefront along x
+constexpr int kColY = 4, kDecColY = 2;      // its coarse rows: restriction, decomposition
+
+// Decomposition of a 3-axis level by columns of wavefronts (else tiled).  A
+// wavefront takes 62 columns whatever the contiguous axis holds, a tile 16 (FP32
+// input) or 8 (FP64), so an axis of few values leaves the wavefront's lanes idle.
+// Over 55 sizes a type, 5 to 513 values along x and 4 to 36 million points,
+// columns take about 1.1 ns a step (62 columns x 2 rows of one coarse plane) and
+// 10 us to get going, tiles about 18 ns (FP32) and 7 to 8 ns (FP64) each.  Columns against
+// tiles, us: 513 x 513 x 17 63 / 52 and FP64 65 / 45; 1025 x 1025 x 17 163 / 165
+// and 174 / 148; 513 x 513 x 33 61 / 91 and 66 / 64; 1449 x 1449 x 5 289 / 309
+// and 311 / 141; 509 x 509 x 65 51 / 122 and 59 / 95.  The rule takes the faster
+// one but for at most 1 % (FP32) and 7 % (FP64).  (The restriction's columns have
+// no such side: 2897 x 2897 x 3 591 / 616, 1025 x 1025 x 17 105 / 167.)
+constexpr bool dec_takes_columns(const int64_t (&nf)[3], const int64_t (&nc)[3], bool f32) {
+  if (nf[0] * nf[1] * nf[2] < kDecColsMin) return false;
+  const int64_t steps = route_ceil(nc[2], kColX) * route_ceil(nc[1], kDecColY) * nc[0];
+  const int64_t tiles = route_ceil(nc[0], 4) * route_ceil(nc[1], 8) * route_ceil(nc[2], f32 ? 16 : 8);
+  return f32 ? steps + 9000 <= 17 * tiles : steps + 6000 <= 6 * tiles;
+}
+
+}  // namespace mgc

@@ -16,6 +16,7 @@
 // G_l[coarse] = G_{l-1} - z (fused into the last sweep), then
 // G_l = P G_l[coarse] + c_l.
 #include "kernels.hpp"
+#include "routes.hpp"
 
 #include <cfloat>
 #include <cmath>
@@ -1007,14 +1008,7 @@ __device__ __forceinline__ void coeff_values(const CoeffSrc& src, const uint32_t
 // a base that the whole wavefront shares.  The neighbour cells' values along x
 // come from the neighbour lanes, rows and planes are added to the running sums
 // of the outputs that they reach, in the order of the taps: no LDS, no barrier.
-constexpr int kColX = 62, kColY = 4;
-// Levels with fewer fine points use the tiled kernels: there are too few
-// wavefronts to fill the chip, each a serial chain of planes.  Decomposition in
-// FP64: 129^3 26 us (tiled 18), 75 x 100 x 125 with many escaped values 42
-// (32), 150 x 200 x 250 50 (69), 257^3 59 (94).  Restriction of coefficients:
-// 129^3 22 us (18), 150 x 200 x 250 with many escaped values 167 (87), 257^3 34
-// (55).
-constexpr int64_t kDecColsMin = int64_t(1) << 22, kRecColsMin = int64_t(1) << 24;
+// (kColX, kColY and when they are taken: routes.hpp.)
 constexpr uint32_t kColEsc = 256;  // escaped values of a wavefront's plane that are searched together
 
 // Value i (the same for the wavefront) of a table that no kernel writes while
@@ -1095,7 +1089,6 @@ __device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t row, uint32_t b
 // whose waits drained every access in flight, 373 us.  Two rows a wavefront: of
 // three the registers (156) leave three wavefronts a SIMD, 384 us against 373.
 constexpr int kDecColEsc = 768;  // escaped values a wavefront collects between flushes
-constexpr int kDecColY = 2;
 static_assert(kDecColEsc >= 64 * 4 * kDecColY, "a plane's escaped values fit");
 
 template <typename Tin, bool QUANT>
@@ -3787,7 +3780,7 @@ void dec_dispatch(const void* G, const LevelGeom& g, double* fout, uint16_t* sym
                   const unsigned* gate, hipStream_t s, int cand = 0) {
   const Tin* Gp = static_cast<const Tin*>(G);
   const int D = active_axes(g);
-  if (D == 3 && MODE != 2 && cand == 0 && g.nf[0] * g.nf[1] * g.nf[2] >= kDecColsMin) {
+  if (D == 3 && MODE != 2 && cand == 0 && dec_takes_columns(g.nf, g.nc, sizeof(Tin) == 4)) {
     const StreamGrid sg = cols_grid(g, kDecColY);
     hipLaunchKernelGGL((k_dec_cols<Tin, MODE == 0>), dim3(sg.grid), dim3(256), 0, s, Gp, g, fout,
                        sym, raw, rp, ob, status, gate, sg.seg, sg.n_blocks);
