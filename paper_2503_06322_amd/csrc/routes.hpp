@@ -36,4 +36,21 @@ constexpr bool dec_takes_columns(const int64_t (&nf)[3], const int64_t (&nc)[3],
   return f32 ? steps + 9000 <= 17 * tiles : steps + 6000 <= 6 * tiles;
 }
 
+// 2-axis levels streamed along the rows (else tiled).  With fewer fine points a
+// streamed column's steps are a serial chain (decomposition of 2049^2 26 us
+// streamed, 24 tiled; 4097^2 53 and 78; the restriction of recomposition 18 and
+// 23 us, 33 and 78).  A block takes 254 columns whatever the contiguous axis
+// holds, a tile 32, so a row needs four tiles (decomposition) or two (restriction)
+// to keep enough of them busy.  Streamed against tiled, us: decomposition of
+// 130,000 x 65 95 / 66, 66,000 x 129 57 / 51, 33,000 x 257 36 / 45, 16,384 x 513
+// 40 / 41; restriction of 123,362 x 34 51 / 40, 64,000 x 40 31 / 24, 64,528 x 65
+// 32 / 42, 65,027 x 129 34 / 59.
+constexpr int64_t kStream2MinPoints = int64_t(1) << 23, kRecStream2MinPoints = int64_t(1) << 22;
+constexpr bool dec_streams_rows(const int64_t (&nf)[3], const int64_t (&nc)[3]) {
+  return nf[1] * nf[2] >= kStream2MinPoints && nc[2] > 3 * 32;
+}
+constexpr bool rec_streams_rows(const int64_t (&nf)[3], const int64_t (&nc)[3]) {
+  return nf[1] * nf[2] >= kRecStream2MinPoints && nc[2] > 32;
+}
+
 }  // namespace mgc

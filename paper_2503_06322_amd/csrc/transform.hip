@@ -805,11 +805,6 @@ __global__ __launch_bounds__(256) void k_dec_level(const Tin* __restrict__ G, co
 // outputs reads 19 x 67 values for 16 x 64).
 constexpr int kStream2SX = 254;                // outputs of a block: 512 region slots
 constexpr int kStream2E = 2 * 256;
-// levels with fewer fine points use the tiled kernels: a streamed column's
-// steps are a serial chain (2049^2: 26 us streamed, 24 tiled; 4097^2: 53 and
-// 78; the restriction of recomposition 18 and 23 us, 33 and 78)
-constexpr int64_t kStream2MinPoints = int64_t(1) << 23;
-constexpr int64_t kRecStream2MinPoints = int64_t(1) << 22;
 
 template <typename Tin, bool QUANT>
 __global__ __launch_bounds__(256) void k_dec_stream2(
@@ -3794,7 +3789,7 @@ void dec_dispatch(const void* G, const LevelGeom& g, double* fout, uint16_t* sym
       case 3: dec_3<Tin, MODE, 3>(Gp, g, fout, sym, raw, rp, ob, status, gate, s); break;
       default: dec_3<Tin, MODE, 0>(Gp, g, fout, sym, raw, rp, ob, status, gate, s);
     }
-  } else if (D == 2 && MODE != 2 && cand == 0 && g.nf[1] * g.nf[2] >= kStream2MinPoints) {
+  } else if (D == 2 && MODE != 2 && cand == 0 && dec_streams_rows(g.nf, g.nc)) {
     const StreamGrid sg = stream2_grid(g);
     hipLaunchKernelGGL((k_dec_stream2<Tin, MODE == 0>), dim3(sg.grid), dim3(256), 0, s, Gp, g, fout,
                        sym, raw, rp, ob, status, gate, sg.seg, sg.n_blocks);
@@ -3825,7 +3820,7 @@ void rec_restrict_dispatch(const LevelGeom& g, const CoeffSrc& src, double q, do
     const TileGrid t = tile_grid(g, 4, 8, 8);
     hipLaunchKernelGGL((k_rec_restrict<4, 8, 8, RAW>), dim3(t.grid), dim3(256), 0, s, g, src, q,
                        fout, t.n_tiles);
-  } else if (D == 2 && g.nf[1] * g.nf[2] >= kRecStream2MinPoints) {
+  } else if (D == 2 && rec_streams_rows(g.nf, g.nc)) {
     const StreamGrid sg = stream2_grid(g);
     hipLaunchKernelGGL((k_rec_stream2<RAW>), dim3(sg.grid), dim3(256), 0, s, g, src, q, fout,
                        sg.seg, sg.n_blocks);

@@ -10,11 +10,24 @@ CSRC = os.path.join(os.path.dirname(os.path.dirname(os.path.abspath(__file__))),
 PROGRAM = """
 #include "routes.hpp"
 using namespace mgc;
+struct Level {
+  int64_t nf[3], nc[3];
+  explicit Level(const int64_t* n) {
+    for (int k = 0; k < 3; ++k) nf[k] = n[k], nc[k] = n[k] > 1 ? n[k] / 2 + 1 : 1;
+  }
+};
 extern "C" {
 int dec_columns(const int64_t* n, int f32) {
-  int64_t nf[3], nc[3];
-  for (int k = 0; k < 3; ++k) nf[k] = n[k], nc[k] = n[k] / 2 + 1;
-  return dec_takes_columns(nf, nc, f32);
+  const Level l(n);
+  return dec_takes_columns(l.nf, l.nc, f32);
+}
+int dec_rows(const int64_t* n) {
+  const Level l(n);
+  return dec_streams_rows(l.nf, l.nc);
+}
+int rec_rows(const int64_t* n) {
+  const Level l(n);
+  return rec_streams_rows(l.nf, l.nc);
 }
 }
 """
@@ -41,3 +54,13 @@ def rules(tmp_path_factory):
 def test_decomposition_columns(rules, shape, f32, f64):
     n = (ctypes.c_int64 * 3)(*shape)
     assert (rules.dec_columns(n, 1), rules.dec_columns(n, 0)) == (f32, f64)
+
+
+# (decomposition, restriction): streamed along the rows where that was the faster side
+@pytest.mark.parametrize("shape,dec,rec", [
+    ((130000, 65), 0, 1), ((66000, 129), 0, 1), ((33000, 257), 1, 1), ((16384, 513), 1, 1), ((8193, 8193), 1, 1),
+    ((123362, 34), 0, 0), ((254201, 33), 0, 0), ((64528, 65), 0, 1), ((4097, 4097), 1, 1), ((2049, 2049), 0, 1),
+    ((17, 1 << 20), 1, 1), ((2047, 2047), 0, 0)])
+def test_rows_streamed(rules, shape, dec, rec):
+    n = (ctypes.c_int64 * 3)(1, *shape)
+    assert (rules.dec_rows(n), rules.rec_rows(n)) == (dec, rec)
