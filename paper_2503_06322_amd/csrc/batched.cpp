@@ -22,6 +22,7 @@
 #include <vector>
 
 #include "host.hpp"
+#include "routes.hpp"
 
 #pragma clang fp contract(off)
 
@@ -59,6 +60,7 @@ struct BLaunch {
 
 struct BatchPlan {
   int n = 0;
+  bool spread = false;  // batch_spreads_codebooks
   std::vector<const Plan*> plans;
   std::vector<mgc_dtype> dt;
   std::vector<int> ndim;
@@ -315,7 +317,7 @@ void launch_one(const BatchPlan& b, const BLaunch& L, const int t[kTuneKinds], h
       break;
     case BK::Level0: launch_b_level0(J, m, L.nb, L.f32, s); break;
     case BK::Hist: launch_b_histogram(J, m, L.nb, s); break;
-    case BK::Codebook: launch_b_codebook(J, b.n, s); break;
+    case BK::Codebook: launch_b_codebook(J, b.n, b.spread, s); break;
     case BK::ChunkW: launch_b_chunk_words(J, m, L.nb, s); break;
     case BK::Scan: launch_b_layout_scan(J, b.n, s); break;
     case BK::OSort: launch_b_escape_order(J, b.n, s); break;
@@ -435,6 +437,9 @@ BatchPlan* get_batch(mgc_ctx ctx, int n, const int* ndims, const uint64_t* shape
       b->ndim.push_back(ndims[j]);
       b->shape.push_back({shapes[3 * j], shapes[3 * j + 1], shapes[3 * j + 2]});
     }
+    int64_t most = 0;
+    for (const Plan* p : b->plans) most = std::max(most, p->N);
+    b->spread = batch_spreads_codebooks(n, most);
     layout_offsets(b->plans, outlier_cap, b->cap, b->ws_off, b->out_off, b->ws_total,
                    b->out_total);
     MGC_HIP(hipMalloc(&b->d_jobs, n * sizeof(Job)));

@@ -2865,12 +2865,8 @@ void launch_histogram(const uint16_t* sym, int64_t n, unsigned* hist, hipStream_
 void launch_b_histogram(const Job* jobs, const JobBlock* map, uint32_t nb, hipStream_t s) {
   hipLaunchKernelGGL(kb_histogram, dim3(nb), dim3(1024), 0, s, jobs, map, nb);
 }
-void launch_b_codebook(const Job* jobs, int n, hipStream_t s) {
-  // One workgroup per array for everything takes as long as its largest array
-  // (540 us with 48 arrays of up to 32,000 codes, 545 with 256); the sort and
-  // the codes on many blocks take that out but their launches grow with the
-  // arrays (350 us with 48, 950 with 256: 2.9 us an array): even at about 115.
-  if (n > 96) {
+void launch_b_codebook(const Job* jobs, int n, bool spread, hipStream_t s) {
+  if (!spread) {
     hipLaunchKernelGGL(kb_codebook_whole, dim3((unsigned)n), dim3(1024), 0, s, jobs);
     return;
   }

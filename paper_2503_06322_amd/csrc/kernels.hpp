@@ -200,7 +200,8 @@ void launch_b_thomas_part(int axis, int c, int waves, const Job* jobs, const Job
 void launch_b_level0(const Job* jobs, const JobBlock* map, uint32_t nb, bool f32,
                      hipStream_t s);
 void launch_b_histogram(const Job* jobs, const JobBlock* map, uint32_t nb, hipStream_t s);
-void launch_b_codebook(const Job* jobs, int n, hipStream_t s);
+// spread: leaf sorts and canonical codes on many blocks (batch_spreads_codebooks).
+void launch_b_codebook(const Job* jobs, int n, bool spread, hipStream_t s);
 void launch_b_chunk_words(const Job* jobs, const JobBlock* map, uint32_t nb, hipStream_t s);
 void launch_b_layout_scan(const Job* jobs, int n, hipStream_t s);
 void launch_b_outlier_sort(const Job* jobs, int n, hipStream_t s);

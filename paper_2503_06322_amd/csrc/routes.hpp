@@ -53,4 +53,21 @@ constexpr bool rec_streams_rows(const int64_t (&nf)[3], const int64_t (&nc)[3]) 
   return nf[1] * nf[2] >= kRecStream2MinPoints && nc[2] > 32;
 }
 
+// Codebooks of a batch with their leaf sorts and canonical codes on many blocks
+// (else one workgroup an array for everything).  One workgroup each takes as long
+// as the largest codebook, however many there are; the many blocks take that out
+// but cost 1.8 to 2.5 us an array.  How many arrays that is worth grows with the
+// codes there can be, known here by the largest array's values.  Many blocks
+// against one each, us, for smooth / rough fields: 64 arrays of 17^3 177 / 178
+// against 69 / 69, 24 of 33^3 145 / 150 against 138 / 169, 48 of 65^3 229 / 249
+// against 199 / 289, 64 of 129^3 315 / 367 against 248 / 473, 64 of 257^3 397 /
+// 441 against 460 / 642; 48 arrays of 33^3 to 257^3 350 against 540.
+constexpr int kSpreadBatchMax = 96;
+constexpr bool batch_spreads_codebooks(int arrays, int64_t most_values) {
+  int bits = -1;  // floor(log2(most_values))
+  for (int64_t v = most_values; v > 0; v >>= 1) ++bits;
+  const int limit = 8 * (bits - 12);
+  return arrays <= (limit < kSpreadBatchMax ? limit : kSpreadBatchMax);
+}
+
 }  // namespace mgc

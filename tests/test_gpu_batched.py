@@ -237,3 +237,21 @@ def test_codebooks_spread_and_whole_equal_plain(n):
     got = mgc.compress_batched(xs, bounds, flags=mgc.BATCH_NO_TUNE)
     for x, b, s in zip(xs, bounds, got):
         assert torch.equal(s, mgc.compress(x, b))
+
+
+# the largest array's size decides how many arrays have their codebooks built on
+# many blocks: the last number that has and the first that has not, arrays without
+# values and without a codebook among them
+@pytest.mark.parametrize("side,n", [(17, 1), (25, 8), (25, 9), (33, 24), (33, 25), (65, 48), (65, 49)])
+def test_codebook_forms_by_size_equal_plain(side, n):
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(side + n)
+    xs = [torch.randn((side, side, side) if k == 0 else (5 + k % 9, 20, 17), device="cuda", generator=gen).cumsum(0)
+          for k in range(n)]
+    if n > 4:
+        xs[2] = torch.zeros((0, 5), device="cuda")
+        xs[3] = torch.full((6, 7), 2.5, device="cuda")
+    bounds = [10.0 ** -(1 + k % 4) for k in range(n)]
+    got = mgc.compress_batched(xs, bounds, flags=mgc.BATCH_NO_TUNE)
+    for x, b, s in zip(xs, bounds, got):
+        assert torch.equal(s, mgc.compress(x, b))

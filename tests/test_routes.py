@@ -29,6 +29,7 @@ int rec_rows(const int64_t* n) {
   const Level l(n);
   return rec_streams_rows(l.nf, l.nc);
 }
+int batch_spread(int arrays, int64_t most) { return batch_spreads_codebooks(arrays, most); }
 }
 """
 
@@ -64,3 +65,12 @@ def test_decomposition_columns(rules, shape, f32, f64):
 def test_rows_streamed(rules, shape, dec, rec):
     n = (ctypes.c_int64 * 3)(1, *shape)
     assert (rules.dec_rows(n), rules.rec_rows(n)) == (dec, rec)
+
+
+# codebooks on many blocks up to a number of arrays that grows with the largest one
+@pytest.mark.parametrize("side,few,many", [(9, 0, 1), (17, 0, 1), (25, 8, 9), (33, 24, 25), (65, 48, 49), (129, 72, 73),
+                                           (257, 96, 97), (513, 96, 97)])
+def test_codebooks_of_a_batch(rules, side, few, many):
+    most = ctypes.c_int64(side ** 3)
+    assert (few == 0 or rules.batch_spread(few, most)) and not rules.batch_spread(many, most)
+    assert not rules.batch_spread(1, ctypes.c_int64(0))
