@@ -207,10 +207,11 @@ __device__ __forceinline__ void histogram_body(const uint16_t* __restrict__ sym,
   const int64_t stride = (int64_t)nblk * 1024;
   const int64_t nvec = (reinterpret_cast<uintptr_t>(sym) & 15) == 0 ? n / 8 : 0;
   // the sample: a vector per thread from two thirds on (a compression's
-  // finest level, most of its symbols), where the block has at least eight
+  // finest level, most of its symbols), where the block has at least four: with
+  // hist_blocks any array above 65,536 symbols
   unsigned out = 0;
   const int64_t per = nvec / stride;
-  if (per >= 8) {
+  if (per >= 4) {
     const uint4 w = reinterpret_cast<const uint4*>(sym)[(int64_t)blk * 1024 + threadIdx.x +
                                                         per * 2 / 3 * stride];
     const unsigned a[4] = {w.x, w.y, w.z, w.w};

@@ -317,3 +317,44 @@ def test_forced_shape_beside_the_largest_codebook_it_fits(codes, waves, forced_d
     forced_decoder(1, waves)
     assert bool((mgc.huffman_decode(enc, len(sym)) == t).all())
     assert mgc.decoder_info() == (1, waves)
+
+
+# blocks of four to seven whole vectors a thread, with remainders after them: a
+# last vector stride that only some threads have, symbols after the last vector
+@pytest.mark.parametrize("n", [65537, 4 * 65536 + 5, 5 * 65536 + 8191, 12 * 65536 - 3])
+@pytest.mark.parametrize("share", [0.5, 0.1])
+def test_histogram_read_twice_with_remainders(n, share):
+    torch, mgc = gpu()
+    rng = np.random.default_rng(n)
+    inner = 32768 + np.round(rng.laplace(0.0, 200.0, size=n)).astype(np.int64)
+    outer = (rng.integers(49152, 49152 + 32768, size=n)) % 65536
+    sym = np.where(rng.random(n) < share, outer, np.clip(inner, 16384, 49151))
+    sym[-3:] = [7, 65000, 9]   # (the last symbols lie outside the window)
+    t = torch.from_numpy(sym.astype(np.uint16).view(np.int16)).cuda()
+    assert to_bytes(mgc.huffman_encode(t)) == oracle_huffman_stream(sym, 1024)
+
+
+@pytest.mark.parametrize("n", [300_000, 7_500_000])
+def test_histogram_of_few_symbols_outside_its_window(n):
+    """A quarter of the symbols on ten values outside the window, whose atomics wait
+    for each other: a second reading takes about as long as the first, where the
+    atomics take a hundred times that."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(n)
+    inside = 32768 + torch.round(200 * torch.randn(n, device="cuda", generator=gen)).to(torch.int32)
+    outside = torch.randint(100, 110, (n,), device="cuda", generator=gen, dtype=torch.int32)
+    mixed = torch.where(torch.rand(n, device="cuda", generator=gen) < 0.25, outside, inside)
+
+    def us(sym):
+        mgc.huffman_encode(sym)
+        mgc.profile_enable(True)
+        mgc.profile_reset()
+        for _ in range(5):
+            mgc.huffman_encode(sym)
+        ms = mgc.profile_read()["histogram"][1]
+        mgc.profile_enable(False)
+        return ms / 5 * 1e3
+
+    a, b = us(inside), us(mixed)
+    print("histogram of %d symbols: %.1f us inside, %.1f us with a quarter outside" % (n, a, b))
+    assert b <= 6 * a + 20
