@@ -418,13 +418,16 @@ mgc_status mgc_hx_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, voi
  *   serial sweeps everywhere (8 / 4 values in flight; 32 / 8-value
  *   segments), whose results agree with candidate 0 up to rounding.  Batched
  *   and plain calls under the same candidates give identical streams.
+ *   MGC_TUNE_REC - level kernels of decompression and recomposition (no batched
+ *   call runs them): candidate 0 streams large levels, 1 tiles every level;
+ *   both give identical output.
  * mgc_tuning_info: the candidate count of a kind and the choice used by the
  *   context's most recent batched call (-1 before any).
  * ---------------------------------------------------------------------- */
 #define MGC_BATCH_EAGER 1
 #define MGC_BATCH_NO_TUNE 2
 enum { MGC_TUNE_DEC_F32 = 0, MGC_TUNE_DEC_F64 = 1, MGC_TUNE_THOMAS_STRIDED = 2,
-       MGC_TUNE_THOMAS_ROWS = 3 };
+       MGC_TUNE_THOMAS_ROWS = 3, MGC_TUNE_REC = 4 };
 mgc_status mgc_batch_query(int n, const int* ndims, const uint64_t* shapes,
                            const mgc_dtype* dtypes, uint64_t outlier_cap, size_t* ws_bytes,
                            size_t* out_bytes, uint64_t* h_out_offsets);

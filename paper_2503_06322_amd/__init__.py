@@ -358,7 +358,7 @@ def compress(x, error_bound: float, norm: str = "linf", mode: str = "rel",
 
 BATCH_EAGER = 1
 BATCH_NO_TUNE = 2
-TUNE_KINDS = {"dec_f32": 0, "dec_f64": 1, "thomas_strided": 2, "thomas_rows": 3}
+TUNE_KINDS = {"dec_f32": 0, "dec_f64": 1, "thomas_strided": 2, "thomas_rows": 3, "rec": 4}
 
 
 def _batch_desc(shapes, dtypes):
@@ -459,8 +459,8 @@ def compress_batched(tensors, bounds, norm: str = "linf", mode: str = "rel",
 
 
 def set_tuning(kind: str, candidate: int, device=None):
-    """Force candidate ``candidate`` of a tuning kind for later batched calls
-    (-1: autotune)."""
+    """Force candidate ``candidate`` of a tuning kind for later calls, batched and
+    plain (-1: autotune, and the default in plain calls)."""
     torch = _torch()
     dev = device if device is not None else torch.cuda.current_device()
     _check(_load().mgc_set_tuning(_ctx(dev), TUNE_KINDS[kind], int(candidate)))

@@ -396,12 +396,13 @@ void run_levels_recompose(mgc_ctx ctx, const Plan& p, const CoeffSrc& src,
   }
   double* Gprev = slot[0];
   double* F = gB;
+  const bool tiled = tuned(ctx, MGC_TUNE_REC) != 0;
   for (int l = top + 1; l <= p.L; ++l) {
     const LevelGeom g = p.geom(l);
     const bool fin = l == p.L;
     {
       StageScope sc(&ctx->prof, fin ? "rec_restrict[finest]" : "rec_restrict", s);
-      launch_rec_restrict(g, src_of(l), q[l], F, s);
+      launch_rec_restrict(g, src_of(l), q[l], F, tiled, s);
     }
     // (the output is written last: until then it can hold a coarse grid)
     const size_t need = (size_t)p.points(l - 1) * sizeof(double);
@@ -412,7 +413,7 @@ void run_levels_recompose(mgc_ctx ctx, const Plan& p, const CoeffSrc& src,
     {
       StageScope sc(&ctx->prof, fin ? "rec_interp[finest]" : "rec_interp", s);
       double* dst = levels ? slot[l] : Gprev;
-      launch_rec_interp(F, g, src_of(l), q[l], fin ? d_out : (void*)dst, fin && out_f32, s);
+      launch_rec_interp(F, g, src_of(l), q[l], fin ? d_out : (void*)dst, fin && out_f32, tiled, s);
       if (!fin) Gprev = dst;
     }
   }

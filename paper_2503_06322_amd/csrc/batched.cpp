@@ -34,8 +34,9 @@ enum {
   TUNE_THOMAS_STRIDED = MGC_TUNE_THOMAS_STRIDED,
   TUNE_THOMAS_ROWS = MGC_TUNE_THOMAS_ROWS
 };
-constexpr int kTuneKinds = 4;
-int tune_candidates(int kind) { return kind < 2 ? kDecCands : kThomasCands; }
+int tune_candidates(int kind) {
+  return kind < 2 ? kDecCands : kind == MGC_TUNE_REC ? 2 : kThomasCands;
+}
 
 // Candidates the autotuner compares: every tile shape of the decomposition
 // kernel (identical results); the Thomas kinds stay at candidate 0 (the
@@ -76,8 +77,8 @@ struct BatchPlan {
   hipEvent_t done_ev = nullptr;  // after the last run
   JobBlock* d_map = nullptr;
   std::vector<BLaunch> launches;
-  int tune[kTuneKinds] = {-1, -1, -1, -1};  // candidates of the current maps and graph
-  int autotuned[kTuneKinds] = {-1, -1, -1, -1};
+  int tune[kTuneKinds] = {-1, -1, -1, -1, -1};  // candidates of the current maps and graph
+  int autotuned[kTuneKinds] = {-1, -1, -1, -1, -1};
   hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
 };
@@ -399,7 +400,7 @@ void upload_jobs(BatchPlan& b, const std::vector<Job>& jobs, hipStream_t s) {
 
 void autotune(mgc_ctx ctx, BatchPlan& b, hipStream_t s) {
   std::vector<double> best(kTuneKinds, std::numeric_limits<double>::infinity());
-  int choice[kTuneKinds] = {0, 0, 0, 0};
+  int choice[kTuneKinds] = {0, 0, 0, 0, 0};
   int rounds = 0;
   for (int k = 0; k < kTuneKinds; ++k) rounds = std::max(rounds, autotune_candidates(k));
   for (int c = 0; c < rounds; ++c) {

@@ -122,6 +122,8 @@ mgc_status guard(F&& f) {
   }
 }
 
+constexpr int kTuneKinds = MGC_TUNE_REC + 1;
+
 struct BatchPlan;
 void free_batch_plan(BatchPlan* b);
 
@@ -146,8 +148,8 @@ struct mgc_ctx_s {
   // on, and tuning choices forced by the caller (-1 = autotune)
   std::map<std::vector<uint64_t>, mgc::BatchPlan*> batches;
   hipStream_t capture_stream = nullptr;
-  int forced_tuning[4] = {-1, -1, -1, -1};
-  int last_tuning[4] = {-1, -1, -1, -1};
+  int forced_tuning[mgc::kTuneKinds] = {-1, -1, -1, -1, -1};
+  int last_tuning[mgc::kTuneKinds] = {-1, -1, -1, -1, -1};
   // decoder launch shape forced by the caller (0 = automatic) and the one
   // the latest decode used
   mgc::DecodeShape dec_force, dec_last;

@@ -129,11 +129,12 @@ void launch_level0(const void* G0, bool g_is_f32, int64_t m0, uint16_t* sym, dou
                    const double* rp, const OutlierBuf& ob, unsigned* status,
                    const unsigned* gate, hipStream_t s);
 // Recomposition: f = (P^T M_l) c_l on the coarse grid from the coefficients.
+// tiled: the tiled kernel for a level of any size (same results; MGC_TUNE_REC).
 void launch_rec_restrict(const LevelGeom& g, const CoeffSrc& src, double q, double* fout,
-                         hipStream_t s);
-// Recomposition: G_l = P Gc + c_l (out in FP32 or FP64).
+                         bool tiled, hipStream_t s);
+// Recomposition: G_l = P Gc + c_l (out in FP32 or FP64); tiled as above.
 void launch_rec_interp(const double* Gc, const LevelGeom& g, const CoeffSrc& src, double q,
-                       void* out, bool out_f32, hipStream_t s);
+                       void* out, bool out_f32, bool tiled, hipStream_t s);
 // Dequantised coefficients of stream positions [0, m) (levels 0 .. n-1 of lb,
 // level l starting at off[l], bin q[l]) into raw, escaped values included.
 struct LevelBins {

@@ -3808,9 +3808,9 @@ void dec_dispatch(const void* G, const LevelGeom& g, double* fout, uint16_t* sym
 
 template <bool RAW>
 void rec_restrict_dispatch(const LevelGeom& g, const CoeffSrc& src, double q, double* fout,
-                           hipStream_t s) {
+                           bool tiled, hipStream_t s) {
   const int D = active_axes(g);
-  if (D == 3 && g.nf[0] * g.nf[1] * g.nf[2] >= kRecColsMin) {
+  if (D == 3 && !tiled && g.nf[0] * g.nf[1] * g.nf[2] >= kRecColsMin) {
     const StreamGrid sg = cols_grid(g, kColY);
     hipLaunchKernelGGL((k_rec_cols<RAW>), dim3(sg.grid), dim3(256), 0, s, g, src, q, fout, sg.seg,
                        sg.n_blocks);
@@ -3820,7 +3820,7 @@ void rec_restrict_dispatch(const LevelGeom& g, const CoeffSrc& src, double q, do
     const TileGrid t = tile_grid(g, 4, 8, 8);
     hipLaunchKernelGGL((k_rec_restrict<4, 8, 8, RAW>), dim3(t.grid), dim3(256), 0, s, g, src, q,
                        fout, t.n_tiles);
-  } else if (D == 2 && rec_streams_rows(g.nf, g.nc)) {
+  } else if (D == 2 && !tiled && rec_streams_rows(g.nf, g.nc)) {
     const StreamGrid sg = stream2_grid(g);
     hipLaunchKernelGGL((k_rec_stream2<RAW>), dim3(sg.grid), dim3(256), 0, s, g, src, q, fout,
                        sg.seg, sg.n_blocks);
@@ -3837,10 +3837,10 @@ void rec_restrict_dispatch(const LevelGeom& g, const CoeffSrc& src, double q, do
 
 template <typename Tout, int SRC>
 void rec_interp_dispatch(const double* Gc, const LevelGeom& g, const CoeffSrc& src, double q,
-                         Tout* out, hipStream_t s) {
+                         Tout* out, bool tiled, hipStream_t s) {
   const int D = active_axes(g);
   const int64_t points = g.nf[0] * g.nf[1] * g.nf[2];
-  if (D >= 2 && points >= kInterpStreamMin) {
+  if (D >= 2 && !tiled && points >= kInterpStreamMin) {
     // Segments of eight cells at least (a segment reads one coarse plane more
     // than it owns and sets up anew; 513^3 FP32: 188 us, with 18 cells, 3,885
     // blocks, 229), at most 8,192 blocks; of four where eight would leave the
@@ -4060,19 +4060,19 @@ void launch_level0(const void* G0, bool g_is_f32, int64_t m0, uint16_t* sym, dou
 }
 
 void launch_rec_restrict(const LevelGeom& g, const CoeffSrc& src, double q, double* fout,
-                         hipStream_t s) {
-  if (src.raw) rec_restrict_dispatch<true>(g, src, q, fout, s);
-  else rec_restrict_dispatch<false>(g, src, q, fout, s);
+                         bool tiled, hipStream_t s) {
+  if (src.raw) rec_restrict_dispatch<true>(g, src, q, fout, tiled, s);
+  else rec_restrict_dispatch<false>(g, src, q, fout, tiled, s);
 }
 
 void launch_rec_interp(const double* Gc, const LevelGeom& g, const CoeffSrc& src, double q,
-                       void* out, bool out_f32, hipStream_t s) {
+                       void* out, bool out_f32, bool tiled, hipStream_t s) {
   if (out_f32) {
-    if (src.raw) rec_interp_dispatch<float, 1>(Gc, g, src, q, static_cast<float*>(out), s);
-    else rec_interp_dispatch<float, 0>(Gc, g, src, q, static_cast<float*>(out), s);
+    if (src.raw) rec_interp_dispatch<float, 1>(Gc, g, src, q, static_cast<float*>(out), tiled, s);
+    else rec_interp_dispatch<float, 0>(Gc, g, src, q, static_cast<float*>(out), tiled, s);
   } else {
-    if (src.raw) rec_interp_dispatch<double, 1>(Gc, g, src, q, static_cast<double*>(out), s);
-    else rec_interp_dispatch<double, 0>(Gc, g, src, q, static_cast<double*>(out), s);
+    if (src.raw) rec_interp_dispatch<double, 1>(Gc, g, src, q, static_cast<double*>(out), tiled, s);
+    else rec_interp_dispatch<double, 0>(Gc, g, src, q, static_cast<double*>(out), tiled, s);
   }
 }
 

@@ -413,3 +413,35 @@ def test_mostly_escaped_values_match_oracle(shape):
     ref = oracle.compress(u, 1e-7, mode="abs")
     assert oracle.parse_header(ref)["n_outliers"] > 0.5 * u.size
     assert_stream_matches_oracle(blob, ref, "linf")
+
+
+# 3-axis levels from 2^20 points (interpolation) and 2^24 (restriction) on and
+# 2-axis ones from 2^20 and 2^22 on: both kinds of axis ends, partial strips, columns
+# and segments; no escaped value, some, more of a plane than are searched together
+@pytest.mark.parametrize("shape,share", [((257, 258, 259), 0.0), ((258, 257, 256), 1e-4), ((3, 2400, 2401), 0.02),
+                                         ((2401, 2402, 3), 0.3), ((2050, 4, 2049), 1e-3), ((101, 102, 103), 0.01),
+                                         ((2897, 2898), 1e-3), ((2050, 2049), 0.3), ((1030, 1025), 0.0),
+                                         ((16385, 513), 0.05), ((64528, 65), 0.01)])
+def test_way_back_streamed_equals_tiled(shape, share):
+    """Decompression and recomposition of large levels against the tiled kernels
+    (forced candidate 1): equal values, from symbols and from FP64 coefficients, in
+    both output types."""
+    torch, mgc = gpu()
+    gen = torch.Generator(device="cuda").manual_seed(11)
+    x = torch.randn(shape, device="cuda", generator=gen, dtype=torch.float64) * 1e-2
+    spike = torch.rand(shape, device="cuda", generator=gen) < share
+    x = torch.where(spike, torch.randn(shape, device="cuda", generator=gen, dtype=torch.float64) * 300.0, x)
+    streams = [mgc.compress(y, 1e-3, mode="abs", outlier_cap=y.numel()) for y in (x, x.float())]
+    c = mgc.decompose(x)
+
+    def back():
+        return [mgc.decompress(s) for s in streams] + [mgc.recompose(c, shape, t) for t in (torch.float64, torch.float32)]
+
+    a = back()
+    mgc.set_tuning("rec", 1)
+    try:
+        b = back()
+    finally:
+        mgc.set_tuning("rec", -1)
+    for u, v in zip(a, b):
+        assert torch.equal(u, v)
