@@ -625,6 +625,11 @@ const unsigned* decompress_enqueue(mgc_ctx ctx, const uint8_t* head, size_t head
   }
   CoeffSrc src{w.sym, nullptr, reinterpret_cast<const uint64_t*>(in + opos),
                reinterpret_cast<const int64_t*>(in + oval), (int64_t)h.n_outliers};
+  {
+    // (over the decoding tables, which nothing reads any more)
+    StageScope st(&ctx->prof, "escape_index", s);
+    launch_escape_index(src, p.N, w.tables, decode_tables_bytes(), s);
+  }
   if (p.L >= 2) {
     // levels 0 .. L-2 dequantised ahead (escaped values resolved once)
     LevelBins lb{};

@@ -100,6 +100,9 @@ struct CoeffSrc {
   const uint64_t* opos;  // sorted escape positions
   const int64_t* oval;   // their values
   int64_t n_out;
+  // eidx[b]: the escapes at positions below b << eshift (null: not built)
+  const uint32_t* eidx = nullptr;
+  int eshift = 0;
 };
 
 // Scratch of the single-block codebook construction (65536 entries each).

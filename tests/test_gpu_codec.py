@@ -445,3 +445,53 @@ def test_way_back_streamed_equals_tiled(shape, share):
         mgc.set_tuning("rec", -1)
     for u, v in zip(a, b):
         assert torch.equal(u, v)
+
+
+def _spiked(torch, shape, nodes, dtype, seed=12):
+    gen = torch.Generator(device="cuda").manual_seed(seed)
+    x = torch.randn(shape, device="cuda", generator=gen, dtype=torch.float64) * 1e-2
+    x.reshape(-1)[nodes] = 300.0 + torch.rand(len(nodes), device="cuda", generator=gen, dtype=torch.float64)
+    return x.to(dtype)
+
+
+# escaped values too few for an index of their records and enough for one, in
+# clusters and alone, at both ends of the stream; arrays whose index has an entry
+# every 64 positions and one every few hundred
+@pytest.mark.parametrize("shape", [(40, 41, 42), (700, 33), (161, 162, 163), (3000,)])
+def test_escaped_values_found_through_their_index(shape):
+    torch, mgc = gpu()
+    n = int(np.prod(shape))
+    rng = np.random.default_rng(n)
+    below = above = 0
+    for spikes in (1, 4, 9, 11, 13, 16, 25, 60, 300, min(n // 3, 40000)):
+        nodes = np.unique(np.concatenate([[0, n - 1], rng.integers(0, n, spikes), n // 2 + np.arange(min(spikes, 40))]))
+        x = _spiked(torch, shape, torch.from_numpy(nodes).cuda(), torch.float64)
+        s = mgc.compress(x, 1e-3, mode="abs", outlier_cap=n)
+        esc = parse_header(to_bytes(s[:1024].contiguous()) + bytes(8))["n_outliers"]
+        below, above = below + (0 < esc < 128), above + (esc >= 128)
+        assert torch.max(torch.abs(mgc.decompress(s) - x)).item() <= 1e-3, (spikes, esc)
+    assert above and (below or len(shape) > 2)
+
+
+def test_one_in_a_hundred_escaped_values_cost_little_on_the_way_back():
+    """The level kernels of 150 x 200 x 250 with 1 % of the values escaped against none:
+    a search through all records for each made them take eight times as long."""
+    torch, mgc = gpu()
+    shape = (150, 200, 250)
+    n = int(np.prod(shape))
+    nodes = torch.from_numpy(np.random.default_rng(1).choice(n, n // 100, replace=False)).cuda()
+
+    def us(x):
+        s = mgc.compress(x, 1e-3, mode="abs", outlier_cap=n)
+        mgc.decompress(s)
+        mgc.profile_enable(True)
+        mgc.profile_reset()
+        for _ in range(5):
+            mgc.decompress(s)
+        r = mgc.profile_read()
+        mgc.profile_enable(False)
+        return sum(r[k][1] for k in ("rec_restrict[finest]", "rec_interp[finest]")) / 5 * 1e3
+
+    a, b = us(_spiked(torch, shape, nodes[:0], torch.float32)), us(_spiked(torch, shape, nodes, torch.float32))
+    print("finest level back: %.1f us without, %.1f us with escaped values" % (a, b))
+    assert b <= 5 * a
