@@ -625,11 +625,6 @@ const unsigned* decompress_enqueue(mgc_ctx ctx, const uint8_t* head, size_t head
   }
   CoeffSrc src{w.sym, nullptr, reinterpret_cast<const uint64_t*>(in + opos),
                reinterpret_cast<const int64_t*>(in + oval), (int64_t)h.n_outliers};
-  {
-    // (over the decoding tables, which nothing reads any more)
-    StageScope st(&ctx->prof, "escape_index", s);
-    launch_escape_index(src, p.N, w.tables, decode_tables_bytes(), s);
-  }
   if (p.L >= 2) {
     // levels 0 .. L-2 dequantised ahead (escaped values resolved once)
     LevelBins lb{};
@@ -641,7 +636,8 @@ const unsigned* decompress_enqueue(mgc_ctx ctx, const uint8_t* head, size_t head
     const int64_t m = p.points(p.L - 2);
     {
       StageScope st(&ctx->prof, "dequant_coarse", s);
-      launch_dequant_prefix(src, m, lb, w.coarse, s);
+      // (the index goes over the decoding tables, which nothing reads any more)
+      launch_dequant_prefix(src, m, lb, w.coarse, p.N, w.tables, decode_tables_bytes(), s);
     }
     const CoeffSrc coarse{nullptr, w.coarse, nullptr, nullptr, 0};
     run_levels_recompose(ctx, p, src, q, w.gA, w.gB, d_out, dt == MGC_F32, s, nullptr,

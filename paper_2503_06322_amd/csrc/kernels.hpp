@@ -135,20 +135,19 @@ void launch_rec_restrict(const LevelGeom& g, const CoeffSrc& src, double q, doub
 // Recomposition: G_l = P Gc + c_l (out in FP32 or FP64); tiled as above.
 void launch_rec_interp(const double* Gc, const LevelGeom& g, const CoeffSrc& src, double q,
                        void* out, bool out_f32, bool tiled, hipStream_t s);
-// Index of the escapes of src (positions below N) in a table of `bytes` (at least a
-// few hundred) bytes that stays until the last launch that reads src; not built for
-// few escapes, whose search is short.
-constexpr int64_t kEscapeIndexMin = 128;
-void launch_escape_index(CoeffSrc& src, int64_t N, void* table, size_t bytes, hipStream_t s);
 // Dequantised coefficients of stream positions [0, m) (levels 0 .. n-1 of lb,
-// level l starting at off[l], bin q[l]) into raw, escaped values included.
+// level l starting at off[l], bin q[l]) into raw, escaped values included.  With
+// escapes enough for their search to be long it also builds src's index (positions
+// below N) in a table of `bytes` bytes (a few hundred at least) that stays until the
+// last launch that reads src.
+constexpr int64_t kEscapeIndexMin = 128;
 struct LevelBins {
   int64_t off[kMaxLevels + 1];
   double q[kMaxLevels + 1];
   int n;
 };
-void launch_dequant_prefix(const CoeffSrc& src, int64_t m, const LevelBins& lb, double* raw,
-                           hipStream_t s);
+void launch_dequant_prefix(CoeffSrc& src, int64_t m, const LevelBins& lb, double* raw, int64_t N,
+                           void* table, size_t bytes, hipStream_t s);
 void launch_rec_level0(const CoeffSrc& src, int64_t m0, double q, void* out, bool out_f32,
                        hipStream_t s);
 // The smallest levels in one workgroup with their grids in LDS.  Level l

@@ -191,15 +191,15 @@ __device__ __forceinline__ double coeff_at(const CoeffSrc& s, int64_t pos, doubl
   return (double)escaped_k(s, (uint64_t)pos) * q;
 }
 
-// eidx for n_entries entries.  With 1 % of 150 x 200 x 250 values escaped the finest
+// One block's 256 of the n_entries entries of eidx.  With 1 % of 150 x 200 x 250 values escaped the finest
 // level back takes 142 + 60 us (345 + 168 without the index), decompression 855
 // (1,245).  A wavefront finds the records before and after its 64 entries
 // together, 32 lanes narrowing each to a 32nd a step, then every lane its own among
 // those.
-__global__ __launch_bounds__(256) void k_escape_index(const uint64_t* __restrict__ opos,
-                                                       int64_t n, int shift, uint32_t n_entries,
-                                                       uint32_t* __restrict__ eidx) {
-  const uint32_t b = blockIdx.x * 256 + threadIdx.x, b0 = b & ~63u;
+__device__ __forceinline__ void escape_index_body(const uint64_t* __restrict__ opos, int64_t n,
+                                                  int shift, uint32_t n_entries,
+                                                  uint32_t* __restrict__ eidx, uint32_t blk) {
+  const uint32_t b = blk * 256 + threadIdx.x, b0 = b & ~63u;
   const int lane = (int)(threadIdx.x & 63), l = lane & 31;
   if (b0 >= n_entries) return;
   const uint64_t at = (uint64_t)(lane < 32 ? b0 : b0 + 63) << shift;
@@ -3540,12 +3540,21 @@ __device__ __forceinline__ int level_of(const LevelBins& lb, int64_t pos) {
   return lo;
 }
 
-__global__ __launch_bounds__(256) void k_dequant_prefix(const uint16_t* __restrict__ sym,
-                                                         int64_t m, const LevelBins lb,
-                                                         double* __restrict__ raw) {
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += stride) {
-    const uint16_t v = sym[i];
+// The first idx_blocks blocks build the index of the escapes (eidx, n_entries)
+// beside the others, which they would keep waiting in a launch of their own.
+__global__ __launch_bounds__(256) void k_dequant_prefix(const CoeffSrc src, int64_t m,
+                                                         const LevelBins lb,
+                                                         double* __restrict__ raw,
+                                                         uint32_t* __restrict__ eidx,
+                                                         uint32_t n_entries, uint32_t idx_blocks) {
+  if (blockIdx.x < idx_blocks) {
+    escape_index_body(src.opos, src.n_out, src.eshift, n_entries, eidx, blockIdx.x);
+    return;
+  }
+  const int64_t stride = (int64_t)(gridDim.x - idx_blocks) * blockDim.x;
+  for (int64_t i = (int64_t)(blockIdx.x - idx_blocks) * blockDim.x + threadIdx.x; i < m;
+       i += stride) {
+    const uint16_t v = src.sym[i];
     raw[i] = v != 0 ? (double)((int64_t)v - 32768) * lb.q[level_of(lb, i)] : 0.0;
   }
 }
@@ -4134,28 +4143,25 @@ void launch_adj_coeff(const double* v, const double* gl, const LevelGeom& g, dou
                      g, cbar, (int)seg, (uint32_t)n);
 }
 
-void launch_dequant_prefix(const CoeffSrc& src, int64_t m, const LevelBins& lb, double* raw,
-                           hipStream_t s) {
-  if (m <= 0) return;
+void launch_dequant_prefix(CoeffSrc& src, int64_t m, const LevelBins& lb, double* raw, int64_t N,
+                           void* table, size_t bytes, hipStream_t s) {
+  uint32_t n_entries = 0, idx_blocks = 0;
+  if (src.n_out >= kEscapeIndexMin) {
+    int shift = 6;
+    while (((N >> shift) + 2) * 4 > (int64_t)bytes) ++shift;
+    n_entries = (uint32_t)((N >> shift) + 2);
+    idx_blocks = (n_entries + 255) / 256;
+    src.eidx = static_cast<const uint32_t*>(table);
+    src.eshift = shift;
+  }
   const unsigned b = (unsigned)std::min<int64_t>((m + 255) / 256, 4096);
-  hipLaunchKernelGGL(k_dequant_prefix, dim3(b), dim3(256), 0, s, src.sym, m, lb, raw);
+  hipLaunchKernelGGL(k_dequant_prefix, dim3(idx_blocks + b), dim3(256), 0, s, src, m, lb, raw,
+                     static_cast<uint32_t*>(table), n_entries, idx_blocks);
   if (src.n_out > 0) {
     const unsigned bo = (unsigned)std::min<int64_t>((src.n_out + 255) / 256, 2048);
     hipLaunchKernelGGL(k_dequant_escapes, dim3(bo), dim3(256), 0, s, src.opos, src.oval,
                        src.n_out, m, lb, raw);
   }
-}
-
-void launch_escape_index(CoeffSrc& src, int64_t N, void* table, size_t bytes, hipStream_t s) {
-  if (src.n_out < kEscapeIndexMin) return;
-  int shift = 6;
-  while (((N >> shift) + 2) * 4 > (int64_t)bytes) ++shift;
-  const uint32_t n_entries = (uint32_t)((N >> shift) + 2);
-  uint32_t* const eidx = static_cast<uint32_t*>(table);
-  hipLaunchKernelGGL(k_escape_index, dim3((n_entries + 255) / 256), dim3(256), 0, s, src.opos,
-                     src.n_out, shift, n_entries, eidx);
-  src.eidx = eidx;
-  src.eshift = shift;
 }
 
 bool tail_level_fits(const LevelGeom& g) {
