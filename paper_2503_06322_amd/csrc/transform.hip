@@ -1043,7 +1043,7 @@ __device__ __forceinline__ void coeff_values(const CoeffSrc& src, const uint32_t
 // come from the neighbour lanes, rows and planes are added to the running sums
 // of the outputs that they reach, in the order of the taps: no LDS, no barrier.
 // (kColX, kColY and when they are taken: routes.hpp.)
-constexpr uint32_t kColEsc = 256;  // escaped values of a wavefront's plane that are searched together
+constexpr uint32_t kColEsc = 768;  // escaped values of a wavefront's plane that are searched together
 
 // Value i (the same for the wavefront) of a table that no kernel writes while
 // it is read: a scalar load.  (A vector load would be waited for in order,
@@ -1363,6 +1363,7 @@ __global__ __launch_bounds__(256, RAW ? 3 : 4) void k_rec_cols(const LevelGeom g
                                                    const int seg, const uint32_t n_blocks) {
   constexpr int R = kColY, NR = 2 * R + 3;
   __shared__ double esc_list[RAW ? 1 : 4][RAW ? 1 : kColEsc];  // a list for each wavefront
+  __shared__ uint16_t esc_sym[RAW ? 1 : 4][RAW ? 1 : 2 * NR][64];
   using V = typename std::conditional<RAW, double, uint32_t>::type;
   const uint32_t b = xcd_tile(blockIdx.x, gridDim.x);
   if (b >= n_blocks) return;
@@ -1446,14 +1447,25 @@ __global__ __launch_bounds__(256, RAW ? 3 : 4) void k_rec_cols(const LevelGeom g
   };
   // A plane with escaped values: the wavefront lists their positions and its
   // lanes search the records for one each, so a plane usually costs one search
-  // instead of one a row.  Rolled loops over symbols read again: unrolled, the
-  // searches took registers from the planes without any.
-  auto reduce_escaped = [&](bool zn, int J, double (&Y)[R]) {
+  // instead of one a row.  The symbols go to LDS for rolled loops over them:
+  // unrolled, they took registers from the planes without any; read again from
+  // memory a row at a time, 257 x 258 x 259 with 1 % escaped took 396 us, now 289.
+  // (What lies outside the grid counts with tap 0 and is not looked up: lanes past
+  // the grid's end, most of them with 17 values along x, looked up their edge's.)
+  auto reduce_escaped = [&](auto zn, int J, const Plane& p, double (&Y)[R]) {
     J = min(max(J, 0), (zn ? nn0 : nc0) - 1);
     double* list = esc_list[threadIdx.x >> 6];
+    uint16_t(*kept)[64] = esc_sym[threadIdx.x >> 6];
+    const bool in_o = J2 >= 0 && J2 < nc2, in_n = J2 >= 0 && J2 < nn2;
     uint32_t n = 0;
-    auto collect = [&](uint32_t pos) {
-      const bool e = src.sym[pos] == 0;
+#pragma unroll
+    for (int r = 0; r < NR; ++r) {
+      kept[2 * r][lane] = (uint16_t)(in_n ? p.n[r] : 32768u);
+      if (zn || (r & 1)) kept[2 * r + 1][lane] = (uint16_t)(in_o ? p.o[r] : 32768u);
+    }
+    wave_lds_fence();
+    auto collect = [&](uint32_t row, uint32_t pos) {
+      const bool e = kept[row][lane] == 0;
       const uint64_t m = __ballot(e);
       const uint32_t k = n + below(m);
       if (e && k < kColEsc) list[k] = (double)pos;
@@ -1461,16 +1473,16 @@ __global__ __launch_bounds__(256, RAW ? 3 : 4) void k_rec_cols(const LevelGeom g
     };
 #pragma unroll 1
     for (int r = 0; r < NR; ++r) {
-      collect(row_at(zn, J, r, true) + xn);
-      if (zn || (r & 1)) collect(row_at(zn, J, r, false) + xo);
+      collect(2 * r, row_at(zn, J, r, true) + xn);
+      if (zn || (r & 1)) collect(2 * r + 1, row_at(zn, J, r, false) + xo);
     }
     wave_lds_fence();
     for (uint32_t k = (uint32_t)lane; k < min(n, kColEsc); k += 64)
       list[k] = (double)escaped_k(src, (uint64_t)list[k]) * q;
     wave_lds_fence();
     n = 0;
-    auto value = [&](uint32_t pos) -> double {
-      const uint32_t s = src.sym[pos];
+    auto value = [&](uint32_t row, uint32_t pos) -> double {
+      const uint32_t s = kept[row][lane];
       const uint64_t m = __ballot(s == 0);
       const uint32_t k = n + below(m);
       n += (uint32_t)__popcll(m);
@@ -1482,8 +1494,8 @@ __global__ __launch_bounds__(256, RAW ? 3 : 4) void k_rec_cols(const LevelGeom g
 #pragma unroll 1
     for (int r = 0; r < NR; ++r) {
       const bool both = zn || (r & 1);
-      const double c = value(row_at(zn, J, r, true) + xn);
-      const double o = both ? value(row_at(zn, J, r, false) + xo) : 0.0;
+      const double c = value(2 * r, row_at(zn, J, r, true) + xn);
+      const double o = both ? value(2 * r + 1, row_at(zn, J, r, false) + xo) : 0.0;
       const double X = x_sum(both, o, c);
 #pragma unroll
       for (int j = 0; j < R; ++j)
@@ -1503,7 +1515,7 @@ __global__ __launch_bounds__(256, RAW ? 3 : 4) void k_rec_cols(const LevelGeom g
         if (zn || (r & 1)) least = min(least, p.o[r]);
       }
       if (__builtin_expect(__any(least == 0), 0))
-        reduce_escaped(zn, J, Y);
+        reduce_escaped(zn, J, p, Y);
       else
         rows(zn, [&](int r, bool xnew) -> double {
           return (double)((int)(xnew ? p.n[r] : p.o[r]) - 32768) * q;
