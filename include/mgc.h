@@ -412,9 +412,11 @@ mgc_status mgc_hx_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, voi
  *   MGC_TUNE_THOMAS_STRIDED / MGC_TUNE_THOMAS_ROWS - tridiagonal sweeps of
  *   the strided axes / the contiguous axis: candidate 0 (the default, kept
  *   by the autotuner) solves every coarse grid too large for one workgroup
- *   with partitioned sweeps where its lines fit (512 values on strided axes,
- *   1024 on the contiguous one) and with serial sweeps otherwise (16 values
- *   in flight per line / 16-value LDS segments); candidates 1 and 2 force
+ *   with partitioned sweeps (strided lines above 512 values in overlapping
+ *   windows, contiguous ones above 1024 a block each) and, beside contiguous
+ *   lines above 8704 values or without a second grid buffer, long lines with
+ *   serial sweeps (16 values in flight per line / 16-value LDS segments);
+ *   candidates 1 and 2 force
  *   serial sweeps everywhere (8 / 4 values in flight; 32 / 8-value
  *   segments), whose results agree with candidate 0 up to rounding.  Batched
  *   and plain calls under the same candidates give identical streams.

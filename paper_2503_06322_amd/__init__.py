@@ -242,8 +242,8 @@ def _empty(nbytes: int, device):
 def compress_query(shape, dtype, outlier_cap: int = 0):
     """(workspace bytes, output capacity) of compress for this shape and dtype.
 
-    The library builds the level plan to answer (≈0.1 ms at 513^3), so the
-    answers are kept per (shape, dtype, capacity)."""
+    Computed on the host from the level sizes; the answers are kept per
+    (shape, dtype, capacity)."""
     key = (tuple(int(s) for s in shape), _dtype_code(dtype), int(outlier_cap))
     hit = _query_cache.get(key)
     if hit is None:

@@ -6,8 +6,8 @@
 //    quantised coefficients cluster around the dictionary centre), global
 //    atomics for the rest.
 //  * codebook: the non-zero keys are sorted by (frequency, symbol) with a
-//    stable LSD radix sort over many blocks (k_cbs_count / k_cbs_pass; large
-//    batches sort in the one workgroup below).  Code lengths follow the
+//    stable LSD radix sort over many blocks (k_cbs_count / k_cbs_pass; batches of
+//    many or small arrays sort in the one workgroup below).  Code lengths follow the
 //    two-queue construction (leaves in that order, internal nodes in creation
 //    order, ties to the leaf), computed by one workgroup of 1024 threads in
 //    rounds: with m nodes already taken, no node created later can weigh less
@@ -19,7 +19,7 @@
 //    the frequencies and rebuild.  Codes are canonical (RFC 1951
 //    construction), assigned on many blocks (k_canon_count / k_canon_rank:
 //    each wavefront a run of the symbols with its count of each length in
-//    one lane; large batches assign them in their one workgroup).
+//    one lane; those batches assign them in their one workgroup).
 //  * chunk lengths and layout: one wavefront per chunk sums the code lengths
 //    (and, in a compression, counts the escape symbols per chunk and lane);
 //    an exclusive scan of the chunk word counts over many blocks gives the

@@ -57,11 +57,11 @@ __device__ __forceinline__ void emit_q(int64_t pos, double c, double r, uint16_t
 
 // Escaped values of a block on their way to the outlier records: every device
 // atomic on the one record counter costs about 3 ns, whichever blocks they
-// come from (at half a percent of escapes the finest level of 300x400x500
-// took 785 us with one per coefficient and wavefront, 605 us with one per cell
-// and wavefront and takes 179 us with this list), so a block collects them in LDS
-// and reserves their records together.  Values that find the list full take
-// records of their own.
+// come from, so a block collects them in LDS and reserves their records together.
+// At half a percent of escapes the 150x200x250 level under a 300x400x500 array took
+// 994 us tiled with one per coefficient and wavefront, 69 us with this list.  (The
+// column kernel, which takes that level now, keeps a list a wavefront.)  Values that
+// find the list full take records of their own.
 template <int CAP>
 struct EscList {
   unsigned n, lim;          // slots reserved; the first reservation that did not fit
@@ -413,9 +413,6 @@ __device__ __forceinline__ uint32_t div_small(uint32_t r, uint64_t m) {
 // scalar instructions per call
 __device__ __forceinline__ uint64_t div_magic(uint32_t d) { return (uint64_t)(0xFFFFFFFFu / d) + 1; }
 
-// Workgroups are dispatched round-robin over the 8 XCDs; giving each XCD a
-// contiguous range of tiles keeps neighbouring tiles (which share halos) in
-// the same L2.  grid = n_tiles rounded up to a multiple of 8.
 // Orders a wavefront's LDS accesses (its lanes exchange values through LDS).
 __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
@@ -423,6 +420,9 @@ __device__ __forceinline__ void wave_fence() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// Workgroups are dispatched round-robin over the 8 XCDs; giving each XCD a
+// contiguous range of tiles keeps neighbouring tiles (which share halos) in
+// the same L2.  grid = n_tiles rounded up to a multiple of 8.
 __device__ __forceinline__ uint32_t xcd_tile(uint32_t b, uint32_t grid) {
   return (b & 7u) * (grid >> 3) + (b >> 3);
 }
@@ -920,8 +920,9 @@ __global__ __launch_bounds__(256) void k_dec_stream2(
                          (double)q[1] - lin2(wy0, iold, wy1, ix0), 0.0, 0.0, 0.0, 0.0};
     emit_cell<QUANT>(pos, v, ok, r, sym, raw, ob, status, el);
   };
-  // Step i takes fine rows 2i + 1 and 2i + 2 and finishes coarse row i (see
-  // the 3-axis kernel).
+  // Step i takes fine rows 2i + 1 and 2i + 2, the last that coarse row i needs, and
+  // finishes it.  (An even axis ends on two adjacent coarse rows: the last one is
+  // finished with the one before it.)
   int slot = 0;
   load_rows(2 * (cy0 - 2) + 1);
   for (int i = cy0 - 2; i < cy1; ++i) {
@@ -1118,10 +1119,12 @@ __device__ __forceinline__ void row_store(__amdgpu_buffer_rsrc_t row, uint32_t b
 // before new plane p, whose cells need the corners above.  Each wavefront has
 // its own list of escaped values, which holds a plane's at least.
 // 513^3 FP32: 286 us, 300 x 400 x 500 FP32 143 us, 257^3 FP64 59 us; the pass
-// through LDS, two barriers a step, 397, 179 and (tiled) 94 us.  946 MB at
-// 513^3 take 190 us; 146 us are vector instructions.  Stores behind branches,
-// whose waits drained every access in flight, 373 us.  Two rows a wavefront: of
-// three the registers (156) leave three wavefronts a SIMD, 384 us against 373.
+// through LDS, two barriers a step, 397, 179 and (tiled) 94 us.  The 912 MB it
+// cannot do without at 513^3 take 182 us at 5 TB/s, the 1,157 MB that the counters
+// show (seven rows read for four owned) 231; 146 us are vector instructions.  Stores
+// behind branches, whose waits drained every access in flight, 373 us.  Two rows a
+// wavefront: of three the registers (156) leave three wavefronts a SIMD, 384 us
+// against 373.
 constexpr int kDecColEsc = 768;  // escaped values a wavefront collects between flushes
 static_assert(kDecColEsc >= 64 * 4 * kDecColY, "a plane's escaped values fit");
 
@@ -2457,9 +2460,9 @@ __global__ __launch_bounds__(64) void k_thomas_rows(double* __restrict__ x, int6
 }
 
 
-// Partitioned sweeps for coarse grids above the LDS-tile limit.  A line is
-// cut into segments whose values stay in registers from their load to their
-// store, so every value is read once and written once per axis.  The forward
+// Partitioned sweeps for coarse grids too large for the one-workgroup solve.  A
+// line is cut into segments whose values stay in registers from their load to
+// their store, so every value is read once and written once per axis.  The forward
 // recurrence is affine in its start value: inside a segment starting at s it
 // runs from zero (y^_i), and the true value is y_i = y^_i + alpha_i y_{s-1}
 // with alpha_i = prod_{j=s..i} (-a_j).  The segments' end values chain the
@@ -2491,7 +2494,7 @@ __global__ __launch_bounds__(64) void k_thomas_rows(double* __restrict__ x, int6
 // otherwise).  A NaN or an infinity reaches every value of its line, beyond the
 // windows that hold it: a block that reads one says so in *seen.bits (where the
 // caller wants to know), and launch_spread_nonfinite fills the grid.  At
-// 4097 x 4097 values: LONGUS us, the one-thread-per-line sweep 1219 us (4,097
+// 4097 x 4097 values: 57 us, the one-thread-per-line sweep 1219 us (4,097
 // threads on the whole GPU, every value twice).
 constexpr int kPartWaves = kPartWavesMax;  // segments (wavefronts) per block at most
 constexpr int kLongSeg = 40, kLongHalo = 32;
@@ -2815,7 +2818,7 @@ __global__ __launch_bounds__(64 * kRowScanWaves) void k_thomas_rowscan(
 // are scanned inside each wavefront and chained over the eight wavefronts
 // through LDS.  Rows blk, blk + nblk, ...: the factors stay in registers and
 // the next row's loads are in flight while a row is solved.  At 4097 rows of
-// 4097 values: ROWUS us, the 64-rows-per-wavefront sweep 907 us (65 wavefronts
+// 4097 values: 105 us, the 64-rows-per-wavefront sweep 907 us (65 wavefronts
 // on the whole GPU).
 constexpr int kRowBlkThreads = 512;
 template <int K>
