@@ -408,7 +408,8 @@ mgc_status mgc_hx_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, voi
  *   MGC_TUNE_DEC_F32 / MGC_TUNE_DEC_F64 - tile shape (coarse outputs, z y x)
  *   of the three-axis decomposition kernel on FP32 / FP64 input: f32
  *   {4x8x16, 8x8x8, 4x4x16, 2x8x32}, f64 {4x8x8, 4x4x16, 2x8x16, 8x8x8};
- *   every tile candidate gives bit-identical output.
+ *   in plain calls candidate 0 streams large levels of two and three axes
+ *   instead; every candidate gives bit-identical output.
  *   MGC_TUNE_THOMAS_STRIDED / MGC_TUNE_THOMAS_ROWS - tridiagonal sweeps of
  *   the strided axes / the contiguous axis: candidate 0 (the default, kept
  *   by the autotuner) solves every coarse grid too large for one workgroup
@@ -416,10 +417,10 @@ mgc_status mgc_hx_decompress(mgc_ctx ctx, const void* d_in, size_t in_bytes, voi
  *   windows, contiguous ones above 1024 a block each) and, beside contiguous
  *   lines above 8704 values or without a second grid buffer, long lines with
  *   serial sweeps (16 values in flight per line / 16-value LDS segments);
- *   candidates 1 and 2 force
- *   serial sweeps everywhere (8 / 4 values in flight; 32 / 8-value
- *   segments), whose results agree with candidate 0 up to rounding.  Batched
- *   and plain calls under the same candidates give identical streams.
+ *   candidates 1 and 2 force serial sweeps everywhere (8 / 4 values in flight;
+ *   32 / 8-value segments), whose results agree with candidate 0 up to
+ *   rounding.  Batched and plain calls under the same candidates give
+ *   identical streams.
  *   MGC_TUNE_REC - level kernels of decompression and recomposition (no batched
  *   call runs them): candidate 0 streams large levels, 1 tiles every level;
  *   both give identical output.
