@@ -3003,13 +3003,13 @@ void launch_encode(const uint16_t* sym, int64_t N, int C, const uint32_t* code,
   constexpr int64_t kCUs = 256;
   if (C == kEncC && n_chunks >= 2 * kCUs * kEncWaves &&
       (reinterpret_cast<uintptr_t>(sym) & 15) == 0 && (reinterpret_cast<uintptr_t>(pk) & 15) == 0) {
-    static bool attr = false;
-    if (!attr) {
+    static const bool attr = [] {
       MGC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_encode_win),
                                   hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)enc_win_lds_bytes()));
-      attr = true;
-    }
+      return true;
+    }();
+    (void)attr;
     const int64_t blocks = std::min<int64_t>(kCUs, (n_chunks + kEncWaves - 1) / kEncWaves);
     hipLaunchKernelGGL(k_encode_win, dim3((unsigned)blocks), dim3(64 * kEncWaves),
                        enc_win_lds_bytes(), s, sym, N, pk, out, lay, gate);
@@ -3044,15 +3044,14 @@ namespace {
 template <int RW, int G, int P>
 size_t decode_room() {
   // the dynamic LDS the kernel can take on top of its static LDS (160 KiB per CU)
-  static size_t room = 0;
-  if (room == 0) {
+  static const size_t room = [] {
     hipFuncAttributes fa;
     MGC_HIP(hipFuncGetAttributes(&fa, reinterpret_cast<const void*>(k_decode<RW, G, P>)));
     const size_t r = 163840 - fa.sharedSizeBytes;
     MGC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_decode<RW, G, P>),
                                 hipFuncAttributeMaxDynamicSharedMemorySize, (int)r));
-    room = r;
-  }
+    return r;
+  }();
   return room;
 }
 }  // namespace

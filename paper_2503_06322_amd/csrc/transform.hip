@@ -4087,13 +4087,13 @@ bool thomas_grid_fits(const LevelGeom& g) {
 void launch_thomas_grid(double* x, const LevelGeom& g, const double* sub, hipStream_t s) {
   const int64_t n = g.nc[0] * g.nc[1] * g.nc[2];
   if (n > kThomasGridMax) throw std::logic_error("launch_thomas_grid: grid exceeds LDS");
-  static bool attr = false;
-  if (!attr) {
+  static const bool attr = [] {
     MGC_HIP(hipFuncSetAttribute(reinterpret_cast<const void*>(k_thomas_grid),
                                 hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)(kThomasGridMax * sizeof(double))));
-    attr = true;
-  }
+    return true;
+  }();
+  (void)attr;
   Thomas3Args a;
   for (int k = 0; k < 3; ++k) {
     a.ta[k] = g.ax[k].ta;
