@@ -106,7 +106,7 @@ def stage_bytes(N: int, Nc: int, in_size: int, stream_bytes: int):
 
 
 def host_cores() -> int:
-    """Cores this process may run on (the GPU machine's share, not the machine's)."""
+    """Cores this process may run on (its own share, not the whole machine)."""
     try:
         return len(os.sched_getaffinity(0))
     except AttributeError:  # pragma: no cover
