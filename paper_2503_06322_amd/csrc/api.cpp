@@ -1032,7 +1032,6 @@ mgc_status mgc_recompose(mgc_ctx ctx, const double* d_coeffs, int ndim, const ui
 namespace {
 struct AdjointWs {
   double *gA, *gB, *Y, *T;  // T: the sweeps' second buffer
-  unsigned* seen;
 };
 AdjointWs carve_adjoint(Carver& c, const Plan& p) {
   const int64_t n_coarse = p.L >= 1 ? p.points(p.L - 1) : 1;
@@ -1041,7 +1040,6 @@ AdjointWs carve_adjoint(Carver& c, const Plan& p) {
   w.gB = c.take<double>(n_coarse);
   w.Y = c.take<double>(n_coarse);
   w.T = c.take<double>(n_coarse);
-  w.seen = c.take<unsigned>(1);
   return w;
 }
 size_t levels_bytes_of(const Plan& p) {
@@ -1075,7 +1073,9 @@ mgc_status mgc_recompose_adjoint(mgc_ctx ctx, const double* d_grad_u, int ndim,
     AdjointWs w = carve_adjoint(c, p);
     hipStream_t s = as_stream(stream);
     const double* g = d_grad_u;
-    unsigned* const seen = clear_nonfinite(p, w.seen, s);
+    // The word is the first coarsest coefficient's place, which launch_level0 fills
+    // last: no more workspace than the sweeps need.
+    unsigned* const seen = clear_nonfinite(p, reinterpret_cast<unsigned*>(d_grad_coeffs), s);
     for (int l = p.L; l >= 1; --l) {
       const LevelGeom geom = p.geom(l);
       double* Gc = (g == w.gA) ? w.gB : w.gA;

@@ -52,6 +52,20 @@ def test_host_only_queries():
     assert e.value.name == "EUNSUPPORTED"
 
 
+@pytest.mark.parametrize("shape", [(3,), (1000,), (600, 600), (17, 17, 17), (3, 700, 3)])
+def test_adjoint_workspace_is_four_coarse_grids(shape):
+    """What mgc_adjoint_query asks for is the four coarse grids (each at a multiple of
+    256 bytes) and no more: a workspace of that size stays enough."""
+    lib = _lib()
+    ws = ctypes.c_size_t()
+    arr = (ctypes.c_uint64 * len(shape))(*shape)
+    assert lib.mgc_adjoint_query(len(shape), arr, ctypes.byref(ws)) == 0
+    grid = 8
+    for n in shape:
+        grid *= n // 2 + 1
+    assert ws.value == 3 * (-(-grid // 256) * 256) + grid
+
+
 def test_header_info_parses_oracle_stream():
     import numpy as np
     import torch
